@@ -79,6 +79,16 @@ void gemm(Ctx& x, QGemm g, const int* skip = nullptr) {
     x.ck(bwla_q_launch_gemm(g, x.st));
 }
 
+// dst_i = R1^T src_i for every row as an n1 x n2 matrix (transposed: R1 src_i); src must differ from dst
+void rotate_left(Ctx& x, const double* R1, const double* src, bool transposed, double* dst) {
+    const QPlan& P = x.P;
+    QGemm b{};
+    b.A = R1; b.B = src; b.C = dst; b.M = P.n1; b.N = P.n2; b.K = P.n1; b.batch = P.n;
+    if (transposed) { b.rsA = P.n1; b.klA = 1; } else { b.rsA = 1; b.klA = P.n1; }
+    b.bsA = 0; b.csB = 1; b.klB = P.n2; b.bsB = P.m; b.rsC = P.n2; b.bsC = P.m; b.alpha = 1.0; b.beta = 0.0;
+    gemm(x, b);
+}
+
 // dst rows = src rows times R1 (x) R2 (transposed = false) or times its transpose R1^T (x) R2^T;
 // half = the (n n1) x n2 intermediate src_i R2.  src may equal dst; half must differ from both.
 void rotate_rows(Ctx& x, const double* src, const double* R1, const double* R2, bool transposed, double* half,
@@ -87,11 +97,7 @@ void rotate_rows(Ctx& x, const double* src, const double* R1, const double* R2, 
     QGemm a = qgemm_plain(src, R2, half, P.n * P.n1, P.n2, P.n2);
     if (transposed) { a.csB = P.n2; a.klB = 1; }
     gemm(x, a);
-    QGemm b{};
-    b.A = R1; b.B = half; b.C = dst; b.M = P.n1; b.N = P.n2; b.K = P.n1; b.batch = P.n;
-    if (transposed) { b.rsA = P.n1; b.klA = 1; } else { b.rsA = 1; b.klA = P.n1; }
-    b.bsA = 0; b.csB = 1; b.klB = P.n2; b.bsB = P.m; b.rsC = P.n2; b.bsC = P.m; b.alpha = 1.0; b.beta = 0.0;
-    gemm(x, b);
+    rotate_left(x, R1, half, transposed, dst);
 }
 
 // Wres = W - A Bt^T (returns W itself when k == 0)
@@ -163,13 +169,13 @@ void polar(Ctx& x, int nn, double* R) {
     gemm(x, g);
 }
 
-// The Procrustes update of one factor at (Wres, R1, R2, c, s2); expects nothing of the scratch.
-void procrustes(Ctx& x, int which, const double* Wres, const double* R1, const double* R2, const double* c,
-                const double* s2, double* Rnew) {
+// The Procrustes update of one factor, from what the scratch holds: big[2] = half = (W - M) R2,
+// big[3] = Y = (W - M) R and ybar its row means.  Overwrites big[4] (which = 1) or big[4] and big[2]
+// (which = 2, leaving R1^T (W - M) there).
+void procrustes_held(Ctx& x, int which, const double* Wres, const double* R1, const double* c, const double* s2,
+                     double* Rnew) {
     const QPlan& P = x.P;
     double *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *T = x.d(P.big[4]), *ybar = x.d(P.ybar);
-    rotate_rows(x, Wres, R1, R2, false, half, Y);
-    x.ck(bwla_q_launch_center(Y, nullptr, ybar, P.n, P.m, x.st));
     x.ck(bwla_q_launch_targets(Y, ybar, c, s2, P.n, P.m, T, x.st));
     QGemm g{};
     g.batch = 1; g.alpha = 1.0; g.beta = 0.0; g.C = x.d(P.C);
@@ -183,15 +189,21 @@ void procrustes(Ctx& x, int which, const double* Wres, const double* R1, const d
         polar(x, P.n1, Rnew);
     } else {
         // P_i = R1^T V_i into `half`, then C2[b][d] = sum_(i,c) P[(i,c)][b] (lambda_i T_i)[(i,c)][d]
-        QGemm b{};
-        b.A = R1; b.B = Wres; b.C = half; b.M = P.n1; b.N = P.n2; b.K = P.n1; b.batch = P.n;
-        b.rsA = 1; b.klA = P.n1; b.csB = 1; b.klB = P.n2; b.bsB = P.m; b.rsC = P.n2; b.bsC = P.m; b.alpha = 1.0;
-        gemm(x, b);
+        rotate_left(x, R1, Wres, false, half);
         g.A = half; g.B = T; g.M = P.n2; g.N = P.n2; g.K = P.n * P.n1;
         g.rsA = 1; g.klA = P.n2; g.csB = 1; g.klB = P.n2; g.rsC = P.n2;
         gemm(x, g);
         polar(x, P.n2, Rnew);
     }
+}
+
+// The same at (Wres, R1, R2, c, s2); expects nothing of the scratch.
+void procrustes(Ctx& x, int which, const double* Wres, const double* R1, const double* R2, const double* c,
+                const double* s2, double* Rnew) {
+    const QPlan& P = x.P;
+    rotate_rows(x, Wres, R1, R2, false, x.d(P.big[2]), x.d(P.big[3]));
+    x.ck(bwla_q_launch_center(x.d(P.big[3]), nullptr, x.d(P.ybar), P.n, P.m, x.st));
+    procrustes_held(x, which, Wres, R1, c, s2, Rnew);
 }
 
 // rank-k truncation of Y (n x m) into A2 (n x k), Bt2 (m x k); lam gets the k leading eigenvalues
@@ -294,12 +306,12 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     times_vs(oth, m, k, Bt2, nullptr);
 }
 
-// M <- truncation of M - (1/mu) dL/dM; A, Bt in place.  Leaves the scratch's big arrays stale.
-void psp(Ctx& x, const double* W, double* A, double* Bt, const double* R1, const double* R2, const double* c,
+// M <- truncation of M - (1/mu) dL/dM; A, Bt in place.  big[4] holds the centered rotated rows of W - M.
+// Leaves the scratch's big arrays stale.
+void psp(Ctx& x, double* A, double* Bt, const double* R1, const double* R2, const double* c,
          const double* s2, double mu, int iters, double tol, double* lam) {
     const QPlan& P = x.P;
     double *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *X = x.d(P.big[4]), *fac = x.d(P.scal);
-    okt(x, W, A, Bt, R1, R2, X, nullptr);
     x.ck(bwla_q_launch_prox_factor(s2, P.n, P.m, mu, fac, x.st));
     x.ck(bwla_q_launch_gradx(X, c, s2, fac, P.n, P.m, Y, x.st));          // Y <- (G_X H) / mu, sign folded in
     rotate_rows(x, Y, R1, R2, true, half, Y);                             // back through R^T
@@ -442,7 +454,8 @@ bwla_status_t bwla_q_psp_step(const double* d_W, double* d_A, double* d_Bt, int3
     Ctx x;
     const bwla_status_t s = open_ctx(x, n, m, n1, n2, k, d_ws, ws_bytes, stream);
     if (s != BWLA_OK) return s;
-    psp(x, d_W, d_A, d_Bt, d_R1, d_R2, d_c, d_s2, mu, iters, tol, x.d(x.P.lam));
+    okt(x, d_W, d_A, d_Bt, d_R1, d_R2, x.d(x.P.big[4]), nullptr);
+    psp(x, d_A, d_Bt, d_R1, d_R2, d_c, d_s2, mu, iters, tol, x.d(x.P.lam));
     return finish(x);
 }
 
@@ -462,7 +475,7 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
     if (s != BWLA_OK) return s;
     const QPlan& P = x.P;
     const size_t nm = (size_t)P.n * P.m;
-    double *W = x.d(P.big[0]), *Y = x.d(P.big[3]), *X = x.d(P.big[4]);
+    double *W = x.d(P.big[0]), *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *X = x.d(P.big[4]);
     double *R1 = x.d(P.R1), *R2 = x.d(P.R2), *A = x.d(P.A), *Bt = x.d(P.Bt), *ybar = x.d(P.ybar);
     double* c = d_c ? d_c : x.d(P.c);
     double* s2 = d_s2 ? d_s2 : x.d(P.s2);
@@ -487,21 +500,36 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
         x.ck(bwla_q_launch_fill_value(Bt, (size_t)P.m * k, 0.0, x.st));
         x.ck(bwla_q_launch_fill_value(lam, k, 0.0, x.st));
     }
-    const double* Wres = okt(x, W, A, Bt, R1, R2, X, ybar);
+    // From here on, at the top of a round, big[2..4] and ybar belong to the current (M, R1, R2): half =
+    // (W - M) R2, Y = (W - M) R, X = Y H.  What a step reads is made once and not again by the step behind
+    // it: the proximal step takes X, the update of R1 half and Y, and R2's half again, as R2 is still the
+    // old one (every step on its own rotated all rows anew: 7 rotations a round, now 3.5, some 200 us each
+    // half on 11008 x 4096).
+    const double* Wres = W;                                               // M = 0
+    rotate_rows(x, W, R1, R2, false, half, Y);
+    x.ck(bwla_q_launch_center(Y, X, ybar, P.n, P.m, x.st));
     x.ck(bwla_q_launch_init_theta(X, P.n, P.m, s2_min, c, s2, x.st));
     record();
     for (int t = 0; t < t_outer; ++t) {
-        // X holds the centered rows at the current M, R1, R2
         x.ck(bwla_q_launch_em(X, P.n, P.m, s2_min, c, s2, x.st));
         record();
         if (k > 0) {
-            psp(x, W, A, Bt, R1, R2, c, s2, mu, svd_iters, svd_tol, lam);
+            psp(x, A, Bt, R1, R2, c, s2, mu, svd_iters, svd_tol, lam);
             Wres = okt(x, W, A, Bt, R1, R2, X, ybar);
         }
         record();
-        procrustes(x, 1, Wres, R1, R2, c, s2, R1);
-        procrustes(x, 2, Wres, R1, R2, c, s2, R2);
-        Wres = okt(x, W, A, Bt, R1, R2, X, ybar);
+        procrustes_held(x, 1, Wres, R1, c, s2, R1);
+        rotate_left(x, R1, half, false, Y);
+        x.ck(bwla_q_launch_center(Y, nullptr, ybar, P.n, P.m, x.st));
+        procrustes_held(x, 2, Wres, R1, c, s2, R2);
+        if (k > 0 || t + 1 == t_outer) {
+            // half = R1^T (W - M) of the update above: one product makes Y.  The next round's update of R1
+            // needs (W - M) R2 there, which the proximal step's okt makes when there is one
+            gemm(x, qgemm_plain(half, R2, Y, P.n * P.n1, P.n2, P.n2));
+        } else {
+            rotate_rows(x, Wres, R1, R2, false, half, Y);
+        }
+        x.ck(bwla_q_launch_center(Y, X, ybar, P.n, P.m, x.st));
         record();
     }
     // Y = (W - M)(R1 (x) R2) at the final factors

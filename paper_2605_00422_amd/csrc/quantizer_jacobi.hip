@@ -3,7 +3,8 @@
 // R = U V^T from the SVD of an n1 x n1 or n2 x n2 matrix) and the small eigenproblems of the
 // subspace iteration behind the truncated SVD of the proximal step (Sec. 3.2; App. A.2.3).
 //
-// The columns of G are kept as contiguous rows of a work array (column j = row j), V likewise.
+// The columns of G are kept as contiguous rows of a work array (column j = row j, in LDS padded to an
+// even length so that a lane moves two elements at a time), V likewise.
 // A sweep visits every pair of columns once, in the round-robin order of a tournament: n / 2
 // disjoint pairs per round, n - 1 rounds.  A pair belongs to a group of lanes that holds both columns
 // in registers (up to four elements per lane), takes the three inner products, and applies the plane
@@ -53,6 +54,24 @@ __device__ __forceinline__ double jgroup_sum(double v) {
     return v;
 }
 
+// Tangent t, cosine of the plane rotation that makes columns with squared norms al, be and inner product
+// ga orthogonal; the sine is cs * t.  Only cs^2 + sn^2 = 1 has to hold to the last bit or so (it keeps the
+// columns' norms and V orthogonal): the tangent may be off by the 2^-20 or better of the hardware's
+// reciprocal and root, which leaves that fraction of the inner product for the next sweep.  With the
+// full-precision quotient, root and reciprocal root this chain of dependent instructions was most of a round.
+__device__ __forceinline__ void jrotation(double al, double be, double ga, double& tt, double& cs) {
+    const double zeta = (be - al) * 0.5 * __builtin_amdgcn_rcp(ga);
+    tt = copysign(__builtin_amdgcn_rcp(fabs(zeta) + __builtin_amdgcn_sqrt(fma(zeta, zeta, 1.0))), zeta);
+    const double w = fma(tt, tt, 1.0);                      // in [1, 2]
+    double y = __builtin_amdgcn_rsq(w);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {                           // y += y (1 - w y^2) / 2: full precision from 2^-20
+        const double e = fma(-w * y, y, 1.0);
+        y = fma(0.5 * y, e, y);
+    }
+    cs = y;
+}
+
 // GW: lanes per pair (16 for n <= 64, 32 for n <= 128, else 64); LDS: the work arrays live in dynamic LDS.
 // ACCV: the rotations are accumulated into V.  Without it (a symmetric positive semidefinite G, whose
 // left and right singular vectors coincide) the right singular vectors are the normalized columns of
@@ -63,48 +82,76 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
     constexpr int JT = jacobi_threads(GW), JW = JT / 64;
     const int n = a.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
-    extern __shared__ double jlds[];
+    extern __shared__ __align__(16) double jlds[];
     double* Wc = LDS ? jlds : a.work;
-    double* Vc = Wc + (size_t)n * n;
-    __shared__ int pos[2][JMAX + 2];
+    const int ld = LDS ? (n + 1) & ~1 : n;                              // pitch of a column
+    double* Vc = Wc + (size_t)n * ld;
     __shared__ int rotated;
     __shared__ double sg[JMAX];
     __shared__ int ord[JMAX];
-    for (int e = t; e < n * n; e += JT) {
-        const int j = e / n, i = e - j * n;
-        Wc[e] = a.G[(size_t)i * n + j];
+    for (int e = t; e < n * ld; e += JT) {
+        const int j = e / ld, i = e - j * ld;
+        Wc[e] = i < n ? a.G[(size_t)i * n + j] : 0.0;
         if (ACCV) Vc[e] = i == j ? 1.0 : 0.0;
     }
     const int np = (n + 1) & ~1;
-    for (int i = t; i < np; i += JT) pos[0][i] = i;
-    int cur = 0;
     constexpr int GROUPS = JT / GW;
     const int gid = t / GW, sl = t % GW;
+    // element pair u of a lane: in LDS two neighbours (16-byte accesses: 16 lanes cover all banks once;
+    // single doubles had the wavefront's four columns meet in the same banks), else GW apart
+    auto idx0 = [&](int u) { return LDS ? 2 * (sl + GW * u) : sl + 2 * GW * u; };
+    constexpr int D = LDS ? 1 : GW;
+    auto load = [&](const double* c, int u, bool live, double& e0, double& e1) {
+        const int i = idx0(u);
+        if (LDS) {
+            double2 v = make_double2(0.0, 0.0);
+            if (live && i < n) v = *reinterpret_cast<const double2*>(c + i);
+            e0 = v.x; e1 = v.y;
+        } else {
+            e0 = live && i < n ? c[i] : 0.0;
+            e1 = live && i + D < n ? c[i + D] : 0.0;
+        }
+    };
+    auto store = [&](double* c, int u, double e0, double e1) {
+        const int i = idx0(u);
+        if (LDS) {
+            if (i < n) *reinterpret_cast<double2*>(c + i) = make_double2(e0, e1);   // (the padding stays zero)
+        } else {
+            if (i < n) c[i] = e0;
+            if (i + D < n) c[i + D] = e1;
+        }
+    };
     __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
         if (t == 0) rotated = 0;
         __syncthreads();
         for (int round = 0; round < np - 1; ++round) {
+            // the column at position i of the tournament: 0 stays, the others move on by one per round
+            auto at = [&](int i) {
+                const int v = i - 1 - round;
+                return i == 0 ? 0 : 1 + (v < 0 ? v + np - 1 : v);
+            };
             for (int base = 0; base < np / 2; base += GROUPS) {        // the same trip count in every lane
                 const int pr = base + gid;
                 int p = 0, q = 0;
                 bool live = pr < np / 2;
                 if (live) {
-                    p = pos[cur][pr];
-                    q = pos[cur][np - 1 - pr];
+                    p = at(pr);
+                    q = at(np - 1 - pr);
                     live = p < n && q < n;                              // else the bye of an odd n
                     if (p > q) { const int s = p; p = q; q = s; }
                 }
-                double* xp = Wc + (size_t)p * n;
-                double* yp = Wc + (size_t)q * n;
+                double* xp = Wc + (size_t)p * ld;
+                double* yp = Wc + (size_t)q * ld;
                 double x[4], y[4];
                 double al = 0.0, be = 0.0, ga = 0.0;
 #pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    load(xp, u, live, x[2 * u], x[2 * u + 1]);
+                    load(yp, u, live, y[2 * u], y[2 * u + 1]);
+                }
+#pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int e = sl + GW * u;
-                    const bool in = live && e < n;
-                    x[u] = in ? xp[e] : 0.0;
-                    y[u] = in ? yp[e] : 0.0;
                     al += x[u] * x[u];
                     be += y[u] * y[u];
                     ga += x[u] * y[u];
@@ -112,33 +159,28 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                 al = jgroup_sum<GW>(al);
                 be = jgroup_sum<GW>(be);
                 ga = jgroup_sum<GW>(ga);
-                // (|ga| > 1e-15 sqrt(al be), without the root; four special-function calls a rotation instead
-                // of six: their dependent chain is most of what a round costs)
+                // (|ga| > 1e-15 sqrt(al be), without the root)
                 if (live && al > 0.0 && be > 0.0 && ga * ga > 1.0e-30 * (al * be)) {
-                    const double zeta = (be - al) / (2.0 * ga);
-                    const double tt = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    const double cs = rsqrt(1.0 + tt * tt), sn = cs * tt;
-                    double* vp = Vc + (size_t)p * n;
-                    double* vq = Vc + (size_t)q * n;
+                    double tt, cs;
+                    jrotation(al, be, ga, tt, cs);
+                    const double sn = cs * tt;
+                    double* vp = Vc + (size_t)p * ld;
+                    double* vq = Vc + (size_t)q * ld;
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int e = sl + GW * u;
-                        if (e < n) {
-                            xp[e] = cs * x[u] - sn * y[u];
-                            yp[e] = sn * x[u] + cs * y[u];
-                            if (ACCV) {
-                                const double vx = vp[e], vy = vq[e];
-                                vp[e] = cs * vx - sn * vy;
-                                vq[e] = sn * vx + cs * vy;
-                            }
+                    for (int u = 0; u < 2; ++u) {
+                        store(xp, u, cs * x[2 * u] - sn * y[2 * u], cs * x[2 * u + 1] - sn * y[2 * u + 1]);
+                        store(yp, u, sn * x[2 * u] + cs * y[2 * u], sn * x[2 * u + 1] + cs * y[2 * u + 1]);
+                        if (ACCV) {
+                            double a0, a1, b0, b1;
+                            load(vp, u, true, a0, a1);
+                            load(vq, u, true, b0, b1);
+                            store(vp, u, cs * a0 - sn * b0, cs * a1 - sn * b1);
+                            store(vq, u, sn * a0 + cs * b0, sn * a1 + cs * b1);
                         }
                     }
                     if (sl == 0) rotated = 1;
                 }
             }
-            // next round of the tournament: position 0 stays, the others move on by one
-            for (int i = t; i < np; i += JT) pos[cur ^ 1][i] = i == 0 ? pos[cur][0] : (i == 1 ? pos[cur][np - 1] : pos[cur][i - 1]);
-            cur ^= 1;
             __syncthreads();
         }
         if (!rotated) break;
@@ -146,7 +188,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     }
     for (int j = w; j < n; j += JW) {
         double s = 0.0;
-        for (int e = lane; e < n; e += 64) s += Wc[(size_t)j * n + e] * Wc[(size_t)j * n + e];
+        for (int e = lane; e < n; e += 64) s += Wc[(size_t)j * ld + e] * Wc[(size_t)j * ld + e];
         s = jgroup_sum<64>(s);
         if (lane == 0) sg[j] = sqrt(s);
     }
@@ -163,8 +205,8 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         double scale = s > 0.0 ? (a.pw == 0.0 ? 1.0 : pow(s, a.pw)) : 0.0;
         if (!ACCV && s > 0.0) scale /= s;                   // v_j = the column of the rotated G over its norm
         for (int e = lane; e < n; e += 64) {
-            if (a.Ws) a.Ws[(size_t)jj * n + e] = Wc[(size_t)j * n + e];
-            if (a.Vs) a.Vs[(size_t)jj * n + e] = scale * (ACCV ? Vc[(size_t)j * n + e] : Wc[(size_t)j * n + e]);
+            if (a.Ws) a.Ws[(size_t)jj * n + e] = Wc[(size_t)j * ld + e];
+            if (a.Vs) a.Vs[(size_t)jj * n + e] = scale * (ACCV ? Vc[(size_t)j * ld + e] : Wc[(size_t)j * ld + e]);
         }
     }
     if (t == 0 && a.prev_sig && a.done) {
@@ -188,7 +230,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st) {
     if (j.n < 1 || j.n > JMAX) return hipErrorInvalidValue;
     const bool in_lds = j.n <= (j.sym ? JLDS_SYM : JLDS);
-    const size_t lds = in_lds ? (size_t)(j.sym ? 1 : 2) * j.n * j.n * sizeof(double) : 0;
+    const size_t lds = in_lds ? (size_t)(j.sym ? 1 : 2) * j.n * ((j.n + 1) & ~1) * sizeof(double) : 0;
     auto launch = [&](auto kern, int threads) {
         if (lds > 48 * 1024) {
             const hipError_t e = bwla_ensure_lds((const void*)kern, lds);

@@ -4,11 +4,13 @@
 // (it stays in L2 between the passes of one kernel).  Sums are taken per thread in a fixed order,
 // then over the wavefront by butterflies and over the four wavefronts in wavefront order, so that a
 // result does not depend on the launch.
+#include "bwla_internal.h"
 #include "quantizer_internal.h"
 
 namespace {
 
 constexpr int RT = 256;
+constexpr int KEEP_M = 10240;
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -63,21 +65,32 @@ __global__ __launch_bounds__(RT) void init_theta_kernel(const double* X, int m, 
     }
 }
 
-// 2 r^+ - 1 = tanh(c x / s^2): the two densities' ratio is exp(2 c x / s^2) (App. A.2.2, E step)
+// 2 r^+ - 1 = tanh(c x / s^2): the two densities' ratio is exp(2 c x / s^2) (App. A.2.2, E step).
+// The hyperbolic tangent is what the kernels that use it are bound by (two passes over a row, each with
+// its own tanh, took 460 us on 11008 x 4096 where the row's two reads take some 100).  Rows of up to
+// KEEP_M columns therefore keep the first pass's values in LDS (80 KiB at most: two workgroups a CU stay
+// resident); longer rows compute them twice, as a workgroup would otherwise have a CU to itself.
 __device__ __forceinline__ double signed_resp(double x, double c, double inv_s2) { return tanh(c * x * inv_s2); }
 
 // one EM update of a row's mixture (App. A.2.2): c from the responsibilities at the old parameters,
-// then s^2 with the new c
+// then s^2 with the new c.  `keep` (dynamic LDS, m doubles when KEEP) holds the responsibilities between
+// the two sums.
+template <bool KEEP>
 __global__ __launch_bounds__(RT) void em_kernel(const double* X, int m, double s2_min, double* c, double* s2) {
+    extern __shared__ double keep[];
     __shared__ double sh[4];
     const double* x = X + (size_t)blockIdx.x * m;
     const double c0 = c[blockIdx.x], inv = 1.0 / s2[blockIdx.x];
     double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += signed_resp(x[j], c0, inv) * x[j];
+    for (int j = threadIdx.x; j < m; j += RT) {
+        const double t = signed_resp(x[j], c0, inv);
+        if (KEEP) keep[j] = t;                              // read back by this thread only
+        s += t * x[j];
+    }
     const double c1 = block_sum(s, sh) / m;
     double q = 0.0;
     for (int j = threadIdx.x; j < m; j += RT) {
-        const double r = 0.5 * (1.0 + signed_resp(x[j], c0, inv));
+        const double r = 0.5 * (1.0 + (KEEP ? keep[j] : signed_resp(x[j], c0, inv)));
         const double dp = x[j] - c1, dm = x[j] + c1;
         q += r * dp * dp + (1.0 - r) * dm * dm;
     }
@@ -94,12 +107,20 @@ __global__ __launch_bounds__(RT) void nll_rows_kernel(const double* X, int m, co
     const double* x = X + (size_t)blockIdx.x * m;
     const double ci = c[blockIdx.x], v = s2[blockIdx.x];
     const double lognorm = -0.5 * log(2.0 * 3.14159265358979323846 * v), h = 0.5 / v;
+    // sum of max(lp, lm) + log1p(exp(-|lp - lm|)) + log(1/2): the logarithms of up to sixteen factors
+    // 1 + exp(.) in [1, 2] are taken as one of their product (a factor's rounding, 1.1e-16, is that of the
+    // sum it went into), which leaves one special function per entry (243 us with both on 11008 x 4096)
     double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double dp = x[j] - ci, dm = x[j] + ci;
-        const double lp = lognorm - dp * dp * h, lm = lognorm - dm * dm * h;
-        const double hi = fmax(lp, lm), lo = fmin(lp, lm);
-        s -= hi + log1p(exp(lo - hi)) + log(0.5);
+    for (int j0 = threadIdx.x; j0 < m; j0 += 16 * RT) {
+        double prod = 1.0;
+        for (int j = j0; j < m && j < j0 + 16 * RT; j += RT) {
+            const double dp = x[j] - ci, dm = x[j] + ci;
+            const double lp = lognorm - dp * dp * h, lm = lognorm - dm * dm * h;
+            const double hi = fmax(lp, lm), lo = fmin(lp, lm);
+            s -= hi + log(0.5);
+            prod *= 1.0 + exp(lo - hi);
+        }
+        s -= log(prod);
     }
     const double tot = block_sum(s, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
@@ -115,16 +136,25 @@ __global__ __launch_bounds__(RT) void sum_scale_kernel(const double* part, int n
 // MM targets on the uncentered rotated rows (App. A.2.2, "MM Surrogate"): m_ij = (2 r_ij - 1) c_i at
 // x = y - ybar; target H m_i + ybar_i 1 (the concave part of the centered objective majorized by its
 // tangent); stored times lambda_i = 1 / s_i^2, the weight of the row in the Procrustes matrices
+template <bool KEEP>
 __global__ __launch_bounds__(RT) void targets_kernel(const double* Y, const double* ybar, const double* c, const double* s2,
                                                      int m, double* T) {
+    extern __shared__ double keep[];
     __shared__ double sh[4];
     const double* y = Y + (size_t)blockIdx.x * m;
     double* tg = T + (size_t)blockIdx.x * m;
     const double yb = ybar[blockIdx.x], ci = c[blockIdx.x], lam = 1.0 / s2[blockIdx.x];
     double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += ci * signed_resp(y[j] - yb, ci, lam);
+    for (int j = threadIdx.x; j < m; j += RT) {
+        const double t = ci * signed_resp(y[j] - yb, ci, lam);
+        if (KEEP) keep[j] = t;
+        s += t;
+    }
     const double mbar = block_sum(s, sh) / m;
-    for (int j = threadIdx.x; j < m; j += RT) tg[j] = lam * (ci * signed_resp(y[j] - yb, ci, lam) - mbar + yb);
+    for (int j = threadIdx.x; j < m; j += RT) {
+        const double t = KEEP ? keep[j] : ci * signed_resp(y[j] - yb, ci, lam);
+        tg[j] = lam * (t - mbar + yb);
+    }
 }
 
 __global__ __launch_bounds__(RT) void prox_factor_kernel(const double* s2, int n, double nm, double mu, double* fac) {
@@ -142,16 +172,25 @@ __global__ __launch_bounds__(RT) void prox_factor_kernel(const double* s2, int n
 
 // fac * H[(x - m) lambda]: minus the gradient of L_GMM in the centered coordinates, over mu
 // (App. A.2.2 for d L / d x_ij = (x_ij - m_ij) / (n m s_i^2); App. A.2.3 for the adjoint's H)
+template <bool KEEP>
 __global__ __launch_bounds__(RT) void gradx_kernel(const double* X, const double* c, const double* s2, const double* fac,
                                                    int m, double* GX) {
+    extern __shared__ double keep[];
     __shared__ double sh[4];
     const double* x = X + (size_t)blockIdx.x * m;
     double* gx = GX + (size_t)blockIdx.x * m;
     const double ci = c[blockIdx.x], lam = 1.0 / s2[blockIdx.x], f = fac[0];
     double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += (x[j] - ci * signed_resp(x[j], ci, lam)) * lam;
+    for (int j = threadIdx.x; j < m; j += RT) {
+        const double g = (x[j] - ci * signed_resp(x[j], ci, lam)) * lam;
+        if (KEEP) keep[j] = g;
+        s += g;
+    }
     const double gbar = block_sum(s, sh) / m;
-    for (int j = threadIdx.x; j < m; j += RT) gx[j] = f * ((x[j] - ci * signed_resp(x[j], ci, lam)) * lam - gbar);
+    for (int j = threadIdx.x; j < m; j += RT) {
+        const double g = KEEP ? keep[j] : (x[j] - ci * signed_resp(x[j], ci, lam)) * lam;
+        gx[j] = f * (g - gbar);
+    }
 }
 
 __device__ __forceinline__ uint32_t hash32(uint32_t x) {
@@ -252,6 +291,20 @@ __global__ __launch_bounds__(RT) void row_stats_kernel(const double* Y, int m, d
     }
 }
 
+// launches `kept` with a row of m doubles of LDS where that fits, else `again`
+template <typename Kern, typename... Args>
+hipError_t launch_rows(Kern kept, Kern again, int n, int m, hipStream_t st, Args... args) {
+    const size_t lds = (size_t)m * sizeof(double);
+    if (m <= KEEP_M) {
+        const hipError_t e = bwla_ensure_lds((const void*)kept, lds + 64);      // (+ the sums' static words)
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kept, dim3(n), dim3(RT), lds, st, args...);
+    } else {
+        hipLaunchKernelGGL(again, dim3(n), dim3(RT), 0, st, args...);
+    }
+    return hipGetLastError();
+}
+
 inline int flat_blocks(size_t count) {
     const size_t b = (count + RT - 1) / RT;
     return (int)(b < 4096 ? (b ? b : 1) : 4096);
@@ -276,8 +329,7 @@ hipError_t bwla_q_launch_init_theta(const double* X, int n, int m, double s2_min
     return hipGetLastError();
 }
 hipError_t bwla_q_launch_em(const double* X, int n, int m, double s2_min, double* c, double* s2, hipStream_t st) {
-    hipLaunchKernelGGL(em_kernel, dim3(n), dim3(RT), 0, st, X, m, s2_min, c, s2);
-    return hipGetLastError();
+    return launch_rows(em_kernel<true>, em_kernel<false>, n, m, st, X, m, s2_min, c, s2);
 }
 hipError_t bwla_q_launch_nll(const double* X, int n, int m, const double* c, const double* s2, double* row_part,
                              double* out, hipStream_t st) {
@@ -289,8 +341,7 @@ hipError_t bwla_q_launch_nll(const double* X, int n, int m, const double* c, con
 }
 hipError_t bwla_q_launch_targets(const double* Y, const double* ybar, const double* c, const double* s2, int n, int m,
                                  double* T, hipStream_t st) {
-    hipLaunchKernelGGL(targets_kernel, dim3(n), dim3(RT), 0, st, Y, ybar, c, s2, m, T);
-    return hipGetLastError();
+    return launch_rows(targets_kernel<true>, targets_kernel<false>, n, m, st, Y, ybar, c, s2, m, T);
 }
 hipError_t bwla_q_launch_prox_factor(const double* s2, int n, int m, double mu, double* fac, hipStream_t st) {
     hipLaunchKernelGGL(prox_factor_kernel, dim3(1), dim3(RT), 0, st, s2, n, (double)n * m, mu, fac);
@@ -298,8 +349,7 @@ hipError_t bwla_q_launch_prox_factor(const double* s2, int n, int m, double mu, 
 }
 hipError_t bwla_q_launch_gradx(const double* X, const double* c, const double* s2, const double* fac, int n, int m,
                                double* GX, hipStream_t st) {
-    hipLaunchKernelGGL(gradx_kernel, dim3(n), dim3(RT), 0, st, X, c, s2, fac, m, GX);
-    return hipGetLastError();
+    return launch_rows(gradx_kernel<true>, gradx_kernel<false>, n, m, st, X, c, s2, fac, m, GX);
 }
 hipError_t bwla_q_launch_fill_hash(double* Q, size_t count, uint32_t seed, hipStream_t st) {
     hipLaunchKernelGGL(fill_hash_kernel, dim3(flat_blocks(count)), dim3(RT), 0, st, Q, count, seed);
