@@ -12,7 +12,6 @@
 //   gemm_prefill_kernel         the remaining shapes: code tiles shared through LDS, double
 //                               buffered, one barrier per 128 columns
 #include "bwla_internal.h"
-#include <algorithm>
 
 namespace {
 
@@ -678,12 +677,75 @@ hipError_t launch_direct(const bwla_layer_t* L, const int8_t* dq, const float* d
     return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, false, WN>);
 }
 
-inline int64_t tiles_for(int64_t M, int64_t N, int BM, int BN) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
+// ------------------------------------------------------------------------------------------
+// Which tile serves M tokens and N channels.  Every variant below wins somewhere between 17 and 4096
+// tokens, and what decides is how its tiles come out in rounds over the CUs: 257 tokens x 8192 channels
+// are 104 to 128 large tiles (half the chip, half of the rows padding) or 430 tiles of 64 x 96, two to a
+// CU.  So each variant carries a small cost, in microseconds: a tile takes base[r - 1] + slice[r - 1] per
+// 128-column slice of K that a wavefront contracts when r workgroups share the CU, full rounds run at the
+// largest r, the last one at the r that it comes to, and `start` is paid once; the smallest sum is taken.  The constants are a
+// least-squares fit of 266 shapes (14 layers, K 512 .. 28672, N 1000 .. 28672, at 19 token counts),
+// within 6 % of the measurement on average.  Over those shapes the choice takes 0.884 of the time of the
+// rules that stood here before (large tiles from 72 of them on, small ones below), 0.51 at best, and
+// stays within 1 % of the best variant on average: 8192 -> 8192 at 257 tokens 62.7 -> 35.8 us,
+// 11008 -> 4096 at 640 72.0 -> 43.4, 4096 -> 22016 at 2048 259 -> 218, 28672 -> 8192 at 4096 735 -> 735.
+struct GdVariant {
+    int ntl, wm, wk, nb, wn;      // template arguments of gemm_prefill_direct_kernel
+    int resident;                 // workgroups a CU holds (LDS of the tile rings, registers)
+    float start, base[4], slice[4];
+    float later;                  // factor when there is more than one round: these four have no neighbour on
+                                  // the CU whose contraction would cover their epilogue's stores
+};
+constexpr GdVariant GD_VARIANTS[] = {
+    {1, 1, 4, 4, 1, 1, 0.4f, {10.3f}, {0.369f}, 1.0f},                                  //  64 x 32, K split in four
+    {2, 1, 4, 4, 1, 1, 0.0f, {13.6f}, {0.433f}, 1.0f},                                  //  64 x 64, K split in four
+    {1, 1, 1, 4, 1, 4, 0.0f, {9.7f, 10.9f, 11.6f, 12.2f}, {0.271f, 0.283f, 0.306f, 0.347f}, 1.0f},   //  64 x 32
+    {2, 1, 2, 4, 1, 2, 1.1f, {11.9f, 14.0f}, {0.358f, 0.407f}, 1.0f},                   //  64 x 64, K split in two
+    {3, 1, 2, 4, 1, 2, 0.3f, {15.2f, 17.8f}, {0.452f, 0.520f}, 1.0f},                   //  64 x 96, K split in two
+    {2, 2, 1, 4, 2, 1, 0.0f, {14.6f}, {0.362f}, 1.0f},                                  // 128 x 128
+    {3, 2, 1, 2, 2, 2, 0.4f, {15.6f, 22.5f}, {0.488f, 1.090f}, 1.0f},                   // 128 x 192
+    {4, 1, 1, 4, 4, 1, 0.0f, {20.8f}, {0.592f}, 1.06f},                                 //  64 x 512: codes once per CU
+    {5, 1, 1, 4, 4, 1, 0.0f, {24.9f}, {0.717f}, 1.06f},                                 //  64 x 640
+    {4, 4, 1, 4, 1, 1, 0.0f, {20.8f}, {0.602f}, 1.06f},                           // 256 x 128, the deeper ring
+    {5, 4, 1, 4, 1, 1, 0.0f, {24.3f}, {0.721f}, 1.06f},                           // 256 x 160
+    {4, 4, 1, 2, 1, 2, 2.5f, {18.6f, 29.0f}, {0.592f, 1.390f}, 1.0f},                   // 256 x 128
+};
+constexpr int GD_NVARIANTS = sizeof(GD_VARIANTS) / sizeof(GD_VARIANTS[0]);
 
-// fraction of the chip kept busy by `tiles` equal workgroups on 256 CUs (last round may be ragged)
-inline double wave_eff(int64_t tiles) {
-    const int64_t rounds = (tiles + 255) / 256;
-    return (double)tiles / (double)(rounds * 256);
+inline float gd_cost(const GdVariant& v, int64_t M, int64_t K, int64_t N, int64_t cus) {
+    const int64_t bm = v.wm * GD_ROWS, bn = v.wn * v.ntl * 32;
+    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), cap = cus * v.resident;
+    const float slices = (float)(((K >> 7) + v.wk - 1) / v.wk);
+    const int64_t full = tiles / cap, rem = tiles - full * cap;
+    float t = v.start + (float)full * (v.base[v.resident - 1] + v.slice[v.resident - 1] * slices);
+    if (rem > 0) {
+        const int r = (int)((rem + cus - 1) / cus);
+        t += v.base[r - 1] + v.slice[r - 1] * slices;
+    }
+    return tiles > cap ? t * v.later : t;
+}
+
+// index into GD_VARIANTS
+inline int gd_pick(int64_t M, int64_t K, int64_t N, int64_t cus) {
+    int best = 0;
+    float cost = gd_cost(GD_VARIANTS[0], M, K, N, cus);
+    for (int i = 1; i < GD_NVARIANTS; ++i) {
+        const float c = gd_cost(GD_VARIANTS[i], M, K, N, cus);
+        if (c < cost) { cost = c; best = i; }
+    }
+    return best;
+}
+
+template <int I>
+hipError_t launch_variant(int pick, const bwla_layer_t* L, const int8_t* dq, const float* dscale,
+                          const int32_t* dqsum, const float* dT, int64_t M, float* dY, int32_t* dacc,
+                          hipStream_t st, uint16_t* dH, bool a4) {
+    constexpr GdVariant v = GD_VARIANTS[I];
+    if (pick == I)
+        return launch_direct<v.ntl, v.wm, v.wk, v.nb, v.wn>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+    if constexpr (I + 1 < GD_NVARIANTS)
+        return launch_variant<I + 1>(pick, L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -694,52 +756,9 @@ bool bwla_gemm_prefill_streams(const bwla_layer_t* L) { return L->N >= 32 && (L-
 hipError_t bwla_launch_gemm_prefill(const bwla_layer_t* L, const int8_t* dq, const float* dscale,
                                     const int32_t* dqsum, const float* dT, int64_t M, float* dY,
                                     int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4) {
-    const int64_t N = L->N;
-    if (bwla_gemm_prefill_streams(L)) {
-        // register-streaming kernel.  Large batches: four wavefronts stacked along the tokens,
-        // 256 x 160 or 256 x 128 tiles, whichever fills the chip better.  Up to 128 tokens: one or
-        // two wavefronts per workgroup and narrow channel tiles, so that enough workgroups exist.
-        // (the large tiles need enough workgroups: 4096 x 4096 at 512 tokens has 52 of them and takes
-        // 36.9 us against 21.0 with one wavefront per 64 x 32 tile; 8192 x 8192 at 256 tokens 63.0
-        // against 35.8; at 104 workgroups the large tiles win, 38.6 against 44.0 and 64.0 against 77.8)
-        const int64_t big = std::min(tiles_for(M, N, 256, 160), tiles_for(M, N, 256, 128));
-        if (M > 128 && big > 72) {
-            const int64_t cus_big = bwla_device_cus();
-            // Four wavefronts side by side on the same 64 token rows (64 x 640 tiles) where such tiles come to
-            // whole rounds over the CUs: the code rows are then fetched once per CU and slice instead of four
-            // times (2048 x 25600 -> 5120: 217 -> 209 us against the 256 x 160 tiles).
-            const int64_t t640 = tiles_for(M, N, 64, 640);
-            if (N % 640 == 0 && t640 % cus_big == 0)
-                return launch_direct<5, 1, 1, 4, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-            // Output-heavy shapes (short rows of K, many channels: every round of tiles ends in a burst of
-            // stores) with an even number of 256 x 128 tiles per CU: two workgroups per CU, each with a
-            // ring of two slices (64 KiB of LDS, at most 256 registers), so that one workgroup's epilogue
-            // and first loads run under the other's contraction.  Measured against the one-workgroup
-            // variants at 4096 tokens: 8192 -> 8192 -3 .. -8 %, 8192 -> 28672 -5 .. -8 %, 28672 -> 8192 -1.5 %.
-            const int64_t t128 = tiles_for(M, N, 256, 128);
-            if (t128 >= 4 * cus_big && t128 % (2 * cus_big) == 0)
-                return launch_direct<4, 4, 1, 2>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-            const double d160 = wave_eff(tiles_for(M, N, 256, 160)), d128 = wave_eff(tiles_for(M, N, 256, 128));
-            if (d160 >= d128) return launch_direct<5, 4, 1, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-            return launch_direct<4, 4, 1, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-        }
-        // Few tokens (or few large tiles): the kernel is bound by how often the code rows are re-read (every workgroup
-        // reads all K of its tokens) and by how many wavefronts are in flight.  With t tiles of
-        // 64 x 32: up to one per CU, four wavefronts share a tile and split K; up to two per CU,
-        // 64 x 64 tiles shared by four wavefronts (half the code traffic, one workgroup per CU);
-        // more, one wavefront per 64 x 32 tile.  Measured (us), in that order of variants:
-        // 8192 x 8192 at 64 tokens (256 tiles) 17.1 / 21.6 / 27.8, at 128 (512) 33.3 / 23.1 / 29.1;
-        // 4096 -> 11008 at 64 (344) 21.8 / 15.8 / 17.3, at 128 (688) 33.5 / 30.7 / 19.1;
-        // 8192 -> 28672 at 64 (896) 62.0 / 42.2 / 31.2.
-        const int64_t tiles = ((M + 63) / 64) * ((N + 31) / 32);
-        const int64_t cus = bwla_device_cus();
-        if (tiles <= cus) return launch_direct<1, 1, 4, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-        if (tiles <= 2 * cus) return launch_direct<2, 1, 4, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-        // beyond three per CU the wavefronts' re-reads of the code rows load the L2 -> CU paths: 64 x 64
-        // tiles shared by two wavefronts halve them (8192 -> 28672 at 64 tokens, 896 tiles: 37.2 -> 32.2 us)
-        if (tiles > 3 * cus) return launch_direct<2, 1, 2, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-        return launch_direct<1, 1, 1, 4>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-    }
+    if (bwla_gemm_prefill_streams(L))
+        return launch_variant<0>(gd_pick(M, L->K, L->N, bwla_device_cus()), L, dq, dscale, dqsum, dT, M, dY, dacc, st,
+                                 dH, a4);
     // shapes the streaming kernel does not take (K not a multiple of 128, fewer than 32 channels):
     // LDS-tiled kernel, 64 x 128 or 128 x 128 tiles (it does not gate: the caller goes through Y)
     if (dH != nullptr || a4) return hipErrorInvalidValue;

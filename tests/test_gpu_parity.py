@@ -228,6 +228,71 @@ def test_nibble_packed_a4_codes(M, K, n1, n2, N, r):
     check_output(Y4[torch.from_numpy(rows).to(DEV)].cpu().numpy(), ref["Y"])
 
 
+@pytest.mark.parametrize("M,K,N,r", [
+    (17, 1152, 50, 16),         # 64 x 32 tiles, four wavefronts split K (9 slices: 3, 3, 3, 0)
+    (40, 256, 64, 8),           # 64 x 32 tiles, one wavefront
+    (65, 2048, 5120, 20),       # 64 x 64, K split in four
+    (70, 4096, 12302, 32),      # 64 x 64, K split in two; ragged channels
+    (257, 4992, 8192, 64),      # 64 x 96, K split in two (39 slices); the last row tile holds one token
+    (65, 128, 20000, 0),        # 128 x 128, one slice: the whole ring is padding
+    (300, 128, 12346, 33),      # 128 x 192
+    (129, 128, 28000, 70),      # 64 x 512, two chunks of ranks
+    (257, 1152, 28000, 16),     # 64 x 640
+    (400, 512, 20000, 96),      # 256 x 160
+    (1220, 512, 6300, 8),       # 256 x 128, ring of four
+    (520, 128, 20002, 64),      # 256 x 128, ring of two, two workgroups a CU
+])
+def test_streaming_gemm_tiles(M, K, N, r):
+    """One shape for each tile the dispatch of the streaming GEMM chooses from: int32 accumulators equal to
+    an exact product, Y to its rounding, the gated and the nibble-packed forms against it."""
+    from parity_util import DEV
+    from paper_2605_00422_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K + N)
+    n1, n2 = B.kron_factor(K)
+    W = torch.randn(N, K, device=DEV, generator=g)
+    U = V = None
+    if r:
+        U = torch.randn(K, r, device=DEV, generator=g).half().float()
+        V = (torch.randn(N, r, device=DEV, generator=g) * 0.1).half().float()
+    layer = B.pack_weights(W, torch.eye(n1, device=DEV), torch.eye(n2, device=DEV), U, V, n1, n2)
+    act = B.Activations(layer, M)
+    act.q.copy_(torch.randint(-7, 8, (M, K), device=DEV, generator=g))
+    act.qsum.copy_(act.q.sum(1, dtype=torch.int32).reshape(act.qsum.shape))
+    act.scale.copy_((torch.rand(act.scale.shape, device=DEV, generator=g) + 0.5) * 0.01)
+    low = mag = 0.0
+    if r:
+        act.T.copy_(torch.randn(act.T.shape, device=DEV, generator=g))
+        low = act.T.double() @ V.double().t()
+        mag = act.T.double().abs() @ V.double().abs().t()
+    sgn, alpha = B.unpack_signs(layer)
+    acc = act.q.float() @ sgn.float().t()                   # exact: |acc| <= 7 K < 2^24
+    main = act.scale.double().reshape(-1, 1) * alpha.double() * acc.double()
+    want = main + low
+    Y = torch.full((M, N), float("nan"), device=DEV)
+    got = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+    B.linear_forward(layer, act, Y, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, acc.to(torch.int32)), "accumulators"
+    # a few fp32 roundings of the main term, T to 2^-22 of its row's largest entry (below 6), fp32 sums of r terms
+    bound = 2.0 ** -20 * (main.abs() + mag) + 2.0 ** -22 * 6.0 * 0.5 * r + 1e-12
+    assert bool(((Y.double() - want).abs() <= bound).all()), "output"
+    if M > 16:
+        q4 = B.pack_codes_a4(act.q)
+        Y4 = torch.full((M, N), float("nan"), device=DEV)
+        B.linear_forward_a4(layer, q4, act, Y4)
+        torch.cuda.synchronize()
+        assert torch.equal(Y4, Y), "packed codes"
+    H = torch.full((M, N // 2), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = B.swiglu_workspace_size(layer, M)
+    B.linear_forward_swiglu(layer, act, H, torch.empty(ws, dtype=torch.uint8, device=DEV) if ws else None)
+    torch.cuda.synchronize()
+    gate, up = Y.double()[:, 0::2], Y.double()[:, 1::2]
+    h = gate / (1.0 + torch.exp(-gate)) * up
+    # bf16's half step and the fp32 exponential
+    assert bool(((H.double() - h).abs() <= (2.0 ** -8 + 1e-5) * h.abs() + 1e-30).all()), "gated output"
+
+
 def test_nibble_packed_a4_refusals():
     from parity_util import pack_on_gpu, DEV
     from paper_2605_00422_amd import binding as B
