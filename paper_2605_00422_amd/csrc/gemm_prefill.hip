@@ -9,6 +9,8 @@
 // with (w >> j) & 0x01010101 right before the MFMA that consumes it.
 //   gemm_prefill_direct_kernel  the main path (K % 128 == 0, N >= 32): every wavefront streams
 //                               its own operands, no workgroup barriers (described further down)
+//   gemm_prefill_shared_kernel  the same with one copy of the code rows for the wavefronts of a
+//                               workgroup, one barrier a slice
 //   gemm_prefill_kernel         the remaining shapes: code tiles shared through LDS, double
 //                               buffered, one barrier per 128 columns
 #include "bwla_internal.h"
@@ -240,8 +242,10 @@ constexpr int gd_vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4
 // A row of a slice is then 64 bytes; a lane reads one packed piece for two contraction steps and
 // moves each nibble to the top of its byte, (x << 4) & 0xf0.. and x & 0xf0..: int8 operands worth 16
 // times the code, so the accumulators are exact multiples of 16 and are shifted down once at the end.
-template <int NTL, int WM, int WK, int NB, bool GATED = false, bool A4 = false, int WN = 1>
-__global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefill_direct_kernel(
+// SHARED: the WN wavefronts side by side work on one ring of code tiles, of which each copies its part,
+// instead of a private ring each: see gemm_prefill_shared_kernel.
+template <int NTL, int WM, int WK, int NB, bool GATED, bool A4, int WN, bool SHARED>
+__device__ __forceinline__ void gd_body(
     const uint4* __restrict__ bits, int chunks, int row_tiles, const int8_t* __restrict__ q, int M, int K,
     const float* __restrict__ scale, const int32_t* __restrict__ qsum, const __half* __restrict__ alpha,
     const __half* __restrict__ V, const float* __restrict__ T, int r, float* __restrict__ Y, int N,
@@ -258,14 +262,16 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
     // (NB = ring depth, 4 or 2: code tiles in LDS and weight slots in registers)
     static_assert(NB == 4 || NB == 2, "ring depth");
     constexpr int NCOPY = A4 ? 4 : 8;                            // code copies per slice
-    constexpr int GD_PER_SLICE = NTL + NCOPY;
+    static_assert(!SHARED || (WK == 1 && NCOPY % WN == 0), "every wavefront copies the same number of pieces");
+    constexpr int MYCOPY = SHARED ? NCOPY / WN : NCOPY;          // those that this wavefront issues
+    constexpr int GD_PER_SLICE = NTL + MYCOPY;
     constexpr int GD_YOUNGER = (NB - 2) * GD_PER_SLICE;
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wk = WK == 1 ? 0 : wave / WM, wn = WK == 1 ? wave / WM : 0;
     const int l32 = lane & 31, lg = lane >> 5;
-    char* mytile = smem + wave * (NB * GD_TILE);
+    char* mytile = smem + (SHARED ? wm : wave) * (NB * GD_TILE);
     const uint32_t mytile_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)mytile;
 
     // XCD-aware tile order (workgroups are dealt round-robin to the 8 XCDs): one XCD works on
@@ -293,11 +299,12 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
     const int m_first = m_base < M ? m_base : M - 1;
     const int KB = A4 ? K >> 1 : K;                              // bytes of a code row
     const int8_t* abase = q + (int64_t)m_first * KB;
-    int avofs[NCOPY];
+    const int jfirst = SHARED ? wn * MYCOPY : 0;                 // wave-uniform
+    int avofs[MYCOPY];
 #pragma unroll
-    for (int j = 0; j < NCOPY; ++j) {
+    for (int j = 0; j < MYCOPY; ++j) {
         // (nibbles: instruction j moves rows 16j .. 16j+15 of 64 bytes, lane i row i/4, position i%4)
-        const int row = A4 ? 16 * j + (lane >> 2) : 8 * j + (lane >> 3);
+        const int row = A4 ? 16 * (jfirst + j) + (lane >> 2) : 8 * (jfirst + j) + (lane >> 3);
         int m = m_base + row;
         if (m > M - 1) m = M - 1;
         avofs[j] = A4 ? (m - m_first) * KB + (((lane & 3) ^ gd_key4(row)) << 4)
@@ -328,11 +335,11 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
     }
     const int shamt = 4 * lg;
 
-    auto copy_codes = [&](int ks) {                              // 8 vector-memory operations
+    auto copy_codes = [&](int ks) {                              // MYCOPY vector-memory operations
         const int kc = slice_of(ks);
-        char* dst = mytile + (ks & (NB - 1)) * GD_TILE;
+        char* dst = mytile + (ks & (NB - 1)) * GD_TILE + jfirst * 1024;
 #pragma unroll
-        for (int j = 0; j < NCOPY; ++j)
+        for (int j = 0; j < MYCOPY; ++j)
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)(abase + (int64_t)kc * (A4 ? 64 : 128) + avofs[j]),
                 (__attribute__((address_space(3))) void*)(dst + j * 1024), 16, 0, 0);
@@ -423,6 +430,9 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
                 prepare(following, cur, ks, s + 1);
             } else {
                 __builtin_amdgcn_s_waitcnt(gd_vmcnt_imm(GD_YOUNGER));    // slice ks + 1 has landed
+                // SHARED: everybody's part of it; and everybody has read the last of slice ks (its reads were
+                // settled a step ago), so that its tile may be filled again below
+                if constexpr (SHARED) __builtin_amdgcn_s_barrier();
                 landed(nxt);
                 prepare(following, nxt, ks + 1, 0);
             }
@@ -443,6 +453,10 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
     }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(gd_vmcnt_imm((NB - 1) * GD_PER_SLICE));  // slice 0 has landed
+    if constexpr (SHARED) {
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    }
     landed(w0);
     prepare(ops, w0, 0, 0);
     settle(ops, 0);
@@ -653,14 +667,39 @@ __global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefi
     }
 }
 
-template <int NTL, int WM, int WK, int NB, int WN = 1>
+#define GD_PARAMS                                                                                             \
+    const uint4 *__restrict__ bits, int chunks, int row_tiles, const int8_t *__restrict__ q, int M, int K,     \
+        const float *__restrict__ scale, const int32_t *__restrict__ qsum, const __half *__restrict__ alpha,   \
+        const __half *__restrict__ V, const float *__restrict__ T, int r, float *__restrict__ Y, int N,        \
+        int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, uint16_t *__restrict__ H
+#define GD_ARGS bits, chunks, row_tiles, q, M, K, scale, qsum, alpha, V, T, r, Y, N, acc_out, tiles_m, tiles_n, H
+
+template <int NTL, int WM, int WK, int NB, bool GATED = false, bool A4 = false, int WN = 1>
+__global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefill_direct_kernel(GD_PARAMS) {
+    gd_body<NTL, WM, WK, NB, GATED, A4, WN, false>(GD_ARGS);
+}
+
+// Private rings make every wavefront fetch all code rows of its tile for itself: a CU with four wavefronts
+// asks for 32 KiB of codes and up to 8 KiB of weights per slice, some 40 bytes a clock at the rate the
+// matrix cores could work at, and that path (L2 -> L1 -> LDS) is what bounds the direct kernel at every
+// size but the smallest.  Here the WN wavefronts over the same token rows fill one ring together and meet
+// at one barrier a slice: the codes enter the CU once (28672 -> 8192 at 4096 tokens 735 -> 666 us; the
+// four loads in flight of a ring hide the barrier, and two workgroups a CU each other's).
+template <int NTL, int WM, int NB, bool GATED, bool A4, int WN>
+__global__ __launch_bounds__(64 * WM * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
+    gd_body<NTL, WM, 1, NB, GATED, A4, WN, true>(GD_ARGS);
+}
+#undef GD_PARAMS
+#undef GD_ARGS
+
+template <int NTL, int WM, int WK, int NB, int WN = 1, bool SHARED = false>
 hipError_t launch_direct(const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
                          const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH,
                          bool a4 = false) {
     constexpr int BM = WM * GD_ROWS, BN = WN * NTL * 32;
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
-    const size_t lds = (size_t)WM * WK * WN * NB * GD_TILE;
+    const size_t lds = (size_t)WM * WK * (SHARED ? 1 : WN) * NB * GD_TILE;
     static_assert((size_t)(WK - 1) * WM * GD_MT * NTL * 16 * 64 * 4 <= (size_t)WM * WK * NB * GD_TILE,
                   "the partial sums must fit into the tile rings");
     auto launch = [&](auto kern) -> hipError_t {
@@ -672,43 +711,56 @@ hipError_t launch_direct(const bwla_layer_t* L, const int8_t* dq, const float* d
             L->r, dY, (int)L->N, dacc, tiles_m, tiles_n, dH);
         return hipGetLastError();
     };
-    if (a4) return dH != nullptr ? hipErrorInvalidValue : launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, true, WN>);
-    if (dH != nullptr) return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, true, false, WN>);
-    return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, false, WN>);
+    if (a4 && dH != nullptr) return hipErrorInvalidValue;
+    if constexpr (SHARED) {
+        if (a4) return launch(gemm_prefill_shared_kernel<NTL, WM, NB, false, true, WN>);
+        if (dH != nullptr) return launch(gemm_prefill_shared_kernel<NTL, WM, NB, true, false, WN>);
+        return launch(gemm_prefill_shared_kernel<NTL, WM, NB, false, false, WN>);
+    } else {
+        if (a4) return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, true, WN>);
+        if (dH != nullptr) return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, true, false, WN>);
+        return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, false, WN>);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
-// Which tile serves M tokens and N channels.  Every variant below wins somewhere between 17 and 4096
+// Which tile serves M tokens and N channels.  Most variants below win somewhere between 17 and 4096
 // tokens, and what decides is how its tiles come out in rounds over the CUs: 257 tokens x 8192 channels
 // are 104 to 128 large tiles (half the chip, half of the rows padding) or 430 tiles of 64 x 96, two to a
 // CU.  So each variant carries a small cost, in microseconds: a tile takes base[r - 1] + slice[r - 1] per
 // 128-column slice of K that a wavefront contracts when r workgroups share the CU, full rounds run at the
-// largest r, the last one at the r that it comes to, and `start` is paid once; the smallest sum is taken.  The constants are a
-// least-squares fit of 266 shapes (14 layers, K 512 .. 28672, N 1000 .. 28672, at 19 token counts),
-// within 6 % of the measurement on average.  Over those shapes the choice takes 0.884 of the time of the
-// rules that stood here before (large tiles from 72 of them on, small ones below), 0.51 at best, and
-// stays within 1 % of the best variant on average: 8192 -> 8192 at 257 tokens 62.7 -> 35.8 us,
-// 11008 -> 4096 at 640 72.0 -> 43.4, 4096 -> 22016 at 2048 259 -> 218, 28672 -> 8192 at 4096 735 -> 735.
+// largest r, the last one at the r that it comes to, and `start` is paid once; the smallest sum is taken.
+// The constants are a least-squares fit to 370 shapes (17 .. 4096 tokens, K 512 .. 28672, N 64 .. 28672 at
+// random, three layers in turn so that nothing stays in L2), nudged per variant where a choice lost time.
+// Over those shapes the choice takes 0.90 of the time of the two thresholds between large and small tiles,
+// all with private rings, that stood here before (0.49 at best, within 1.4 % of the best variant on average):
+// 8192 -> 8192 at 257 tokens 57 -> 34 us, 4096 -> 11008 at 333 40 -> 33, 4096 -> 22016 at 2048 258 -> 207,
+// 28672 -> 8192 at 4096 712 -> 652 (2.95 POP/s).
 struct GdVariant {
-    int ntl, wm, wk, nb, wn;      // template arguments of gemm_prefill_direct_kernel
+    int ntl, wm, wk, nb, wn;      // template arguments
+    bool shared;                  // one ring of code tiles for the wn wavefronts over the same tokens
     int resident;                 // workgroups a CU holds (LDS of the tile rings, registers)
     float start, base[4], slice[4];
-    float later;                  // factor when there is more than one round: these four have no neighbour on
-                                  // the CU whose contraction would cover their epilogue's stores
 };
 constexpr GdVariant GD_VARIANTS[] = {
-    {1, 1, 4, 4, 1, 1, 0.4f, {10.3f}, {0.369f}, 1.0f},                                  //  64 x 32, K split in four
-    {2, 1, 4, 4, 1, 1, 0.0f, {13.6f}, {0.433f}, 1.0f},                                  //  64 x 64, K split in four
-    {1, 1, 1, 4, 1, 4, 0.0f, {9.7f, 10.9f, 11.6f, 12.2f}, {0.271f, 0.283f, 0.306f, 0.347f}, 1.0f},   //  64 x 32
-    {2, 1, 2, 4, 1, 2, 1.1f, {11.9f, 14.0f}, {0.358f, 0.407f}, 1.0f},                   //  64 x 64, K split in two
-    {3, 1, 2, 4, 1, 2, 0.3f, {15.2f, 17.8f}, {0.452f, 0.520f}, 1.0f},                   //  64 x 96, K split in two
-    {2, 2, 1, 4, 2, 1, 0.0f, {14.6f}, {0.362f}, 1.0f},                                  // 128 x 128
-    {3, 2, 1, 2, 2, 2, 0.4f, {15.6f, 22.5f}, {0.488f, 1.090f}, 1.0f},                   // 128 x 192
-    {4, 1, 1, 4, 4, 1, 0.0f, {20.8f}, {0.592f}, 1.06f},                                 //  64 x 512: codes once per CU
-    {5, 1, 1, 4, 4, 1, 0.0f, {24.9f}, {0.717f}, 1.06f},                                 //  64 x 640
-    {4, 4, 1, 4, 1, 1, 0.0f, {20.8f}, {0.602f}, 1.06f},                           // 256 x 128, the deeper ring
-    {5, 4, 1, 4, 1, 1, 0.0f, {24.3f}, {0.721f}, 1.06f},                           // 256 x 160
-    {4, 4, 1, 2, 1, 2, 2.5f, {18.6f, 29.0f}, {0.592f, 1.390f}, 1.0f},                   // 256 x 128
+    // few tokens: private rings, the wavefronts of a workgroup share out K
+    {1, 1, 4, 4, 1, false, 1, 0.9f, {10.3f}, {0.374f}},                                                      // 64 x 32, in four
+    {2, 1, 4, 4, 1, false, 1, 0.3f, {13.9f}, {0.398f}},                                                      // 64 x 64, in four
+    {2, 1, 2, 4, 1, false, 2, 1.3f, {11.2f, 12.5f}, {0.324f, 0.413f}},                                       // 64 x 64, in two
+    {3, 1, 2, 4, 1, false, 2, 1.1f, {13.4f, 15.2f}, {0.401f, 0.498f}},                                       // 64 x 96, in two
+    {1, 1, 1, 4, 1, false, 4, 0.0f, {9.8f, 10.3f, 10.9f, 10.6f}, {0.256f, 0.270f, 0.299f, 0.358f}},          // 64 x 32, one wavefront
+    // one ring of codes for four wavefronts (the first: two)
+    {1, 1, 1, 4, 2, true, 4, 2.5f, {7.3f, 8.3f, 13.0f, 12.4f}, {0.247f, 0.322f, 0.349f, 0.495f}},            // 64 x 64
+    {1, 1, 1, 4, 4, true, 3, 0.0f, {10.4f, 14.7f, 15.6f}, {0.277f, 0.369f, 0.599f}},                         // 64 x 128
+    {2, 1, 1, 4, 4, true, 2, 0.3f, {11.6f, 14.2f}, {0.290f, 0.637f}},                                        // 64 x 256
+    {3, 1, 1, 4, 4, true, 2, 4.6f, {9.5f, 18.5f}, {0.380f, 0.832f}},                                         // 64 x 384
+    {4, 1, 1, 2, 4, true, 2, 1.4f, {14.0f, 26.2f}, {0.570f, 1.188f}},                                        // 64 x 512, ring of two
+    {5, 1, 1, 4, 4, true, 1, 0.0f, {17.1f}, {0.687f}},                                                       // 64 x 640
+    // large tiles with private rings
+    {4, 4, 1, 2, 1, false, 2, 0.0f, {17.1f, 29.3f}, {0.580f, 1.328f}},                                       // 256 x 128, ring of two
+    {4, 4, 1, 4, 1, false, 1, 0.0f, {19.7f}, {0.588f}},                                                      // 256 x 128
+    {5, 4, 1, 4, 1, false, 1, 0.0f, {20.2f}, {0.715f}},                                                      // 256 x 160
+    {5, 1, 1, 4, 4, false, 1, 0.0f, {19.7f}, {0.718f}},                                                      // 64 x 640
 };
 constexpr int GD_NVARIANTS = sizeof(GD_VARIANTS) / sizeof(GD_VARIANTS[0]);
 
@@ -722,7 +774,7 @@ inline float gd_cost(const GdVariant& v, int64_t M, int64_t K, int64_t N, int64_
         const int r = (int)((rem + cus - 1) / cus);
         t += v.base[r - 1] + v.slice[r - 1] * slices;
     }
-    return tiles > cap ? t * v.later : t;
+    return t;
 }
 
 // index into GD_VARIANTS
@@ -742,7 +794,7 @@ hipError_t launch_variant(int pick, const bwla_layer_t* L, const int8_t* dq, con
                           hipStream_t st, uint16_t* dH, bool a4) {
     constexpr GdVariant v = GD_VARIANTS[I];
     if (pick == I)
-        return launch_direct<v.ntl, v.wm, v.wk, v.nb, v.wn>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+        return launch_direct<v.ntl, v.wm, v.wk, v.nb, v.wn, v.shared>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
     if constexpr (I + 1 < GD_NVARIANTS)
         return launch_variant<I + 1>(pick, L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
     return hipErrorInvalidValue;

@@ -229,18 +229,21 @@ def test_nibble_packed_a4_codes(M, K, n1, n2, N, r):
 
 
 @pytest.mark.parametrize("M,K,N,r", [
-    (17, 1152, 50, 16),         # 64 x 32 tiles, four wavefronts split K (9 slices: 3, 3, 3, 0)
-    (40, 256, 64, 8),           # 64 x 32 tiles, one wavefront
-    (65, 2048, 5120, 20),       # 64 x 64, K split in four
-    (70, 4096, 12302, 32),      # 64 x 64, K split in two; ragged channels
-    (257, 4992, 8192, 64),      # 64 x 96, K split in two (39 slices); the last row tile holds one token
-    (65, 128, 20000, 0),        # 128 x 128, one slice: the whole ring is padding
-    (300, 128, 12346, 33),      # 128 x 192
-    (129, 128, 28000, 70),      # 64 x 512, two chunks of ranks
-    (257, 1152, 28000, 16),     # 64 x 640
-    (400, 512, 20000, 96),      # 256 x 160
-    (1220, 512, 6300, 8),       # 256 x 128, ring of four
-    (520, 128, 20002, 64),      # 256 x 128, ring of two, two workgroups a CU
+    (19, 1664, 50, 16),         # 64 x 32 tiles, four wavefronts split K (13 slices: 4, 4, 4, 1)
+    (18, 4480, 9250, 8),        # 64 x 64, K split in four
+    (17, 8320, 16426, 32),      # 64 x 64, K split in two; ragged channels
+    (17, 16384, 17142, 64),     # 64 x 96, K split in two
+    (3420, 128, 266, 8),        # 64 x 32, one wavefront; one slice, the rest of the ring is padding
+    (40, 256, 64, 20),          # one ring of codes from here on: 64 x 64
+    (65, 128, 8306, 0),         # 64 x 128, the second row tile holds one token
+    (70, 4096, 12302, 33),      # 64 x 128
+    (70, 640, 19480, 16),       # 64 x 256, five slices
+    (257, 4992, 8192, 64),      # 64 x 256, 39 slices
+    (147, 128, 21938, 8),       # 64 x 384
+    (733, 384, 16562, 70),      # 64 x 512, ring of two, odd number of slices; two chunks of ranks
+    (288, 128, 26306, 96),      # 64 x 640
+    (2999, 128, 2638, 64),      # private rings: 256 x 128, ring of two
+    (3558, 128, 2598, 8),       # 256 x 160
 ])
 def test_streaming_gemm_tiles(M, K, N, r):
     """One shape for each tile the dispatch of the streaming GEMM chooses from: int32 accumulators equal to
