@@ -170,7 +170,10 @@ __device__ __forceinline__ void chunk_store(float* dst, const ChunkSlots& cs, co
     }
 }
 
-template <bool BF16>
+// MAXT: 16 x 16 tiles of the token a wavefront may carry.  Their accumulators are what the registers go to
+// (and the code, fully unrolled over them, what the instruction cache): with all 32 of the largest factors
+// a CU holds one workgroup, with the two of 64 x 64 it holds three.
+template <bool BF16, int MAXT>
 __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict__ X, int64_t t, int64_t K, int n1,
                                              int n2, const float* __restrict__ R1, const float* __restrict__ R2,
                                              int8_t* __restrict__ q, float* __restrict__ scale,
@@ -192,9 +195,9 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
     // last tile is paired with a copy of itself whose result is never used.
 #define RQ_PAIR_SLOTS(g) const int s0 = 2 * (g), s1 = (2 * (g) + 1 < my_tiles) ? 2 * (g) + 1 : 2 * (g)
 
-    v4f acc[RQ_MAXT];
+    v4f acc[MAXT];
 #pragma unroll
-    for (int s = 0; s < RQ_MAXT; ++s) acc[s] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < MAXT; ++s) acc[s] = v4f{0.f, 0.f, 0.f, 0.f};
 
     fill_lds<BF16>(X, t * K, n1, n2, R1, R2, sh, reg, fac, fac + sh.n2p * sh.ld2t);
 
@@ -204,7 +207,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
         __syncthreads();
         // stage 1: Z[a][d] = sum_b V[a][b] R2[b][d];   tile (ti over a, tj over d)
 #pragma unroll
-        for (int g = 0; g < RQ_MAXT / 2; ++g) {
+        for (int g = 0; g < MAXT / 2; ++g) {
             if (2 * g < my_tiles) {
                 RQ_PAIR_SLOTS(g);
                 const int tau0 = wave + s0 * RQ_WAVES, tau1 = wave + s1 * RQ_WAVES;
@@ -224,7 +227,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
         bwla_lds_barrier();                                        // every wave is done reading V
         // lane holds Z[a = ti*16 + 4*lg + v][d = tj*16 + li]: one 128-bit store into ZT[d][a..a+3]
 #pragma unroll
-        for (int s = 0; s < RQ_MAXT; ++s) {
+        for (int s = 0; s < MAXT; ++s) {
             if (s < my_tiles) {
                 const int tau = wave + s * RQ_WAVES;
                 const int ti = dt2.div(tau), tj = tau - ti * tiles2;
@@ -236,7 +239,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
         bwla_lds_barrier();                                        // ZT is published
         // stage 2: Yt[d][c] = sum_a ZT[d][a] R1[a][c];   tile (ti over d, tj over c)
 #pragma unroll
-        for (int g = 0; g < RQ_MAXT / 2; ++g) {
+        for (int g = 0; g < MAXT / 2; ++g) {
             if (2 * g < my_tiles) {
                 RQ_PAIR_SLOTS(g);
                 const int tau0 = wave + s0 * RQ_WAVES, tau1 = wave + s1 * RQ_WAVES;
@@ -280,7 +283,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
                     if (c < nchunks) {
                         const float* cur = cb + (c & 1) * cbs;
 #pragma unroll
-                        for (int g = 0; g < RQ_MAXT / 2; ++g) {
+                        for (int g = 0; g < MAXT / 2; ++g) {
                             if (2 * g < my_tiles) {
                                 RQ_PAIR_SLOTS(g);
                                 const int tau0 = wave + s0 * RQ_WAVES, tau1 = wave + s1 * RQ_WAVES;
@@ -304,7 +307,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
                 // lane holds Z[a = ti*16 + 4*lg + v][d = tj*16 + li] -> ZT[d][a..a+3]; V is dead
                 // (every wave passed the last barrier of the loop)
 #pragma unroll
-                for (int s = 0; s < RQ_MAXT; ++s) {
+                for (int s = 0; s < MAXT; ++s) {
                     if (s < my_tiles) {
                         const int tau = wave + s * RQ_WAVES;
                         const int ti = dt2.div(tau), tj = tau - ti * tiles2;
@@ -320,7 +323,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
     // ================= per-token max magnitude
     float mx = 0.0f, mn = 0.0f;
 #pragma unroll
-    for (int s = 0; s < RQ_MAXT; ++s)
+    for (int s = 0; s < MAXT; ++s)
         if (s < my_tiles) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) { mx = fmaxf(mx, acc[s][v]); mn = fminf(mn, acc[s][v]); }
@@ -339,7 +342,7 @@ __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict_
     int8_t* codes = reinterpret_cast<int8_t*>(reg);
     int lsum = 0;
 #pragma unroll
-    for (int s = 0; s < RQ_MAXT; ++s) {
+    for (int s = 0; s < MAXT; ++s) {
         if (s < my_tiles) {
             const int tau = wave + s * RQ_WAVES;
             const int ti = dt1.div(tau), tj = tau - ti * tiles1;

@@ -26,6 +26,8 @@
 #include "rotate_split_device.h"
 #include "psp_block_device.h"
 
+int bwla_rotate_tiles(int n1, int n2);
+
 namespace {
 
 struct RqArgs {
@@ -51,11 +53,12 @@ __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb,
                     rest % a.JG, a.JG);
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(RQ_THREADS) void rotate_quant_kernel(RqArgs a) {
+// (up to 128 registers: two workgroups a CU where LDS lets them)
+template <bool BF16, int MAXT>
+__global__ __launch_bounds__(RQ_THREADS, MAXT <= 4 ? 4 : 2) void rotate_quant_kernel(RqArgs a) {
     extern __shared__ __align__(16) float lds[];
     if ((int64_t)blockIdx.x < a.rot_blocks) {
-        rotate_token<BF16>(lds, a.X, blockIdx.x, a.K, a.n1, a.n2, a.R1, a.R2, a.q, a.scale, a.qsum, a.tmode, a.tp, a.qmax,
+        rotate_token<BF16, MAXT>(lds, a.X, blockIdx.x, a.K, a.n1, a.n2, a.R1, a.R2, a.q, a.scale, a.qsum, a.tmode, a.tp, a.qmax,
                            a.asym != 0, a.shift != 0);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
@@ -108,6 +111,19 @@ hipError_t launch_rotate3(const RqArgs& a, int64_t blocks, int threads, size_t l
     }
     if (a.rot_blocks < a.M) return launch_rotate3_v<ATM, THREADS, true>(a, blocks, threads, lds, st);
     return launch_rotate3_v<ATM, THREADS, false>(a, blocks, threads, lds, st);
+}
+
+// the smallest kernel that holds a wavefront's share of the tiles
+template <bool BF16>
+hipError_t launch_rotate_f32(const RqArgs& a, unsigned blocks, size_t lds, hipStream_t st) {
+    const int per_wave = (bwla_rotate_tiles(a.n1, a.n2) + RQ_WAVES - 1) / RQ_WAVES;
+    const auto kern = per_wave <= 2   ? rotate_quant_kernel<BF16, 2>
+                      : per_wave <= 4 ? rotate_quant_kernel<BF16, 4>
+                                      : rotate_quant_kernel<BF16, RQ_MAXT>;
+    hipError_t e = bwla_ensure_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<dim3(blocks), dim3(RQ_THREADS), lds, st>>>(a);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void code_sums_kernel(const int8_t* __restrict__ q, int64_t K,
@@ -305,16 +321,8 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         return hipSuccess;
     }
     const size_t lds = plds > sh.lds_bytes ? plds : sh.lds_bytes;
-    if (xdtype == BWLA_X_BF16) {
-        e = bwla_ensure_lds((const void*)rotate_quant_kernel<true>, lds);
-        if (e != hipSuccess) return e;
-        rotate_quant_kernel<true><<<dim3((unsigned)(M + pblocks)), dim3(RQ_THREADS), lds, st>>>(a);
-    } else {
-        e = bwla_ensure_lds((const void*)rotate_quant_kernel<false>, lds);
-        if (e != hipSuccess) return e;
-        rotate_quant_kernel<false><<<dim3((unsigned)(M + pblocks)), dim3(RQ_THREADS), lds, st>>>(a);
-    }
-    e = hipGetLastError();
+    const unsigned grid = (unsigned)(M + pblocks);
+    e = xdtype == BWLA_X_BF16 ? launch_rotate_f32<true>(a, grid, lds, st) : launch_rotate_f32<false>(a, grid, lds, st);
     if (e != hipSuccess) return e;
     if (ru > 0 && !merged) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
     return hipSuccess;
