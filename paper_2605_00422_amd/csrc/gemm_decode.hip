@@ -48,15 +48,59 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
         }
     }
 
-    // ---- stage the code rows into LDS (zero beyond K)
+    // ---- what the epilogue needs of the token, asked for early: two round trips to memory less at the end
+    const int t = li;
+    const bool tok_ok = t < M;
+    const float st = tok_ok ? scale[t] : 0.0f;
+    const int qs = tok_ok ? qsum[t] : 0;
+    const int JT = (r + 15) >> 4;
+    const int rp = JT * 16;                            // V rows are stored padded to rp halfs
+    // low-rank operands of tile `tile`, ranks 16 u + 4 lg + 0 .. 3: V row li of the tile, T row of token li
+    auto low_operands = [&](int tile, int u, float (&vv)[4], float (&tv)[4]) {
+        const int j0 = u * 16 + 4 * lg, vrow = tile * 16 + li;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vv[e] = tv[e] = 0.0f;
+        if (vrow < N) {
+            const uint2 raw = *reinterpret_cast<const uint2*>(V + (int64_t)vrow * rp + j0);
+            const __half2 h0 = *reinterpret_cast<const __half2*>(&raw.x);
+            const __half2 h1 = *reinterpret_cast<const __half2*>(&raw.y);
+            vv[0] = __low2float(h0); vv[1] = __high2float(h0);
+            vv[2] = __low2float(h1); vv[3] = __high2float(h1);
+        }
+        if (tok_ok) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j0 + e < r) tv[e] = T[(int64_t)t * r + j0 + e];
+        }
+    };
+    float v0[4] = {0.f, 0.f, 0.f, 0.f}, t0[4] = {0.f, 0.f, 0.f, 0.f}, al[4];
+    if (JT > 0) low_operands(tile0, 0, v0, t0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int n = tile0 * 16 + 4 * lg + v;
+        al[v] = __half2float(alpha[n < N ? n : N - 1]);
+    }
+
+    // ---- stage the code rows into LDS (zero beyond K), eight loads of a thread in flight: a workgroup of one
+    // wavefront (K <= 512) has eight to make, and waited for each before the next
     {
         const int gran_per_row = Kp >> 4;
-        const int total = rows * gran_per_row;
-        for (int idx = tid; idx < total; idx += blockDim.x) {
-            const int row = idx / gran_per_row, gcol = idx - row * gran_per_row;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (gcol * 16 < K) v = *reinterpret_cast<const uint4*>(q + (int64_t)row * K + gcol * 16);
-            *reinterpret_cast<uint4*>(smem + q_swz(row, gcol * 16, Kp)) = v;
+        const int total = rows * gran_per_row, step = (int)blockDim.x;
+        for (int base = tid; base < total; base += 8 * step) {
+            uint4 v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int idx = base + e * step;
+                const int row = idx / gran_per_row, gcol = idx - row * gran_per_row;
+                v[e] = make_uint4(0, 0, 0, 0);
+                if (idx < total && gcol * 16 < K) v[e] = *reinterpret_cast<const uint4*>(q + (int64_t)row * K + gcol * 16);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int idx = base + e * step;
+                const int row = idx / gran_per_row, gcol = idx - row * gran_per_row;
+                if (idx < total) *reinterpret_cast<uint4*>(smem + q_swz(row, gcol * 16, Kp)) = v[e];
+            }
         }
     }
     __syncthreads();
@@ -121,12 +165,6 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
     }
 
     // ---- epilogue: lane holds token li, output rows n = 16*tile + 4*lg + v
-    const int t = li;
-    const bool tok_ok = t < M;
-    const float st = tok_ok ? scale[t] : 0.0f;
-    const int qs = tok_ok ? qsum[t] : 0;
-    const int JT = (r + 15) >> 4;
-    const int rp = JT * 16;                            // V rows are stored padded to rp halfs
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int tile = tile0 + nt;
@@ -136,23 +174,9 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
         // j = 16u + 4*lg + e in step e of group u for both operands
         v4f low = v4f{0.f, 0.f, 0.f, 0.f};
         for (int u = 0; u < JT; ++u) {
-            const int j0 = u * 16 + 4 * lg;
-            const int vrow = n0 + li;
-            float vv[4] = {0.f, 0.f, 0.f, 0.f}, tv[4] = {0.f, 0.f, 0.f, 0.f};
-            if (vrow < N) {
-                const uint2 raw = *reinterpret_cast<const uint2*>(V + (int64_t)vrow * rp + j0);
-                const __half2 h0 = *reinterpret_cast<const __half2*>(&raw.x);
-                const __half2 h1 = *reinterpret_cast<const __half2*>(&raw.y);
-                vv[0] = __low2float(h0); vv[1] = __high2float(h0);
-                vv[2] = __low2float(h1); vv[3] = __high2float(h1);
-            }
-            if (tok_ok) {
+            if (nt > 0 || u > 0) low_operands(tile, u, v0, t0);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (j0 + e < r) tv[e] = T[(int64_t)t * r + j0 + e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) low = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], tv[e], low, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) low = __builtin_amdgcn_mfma_f32_16x16x4f32(v0[e], t0[e], low, 0, 0, 0);
         }
         if (!tok_ok) continue;
 #pragma unroll
@@ -160,8 +184,8 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
             const int n = n0 + 4 * lg + v;
             if (n < N) {
                 const int a = 2 * res[nt][v] - qs;
-                const float al = __half2float(alpha[n]);
-                Y[(int64_t)t * N + n] = st * al * (float)a + low[v];
+                const float an = nt == 0 ? al[v] : __half2float(alpha[n]);
+                Y[(int64_t)t * N + n] = st * an * (float)a + low[v];
                 if (acc_out) acc_out[(int64_t)t * N + n] = a;
             }
         }
