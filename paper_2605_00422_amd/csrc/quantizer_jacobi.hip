@@ -7,10 +7,11 @@
 // even length so that a lane moves two elements at a time), V likewise.
 // A sweep visits every pair of columns once, in the round-robin order of a tournament: n / 2
 // disjoint pairs per round, n - 1 rounds.  A pair belongs to a group of lanes that holds both columns
-// in registers (up to four elements per lane), takes the three inner products, and applies the plane
+// in registers (up to four elements per lane), takes their inner product, and applies the plane
 // rotation that makes the two columns orthogonal to them and to the matching columns of V.  Up to
 // n = 64 a group is one row of 16 lanes -- four pairs per wavefront, all pairs of a round at once,
-// the inner products summed on DPP row operations alone; larger matrices give a pair two rows (one
+// the inner product summed on DPP row operations alone, and the tournament is one of blocks of four
+// columns whose sixteen pairs a wavefront takes in registers; larger matrices give a pair two rows (one
 // lane exchange more) or a whole wavefront (row sums on DPP, the four rows added through lane reads).  Sweeps end when one passes
 // without a rotation (every pair orthogonal to 1e-15 relative) or after 60.  At the end the column
 // norms are the singular values, the normalized columns U, and V holds the right singular vectors.
@@ -54,6 +55,19 @@ __device__ __forceinline__ double jgroup_sum(double v) {
     return v;
 }
 
+// the value of the lane 16 (by32: 32) away under exclusive or: rows of lanes change places
+__device__ __forceinline__ double jrow_xor(double v, bool by32, int lane) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    if (by32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return lane & 32 ? __hiloint2double((int)h[0], (int)l[0]) : __hiloint2double((int)h[1], (int)l[1]);
+    }
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return lane & 16 ? __hiloint2double((int)h[0], (int)l[0]) : __hiloint2double((int)h[1], (int)l[1]);
+}
+
 // Tangent t, cosine of the plane rotation that makes columns with squared norms al, be and inner product
 // ga orthogonal; the sine is cs * t.  Only cs^2 + sn^2 = 1 has to hold to the last bit or so (it keeps the
 // columns' norms and V orthogonal): the tangent may be off by the 2^-20 or better of the hardware's
@@ -85,13 +99,15 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     extern __shared__ __align__(16) double jlds[];
     double* Wc = LDS ? jlds : a.work;
     const int ld = LDS ? (n + 1) & ~1 : n;                              // pitch of a column
-    double* Vc = Wc + (size_t)n * ld;
+    constexpr bool BLOCKED = GW == 16;                                  // (always in LDS)
+    const int ncol = BLOCKED ? (n + 7) & ~7 : n;                        // columns, padded with zero ones
+    double* Vc = Wc + (size_t)ncol * ld;
     __shared__ int rotated;
-    __shared__ double sg[JMAX];
+    __shared__ double sg[JMAX];                             // during the sweeps: squared norms of the columns
     __shared__ int ord[JMAX];
-    for (int e = t; e < n * ld; e += JT) {
+    for (int e = t; e < ncol * ld; e += JT) {
         const int j = e / ld, i = e - j * ld;
-        Wc[e] = i < n ? a.G[(size_t)i * n + j] : 0.0;
+        Wc[e] = i < n && j < n ? a.G[(size_t)i * n + j] : 0.0;
         if (ACCV) Vc[e] = i == j ? 1.0 : 0.0;
     }
     const int np = (n + 1) & ~1;
@@ -121,67 +137,169 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             if (i + D < n) c[i + D] = e1;
         }
     };
+    // one pair of columns through memory, by the GW lanes of a group (all lanes of the workgroup call it)
+    auto pair = [&](int p, int q, bool live) {
+        double* xp = Wc + (size_t)p * ld;
+        double* yp = Wc + (size_t)q * ld;
+        double x[4], y[4];
+        const double al = sg[p], be = sg[q < ncol ? q : 0];
+        double ga = 0.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            load(xp, u, live, x[2 * u], x[2 * u + 1]);
+            load(yp, u, live, y[2 * u], y[2 * u + 1]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ga += x[u] * y[u];
+        ga = jgroup_sum<GW>(ga);
+        // (|ga| > 1e-15 sqrt(al be), without the root)
+        if (live && al > 0.0 && be > 0.0 && ga * ga > 1.0e-30 * (al * be)) {
+            double tt, cs;
+            jrotation(al, be, ga, tt, cs);
+            const double sn = cs * tt;
+            double* vp = Vc + (size_t)p * ld;
+            double* vq = Vc + (size_t)q * ld;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                store(xp, u, cs * x[2 * u] - sn * y[2 * u], cs * x[2 * u + 1] - sn * y[2 * u + 1]);
+                store(yp, u, sn * x[2 * u] + cs * y[2 * u], sn * x[2 * u + 1] + cs * y[2 * u + 1]);
+                if (ACCV) {
+                    double a0, a1, b0, b1;
+                    load(vp, u, true, a0, a1);
+                    load(vq, u, true, b0, b1);
+                    store(vp, u, cs * a0 - sn * b0, cs * a1 - sn * b1);
+                    store(vq, u, sn * a0 + cs * b0, sn * a1 + cs * b1);
+                }
+            }
+            if (sl == 0) {
+                const double c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
+                sg[p] = c2 * (al - g2 + t2 * be);
+                sg[q] = c2 * (be + g2 + t2 * al);
+                rotated = 1;
+            }
+        }
+    };
+    // position i of a tournament of m (even): 0 stays, the others move on by one per round
+    auto at = [](int i, int round, int m) {
+        const int v = i - 1 - round;
+        return i == 0 ? 0 : 1 + (v < 0 ? v + m - 1 : v);
+    };
     __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
         if (t == 0) rotated = 0;
+        // Squared norms: taken anew at the start of a sweep, carried along by the rotations within it (their
+        // error is then that of a sweep's rotations, and a sweep that rotates nothing, the one that ends the
+        // loop, has tested every pair on exact ones).  A rotation so needs one inner product instead of three.
+        for (int base = 0; base < ncol; base += GROUPS) {
+            const int j = base + gid;
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                double e0, e1;
+                load(Wc + (size_t)(j < n ? j : 0) * ld, u, j < n, e0, e1);
+                s += e0 * e0;
+                s += e1 * e1;
+            }
+            s = jgroup_sum<GW>(s);
+            if (j < ncol && sl == 0) sg[j] = s;
+        }
         __syncthreads();
-        for (int round = 0; round < np - 1; ++round) {
-            // the column at position i of the tournament: 0 stays, the others move on by one per round
-            auto at = [&](int i) {
-                const int v = i - 1 - round;
-                return i == 0 ? 0 : 1 + (v < 0 ? v + np - 1 : v);
-            };
-            for (int base = 0; base < np / 2; base += GROUPS) {        // the same trip count in every lane
-                const int pr = base + gid;
-                int p = 0, q = 0;
-                bool live = pr < np / 2;
-                if (live) {
-                    p = at(pr);
-                    q = at(np - 1 - pr);
-                    live = p < n && q < n;                              // else the bye of an odd n
-                    if (p > q) { const int s = p; p = q; q = s; }
-                }
-                double* xp = Wc + (size_t)p * ld;
-                double* yp = Wc + (size_t)q * ld;
-                double x[4], y[4];
-                double al = 0.0, be = 0.0, ga = 0.0;
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    load(xp, u, live, x[2 * u], x[2 * u + 1]);
-                    load(yp, u, live, y[2 * u], y[2 * u + 1]);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    al += x[u] * x[u];
-                    be += y[u] * y[u];
-                    ga += x[u] * y[u];
-                }
-                al = jgroup_sum<GW>(al);
-                be = jgroup_sum<GW>(be);
-                ga = jgroup_sum<GW>(ga);
-                // (|ga| > 1e-15 sqrt(al be), without the root)
-                if (live && al > 0.0 && be > 0.0 && ga * ga > 1.0e-30 * (al * be)) {
-                    double tt, cs;
-                    jrotation(al, be, ga, tt, cs);
-                    const double sn = cs * tt;
-                    double* vp = Vc + (size_t)p * ld;
-                    double* vq = Vc + (size_t)q * ld;
+        if constexpr (BLOCKED) {
+            // Blocks of four columns.  Within the blocks: three rounds through LDS, column i with i ^ r.
+            for (int r = 1; r < 4; ++r) {
+                const int p = 4 * (gid >> 1) + ((gid & 1) ? (r == 1 ? 2 : 1) : 0);
+                const bool live = p < ncol;
+                pair(live ? p : 0, live ? p ^ r : 0, live);
+                __syncthreads();
+            }
+            // Between blocks: a tournament of the blocks, a wavefront per pair of them.  It keeps the eight
+            // columns in registers over all sixteen pairs -- four rounds, between which the rows of lanes pass
+            // the second block's columns round (g ^ 1, g ^ 3, g ^ 2) -- so that LDS and the barrier are met
+            // once in four rounds (64 x 64 with V, whole call: 593 -> 408 us; Gram matrices of 64 columns, on average, 395 -> 280).
+            const int nb = ncol >> 2, g4 = lane >> 4;
+            for (int round = 0; round < nb - 1; ++round) {
+                if (w < nb / 2) {
+                    const int cx = 4 * at(w, round, nb) + g4, by = 4 * at(nb - 1 - w, round, nb);
+                    double x[4], y[4], vx[4], vy[4];
+                    double nx = sg[cx], ny = sg[by + g4];
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
-                        store(xp, u, cs * x[2 * u] - sn * y[2 * u], cs * x[2 * u + 1] - sn * y[2 * u + 1]);
-                        store(yp, u, sn * x[2 * u] + cs * y[2 * u], sn * x[2 * u + 1] + cs * y[2 * u + 1]);
+                        load(Wc + (size_t)cx * ld, u, true, x[2 * u], x[2 * u + 1]);
+                        load(Wc + (size_t)(by + g4) * ld, u, true, y[2 * u], y[2 * u + 1]);
                         if (ACCV) {
-                            double a0, a1, b0, b1;
-                            load(vp, u, true, a0, a1);
-                            load(vq, u, true, b0, b1);
-                            store(vp, u, cs * a0 - sn * b0, cs * a1 - sn * b1);
-                            store(vq, u, sn * a0 + cs * b0, sn * a1 + cs * b1);
+                            load(Vc + (size_t)cx * ld, u, true, vx[2 * u], vx[2 * u + 1]);
+                            load(Vc + (size_t)(by + g4) * ld, u, true, vy[2 * u], vy[2 * u + 1]);
                         }
                     }
-                    if (sl == 0) rotated = 1;
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (k > 0) {
+                            const bool by32 = k == 2;
+                            ny = jrow_xor(ny, by32, lane);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                y[u] = jrow_xor(y[u], by32, lane);
+                                if (ACCV) vy[u] = jrow_xor(vy[u], by32, lane);
+                            }
+                        }
+                        const double ga = jrow_sum((x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]));
+                        const bool turn = nx > 0.0 && ny > 0.0 && ga * ga > 1.0e-30 * (nx * ny);
+                        if (turn) {
+                            double tt, cs;
+                            jrotation(nx, ny, ga, tt, cs);
+                            const double sn = cs * tt, c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
+                            const double mx = c2 * (nx - g2 + t2 * ny);
+                            ny = c2 * (ny + g2 + t2 * nx);
+                            nx = mx;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const double xu = x[u], yu = y[u];
+                                x[u] = cs * xu - sn * yu;
+                                y[u] = sn * xu + cs * yu;
+                                if (ACCV) {
+                                    const double vu = vx[u], wu = vy[u];
+                                    vx[u] = cs * vu - sn * wu;
+                                    vy[u] = sn * vu + cs * wu;
+                                }
+                            }
+                            any = true;
+                        }
+                    }
+                    const int cy = by + (g4 ^ 2);                       // whose column the last exchange left here
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        store(Wc + (size_t)cx * ld, u, x[2 * u], x[2 * u + 1]);
+                        store(Wc + (size_t)cy * ld, u, y[2 * u], y[2 * u + 1]);
+                        if (ACCV) {
+                            store(Vc + (size_t)cx * ld, u, vx[2 * u], vx[2 * u + 1]);
+                            store(Vc + (size_t)cy * ld, u, vy[2 * u], vy[2 * u + 1]);
+                        }
+                    }
+                    if (sl == 0) {
+                        sg[cx] = nx;
+                        sg[cy] = ny;
+                        if (any) rotated = 1;
+                    }
                 }
+                __syncthreads();
             }
-            __syncthreads();
+        } else {
+            for (int round = 0; round < np - 1; ++round) {
+                for (int base = 0; base < np / 2; base += GROUPS) {    // the same trip count in every lane
+                    const int pr = base + gid;
+                    int p = 0, q = 0;
+                    bool live = pr < np / 2;
+                    if (live) {
+                        p = at(pr, round, np);
+                        q = at(np - 1 - pr, round, np);
+                        live = p < n && q < n;                          // else the bye of an odd n
+                        if (p > q) { const int s = p; p = q; q = s; }
+                    }
+                    pair(p, q, live);
+                }
+                __syncthreads();
+            }
         }
         if (!rotated) break;
         __syncthreads();
@@ -230,7 +348,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st) {
     if (j.n < 1 || j.n > JMAX) return hipErrorInvalidValue;
     const bool in_lds = j.n <= (j.sym ? JLDS_SYM : JLDS);
-    const size_t lds = in_lds ? (size_t)(j.sym ? 1 : 2) * j.n * ((j.n + 1) & ~1) * sizeof(double) : 0;
+    const size_t lds = in_lds ? (size_t)(j.sym ? 1 : 2) * (j.n <= 64 ? (j.n + 7) & ~7 : j.n) * ((j.n + 1) & ~1) * sizeof(double) : 0;
     auto launch = [&](auto kern, int threads) {
         if (lds > 48 * 1024) {
             const hipError_t e = bwla_ensure_lds((const void*)kern, lds);
