@@ -234,25 +234,33 @@ __global__ __launch_bounds__(PF_THREADS) void psp_prefill_kernel(PfArgs a) {
     if (!bwla_partials_arrive(&a.counters[unit], a.S, is_last)) return;
     // last workgroup of this tile: add the S partial tiles in slice order
     const float* pbase = a.partials + (int64_t)unit * a.S * (TILE_F4 * 4);
+    // PF_BATCH slices of all my vectors in flight at a time (slices past S re-read the last one and add zero): a
+    // batch is a round trip to memory, and vector by vector there were four to eight of them one after the other
+    // (257 tokens of 8192, rank 64, sixteen slices: whole launch 15.0 -> 13.0 us; 2048 of 4096 14.0 -> 12.9)
+    constexpr int PF_BATCH = 4;
+    v4f sum4[NJT];
 #pragma unroll
-    for (int i = 0; i < NJT; ++i) {
-        const int e4 = tid + i * PF_THREADS;
-        // batches of eight loads in flight; slices past S re-read the last one and add zero
-        v4f sum4 = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int ss = 0; ss < a.S; ss += 8) {
-            v4f v[8];
+    for (int i = 0; i < NJT; ++i) sum4[i] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int ss = 0; ss < a.S; ss += PF_BATCH) {
+        v4f v[PF_BATCH][NJT];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int sc = ss + u < a.S ? ss + u : a.S - 1;
-                const float* p = pbase + (int64_t)sc * (TILE_F4 * 4) + e4;
-                v[u] = v4f{bwla_load_agent(p), bwla_load_agent(p + TILE_F4), bwla_load_agent(p + 2 * TILE_F4),
-                           bwla_load_agent(p + 3 * TILE_F4)};
+        for (int u = 0; u < PF_BATCH; ++u) {
+            const int sc = ss + u < a.S ? ss + u : a.S - 1;
+#pragma unroll
+            for (int i = 0; i < NJT; ++i) {
+                const float* p = pbase + (int64_t)sc * (TILE_F4 * 4) + tid + i * PF_THREADS;
+                v[u][i] = v4f{bwla_load_agent(p), bwla_load_agent(p + TILE_F4), bwla_load_agent(p + 2 * TILE_F4),
+                              bwla_load_agent(p + 3 * TILE_F4)};
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sum4 += ss + u < a.S ? v[u] : v4f{0.f, 0.f, 0.f, 0.f};
         }
-        store_T(e4, make_float4(sum4[0], sum4[1], sum4[2], sum4[3]));
+#pragma unroll
+        for (int u = 0; u < PF_BATCH; ++u)
+#pragma unroll
+            for (int i = 0; i < NJT; ++i) sum4[i] += ss + u < a.S ? v[u][i] : v4f{0.f, 0.f, 0.f, 0.f};
     }
+#pragma unroll
+    for (int i = 0; i < NJT; ++i)
+        store_T(tid + i * PF_THREADS, make_float4(sum4[i][0], sum4[i][1], sum4[i][2], sum4[i][3]));
     if (tid == 0) a.counters[unit] = 0;                // leave the counters as they were found
 }
 
