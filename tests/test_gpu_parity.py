@@ -296,6 +296,15 @@ def test_streaming_gemm_tiles(M, K, N, r):
     assert bool(((H.double() - h).abs() <= (2.0 ** -8 + 1e-5) * h.abs() + 1e-30).all()), "gated output"
 
 
+@pytest.mark.parametrize("n1,n2", [(16, 32), (64, 64), (64, 80), (128, 64), (128, 86), (160, 160)])
+def test_fp32_rotation_by_tiles_a_wavefront(n1, n2):
+    """2, 4 and 16 tiles a wavefront: the first and last factors of each kernel."""
+    from parity_util import run_case
+    K = n1 * n2
+    cfg = syn.LayerConfig(f"f32rot_{n1}x{n2}", 18, K, n1, n2, 48, 8, "f32", max(1, K // 100), 20.0, seed=41)
+    print(run_case(cfg), flush=True)
+
+
 def test_nibble_packed_a4_refusals():
     from parity_util import pack_on_gpu, DEV
     from paper_2605_00422_amd import binding as B

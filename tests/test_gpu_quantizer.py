@@ -129,6 +129,54 @@ def test_svd_square_against_lapack(nn):
     assert np.max(np.abs(u @ u.T - np.eye(nn))) < 1e-9
 
 
+@pytest.mark.parametrize("nn", [3, 7, 8, 9, 12, 17, 57, 63])
+def test_svd_square_blocks_of_columns(nn):
+    """Numbers of columns around the blocks of four (and pairs of blocks) that a wavefront holds up to 64;
+    a zero and a repeated column among them."""
+    qb = _qb()
+    rng = np.random.default_rng(100 + nn)
+    G = rng.standard_normal((nn, nn)) * np.exp(rng.standard_normal((1, nn)))
+    G[:, 1] = G[:, 0]
+    if nn > 3:
+        G[:, nn - 1] = 0.0
+    sig = torch.empty(nn, dtype=torch.float64, device="cuda")
+    Ut = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    Vt = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(2 * nn * nn * 8 + 256, dtype=torch.uint8, device="cuda")
+    qb.svd_square(_dev(G), sig, Ut, Vt, ws)
+    s, us, v = sig.cpu().numpy(), Ut.cpu().numpy(), Vt.cpu().numpy()
+    so = np.linalg.svd(G, compute_uv=False)
+    assert np.all(np.diff(s) <= 0)
+    assert np.allclose(s, so, rtol=1e-11, atol=1e-13 * so[0])
+    # exact null directions are given as zero vectors: compare what is unique
+    assert np.max(np.abs(us.T @ v - G)) < 1e-12 * so[0]
+    live = s > 1e-12 * so[0]
+    assert np.max(np.abs(v[live] @ v[live].T - np.eye(int(live.sum())))) < 1e-12
+
+
+@pytest.mark.parametrize("n1,n2", [(128, 80), (128, 82)])
+def test_rows_at_the_length_that_lds_keeps(n1, n2):
+    """Rows of 10240 columns keep their first pass's values in LDS, longer ones take them again."""
+    qb = _qb()
+    n, m = 4, n1 * n2
+    _, W, _, _, R1, R2 = _problem(7, n, n1, n2, 1)
+    X = Q.okt_rows(W, np.zeros_like(W), R1, R2)
+    c, s2 = Q.init_theta(X)
+    cd, sd = _dev(c), _dev(s2)
+    qb.em_step(_dev(X), Q.S2_MIN, cd, sd)
+    c, s2 = Q.em_step(X, c, s2)
+    assert np.allclose(cd.cpu().numpy(), c, rtol=1e-10) and np.allclose(sd.cpu().numpy(), s2, rtol=1e-10)
+    ws = _ws(n, m, n1, n2, 0)
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    qb.gmm_nll(_dev(X), cd, sd, out, ws)
+    assert abs(out.item() - Q.gmm_nll(X, c, s2)) < 1e-11 * abs(Q.gmm_nll(X, c, s2))
+    targets, lam = Q.mm_row_targets(W, R1, R2, c, s2)
+    Rn = torch.empty(n1, n1, dtype=torch.float64, device="cuda")
+    qb.procrustes(1, _dev(W), _dev(R1), _dev(R2), cd, sd, Rn, ws)
+    want = Q.procrustes_r1(W, R2, targets, lam, n1, n2)
+    assert np.max(np.abs(Rn.cpu().numpy() - want)) < 1e-8
+
+
 @pytest.mark.parametrize("n,n1,n2,k", SHAPES)
 def test_procrustes_updates(n, n1, n2, k):
     """Both Procrustes updates against the oracle's (App. A.2.2); the new factor is orthogonal and
