@@ -21,7 +21,21 @@ __device__ __forceinline__ int q_swz(int row, int kbyte, int Kp) {
     return row * Kp + (((gran & ~15) | ((gran ^ row) & 15)) << 4) + (kbyte & 15);
 }
 
-template <int NT>
+// MANY: code rows are staged with eight loads of a thread in flight; waiting for each before the next is most of
+// a short launch that has many to make.
+// EARLY: the epilogue's operands (scale, code sum, alpha, the first ranks of T and V) are asked for before the
+// contraction, two round trips to memory less at the end.  That holds 24 registers over the loop (98 against 74:
+// four wavefronts a SIMD instead of six), and of the wavefronts that share K all but one would ask for nothing.
+// Which form: at most GD_FEW granules a thread, the plain one (one token of 512, rank 8, 512 / 11008 channels:
+// 3.75 / 3.85 us plain, 4.3 / 4.5 many and early); more, and a wavefront has its tile to itself, both (16 tokens:
+// 5.0 / 5.8 -> 4.8 / 4.8; of 2560, rank 96: 13.4 / 16.2 -> 11.2 / 12.5); more, and two or four wavefronts
+// share K, many loads in flight while they do not fill the chip (GD_BUSY wavefronts a CU: 16 tokens of 1024, rank 32,
+// 4096 channels 6.0 -> 5.5; of 2048, rank 40, 4096 / 11008 channels 6.6 -> 5.9 / 7.1 -> 7.9).  Eight
+// sharing K hide their loads from one another (4096 -> 4096, rank 112, 16 tokens 8.4 plain, 8.8).
+constexpr int GD_BUSY = 8;
+constexpr int GD_FEW = 4;
+
+template <int NT, bool MANY, bool EARLY>
 __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
     const uint4* __restrict__ bits, int chunks, int row_tiles, const int8_t* __restrict__ q, int M, int K,
     const float* __restrict__ scale, const int32_t* __restrict__ qsum, const __half* __restrict__ alpha,
@@ -48,11 +62,15 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
         }
     }
 
-    // ---- what the epilogue needs of the token, asked for early: two round trips to memory less at the end
+    // ---- what the epilogue needs
     const int t = li;
     const bool tok_ok = t < M;
-    const float st = tok_ok ? scale[t] : 0.0f;
-    const int qs = tok_ok ? qsum[t] : 0;
+    float st = 0.0f;
+    int qs = 0;
+    auto token_operands = [&] {
+        st = tok_ok ? scale[t] : 0.0f;
+        qs = tok_ok ? qsum[t] : 0;
+    };
     const int JT = (r + 15) >> 4;
     const int rp = JT * 16;                            // V rows are stored padded to rp halfs
     // low-rank operands of tile `tile`, ranks 16 u + 4 lg + 0 .. 3: V row li of the tile, T row of token li
@@ -74,29 +92,32 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
         }
     };
     float v0[4] = {0.f, 0.f, 0.f, 0.f}, t0[4] = {0.f, 0.f, 0.f, 0.f}, al[4];
-    if (JT > 0) low_operands(tile0, 0, v0, t0);
+    if constexpr (EARLY) {
+        token_operands();
+        if (JT > 0) low_operands(tile0, 0, v0, t0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int n = tile0 * 16 + 4 * lg + v;
-        al[v] = __half2float(alpha[n < N ? n : N - 1]);
+        for (int v = 0; v < 4; ++v) {
+            const int n = tile0 * 16 + 4 * lg + v;
+            al[v] = __half2float(alpha[n < N ? n : N - 1]);
+        }
     }
 
-    // ---- stage the code rows into LDS (zero beyond K), eight loads of a thread in flight: a workgroup of one
-    // wavefront (K <= 512) has eight to make, and waited for each before the next
+    // ---- stage the code rows into LDS (zero beyond K)
     {
+        constexpr int BATCH = MANY ? 8 : 1;            // loads of a thread in flight
         const int gran_per_row = Kp >> 4;
         const int total = rows * gran_per_row, step = (int)blockDim.x;
-        for (int base = tid; base < total; base += 8 * step) {
-            uint4 v[8];
+        for (int base = tid; base < total; base += BATCH * step) {
+            uint4 v[BATCH];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int e = 0; e < BATCH; ++e) {
                 const int idx = base + e * step;
                 const int row = idx / gran_per_row, gcol = idx - row * gran_per_row;
                 v[e] = make_uint4(0, 0, 0, 0);
                 if (idx < total && gcol * 16 < K) v[e] = *reinterpret_cast<const uint4*>(q + (int64_t)row * K + gcol * 16);
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int e = 0; e < BATCH; ++e) {
                 const int idx = base + e * step;
                 const int row = idx / gran_per_row, gcol = idx - row * gran_per_row;
                 if (idx < total) *reinterpret_cast<uint4*>(smem + q_swz(row, gcol * 16, Kp)) = v[e];
@@ -165,6 +186,7 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
     }
 
     // ---- epilogue: lane holds token li, output rows n = 16*tile + 4*lg + v
+    if constexpr (!EARLY) token_operands();
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int tile = tile0 + nt;
@@ -174,7 +196,7 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
         // j = 16u + 4*lg + e in step e of group u for both operands
         v4f low = v4f{0.f, 0.f, 0.f, 0.f};
         for (int u = 0; u < JT; ++u) {
-            if (nt > 0 || u > 0) low_operands(tile, u, v0, t0);
+            if (!EARLY || nt > 0 || u > 0) low_operands(tile, u, v0, t0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) low = __builtin_amdgcn_mfma_f32_16x16x4f32(v0[e], t0[e], low, 0, 0, 0);
         }
@@ -184,7 +206,7 @@ __global__ __launch_bounds__(64 * GD_MAX_WAVES) void gemm_decode_kernel(
             const int n = n0 + 4 * lg + v;
             if (n < N) {
                 const int a = 2 * res[nt][v] - qs;
-                const float an = nt == 0 ? al[v] : __half2float(alpha[n]);
+                const float an = EARLY && nt == 0 ? al[v] : __half2float(alpha[n]);
                 Y[(int64_t)t * N + n] = st * an * (float)a + low[v];
                 if (acc_out) acc_out[(int64_t)t * N + n] = a;
             }
@@ -213,9 +235,15 @@ hipError_t bwla_launch_gemm_decode(const bwla_layer_t* L, const int8_t* dq, cons
     size_t lds = (size_t)rows * chunks * BWLA_CHUNK_COLS;
     const size_t red = (size_t)waves * NT * 64 * 16;
     if (lds < red) lds = red;
-    hipError_t e = bwla_ensure_lds((const void*)gemm_decode_kernel<1>, lds);
+    const bool alone = ksplit == 1;
+    const bool many = rows * chunks * (BWLA_CHUNK_COLS / 16) > GD_FEW * 64 * waves &&
+                      (alone || (ksplit <= 4 && groups * waves < GD_BUSY * bwla_device_cus()));
+    const auto kern = !many   ? gemm_decode_kernel<1, false, false>
+                      : alone ? gemm_decode_kernel<1, true, true>
+                              : gemm_decode_kernel<1, true, false>;
+    hipError_t e = bwla_ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
-    gemm_decode_kernel<1><<<dim3((unsigned)groups), dim3(64 * waves), lds, st>>>(
+    kern<<<dim3((unsigned)groups), dim3(64 * waves), lds, st>>>(
         (const uint4*)(blob + L->off_bits), chunks, row_tiles, dq, (int)M, (int)L->K, dscale, dqsum,
         (const __half*)(blob + L->off_alpha), (const __half*)(blob + L->off_V), dT, L->r, dY, (int)L->N, dacc,
         ksplit, wn);

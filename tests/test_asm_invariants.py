@@ -169,3 +169,19 @@ def test_partial_sums_are_acknowledged_before_the_arrival_count(src, min_sites):
         assert waits, f"{src}: no vmcnt(0) wait between the partial stores (line {st}) and the barrier (line {bar})"
         assert not any(lines[j].startswith("global_store") for j in range(waits[-1], bar))
     assert sites >= min_sites
+
+
+def test_decode_fallback_asks_early_only_where_a_wavefront_has_its_tile_alone():
+    """gemm_decode_kernel<NT, MANY, EARLY>: operands of the epilogue held over the contraction cost registers
+    (98: four wavefronts a SIMD) and, where wavefronts share K, loads that all but one of them throw away.  The
+    forms that such workgroups are launched with stay at six wavefronts a SIMD (512 / 6 = 85 registers) and ask for nothing
+    before the contraction but sign bits (16 bytes a lane) and code rows."""
+    lines = _device_asm("gemm_decode.hip")
+    for many in (0, 1):
+        start = next(i for i, l in enumerate(lines) if re.match(rf"_ZN.*gemm_decode_kernelILi1ELb{many}ELb0E.*:", l))
+        body = lines[start:next(i for i in range(start, len(lines)) if lines[i].startswith("s_endpgm"))]
+        meta = next(i for i in range(start, len(lines)) if lines[i].startswith(".amdhsa_next_free_vgpr"))
+        assert int(lines[meta].split()[1]) <= 84
+        head = body[:next(i for i, l in enumerate(body) if l.startswith("s_barrier"))]
+        assert any(l.startswith("global_load_dwordx4") for l in head)
+        assert not any(re.match(r"global_load_(dword |dwordx2|ushort|short)", l) for l in head)

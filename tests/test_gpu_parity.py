@@ -296,6 +296,19 @@ def test_streaming_gemm_tiles(M, K, N, r):
     assert bool(((H.double() - h).abs() <= (2.0 ** -8 + 1e-5) * h.abs() + 1e-30).all()), "gated output"
 
 
+@pytest.mark.parametrize("M,K,N,r", [
+    (8, 512, 90, 20), (9, 512, 90, 20),             # one wavefront a tile: four granules a thread, then more (early operands)
+    (16, 256, 18, 0),
+    (2, 1536, 200, 40), (3, 1536, 200, 40),         # three chunks: one wavefront a tile, rows padded to no power of two
+    (8, 1024, 100, 96), (9, 1024, 100, 96),         # two wavefronts share K
+    (16, 2048, 8176, 40), (16, 2048, 8192, 40),     # four share K: the last size that does not fill the chip, the first that does
+    (16, 4096, 80, 112),                            # eight share K
+])
+def test_decode_fallback_forms(M, K, N, r):
+    """The decode GEMM behind the streaming one, at the edges of the rule that picks its form."""
+    test_streaming_gemm_tiles(M, K, N, r)
+
+
 @pytest.mark.parametrize("n1,n2", [(16, 32), (64, 64), (64, 80), (128, 64), (128, 86), (160, 160)])
 def test_fp32_rotation_by_tiles_a_wavefront(n1, n2):
     """2, 4 and 16 tiles a wavefront: the first and last factors of each kernel."""
