@@ -236,8 +236,11 @@ __global__ __launch_bounds__(PF_THREADS) void psp_prefill_kernel(PfArgs a) {
     const float* pbase = a.partials + (int64_t)unit * a.S * (TILE_F4 * 4);
     // PF_BATCH slices of all my vectors in flight at a time (slices past S re-read the last one and add zero): a
     // batch is a round trip to memory, and vector by vector there were four to eight of them one after the other
-    // (257 tokens of 8192, rank 64, sixteen slices: whole launch 15.0 -> 13.0 us; 2048 of 4096 14.0 -> 12.9)
-    constexpr int PF_BATCH = 4;
+    // (257 tokens of 8192, rank 64, sixteen slices: whole launch 15.0 -> 13.0 us; 2048 of 4096 14.0 -> 12.9).
+    // Four slices of four vectors or eight of two are 64 registers; one vector takes eight slices as well (their
+    // number is a multiple of eight wherever the launch is resident at once): four cost it a round trip more
+    // (rank 8: 512 tokens of 11008 9.6 us with eight, 10.3 with four; 2048 of 4096 7.9 and 8.5).
+    constexpr int PF_BATCH = NJT > 2 ? 4 : 8;
     v4f sum4[NJT];
 #pragma unroll
     for (int i = 0; i < NJT; ++i) sum4[i] = v4f{0.f, 0.f, 0.f, 0.f};

@@ -185,3 +185,21 @@ def test_decode_fallback_asks_early_only_where_a_wavefront_has_its_tile_alone():
         head = body[:next(i for i, l in enumerate(body) if l.startswith("s_barrier"))]
         assert any(l.startswith("global_load_dwordx4") for l in head)
         assert not any(re.match(r"global_load_(dword |dwordx2|ushort|short)", l) for l in head)
+
+
+def test_last_workgroup_of_a_projection_tile_keeps_enough_slices_in_flight():
+    """psp_prefill_kernel<BF16, NJT>: the partial sums of eight slices (four, of four vectors a thread: the counter of loads
+    in flight holds 63) are requested before the first of them is waited for, whatever the number of vectors."""
+    lines = _device_asm("psp_prefill.hip")
+    for bf16 in (0, 1):
+        for njt, least in ((1, 8 * 4), (2, 8 * 2 * 4), (4, 40)):
+            start = next(i for i, l in enumerate(lines) if re.match(rf"_ZN.*psp_prefill_kernelILb{bf16}ELi{njt}E.*:", l))
+            end = next(i for i in range(start, len(lines)) if lines[i].startswith(".amdhsa_next_free_vgpr"))
+            run = best = 0
+            for l in lines[start:end]:
+                if l.startswith("global_load_dword ") and l.endswith("sc1"):
+                    run += 1
+                    best = max(best, run)
+                elif l.startswith("s_waitcnt") and "vmcnt" in l:
+                    run = 0
+            assert best >= least, (bf16, njt, best)
