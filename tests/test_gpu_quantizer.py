@@ -177,6 +177,29 @@ def test_rows_at_the_length_that_lds_keeps(n1, n2):
     assert np.max(np.abs(Rn.cpu().numpy() - want)) < 1e-8
 
 
+def test_nll_keeps_the_terms_below_the_rounding_of_one():
+    """Entries on a component whose other component is 40 nats down add log1p(exp(-40)) = 4.2e-18 each, less than
+    the rounding of 1 + exp(-40).  With s^2 next to 1 / (8 pi) the leading terms, log 2 - log 2, vanish exactly at some
+    of the neighbouring doubles (rounding of log decides at which), and what is left there is the sum of these."""
+    qb = _qb()
+    m = 5000
+    tail = np.log1p(np.exp(-40.0))
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    got = []
+    v = 1.0 / (8.0 * np.pi)
+    for _ in range(8):
+        v = np.nextafter(v, 0.0)
+    for _ in range(16):
+        v = np.nextafter(v, 1.0)
+        c = np.sqrt(20.0 * v)                               # 2 c^2 / s^2 = 40
+        qb.gmm_nll(torch.full((1, m), c, dtype=torch.float64, device="cuda"), _dev(np.array([c])), _dev(np.array([v])), out, ws)
+        got.append(out.item())
+    # exp's argument is off by a few roundings of 40, the sums by m roundings at the very most
+    assert any(abs(g + tail) < 1e-10 * tail for g in got), got
+    assert all(abs(g) < 1e-14 for g in got)
+
+
 @pytest.mark.parametrize("n,n1,n2,k", SHAPES)
 def test_procrustes_updates(n, n1, n2, k):
     """Both Procrustes updates against the oracle's (App. A.2.2); the new factor is orthogonal and
