@@ -154,6 +154,72 @@ def test_svd_square_blocks_of_columns(nn):
     assert np.max(np.abs(v[live] @ v[live].T - np.eye(int(live.sum())))) < 1e-12
 
 
+def _singular_values_80_bits(G):
+    """One-sided Jacobi in the host's extended precision, every rotation from its three inner products."""
+    W = G.astype(np.longdouble)
+    n = W.shape[1]
+    for _ in range(60):
+        rotated = False
+        for p in range(n - 1):
+            for q in range(p + 1, n):
+                x, y = W[:, p], W[:, q]
+                al, be, ga = x @ x, y @ y, x @ y
+                if al > 0 and be > 0 and abs(ga) > np.longdouble(1e-18) * np.sqrt(al) * np.sqrt(be):
+                    z = (be - al) / (2 * ga)
+                    t = (1 if z >= 0 else -1) / (abs(z) + np.sqrt(1 + z * z))
+                    c = 1 / np.sqrt(1 + t * t)
+                    W[:, p], W[:, q] = c * x - c * t * y, c * t * x + c * y
+                    rotated = True
+        if not rotated:
+            break
+    return np.sort(np.sqrt((W * W).sum(0)))[::-1]
+
+
+@pytest.mark.parametrize("kind", ["normal", "graded", "half rank", "condition", "gram"])
+@pytest.mark.parametrize("nn", [16, 33, 48, 72])
+def test_svd_square_errors_stay_at_the_roundings(nn, kind):
+    """Against extended precision.  A column takes part in nn - 1 rotations a sweep, some ten sweeps; each errs by three
+    roundings of its norm, which add up as a random walk: 3 eps sqrt(10 nn), and the largest of nn^2 entries lies
+    within four times that."""
+    qb = _qb()
+    rng = np.random.default_rng(200 + nn)
+    q, p = _rand_orth(rng, nn), _rand_orth(rng, nn)
+    G = {"normal": lambda: rng.standard_normal((nn, nn)),
+         "graded": lambda: rng.standard_normal((nn, nn)) * 10.0 ** -np.linspace(0, 12, nn)[None, :],
+         "half rank": lambda: rng.standard_normal((nn, nn // 2)) @ rng.standard_normal((nn // 2, nn)),
+         "condition": lambda: (q * 10.0 ** -np.linspace(0, 14, nn)) @ p.T,
+         "gram": lambda: (q * 10.0 ** -np.linspace(0, 14, nn)) @ q.T}[kind]()
+    sig = torch.empty(nn, dtype=torch.float64, device="cuda")
+    Ut = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    Vt = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    qb.svd_square(_dev(G), sig, Ut, Vt, torch.zeros(2 * nn * nn * 8 + 256, dtype=torch.uint8, device="cuda"))
+    s, us, v = (t.cpu().numpy().astype(np.longdouble) for t in (sig, Ut, Vt))
+    want = _singular_values_80_bits(G)
+    bound = 4 * 3 * 2.0 ** -52 * np.sqrt(10.0 * nn)
+    errs = (np.max(np.abs(s - want)) / want[0], np.max(np.abs(us.T @ v - G)) / want[0], np.max(np.abs(v @ v.T - np.eye(nn))))
+    print(kind, nn, ["%.1e" % e for e in errs], "%.1e" % bound)
+    assert max(errs) < bound
+
+
+@pytest.mark.parametrize("exponent", [-60, 60])
+def test_svd_square_of_scaled_columns(exponent):
+    """Rotations between columns whose norms are 60 decades apart, and inner products far from one: the tangent's
+    reciprocals and root at the ends of their range."""
+    qb = _qb()
+    nn = 12
+    rng = np.random.default_rng(3)
+    G = rng.standard_normal((nn, nn)) * 10.0 ** np.where(np.arange(nn) % 2, exponent, 0)[None, :]
+    sig = torch.empty(nn, dtype=torch.float64, device="cuda")
+    Ut = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    Vt = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+    qb.svd_square(_dev(G), sig, Ut, Vt, torch.zeros(2 * nn * nn * 8 + 256, dtype=torch.uint8, device="cuda"))
+    want = _singular_values_80_bits(G)
+    s, us, v = (t.cpu().numpy() for t in (sig, Ut, Vt))
+    # one-sided rotations keep each singular value to its own size while the scaled columns are well conditioned
+    assert np.max(np.abs(s - want) / want) < 1e-12
+    assert np.max(np.abs(v @ v.T - np.eye(nn))) < 1e-13 and np.max(np.abs(us.T @ v - G) / np.linalg.norm(G, axis=0)) < 1e-13
+
+
 @pytest.mark.parametrize("n1,n2", [(128, 80), (128, 82)])
 def test_rows_at_the_length_that_lds_keeps(n1, n2):
     """Rows of 10240 columns keep their first pass's values in LDS, longer ones take them again."""
