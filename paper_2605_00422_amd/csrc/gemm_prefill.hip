@@ -14,6 +14,7 @@
 //   gemm_prefill_kernel         the remaining shapes: code tiles shared through LDS, double
 //                               buffered, one barrier per 128 columns
 #include "bwla_internal.h"
+#include "gemm_tiles.h"
 
 namespace {
 
@@ -185,8 +186,8 @@ hipError_t launch_cfg(const bwla_layer_t* L, const int8_t* dq, const float* dsca
 }
 
 // ------------------------------------------------------------------------------------------
-// Large token batches: every wavefront streams its own operands and synchronizes with nobody --
-// no workgroup barriers.  A wavefront owns 64 token rows x NTL*32 output channels.  Per
+// Every wavefront streams its own operands -- no workgroup barriers in the loop, but for the one a slice of the
+// kernels with one ring of codes.  A wavefront owns 64 token rows x NTL*32 output channels.  Per
 // 128-column slice of K
 //   * its 64 code rows travel global -> LDS asynchronously (16 bytes per lane, 8 lanes per
 //     128-byte row segment, no registers involved) into a private ring of four swizzled 8 KiB
@@ -194,8 +195,7 @@ hipError_t launch_cfg(const bwla_layer_t* L, const int8_t* dq, const float* dsca
 //     lane (row l32, half lg) gets columns [64*lg, 64*lg + 64) of the slice, 16 per step;
 //   * the 16-byte bit slice of each of its NTL weight rows goes straight into a ring of four
 //     register slots, four slices ahead.
-// Step s of a slice contracts the 16-column group 4*lg + s on both operands.  The four
-// wavefronts of a workgroup share the weight rows (L1 hits) and take different token rows.
+// Step s of a slice contracts the 16-column group 4*lg + s on both operands.
 //
 // The compiler cannot tell which ring tile an LDS read touches, and with an asynchronous copy
 // in flight it turns every wait for a vector-memory result into a wait for all of them.  The
@@ -206,18 +206,8 @@ hipError_t launch_cfg(const bwla_layer_t* L, const int8_t* dq, const float* dsca
 // register written by such a load is not touched between the load and its wait.
 constexpr int GD_MT = 2;
 constexpr int GD_ROWS = GD_MT * 32;                 // token rows per wavefront
+static_assert(GD_ROWS == GD_TILE_TOKENS, "gemm_tiles.h");
 constexpr int GD_TILE = GD_ROWS * 128;              // bytes of one private code tile
-constexpr int GD_BUFS = 4;                          // private code tiles per wavefront
-
-typedef __attribute__((ext_vector_type(8))) __bf16 v8bf;
-
-// x = h1 + h2 + h3 exactly, each a bf16
-__device__ __forceinline__ void gd_split3(float x, __bf16& h1, __bf16& h2, __bf16& h3) {
-    h1 = (__bf16)x;
-    const float r1 = x - (float)h1;
-    h2 = (__bf16)r1;
-    h3 = (__bf16)(r1 - (float)h2);
-}
 
 // 16-byte position of piece `c16` of row `row` inside its 128-byte LDS row; the XOR key makes
 // the column-wise operand reads conflict free
@@ -242,21 +232,20 @@ constexpr int gd_vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4
 // A row of a slice is then 64 bytes; a lane reads one packed piece for two contraction steps and
 // moves each nibble to the top of its byte, (x << 4) & 0xf0.. and x & 0xf0..: int8 operands worth 16
 // times the code, so the accumulators are exact multiples of 16 and are shifted down once at the end.
-// SHARED: the WN wavefronts side by side work on one ring of code tiles, of which each copies its part,
-// instead of a private ring each: see gemm_prefill_shared_kernel.
-template <int NTL, int WM, int WK, int NB, bool GATED, bool A4, int WN, bool SHARED>
+// A tile is 64 tokens by NTL * 32 channels of a wavefront.  WK wavefronts take the same tile and split its slices of
+// K, each with a ring of its own (few tokens: more wavefronts in flight), and add their accumulators through LDS;
+// or WN wavefronts stand side by side along the channels and work on one ring of code tiles, of which each copies
+// its part: see gemm_prefill_shared_kernel.
+template <int NTL, int WK, int NB, int WN, bool GATED, bool A4>
 __device__ __forceinline__ void gd_body(
     const uint4* __restrict__ bits, int chunks, int row_tiles, const int8_t* __restrict__ q, int M, int K,
     const float* __restrict__ scale, const int32_t* __restrict__ qsum, const __half* __restrict__ alpha,
     const __half* __restrict__ V, const float* __restrict__ T, int r, float* __restrict__ Y, int N,
     int32_t* __restrict__ acc_out, int tiles_m, int tiles_n, uint16_t* __restrict__ H) {
     constexpr int MT = GD_MT;
-    // WM wavefronts stacked along the tokens; WK wavefronts share one tile and split its slices of K
-    // (small batches: more wavefronts in flight), their accumulators are added through LDS
-    // WN wavefronts side by side along the channels (wavefronts with the same token rows then ask for the
-    // same code rows at about the same time: the second request is served by the CU's L1)
     static_assert(WN == 1 || WK == 1, "channel-wise stacking is for unsplit K");
-    constexpr int BM = WM * GD_ROWS, BN = WN * NTL * 32;
+    constexpr bool SHARED = WN > 1;
+    constexpr int BM = GD_ROWS, BN = WN * NTL * 32;
     // vector-memory operations per slice and wavefront: NTL weight loads, then 8 code copies;
     // when slice j + 1 is needed, the operations of slices j + 2 and j + 3 may still be in flight
     // (NB = ring depth, 4 or 2: code tiles in LDS and weight slots in registers)
@@ -269,9 +258,9 @@ __device__ __forceinline__ void gd_body(
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WM, wk = WK == 1 ? 0 : wave / WM, wn = WK == 1 ? wave / WM : 0;
+    const int wk = WK == 1 ? 0 : wave, wn = WK == 1 ? wave : 0;
     const int l32 = lane & 31, lg = lane >> 5;
-    char* mytile = smem + (SHARED ? wm : wave) * (NB * GD_TILE);
+    char* mytile = smem + (SHARED ? 0 : wave) * (NB * GD_TILE);
     const uint32_t mytile_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)mytile;
 
     // XCD-aware tile order (workgroups are dealt round-robin to the 8 XCDs): one XCD works on
@@ -280,7 +269,7 @@ __device__ __forceinline__ void gd_body(
     const int nblocks = gridDim.x;
     if ((nblocks & 7) == 0) pid = (pid & 7) * (nblocks >> 3) + (pid >> 3);
     const int tm = pid / tiles_n, tn = pid - tm * tiles_n;
-    const int m_base = tm * BM + wm * GD_ROWS, n_base = tn * BN + wn * (NTL * 32);
+    const int m_base = tm * BM, n_base = tn * BN + wn * (NTL * 32);
     // my slices of K: [s_begin, s_begin + nslices) of K / 128 (K % 128 == 0, checked by the launcher)
     const int ns_all = K >> 7;
     const int ns_per = (ns_all + WK - 1) / WK;
@@ -497,7 +486,7 @@ __device__ __forceinline__ void gd_body(
                 for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                        red[((wk - 1) * WM + wm) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane] = acc[mt][nt][v];
+                        red[(wk - 1) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane] = acc[mt][nt][v];
         }
         __syncthreads();
         if (wk > 0) return;
@@ -509,7 +498,7 @@ __device__ __forceinline__ void gd_body(
                 for (int nt = 0; nt < NTL; ++nt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                        acc[mt][nt][v] += red[((w - 1) * WM + wm) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane];
+                        acc[mt][nt][v] += red[(w - 1) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane];
     }
 
     if constexpr (A4) {
@@ -674,129 +663,63 @@ __device__ __forceinline__ void gd_body(
         int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, uint16_t *__restrict__ H
 #define GD_ARGS bits, chunks, row_tiles, q, M, K, scale, qsum, alpha, V, T, r, Y, N, acc_out, tiles_m, tiles_n, H
 
-template <int NTL, int WM, int WK, int NB, bool GATED = false, bool A4 = false, int WN = 1>
-__global__ __launch_bounds__(64 * WM * WK * WN, NB == 2 ? 2 : 1) void gemm_prefill_direct_kernel(GD_PARAMS) {
-    gd_body<NTL, WM, WK, NB, GATED, A4, WN, false>(GD_ARGS);
+template <int NTL, int WK, int NB, bool GATED, bool A4>
+__global__ __launch_bounds__(64 * WK, 1) void gemm_prefill_direct_kernel(GD_PARAMS) {
+    gd_body<NTL, WK, NB, 1, GATED, A4>(GD_ARGS);
 }
 
 // Private rings make every wavefront fetch all code rows of its tile for itself: a CU with four wavefronts
 // asks for 32 KiB of codes and up to 8 KiB of weights per slice, some 40 bytes a clock at the rate the
 // matrix cores could work at, and that path (L2 -> L1 -> LDS) is what bounds the direct kernel at every
 // size but the smallest.  Here the WN wavefronts over the same token rows fill one ring together and meet
-// at one barrier a slice: the codes enter the CU once (28672 -> 8192 at 4096 tokens 735 -> 666 us; the
+// at one barrier a slice: the codes enter the CU once (28672 -> 8192 at 4096 tokens 733 -> 680 us; the
 // four loads in flight of a ring hide the barrier, and two workgroups a CU each other's).
-template <int NTL, int WM, int NB, bool GATED, bool A4, int WN>
-__global__ __launch_bounds__(64 * WM * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
-    gd_body<NTL, WM, 1, NB, GATED, A4, WN, true>(GD_ARGS);
+template <int NTL, int NB, int WN, bool GATED, bool A4>
+__global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
+    gd_body<NTL, 1, NB, WN, GATED, A4>(GD_ARGS);
 }
 #undef GD_PARAMS
 #undef GD_ARGS
 
-template <int NTL, int WM, int WK, int NB, int WN = 1, bool SHARED = false>
-hipError_t launch_direct(const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
-                         const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH,
-                         bool a4 = false) {
-    constexpr int BM = WM * GD_ROWS, BN = WN * NTL * 32;
+template <int NTL, int WK, int NB, int WN>
+hipError_t launch_streaming(const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
+                            const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH,
+                            bool a4) {
+    constexpr int BM = GD_ROWS, BN = WN * NTL * 32;
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
-    const size_t lds = (size_t)WM * WK * (SHARED ? 1 : WN) * NB * GD_TILE;
-    static_assert((size_t)(WK - 1) * WM * GD_MT * NTL * 16 * 64 * 4 <= (size_t)WM * WK * NB * GD_TILE,
+    const size_t lds = (size_t)WK * NB * GD_TILE;
+    static_assert((size_t)(WK - 1) * GD_MT * NTL * 16 * 64 * 4 <= (size_t)WK * NB * GD_TILE,
                   "the partial sums must fit into the tile rings");
     auto launch = [&](auto kern) -> hipError_t {
         hipError_t e = bwla_ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
-        kern<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * WM * WK * WN), lds, st>>>(
+        kern<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * WK * WN), lds, st>>>(
             (const uint4*)(blob + L->off_bits), (int)bwla_chunks(L->K), (int)bwla_row_tiles(L->N), dq, (int)M,
             (int)L->K, dscale, dqsum, (const __half*)(blob + L->off_alpha), (const __half*)(blob + L->off_V), dT,
             L->r, dY, (int)L->N, dacc, tiles_m, tiles_n, dH);
         return hipGetLastError();
     };
     if (a4 && dH != nullptr) return hipErrorInvalidValue;
-    if constexpr (SHARED) {
-        if (a4) return launch(gemm_prefill_shared_kernel<NTL, WM, NB, false, true, WN>);
-        if (dH != nullptr) return launch(gemm_prefill_shared_kernel<NTL, WM, NB, true, false, WN>);
-        return launch(gemm_prefill_shared_kernel<NTL, WM, NB, false, false, WN>);
+    if constexpr (WN > 1) {
+        if (a4) return launch(gemm_prefill_shared_kernel<NTL, NB, WN, false, true>);
+        if (dH != nullptr) return launch(gemm_prefill_shared_kernel<NTL, NB, WN, true, false>);
+        return launch(gemm_prefill_shared_kernel<NTL, NB, WN, false, false>);
     } else {
-        if (a4) return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, true, WN>);
-        if (dH != nullptr) return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, true, false, WN>);
-        return launch(gemm_prefill_direct_kernel<NTL, WM, WK, NB, false, false, WN>);
+        if (a4) return launch(gemm_prefill_direct_kernel<NTL, WK, NB, false, true>);
+        if (dH != nullptr) return launch(gemm_prefill_direct_kernel<NTL, WK, NB, true, false>);
+        return launch(gemm_prefill_direct_kernel<NTL, WK, NB, false, false>);
     }
-}
-
-// ------------------------------------------------------------------------------------------
-// Which tile serves M tokens and N channels.  Most variants below win somewhere between 17 and 4096
-// tokens, and what decides is how its tiles come out in rounds over the CUs: 257 tokens x 8192 channels
-// are 104 to 128 large tiles (half the chip, half of the rows padding) or 430 tiles of 64 x 96, two to a
-// CU.  So each variant carries a small cost, in microseconds: a tile takes base[r - 1] + slice[r - 1] per
-// 128-column slice of K that a wavefront contracts when r workgroups share the CU, full rounds run at the
-// largest r, the last one at the r that it comes to, and `start` is paid once; the smallest sum is taken.
-// The constants are a least-squares fit to 370 shapes (17 .. 4096 tokens, K 512 .. 28672, N 64 .. 28672 at
-// random, three layers in turn so that nothing stays in L2), nudged per variant where a choice lost time.
-// Over those shapes the choice takes 0.90 of the time of the two thresholds between large and small tiles,
-// all with private rings, that stood here before (0.49 at best, within 1.4 % of the best variant on average):
-// 8192 -> 8192 at 257 tokens 57 -> 34 us, 4096 -> 11008 at 333 40 -> 33, 4096 -> 22016 at 2048 258 -> 207,
-// 28672 -> 8192 at 4096 712 -> 652 (2.95 POP/s).
-struct GdVariant {
-    int ntl, wm, wk, nb, wn;      // template arguments
-    bool shared;                  // one ring of code tiles for the wn wavefronts over the same tokens
-    int resident;                 // workgroups a CU holds (LDS of the tile rings, registers)
-    float start, base[4], slice[4];
-};
-constexpr GdVariant GD_VARIANTS[] = {
-    // few tokens: private rings, the wavefronts of a workgroup share out K
-    {1, 1, 4, 4, 1, false, 1, 0.9f, {10.3f}, {0.374f}},                                                      // 64 x 32, in four
-    {2, 1, 4, 4, 1, false, 1, 0.3f, {13.9f}, {0.398f}},                                                      // 64 x 64, in four
-    {2, 1, 2, 4, 1, false, 2, 1.3f, {11.2f, 12.5f}, {0.324f, 0.413f}},                                       // 64 x 64, in two
-    {3, 1, 2, 4, 1, false, 2, 1.1f, {13.4f, 15.2f}, {0.401f, 0.498f}},                                       // 64 x 96, in two
-    {1, 1, 1, 4, 1, false, 4, 0.0f, {9.8f, 10.3f, 10.9f, 10.6f}, {0.256f, 0.270f, 0.299f, 0.358f}},          // 64 x 32, one wavefront
-    // one ring of codes for four wavefronts (the first: two)
-    {1, 1, 1, 4, 2, true, 4, 2.5f, {7.3f, 8.3f, 13.0f, 12.4f}, {0.247f, 0.322f, 0.349f, 0.495f}},            // 64 x 64
-    {1, 1, 1, 4, 4, true, 3, 0.0f, {10.4f, 14.7f, 15.6f}, {0.277f, 0.369f, 0.599f}},                         // 64 x 128
-    {2, 1, 1, 4, 4, true, 2, 0.3f, {11.6f, 14.2f}, {0.290f, 0.637f}},                                        // 64 x 256
-    {3, 1, 1, 4, 4, true, 2, 4.6f, {9.5f, 18.5f}, {0.380f, 0.832f}},                                         // 64 x 384
-    {4, 1, 1, 2, 4, true, 2, 1.4f, {14.0f, 26.2f}, {0.570f, 1.188f}},                                        // 64 x 512, ring of two
-    {5, 1, 1, 4, 4, true, 1, 0.0f, {17.1f}, {0.687f}},                                                       // 64 x 640
-    // large tiles with private rings
-    {4, 4, 1, 2, 1, false, 2, 0.0f, {17.1f, 29.3f}, {0.580f, 1.328f}},                                       // 256 x 128, ring of two
-    {4, 4, 1, 4, 1, false, 1, 0.0f, {19.7f}, {0.588f}},                                                      // 256 x 128
-    {5, 4, 1, 4, 1, false, 1, 0.0f, {20.2f}, {0.715f}},                                                      // 256 x 160
-    {5, 1, 1, 4, 4, false, 1, 0.0f, {19.7f}, {0.718f}},                                                      // 64 x 640
-};
-constexpr int GD_NVARIANTS = sizeof(GD_VARIANTS) / sizeof(GD_VARIANTS[0]);
-
-inline float gd_cost(const GdVariant& v, int64_t M, int64_t K, int64_t N, int64_t cus) {
-    const int64_t bm = v.wm * GD_ROWS, bn = v.wn * v.ntl * 32;
-    const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), cap = cus * v.resident;
-    const float slices = (float)(((K >> 7) + v.wk - 1) / v.wk);
-    const int64_t full = tiles / cap, rem = tiles - full * cap;
-    float t = v.start + (float)full * (v.base[v.resident - 1] + v.slice[v.resident - 1] * slices);
-    if (rem > 0) {
-        const int r = (int)((rem + cus - 1) / cus);
-        t += v.base[r - 1] + v.slice[r - 1] * slices;
-    }
-    return t;
-}
-
-// index into GD_VARIANTS
-inline int gd_pick(int64_t M, int64_t K, int64_t N, int64_t cus) {
-    int best = 0;
-    float cost = gd_cost(GD_VARIANTS[0], M, K, N, cus);
-    for (int i = 1; i < GD_NVARIANTS; ++i) {
-        const float c = gd_cost(GD_VARIANTS[i], M, K, N, cus);
-        if (c < cost) { cost = c; best = i; }
-    }
-    return best;
 }
 
 template <int I>
-hipError_t launch_variant(int pick, const bwla_layer_t* L, const int8_t* dq, const float* dscale,
-                          const int32_t* dqsum, const float* dT, int64_t M, float* dY, int32_t* dacc,
-                          hipStream_t st, uint16_t* dH, bool a4) {
-    constexpr GdVariant v = GD_VARIANTS[I];
+hipError_t launch_tile(int pick, const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
+                       const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4) {
+    constexpr GdTile v = GD_TILES[I];
     if (pick == I)
-        return launch_direct<v.ntl, v.wm, v.wk, v.nb, v.wn, v.shared>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
-    if constexpr (I + 1 < GD_NVARIANTS)
-        return launch_variant<I + 1>(pick, L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+        return launch_streaming<v.ntl, v.wk, v.nb, v.wn>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+    if constexpr (I + 1 < GD_NTILES)
+        return launch_tile<I + 1>(pick, L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
     return hipErrorInvalidValue;
 }
 
@@ -809,8 +732,8 @@ hipError_t bwla_launch_gemm_prefill(const bwla_layer_t* L, const int8_t* dq, con
                                     const int32_t* dqsum, const float* dT, int64_t M, float* dY,
                                     int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4) {
     if (bwla_gemm_prefill_streams(L))
-        return launch_variant<0>(gd_pick(M, L->K, L->N, bwla_device_cus()), L, dq, dscale, dqsum, dT, M, dY, dacc, st,
-                                 dH, a4);
+        return launch_tile<0>(gd_pick(M, L->K, L->N, bwla_device_cus(), a4), L, dq, dscale, dqsum, dT, M, dY, dacc, st,
+                              dH, a4);
     // shapes the streaming kernel does not take (K not a multiple of 128, fewer than 32 channels):
     // LDS-tiled kernel, 64 x 128 or 128 x 128 tiles (it does not gate: the caller goes through Y)
     if (dH != nullptr || a4) return hipErrorInvalidValue;

@@ -228,23 +228,28 @@ def test_nibble_packed_a4_codes(M, K, n1, n2, N, r):
     check_output(Y4[torch.from_numpy(rows).to(DEV)].cpu().numpy(), ref["Y"])
 
 
-@pytest.mark.parametrize("M,K,N,r", [
-    (19, 1664, 50, 16),         # 64 x 32 tiles, four wavefronts split K (13 slices: 4, 4, 4, 1)
+# (tokens, K, N, rank); with plain codes they take the tiles
+STREAMING_SHAPES = [
+    (19, 1664, 50, 16),         # 64 x 32, four wavefronts split K (13 slices: 4, 4, 4, 1)
     (18, 4480, 9250, 8),        # 64 x 64, K split in four
     (17, 8320, 16426, 32),      # 64 x 64, K split in two; ragged channels
-    (17, 16384, 17142, 64),     # 64 x 96, K split in two
-    (3420, 128, 266, 8),        # 64 x 32, one wavefront; one slice, the rest of the ring is padding
-    (40, 256, 64, 20),          # one ring of codes from here on: 64 x 64
+    (17, 16384, 17142, 64),     # the same, longer rows
+    (71, 9472, 19290, 33),      # 64 x 96, K split in two; two row tiles, the second of seven tokens
+    (3420, 128, 266, 8),        # one ring of codes from here on: 64 x 128; one slice, the rest of the ring is padding
+    (40, 256, 64, 20),          # 64 x 64
     (65, 128, 8306, 0),         # 64 x 128, the second row tile holds one token
-    (70, 4096, 12302, 33),      # 64 x 128
+    (70, 4096, 12302, 33),      # 64 x 128 (nibble codes: 64 x 64, K split in two)
     (70, 640, 19480, 16),       # 64 x 256, five slices
     (257, 4992, 8192, 64),      # 64 x 256, 39 slices
-    (147, 128, 21938, 8),       # 64 x 384
+    (147, 128, 21938, 8),       # 64 x 384 (nibble codes: 64 x 256)
     (733, 384, 16562, 70),      # 64 x 512, ring of two, odd number of slices; two chunks of ranks
     (288, 128, 26306, 96),      # 64 x 640
-    (2999, 128, 2638, 64),      # private rings: 256 x 128, ring of two
-    (3558, 128, 2598, 8),       # 256 x 160
-])
+    (2999, 128, 2638, 64),      # 64 x 640
+    (3558, 128, 2598, 8),       # 64 x 384
+]
+
+
+@pytest.mark.parametrize("M,K,N,r", STREAMING_SHAPES)
 def test_streaming_gemm_tiles(M, K, N, r):
     """One shape for each tile the dispatch of the streaming GEMM chooses from: int32 accumulators equal to
     an exact product, Y to its rounding, the gated and the nibble-packed forms against it."""
