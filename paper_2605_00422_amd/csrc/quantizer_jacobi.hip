@@ -77,21 +77,23 @@ __device__ __forceinline__ double jrcp(double x) {
 }
 
 // Tangent t, cosine of the plane rotation that makes columns with squared norms al, be and inner product
-// ga orthogonal; the sine is cs * t.  z = (be - al) / (2 ga), t = sign(z) / (|z| + sqrt(1 + z^2)).
-// Quotient, root and reciprocal root are the hardware's estimates brought to full precision by Newton steps: the
+// ga orthogonal; the sine is cs * t.  t = sign(d) g / (|d| + sqrt(d^2 + g^2)) with d = be - al, g = 2 ga, both
+// scaled by the power of two of al + be, so that neither square overflows and one that underflows does not count.
+// Root, reciprocal and reciprocal root are the hardware's estimates brought to full precision by Newton steps: the
 // general forms' scaling and special cases, which nothing here needs, made this chain of dependent instructions most
-// of a round (64 x 64 with V, whole call 712 us with them and norms summed anew for every pair, 484 as it is; the
-// estimates alone, whose 2^-20 of the inner product waits for the next sweep, 452).  A pair that is rotated has
-// ga^2 > 1e-30 al be > 0, so ga is no denormal; |z| is held to 1e300, where t is 1 / (2 z) and rounds away.
+// of a round.  64 x 64 with V, whole call: 444 us as it is, 453 with z = d / g formed first (a reciprocal more in the
+// chain), 423 with the estimates alone, whose 2^-20 of the inner product waits for the next sweep; 712 with the general
+// forms and norms summed anew for every pair, on a card where the estimates alone took 452.
 __device__ __forceinline__ void jrotation(double al, double be, double ga, double& tt, double& cs) {
-    const double z = (be - al) * 0.5 * jrcp(ga), az = fmin(fabs(z), 1.0e300);
-    const double q = fma(az, az, 1.0), e0 = __builtin_amdgcn_rsq(q);
-    double g = q * e0, h = 0.5 * e0;                        // sqrt(q), 1 / (2 sqrt(q))
-    const double r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
+    const int e = __builtin_amdgcn_frexp_exp(al + be);
+    const double d = ldexp(be - al, -e), g = ldexp(ga, 1 - e);
+    const double q = fma(g, g, d * d), e0 = __builtin_amdgcn_rsq(q);
+    double s = q * e0, h = 0.5 * e0;                        // sqrt(q), 1 / (2 sqrt(q))
+    const double r = fma(-h, s, 0.5);
+    s = fma(s, r, s);
     h = fma(h, r, h);
-    g = fma(fma(-g, g, q), h, g);
-    tt = copysign(jrcp(az + (az > 1.0e150 ? az : g)), z);   // (q overflows there; the root is az)
+    s = fma(fma(-s, s, q), h, s);
+    tt = g * copysign(jrcp(fabs(d) + s), d);
     const double w = fma(tt, tt, 1.0);                      // in [1, 2]
     double y = __builtin_amdgcn_rsq(w);
 #pragma unroll
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         // Against an 80-bit SVD (16 to 86 columns: normal, graded over twelve decades, of half rank, of condition
         // 1e14, Gram matrices of that condition) the largest errors, relative to the largest singular value, are with
         // carried norms / norms summed for every pair: singular values 1.7e-14 / 1.7e-14, V^T V - I
-        // 5.4e-14 / 5.5e-14, U S V^T - G 6.1e-15 / 6.1e-15; 64 x 64 with V 484 / 516 us.
+        // 5.5e-14 / 5.5e-14, U S V^T - G 6.0e-15 / 6.1e-15; 64 x 64 with V, times of one card, 484 / 516 us.
         for (int base = 0; base < ncol; base += GROUPS) {
             const int j = base + gid;
             double s = 0.0;
