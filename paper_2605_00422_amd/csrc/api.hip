@@ -9,15 +9,8 @@
 
 #include "bwla_internal.h"
 
-size_t bwla_rotate_lds_bytes(int n1, int n2);
-bool bwla_rotate_supported(int n1, int n2);
-int bwla_rotate_tiles(int n1, int n2);
-int bwla_rotate_max_tiles();
-size_t bwla_gemm_decode_lds(int64_t M, int64_t K);
-
 namespace {
 
-constexpr size_t LDS_LIMIT = 160 * 1024;          // per-workgroup LDS on gfx950
 constexpr size_t DECODE_LDS_LIMIT = 128 * 1024;   // code tile of the decode kernel
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

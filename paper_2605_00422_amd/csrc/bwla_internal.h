@@ -100,6 +100,10 @@ hipError_t bwla_launch_pack(const float* dW, const float* dR1, const float* dR2,
                             const bwla_layer_t* L, hipStream_t st);
 hipError_t bwla_launch_unpack(const bwla_layer_t* L, int8_t* d_sgn, float* d_alpha, hipStream_t st);
 
+// the factor pairs that some rotation kernel takes; 16 x 16 tiles of the rotated token, and how many there may be
+bool bwla_rotate_supported(int n1, int n2);
+int bwla_rotate_tiles(int n1, int n2);
+int bwla_rotate_max_tiles();
 // one launch: rotation + quantization workgroups, then the PSP projection workgroups
 hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, int8_t* dq,
                                     float* dscale, int32_t* dqsum, float* dT, void* dws, const bwla_psp_plan& plan,
@@ -146,6 +150,7 @@ hipError_t bwla_launch_decode_layer(const bwla_layer_t* L, const void* dX, int x
 hipError_t bwla_launch_gemm_decode(const bwla_layer_t* L, const int8_t* dq, const float* dscale,
                                    const int32_t* dqsum, const float* dT, int64_t M, float* dY,
                                    int32_t* dacc, hipStream_t st);
+size_t bwla_gemm_decode_lds(int64_t M, int64_t K);      // bytes of the code tile that launch stages
 bool bwla_gemm_decode_bs_supported(int64_t M, int64_t K, int r);
 // (dH not NULL: gated output h as bf16, M x N / 2, instead of Y -- see bwla_linear_forward_swiglu)
 hipError_t bwla_launch_gemm_decode_bs(const bwla_layer_t* L, const int8_t* dq, const float* dscale,

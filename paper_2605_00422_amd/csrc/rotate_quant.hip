@@ -26,8 +26,6 @@
 #include "rotate_split_device.h"
 #include "psp_block_device.h"
 
-int bwla_rotate_tiles(int n1, int n2);
-
 namespace {
 
 struct RqArgs {
@@ -162,7 +160,6 @@ __global__ __launch_bounds__(256) void pack_codes_a4_kernel(const int8_t* __rest
 }  // namespace
 
 
-size_t bwla_rotate_lds_bytes(int n1, int n2) { return rq_shape(n1, n2).lds_bytes; }
 // factors that do not fit into LDS are streamed with 16-byte loads, which needs n % 4 == 0
 bool bwla_rotate_supported(int n1, int n2) {
     const RqShape sh = rq_shape(n1, n2);
