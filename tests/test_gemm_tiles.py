@@ -18,8 +18,8 @@ int main() {
     for (const GdTile& t : GD_TILES) printf(" %d %d %d %d %d", t.ntl, t.wk, t.nb, t.wn, t.resident);
     printf("\\n");
     long long M, K, N;
-    int a4;
-    while (scanf("%lld %lld %lld %d", &M, &K, &N, &a4) == 4) printf("%d\\n", gd_pick(M, K, N, 256, a4 != 0));
+    int r, a4;
+    while (scanf("%lld %lld %lld %d %d", &M, &K, &N, &r, &a4) == 5) printf("%d\\n", gd_pick(M, K, N, r, 256, a4 != 0));
 }
 """
 
@@ -31,7 +31,7 @@ def pick(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", str(d / "pick"), str(d / "pick.cpp")], check=True)
 
     def run(shapes, a4=0):
-        out = subprocess.run([str(d / "pick")], input="".join("%d %d %d %d\n" % (*s, a4) for s in shapes), text=True,
+        out = subprocess.run([str(d / "pick")], input="".join("%d %d %d %d %d\n" % (*s, a4) for s in shapes), text=True,
                              capture_output=True, check=True).stdout.split("\n")
         run.tiles = [tuple(t) for t in zip(*[iter(map(int, out[0].split()[1:]))] * 5)]
         return [int(x) for x in out[1:1 + len(shapes)]]
@@ -44,39 +44,40 @@ def test_every_tile_is_reached(pick):
     kind of codes, and by the shapes of the GPU test."""
     rng = random.Random(0)
     log = lambda lo, hi: int(lo * (hi / lo) ** rng.random())                 # noqa: E731
-    shapes = [(log(17, 4097), 128 * log(1, 225), log(32, 28673)) for _ in range(6000)]
+    shapes = [(log(17, 4097), 128 * log(1, 225), log(32, 28673), rng.choice([0, 8, 32, 64, 96])) for _ in range(6000)]
     for a4 in (0, 1):
         got = pick(shapes, a4)
         for i in range(len(pick.tiles)):
             assert got.count(i) >= 20, (i, pick.tiles[i], got.count(i))
-    assert set(pick([s[:3] for s in STREAMING_SHAPES])) == set(range(len(pick.tiles)))
-    assert set(pick([s[:3] for s in STREAMING_SHAPES], 1)) == set(range(len(pick.tiles)))
+    assert set(pick(STREAMING_SHAPES)) == set(range(len(pick.tiles)))
+    assert set(pick(STREAMING_SHAPES, 1)) == set(range(len(pick.tiles)))
 
 
-# (tokens, K, N, nibble codes): tiles within 4 % of the best of fifteen, measured with three layers in turn, as (32-channel
-# tiles, wavefronts that share K, wavefronts side by side).  The first lines are those where constants fitted to plain codes
-# of a single kind had lost time (in microseconds: best, and what was taken).
+# (tokens, K, N, rank), nibble codes: tiles within 4 % of the best of fifteen, measured with three layers in turn, as
+# (32-channel tiles, wavefronts that share K, wavefronts side by side).  The first lines are those where constants
+# fitted to plain codes alone, with no share of the ranks, had lost time (in microseconds: best, and what was taken).
 RECORDED = [
-    ((18, 1280, 126, 1), [(1, 4, 1)]),                               # 5.7, 7.1
-    ((25, 1280, 492, 1), [(1, 4, 1)]),                               # 7.9, 9.7
-    ((25, 1280, 492, 0), [(1, 4, 1)]),                               # 8.3, 9.0
-    ((484, 1152, 528, 1), [(1, 4, 1)]),                              # 7.7, 9.4
-    ((17, 5120, 25600, 1), [(2, 2, 1)]),                             # 16.6, 20.5
-    ((1024, 28672, 8192, 0), [(2, 1, 4)]),                           # 181, 216
-    ((3696, 13312, 378, 0), [(3, 2, 1), (1, 1, 4)]),                 # 46, 66: 348 tiles of 64 x 64, every XCD fetches all codes
-    ((3418, 25600, 304, 0), [(3, 2, 1)]),                            # 57, 89: likewise
-    ((2048, 11008, 4096, 0), [(2, 1, 4)]),                           # 78.6, 81.5
-    ((4096, 8192, 28672, 0), [(4, 1, 4), (3, 1, 4)]),                # 696, 718; 734 by thresholds
-    ((2048, 4096, 22016, 0), [(3, 1, 4), (2, 1, 4)]),                # 205, 215: ring of two
-    ((4096, 28672, 8192, 0), [(4, 1, 4)]),                           # 631
-    ((2048, 25600, 5120, 0), [(5, 1, 4)]),                           # 192
-    ((64, 8192, 28672, 0), [(2, 2, 1)]),                             # 32.7
-    ((64, 8192, 8192, 0), [(1, 4, 1)]),                              # 14.0
+    ((18, 1280, 126, 0), 1, [(1, 4, 1)]),                            # 5.7, 7.1
+    ((25, 1280, 492, 64), 1, [(1, 4, 1)]),                           # 7.9, 9.7
+    ((25, 1280, 492, 64), 0, [(1, 4, 1)]),                           # 8.3, 9.0
+    ((484, 1152, 528, 0), 1, [(1, 4, 1)]),                           # 7.7, 9.4
+    ((17, 5120, 25600, 32), 1, [(2, 2, 1)]),                         # 16.6, 20.5
+    ((1024, 28672, 8192, 64), 0, [(2, 1, 4)]),                       # 179, 210
+    ((3696, 13312, 378, 96), 0, [(3, 2, 1), (1, 1, 4)]),             # 46, 66: 348 tiles of 64 x 64, every XCD fetches all codes
+    ((3418, 25600, 304, 0), 0, [(3, 2, 1)]),                         # 57, 89: likewise
+    ((4096, 4096, 12288, 96), 0, [(4, 1, 4)]),                       # 243, 268
+    ((2048, 11008, 4096, 32), 0, [(4, 1, 4), (2, 1, 4)]),            # 77.4, 78.4
+    ((4096, 8192, 28672, 64), 0, [(3, 1, 4)]),                       # 788; 830 by thresholds
+    ((4096, 28672, 8192, 64), 0, [(4, 1, 4)]),                       # 673; 711
+    ((2048, 4096, 22016, 64), 0, [(3, 1, 4), (2, 1, 4)]),            # 210, 213; 260
+    ((2048, 25600, 5120, 64), 0, [(5, 1, 4)]),
+    ((64, 8192, 28672, 64), 0, [(2, 2, 1)]),
+    ((64, 8192, 8192, 64), 0, [(1, 4, 1)]),
 ]
 
 
-@pytest.mark.parametrize("shape,tiles", RECORDED)
-def test_recorded_shapes_take_a_fast_tile(pick, shape, tiles):
-    i = pick([shape[:3]], shape[3])[0]
+@pytest.mark.parametrize("shape,a4,tiles", RECORDED)
+def test_recorded_shapes_take_a_fast_tile(pick, shape, a4, tiles):
+    i = pick([shape], a4)[0]
     ntl, wk, _, wn, _ = pick.tiles[i]
     assert (ntl, wk, wn) in tiles

@@ -241,11 +241,13 @@ STREAMING_SHAPES = [
     (70, 4096, 12302, 33),      # 64 x 128 (nibble codes: 64 x 64, K split in two)
     (70, 640, 19480, 16),       # 64 x 256, five slices
     (257, 4992, 8192, 64),      # 64 x 256, 39 slices
-    (147, 128, 21938, 8),       # 64 x 384 (nibble codes: 64 x 256)
+    (147, 128, 21938, 8),       # 64 x 384
     (733, 384, 16562, 70),      # 64 x 512, ring of two, odd number of slices; two chunks of ranks
-    (288, 128, 26306, 96),      # 64 x 640
-    (2999, 128, 2638, 64),      # 64 x 640
+    (288, 128, 26306, 96),      # 64 x 384; two chunks of ranks
+    (2999, 128, 2638, 64),      # 64 x 384
     (3558, 128, 2598, 8),       # 64 x 384
+    (274, 128, 26190, 0),       # 64 x 640
+    (388, 128, 19578, 8),       # 64 x 640
 ]
 
 
