@@ -352,6 +352,15 @@ def microbench(torch, B):
                     "1 MiB + 4 KiB apart over a flushed 384 MiB buffer / 128 bytes apart over 1 MiB read just before"}
 
 
+def gemm_kernel(cfg):
+    """The kernel that bwla_linear_forward runs for a layer whose channels fill it: the streaming decode GEMM up
+    to 16 tokens, then (csrc/gemm_tiles.h) private rings of codes for a single tile of 64 tokens, one ring for the
+    wavefronts side by side beyond that."""
+    if cfg.M <= 16:
+        return "gemm_decode_bs_kernel"
+    return "gemm_prefill_direct_kernel" if cfg.M <= 64 else "gemm_prefill_shared_kernel"
+
+
 def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=None):
     """Roofline of the dominant kernel: the single-launch decode kernel where it serves the layer
     (then the kernel is the layer), else the binary GEMM inside bwla_linear_forward; with the
@@ -361,7 +370,7 @@ def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=N
     if launches == 1:
         kernel, t, nbytes = "decode_layer_kernel", us_layer * 1e-6, layer_bytes(cfg)
     else:
-        kernel = "gemm_decode_bs_kernel" if cfg.M <= 16 else "gemm_prefill_direct_kernel"
+        kernel = gemm_kernel(cfg)
         t, nbytes = us_forward * 1e-6, linear_forward_bytes(cfg)
     tl = us_layer * 1e-6
     if hbm_bound:

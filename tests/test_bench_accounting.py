@@ -50,6 +50,34 @@ def test_roofline_fields_and_bound_selection():
         assert bench.roofline_for(cfg, 2, 20.0, 10.0, None, traffic)["bound"] == ("hbm" if hbm_t >= mfma_t else "mfma")
 
 
+def test_the_kernels_named_are_the_ones_that_run():
+    """roofline.kernel of the prefill workloads against the table the library picks the tile from, and the kernels of the
+    counter summary against the sources: a figure measured on a kernel that is gone would be printed beside a
+    time of another."""
+    import glob
+    import re
+    import tempfile
+    csrc = os.path.join(ROOT, "paper_2605_00422_amd", "csrc")
+    cfgs = [c for M in (64, 4096) for c in syn.block70b_configs(M)] + [syn.CONFIGS["cfg3_qwen32b_down_m2048"]]
+    with tempfile.TemporaryDirectory() as tmp:
+        src = "#include <cstdio>\n#include \"gemm_tiles.h\"\nint main() {\n" + "".join(
+            f'printf("%d\\n", GD_TILES[gd_pick({c.M}, {c.K}, {c.N}, {c.r}, 256, {a4})].wn);\n'
+            for c in cfgs for a4 in ("false", "true")) + "}\n"
+        with open(os.path.join(tmp, "wn.cpp"), "w") as f:
+            f.write(src)
+        subprocess.run(["g++", "-std=c++17", "-I", csrc, "-o", os.path.join(tmp, "wn"), os.path.join(tmp, "wn.cpp")], check=True)
+        wn = subprocess.run([os.path.join(tmp, "wn")], capture_output=True, text=True, check=True).stdout.split()
+    for c, w in zip([c for c in cfgs for _ in (0, 1)], map(int, wn)):
+        assert bench.gemm_kernel(c) == ("gemm_prefill_shared_kernel" if w > 1 else "gemm_prefill_direct_kernel"), c.name
+    sources = "".join(open(f).read() for f in glob.glob(os.path.join(csrc, "*.h*")))
+    traffic = bench.measured_traffic()
+    for _, kernel in traffic:
+        assert re.search(rf"__global__[^;{{]*\b{kernel}\(", sources), kernel
+    for c in (syn.CONFIGS["cfg3_qwen32b_down_m2048"], next(c for c in cfgs if c.name == "cfg4_70b_gate_m4096")):
+        r = bench.roofline_for(c, 2, 450.0, 200.0, None, traffic)
+        assert r["traffic"] == traffic[(c.name, bench.gemm_kernel(c))] >= bench.linear_forward_bytes(c)
+
+
 def test_layer_bytes_are_both_calls_bytes():
     cfg = syn.CONFIGS["cfg1_decode7b"]
     rq = 2 * 4096 + 4 * (64 * 64 + 64 * 64) + 2 * 4096 * 32 + 4096 + 8 + 4 * 32
