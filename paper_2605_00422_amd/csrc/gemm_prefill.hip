@@ -673,7 +673,9 @@ __global__ __launch_bounds__(64 * WK, 1) void gemm_prefill_direct_kernel(GD_PARA
 // matrix cores could work at, and that path (L2 -> L1 -> LDS) is what bounds the direct kernel at every
 // size but the smallest.  Here the WN wavefronts over the same token rows fill one ring together and meet
 // at one barrier a slice: the codes enter the CU once (28672 -> 8192 at 4096 tokens 733 -> 680 us; the
-// four loads in flight of a ring hide the barrier, and two workgroups a CU each other's).
+// four loads in flight of a ring hide the barrier, and two workgroups a CU each other's).  Held to the 256
+// registers that two workgroups a CU leave, 64 x 384 spills 12 (22 with nibble codes, none gated) and 64 x 512
+// 21 (54, 8), all of them outside the loop.
 template <int NTL, int NB, int WN, bool GATED, bool A4>
 __global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
     gd_body<NTL, 1, NB, WN, GATED, A4>(GD_ARGS);

@@ -172,7 +172,7 @@ __device__ __forceinline__ void chunk_store(float* dst, const ChunkSlots& cs, co
 
 // MAXT: 16 x 16 tiles of the token a wavefront may carry.  Their accumulators are what the registers go to
 // (and the code, fully unrolled over them, what the instruction cache): with all 32 of the largest factors
-// a CU holds one workgroup, with the two of 64 x 64 it holds three.
+// a CU holds one workgroup, with the two of 64 x 64 (128 registers, eight wavefronts) two.
 template <bool BF16, int MAXT>
 __device__ __forceinline__ void rotate_token(float* lds, const void* __restrict__ X, int64_t t, int64_t K, int n1,
                                              int n2, const float* __restrict__ R1, const float* __restrict__ R2,

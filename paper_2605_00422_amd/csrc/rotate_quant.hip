@@ -51,7 +51,7 @@ __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb,
                     rest % a.JG, a.JG);
 }
 
-// (up to 128 registers: two workgroups a CU where LDS lets them)
+// (up to 128 registers, of which fp32 activations spill six: two workgroups a CU where LDS lets them)
 template <bool BF16, int MAXT>
 __global__ __launch_bounds__(RQ_THREADS, MAXT <= 4 ? 4 : 2) void rotate_quant_kernel(RqArgs a) {
     extern __shared__ __align__(16) float lds[];
