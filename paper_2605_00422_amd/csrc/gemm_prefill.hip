@@ -668,14 +668,14 @@ __global__ __launch_bounds__(64 * WK, 1) void gemm_prefill_direct_kernel(GD_PARA
     gd_body<NTL, WK, NB, 1, GATED, A4>(GD_ARGS);
 }
 
-// Private rings make every wavefront fetch all code rows of its tile for itself: a CU with four wavefronts
-// asks for 32 KiB of codes and up to 8 KiB of weights per slice, some 40 bytes a clock at the rate the
-// matrix cores could work at, and that path (L2 -> L1 -> LDS) is what bounds the direct kernel at every
-// size but the smallest.  Here the WN wavefronts over the same token rows fill one ring together and meet
-// at one barrier a slice: the codes enter the CU once (28672 -> 8192 at 4096 tokens 733 -> 680 us; the
-// four loads in flight of a ring hide the barrier, and two workgroups a CU each other's).  Held to the 256
-// registers that two workgroups a CU leave, 64 x 384 spills 12 (22 with nibble codes, none gated) and 64 x 512
-// 21 (54, 8), all of them outside the loop.
+// Private rings make every wavefront fetch all code rows of its tile for itself: a CU with four wavefronts asks for
+// 32 KiB of codes and up to 8 KiB of weights per slice, and keeps four copies of the codes in LDS.  Here the WN
+// wavefronts over the same token rows fill one ring together and meet at one barrier a slice.  At one workgroup a CU
+// that changes little (25600 -> 5120 at 2048 tokens, 64 x 640: 196 us with private rings, 192; the matrix cores are busy
+// for 60 and 58 % of the launch).  What pays is the LDS it frees: two or more workgroups a CU, which hide each other's
+// barriers, prologues and epilogues (28672 -> 8192 at 4096 tokens 733 -> 680 us, 4096 -> 22016 at 2048 259 -> 207).
+// Held to the 256 registers that two workgroups a CU leave, 64 x 384 spills 12 (22 with nibble codes, none gated) and
+// 64 x 512 21 (54, 8), all of them outside the loop.
 template <int NTL, int NB, int WN, bool GATED, bool A4>
 __global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
     gd_body<NTL, 1, NB, WN, GATED, A4>(GD_ARGS);
