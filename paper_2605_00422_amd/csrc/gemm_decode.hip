@@ -25,7 +25,7 @@ __device__ __forceinline__ int q_swz(int row, int kbyte, int Kp) {
 // a short launch that has many to make.
 // EARLY: the epilogue's operands (scale, code sum, alpha, the first ranks of T and V) are asked for before the
 // contraction, two round trips to memory less at the end.  That holds 24 registers over the loop (98 against 74:
-// four wavefronts a SIMD instead of six), and of the wavefronts that share K all but one would ask for nothing.
+// four wavefronts a SIMD instead of six), and of the wavefronts that share K all but one would ask in vain.
 // Which form: at most GD_FEW granules a thread, the plain one (one token of 512, rank 8, 512 / 11008 channels:
 // 3.75 / 3.85 us plain, 4.3 / 4.5 many and early); more, and a wavefront has its tile to itself, both (16 tokens:
 // 5.0 / 5.8 -> 4.8 / 4.8; of 2560, rank 96: 13.4 / 16.2 -> 11.2 / 12.5); more, and two or four wavefronts
