@@ -173,12 +173,15 @@ BWLA_API bwla_status_t bwla_unpack_signs(const bwla_layer_t* layer, int8_t* d_sg
  * Bytes of scratch bwla_rotate_quant wants for M tokens: split-K partial sums of X U with their
  * arrival counters, and, for a few tokens of a layer with a large factor R1 (six or more 16-row
  * tiles), the rotated values in fp32 and their extremes between the two launches the rotation
- * then takes.  Returns 0 bytes when neither is used.
+ * then takes.  For more than 64 tokens of a layer that the sparse GEMM serves (K a multiple of 128, N >= 32) it also
+ * counts the room in which bwla_linear_forward_bits and bwla_decode_forward lay out the codes for that kernel (about
+ * M K bytes, at the scratch's end); a scratch without it is accepted everywhere, and the dense kernel runs.  Returns 0
+ * bytes when nothing is used.
  * The scratch must be zero-filled once when it is allocated and then left to the library: its
  * first 7168 bytes are the exchange area of bwla_decode_forward's single-launch kernel (an epoch
  * that every such launch moves on, arrival counts that every launch returns to zero, partial
  * sums tagged with their epoch), then comes one arrival counter per 16-token tile, which every
- * call returns to zero; everything behind them is overwritten by each call.  One scratch may
+ * call returns to zero; everything behind them may be overwritten by each call.  One scratch may
  * serve calls on different layers and token counts; two calls that overlap in time must not
  * share one.
  */
@@ -236,6 +239,18 @@ BWLA_API bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8
                                   float* d_Y, int32_t* d_acc, void* stream);
 
 /*
+ * bwla_linear_forward for codes that bwla_rotate_quant_bits wrote with act_bits (2..8, else BWLA_ERR_UNSUPPORTED), with the
+ * scratch of that call: same results, to the bit.  Codes of at most 7 bits let long prefills run on the sparse INT8 matrix
+ * instructions (csrc/gemm_sparse.hip), which need the codes laid out anew in d_ws.  act_bits says which kernel is worth
+ * starting and nothing more: the codes are looked at, and where one lies outside [-64, 63] its tile is computed on the
+ * dense instructions, correctly and slowly.  d_ws (may be NULL) of ws_bytes: with less than bwla_psp_workspace_size(layer, M)
+ * the call is bwla_linear_forward.
+ */
+BWLA_API bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_ws,
+                                  size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream);
+
+/*
  * The whole forward of one layer, steps 1-5 above (paper Sec. 3.1, Sec. 4.1, Eq. 3-4, Sec. 3.2), in
  * one call: what bwla_rotate_quant followed by bwla_linear_forward compute, with the same
  * buffers (d_q, d_scale, d_qsum, d_T are still written; same arguments, same errors) and to the
@@ -279,8 +294,8 @@ BWLA_API bwla_status_t bwla_decode_forward_launches(const bwla_layer_t* layer, i
  * between the rotation's two launches) lives in a fixed array of BWLA_STATIC_SCRATCH_BYTES inside
  * the library's device image, one per GPU, held until the process ends.  The call allocates
  * nothing and calls no allocating routine; it clears the counters it needs with a small kernel.
- *   - A call whose bwla_psp_workspace_size(layer, M) exceeds BWLA_STATIC_SCRATCH_BYTES returns
- *     BWLA_ERR_BUFSIZE and enqueues nothing (decode batches of the common model widths fit; long
+ *   - A call whose bwla_psp_workspace_size(layer, M), less the sparse GEMM's room, exceeds BWLA_STATIC_SCRATCH_BYTES
+ *     returns BWLA_ERR_BUFSIZE and enqueues nothing (decode batches of the common model widths fit; long
  *     prefills do not: use bwla_decode_forward with a workspace of the caller's).
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap in time on one GPU (two
  *     streams, two host threads) race on it and must be serialized by the caller.
@@ -313,6 +328,12 @@ BWLA_API bwla_status_t bwla_swiglu_workspace_size(const bwla_layer_t* layer, int
 BWLA_API bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
                                          const int32_t* d_qsum, const float* d_T, int64_t M, void* d_H,
                                          void* d_ws, size_t ws_bytes, void* stream);
+/* The same for codes of act_bits, with the scratch of bwla_rotate_quant beside the gating workspace: to
+ * bwla_linear_forward_swiglu what bwla_linear_forward_bits is to bwla_linear_forward. */
+BWLA_API bwla_status_t bwla_linear_forward_swiglu_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_scratch,
+                                  size_t scratch_bytes, void* d_H, void* d_ws, size_t ws_bytes, void* stream);
+
 
 /*
  * 4-bit activation codes two to a byte (paper Table 3 reports W1A4: codes in [-7, 7]), which halves the

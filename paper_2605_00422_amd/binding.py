@@ -21,7 +21,8 @@ EXPORTS = ["bwla_status_string", "bwla_version", "bwla_kron_factor", "bwla_packe
            "bwla_packed_size_mode", "bwla_pack_weights_mode", "bwla_swiglu_workspace_size",
            "bwla_linear_forward_swiglu", "bwla_decode_forward_static", "bwla_probe_hbm_read",
            "bwla_probe_mfma_int8", "bwla_decode_forward_launches", "bwla_decode_forward_bits", "bwla_pack_codes_a4",
-           "bwla_linear_forward_a4", "bwla_probe_empty_launch", "bwla_probe_load_latency", "bwla_probe_clock"]
+           "bwla_linear_forward_a4", "bwla_probe_empty_launch", "bwla_probe_load_latency", "bwla_probe_clock",
+           "bwla_linear_forward_bits", "bwla_linear_forward_swiglu_bits"]
 
 
 class BwlaLayer(Structure):
@@ -89,6 +90,10 @@ def load() -> ctypes.CDLL:
     lib.bwla_swiglu_workspace_size.argtypes = [POINTER(BwlaLayer), c_int64, POINTER(c_size_t)]
     lib.bwla_linear_forward_swiglu.argtypes = [POINTER(BwlaLayer), c_void_p, c_void_p, c_void_p, c_void_p, c_int64,
                                                c_void_p, c_void_p, c_size_t, c_void_p]
+    lib.bwla_linear_forward_bits.argtypes = [POINTER(BwlaLayer), c_void_p, c_void_p, c_void_p, c_void_p, c_int64, c_int,
+                                             c_void_p, c_size_t, c_void_p, c_void_p, c_void_p]
+    lib.bwla_linear_forward_swiglu_bits.argtypes = [POINTER(BwlaLayer), c_void_p, c_void_p, c_void_p, c_void_p, c_int64,
+                                                    c_int, c_void_p, c_size_t, c_void_p, c_void_p, c_size_t, c_void_p]
     for name in EXPORTS:
         if name not in ("bwla_status_string", "bwla_version"):
             getattr(lib, name).restype = c_int
@@ -235,6 +240,9 @@ class Activations:
         ws = psp_workspace_size(layer, M)
         self.ws_bytes = ws
         self.ws = torch.zeros(max(ws, 16), dtype=torch.uint8, device=dev)   # zero-filled once, as the ABI asks
+        # width of the codes that rotate_quant wrote last: which GEMM is worth starting (the library looks at the codes,
+        # so q may be overwritten with others); 8 = any
+        self.act_bits = 8
 
 
 def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> Activations:
@@ -248,6 +256,7 @@ def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> 
         _check(load().bwla_rotate_quant_bits(layer._ref, _ptr(X), xd, act_bits, X.shape[0], _ptr(act.q),
                                              _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws),
                                              act.ws_bytes, _stream()), "bwla_rotate_quant_bits")
+    act.act_bits = act_bits
     return act
 
 
@@ -262,6 +271,7 @@ def decode_forward(layer: PackedLayer, X, act: Activations, Y, acc=None, act_bit
         _check(load().bwla_decode_forward_bits(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
                                                _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
                                                _ptr(Y), _ptr(acc), _stream()), "bwla_decode_forward_bits")
+    act.act_bits = act_bits
     return Y
 
 
@@ -339,6 +349,12 @@ def swiglu_workspace_size(layer: PackedLayer, M: int) -> int:
 def linear_forward_swiglu(layer: PackedLayer, act: Activations, H, ws=None):
     """H (bf16, M x N/2) = silu(gate) * up of a layer whose rows interleave gate and up channels."""
     nbytes = 0 if ws is None else ws.numel() * ws.element_size()
+    if act.act_bits <= 7:
+        _check(load().bwla_linear_forward_swiglu_bits(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum),
+                                                      _ptr(act.T), act.M, act.act_bits, _ptr(act.ws), act.ws_bytes,
+                                                      _ptr(H), _ptr(ws), nbytes, _stream()),
+               "bwla_linear_forward_swiglu_bits")
+        return H
     _check(load().bwla_linear_forward_swiglu(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum),
                                              _ptr(act.T), act.M, _ptr(H), _ptr(ws), nbytes, _stream()),
            "bwla_linear_forward_swiglu")
@@ -346,6 +362,11 @@ def linear_forward_swiglu(layer: PackedLayer, act: Activations, H, ws=None):
 
 
 def linear_forward(layer: PackedLayer, act: Activations, Y, acc=None):
+    if act.act_bits <= 7:
+        _check(load().bwla_linear_forward_bits(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
+                                               act.M, act.act_bits, _ptr(act.ws), act.ws_bytes, _ptr(Y), _ptr(acc),
+                                               _stream()), "bwla_linear_forward_bits")
+        return Y
     _check(load().bwla_linear_forward(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
                                       act.M, _ptr(Y), _ptr(acc), _stream()), "bwla_linear_forward")
     return Y

@@ -8,6 +8,7 @@
 #include <utility>
 
 #include "bwla_internal.h"
+#include "gemm_tiles.h"
 
 namespace {
 
@@ -70,6 +71,24 @@ size_t rq_ws_bytes(const bwla_layer_t* L, const bwla_psp_plan& p, int64_t M) {
     const size_t psp = bwla_psp_ws_bytes(p, M, bwla_rank_u(L));
     const size_t body = split ? (size_t)bwla_align256(psp) + split : psp;
     return body ? (size_t)BWLA_WS_HEAD + body : 0;
+}
+// The sparse GEMM's sums and differences of the codes lie at the end of a scratch.  What a scratch keeps from call to call
+// is at its beginning, and how far that reaches depends on layer and tokens: the head, then an arrival counter per 16
+// tokens, which must stay zero.  A call on any other layer and M' tokens that uses those counters has at least 128 bytes of
+// partial sums a token behind them, so a caller who sized the scratch for it gave it 128 M' bytes more than the M' / 4 that
+// must not be written: starting 64 KiB + (bytes / 64) behind the head, this part never reaches into them.
+size_t sparse_ws_start(size_t need, uint64_t bytes) {
+    const size_t first = (size_t)(BWLA_WS_HEAD + 65536 + bytes / 64);
+    return (size_t)bwla_align256(need > first ? need : first);
+}
+// NULL: the scratch has no room, or the call does not use it
+void* sparse_ws(const bwla_layer_t* L, int64_t M, size_t need, void* d_ws, size_t ws_bytes) {
+    const uint64_t bytes = bwla_gemm_sparse_bytes(L, M);
+    if (bytes == 0 || d_ws == nullptr || ws_bytes < sparse_ws_start(need, bytes) + bytes) return nullptr;
+    return (char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255);
+}
+void* sparse_ws_of(const bwla_layer_t* L, int64_t M, void* d_ws, size_t ws_bytes) {
+    return sparse_ws(L, M, rq_ws_bytes(L, bwla_make_psp_plan(M, L->K, bwla_rank_u(L)), M), d_ws, ws_bytes);
 }
 inline void* ws_body(void* d_ws) { return d_ws ? (char*)d_ws + BWLA_WS_HEAD : nullptr; }
 
@@ -240,7 +259,9 @@ bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_t M, size
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (M <= 0) return BWLA_ERR_SHAPE;
-    *bytes = rq_ws_bytes(layer, bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer)), M);
+    const size_t need = rq_ws_bytes(layer, bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer)), M);
+    const uint64_t sparse = bwla_gemm_sparse_bytes(layer, M);
+    *bytes = sparse == 0 ? need : sparse_ws_start(need, sparse) + (size_t)bwla_align256(sparse);
     return BWLA_OK;
 }
 
@@ -300,7 +321,7 @@ bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_
     if (done) return BWLA_OK;
     s = bwla_rotate_quant_bits(layer, d_X, xdtype, act_bits, M, d_q, d_scale, d_qsum, d_T, d_ws, ws_bytes, stream);
     if (s != BWLA_OK) return s;
-    return bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream);
+    return bwla_linear_forward_bits(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, d_ws, ws_bytes, d_Y, d_acc, stream);
 }
 
 bwla_status_t bwla_decode_forward(const bwla_layer_t* layer, const void* d_X, int xdtype, int64_t M,
@@ -383,6 +404,24 @@ bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8_t* d_q, 
     return e == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
+bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                       const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_ws,
+                                       size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream) {
+    if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
+    if (d_ws && !aligned16(d_ws)) return BWLA_ERR_ALIGN;
+    bwla_status_t s = check_layer(layer);
+    if (s != BWLA_OK) return s;
+    void* z = act_bits <= 7 && M > GS_MIN_TOKENS && M <= (int64_t)1 << 24 ? sparse_ws_of(layer, M, d_ws, ws_bytes) : nullptr;
+    const int pick = z != nullptr ? bwla_gemm_sparse_pick(layer, M) : -1;
+    if (pick < 0) return bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream);
+    if (!d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
+    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
+    if (!aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) || (d_acc && !aligned16(d_acc)))
+        return BWLA_ERR_ALIGN;
+    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, d_Y, d_acc, (hipStream_t)stream, z) == hipSuccess
+               ? BWLA_OK : BWLA_ERR_HIP;
+}
+
 bwla_status_t bwla_pack_codes_a4(const int8_t* d_q, int64_t M, int64_t K, uint8_t* d_q4, void* stream) {
     if (!d_q || !d_q4) return BWLA_ERR_NULL;
     if (M <= 0 || K <= 0 || M > (int64_t)1 << 24) return BWLA_ERR_SHAPE;
@@ -449,6 +488,25 @@ bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t
     if (s != BWLA_OK) return s;
     return bwla_launch_swiglu_rows((const float*)d_ws, M, layer->N, (uint16_t*)d_H, st) == hipSuccess ? BWLA_OK
                                                                                                     : BWLA_ERR_HIP;
+}
+
+bwla_status_t bwla_linear_forward_swiglu_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                              const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits,
+                                              void* d_scratch, size_t scratch_bytes, void* d_H, void* d_ws, size_t ws_bytes,
+                                              void* stream) {
+    if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
+    if (d_scratch && !aligned16(d_scratch)) return BWLA_ERR_ALIGN;
+    size_t need = 0;
+    bwla_status_t s = bwla_swiglu_workspace_size(layer, M, &need);
+    if (s != BWLA_OK) return s;
+    void* z = act_bits <= 7 && M > GS_MIN_TOKENS ? sparse_ws_of(layer, M, d_scratch, scratch_bytes) : nullptr;
+    const int pick = z != nullptr ? bwla_gemm_sparse_pick(layer, M) : -1;
+    if (pick < 0) return bwla_linear_forward_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream);
+    if (!d_q || !d_scale || !d_qsum || !d_H) return BWLA_ERR_NULL;
+    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
+    if (!aligned16(d_q) || !aligned16(d_H) || (d_T && !aligned16(d_T))) return BWLA_ERR_ALIGN;
+    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, nullptr, nullptr, (hipStream_t)stream, z,
+                                   (uint16_t*)d_H) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
 }  // extern "C"

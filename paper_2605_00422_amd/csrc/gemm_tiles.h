@@ -76,3 +76,51 @@ inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4)
     }
     return best;
 }
+
+// Tiles of the sparse GEMM (gemm_sparse.hip), which serves codes of at most 7 bits and more than 64 tokens where it is
+// the faster one.  The same kind of cost, `step` per superstep of 512 columns; in front of it the pass that turns the codes
+// into sums and differences (a launch, and the codes once in and once out).  It contracts twice the columns an instruction
+// but prepares its operands at more cost, in steps of 512 columns, and its wide tiles start and finish slowly: it wins where
+// tiles are many and rows of K long.  Fitted to 279 shapes (65 .. 4096 tokens, K 256 .. 28672, N 64 .. 51200, 73 of them
+// gated), three layers in turn; it is taken where its cost is 5 % below the dense kernel's.  Over those shapes the choice
+// takes 0.974 of the dense kernel's time (0.968 with the best tile of both every time; 0.62 .. 0.9 where M K N > 1e11), with
+// 2 of 279 times more than 2 % above it; without the 5 %, 9.  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and
+// move the average by less than 0.7 % at ten times as many wrong choices.
+struct GsTile {
+    int mt, nt, wn, ring;         // 32-token tiles and 32-channel tiles a wavefront; wavefronts side by side; pairs in the code ring
+    int resident;                 // workgroups a CU holds
+    float start, base[2], step[2], idle, low;
+};
+constexpr int GS_MIN_TOKENS = 64;
+constexpr GsTile GS_TILES[] = {
+    {2, 2, 4, 4, 2, 4.92f, {4.13f, 8.09f}, {1.500f, 2.401f}, 0.513f, 1.257f},       // 64 x 256
+    {2, 5, 4, 4, 1, 0.77f, {16.83f}, {2.774f}, 0.829f, 1.675f},                     // 64 x 640
+    {4, 4, 4, 4, 1, 0.69f, {24.61f}, {3.577f}, 1.122f, 2.267f},                     // 128 x 512
+};
+constexpr int GS_NTILES = sizeof(GS_TILES) / sizeof(GS_TILES[0]);
+
+inline float gs_cost(const GsTile& v, int64_t M, int64_t K, int64_t N, int r, int64_t cus) {
+    const int64_t bm = 32 * v.mt, bn = (int64_t)32 * v.nt * v.wn;
+    const int64_t tiles = (M + bm - 1) / bm * ((N + bn - 1) / bn), cap = cus * v.resident;
+    const float steps = (float)((K + 511) / 512);
+    const int64_t full = tiles / cap, rem = tiles - full * cap;
+    float t = v.start + (float)full * (v.base[v.resident - 1] + v.step[v.resident - 1] * steps);
+    if (rem > 0) {
+        const int share = (int)((rem + cus - 1) / cus);
+        t += v.base[share - 1] + (v.step[share - 1] - v.idle * ((float)share - (float)rem / (float)cus)) * steps;
+    }
+    t += (float)((full + (rem > 0 ? 1 : 0)) * ((r + 15) / 16)) * v.low;
+    return t + 1.5f + (float)(M * K) * 2.0f / 6.3e6f;
+}
+
+// index into GS_TILES, or -1: the dense kernel
+inline int gs_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus) {
+    if (M <= GS_MIN_TOKENS) return -1;
+    int best = -1;
+    float cost = gd_cost(GD_TILES[gd_pick(M, K, N, r, cus, false)], M, K, N, r, cus, false);
+    for (int i = 0; i < GS_NTILES; ++i) {
+        const float c = 1.05f * gs_cost(GS_TILES[i], M, K, N, r, cus);
+        if (c < cost) { cost = c; best = i; }
+    }
+    return best;
+}

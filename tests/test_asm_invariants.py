@@ -201,3 +201,75 @@ def test_last_workgroup_of_a_projection_tile_keeps_enough_slices_in_flight():
                 elif l.startswith("s_waitcnt") and "vmcnt" in l:
                     run = 0
             assert best >= least, (bf16, njt, best)
+
+
+# (token tiles, channel tiles, wavefronts, ring, workgroups a CU) of csrc/gemm_tiles.h
+SPARSE = [(2, 2, 4, 4, 2), (2, 5, 4, 4, 1), (4, 4, 4, 4, 1)]
+
+
+@pytest.fixture(scope="module")
+def sparse_asm():
+    return _device_asm("gemm_sparse.hip")
+
+
+def _registers(l):
+    """Vector registers an instruction names."""
+    found = set()
+    for m in re.finditer(r"\bv(?:\[(\d+):(\d+)\]|(\d+)\b)", l.split(";")[0]):
+        lo = int(m.group(1) or m.group(3))
+        found.update(range(lo, int(m.group(2) or lo) + 1))
+    return found
+
+
+@pytest.mark.parametrize("gated", [0, 1])
+@pytest.mark.parametrize("tile", SPARSE)
+def test_sparse_gemm_loop_structure(sparse_asm, tile, gated):
+    """The sparse GEMM's loop loads nothing to registers from memory, waits for its asynchronous copies by a hand-counted
+    number once a pair of contractions, and reads LDS by inline assembly: a register of such a read is named by nothing
+    before the wait behind it."""
+    mt, nt, wn, ring, resident = tile
+    pat = re.compile(rf"_ZN.*gemm_sparse_kernelILi{mt}ELi{nt}ELi{wn}ELi{ring}ELi{resident}ELb{gated}E.*:")
+    start = next(i for i, l in enumerate(sparse_asm) if pat.match(l))
+    lines = sparse_asm[start:next(i for i in range(start, len(sparse_asm)) if sparse_asm[i].startswith(".amdhsa_next_free_vgpr"))]
+    first = next(i for i, l in enumerate(lines) if l.startswith("v_smfmac"))
+    last = max(i for i, l in enumerate(lines) if l.startswith("v_smfmac"))
+    head = max(i for i in range(first) if lines[i].startswith(".LBB"))
+    branch = next(i for i in range(last, len(lines)) if re.match(rf"s_cbranch\S*\s+{lines[head].split(':')[0]}$|s_branch\s+{lines[head].split(':')[0]}$", lines[i])
+                  or lines[i].startswith("s_cbranch"))
+    loop = [l for l in lines[head:branch] if l and not l.startswith((";", "."))]
+    codes, weights = 2 * (32 * mt * 64) // 1024 // wn, (2 * nt + 3) // 4       # copies a pair and wavefront
+    per = codes + weights
+    assert sum(l.startswith("v_smfmac_i32_32x32x64_i8") for l in loop) == 8 * mt * nt
+    assert sum(l.startswith("global_load_lds_dwordx4") for l in loop) == 4 * per
+    assert not any(l.startswith(("scratch_", "global_store", "buffer_", "flat_", "v_accvgpr")) or
+                   (l.startswith("global_load") and "_lds_" not in l) for l in loop)
+    waits = [i for i, l in enumerate(loop) if l.startswith("s_waitcnt") and "vmcnt" in l]
+    assert [loop[i] for i in waits] == [f"s_waitcnt vmcnt({(ring - 2) * per})"] * 4
+    barriers = [i for i, l in enumerate(loop) if l.startswith("s_barrier")]
+    assert len(barriers) == 4
+    for w, b in zip(waits, barriers):
+        assert w < b and not any(l.startswith(("ds_read", "global_load_lds")) for l in loop[w:b])
+    # from the first asynchronous copy of the kernel on: the prologue's reads, then the loop twice (what is in flight at
+    # its end meets its beginning)
+    begin = next(i for i, l in enumerate(lines) if l.startswith("global_load_lds"))
+    barrier = next(i for i in range(begin, len(lines)) if lines[i].startswith("s_barrier"))
+    pro = next(i for i in range(barrier, len(lines)) if lines[i].startswith("ds_read"))
+    for part in (lines[pro:head] if pro < head else [], loop + loop):
+        pending = set()
+        for l in part:
+            if l.startswith("s_waitcnt") and "lgkmcnt(0)" in l:
+                pending.clear()
+                continue
+            touched = _registers(l)
+            assert not touched & pending, l
+            if l.startswith("ds_read"):
+                pending |= _registers(l.split(",")[0])
+        assert not pending
+    # the flags that are asked for before the copies stay untouched until the first counted wait
+    flags = [i for i in range(begin) if lines[i].startswith("global_load_dword ")]
+    assert len(flags) == 32 * mt // 16
+    wait = next(i for i in range(begin, len(lines)) if lines[i].startswith("s_waitcnt") and "vmcnt" in lines[i])
+    assert lines[wait] == f"s_waitcnt vmcnt({(ring - 1) * per})"
+    for i in flags:
+        regs = _registers(lines[i].split(",")[0])
+        assert not any(_registers(l) & regs for l in lines[i + 1:wait])

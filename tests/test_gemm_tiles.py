@@ -81,3 +81,54 @@ def test_recorded_shapes_take_a_fast_tile(pick, shape, a4, tiles):
     i = pick([shape], a4)[0]
     ntl, wk, _, wn, _ = pick.tiles[i]
     assert (ntl, wk, wn) in tiles
+
+
+# ---- the sparse GEMM's tiles (same header)
+SPARSE_DRIVER = """
+#include <cstdio>
+#include "gemm_tiles.h"
+int main() {
+    printf("%d\\n", GS_NTILES);
+    long long M, K, N;
+    int r;
+    while (scanf("%lld %lld %lld %d", &M, &K, &N, &r) == 4) printf("%d\\n", gs_pick(M, K, N, r, 256));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def sparse_pick(tmp_path_factory):
+    d = tmp_path_factory.mktemp("sparse_tiles")
+    (d / "pick.cpp").write_text(SPARSE_DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", str(d / "pick"), str(d / "pick.cpp")], check=True)
+
+    def run(shapes):
+        out = subprocess.run([str(d / "pick")], input="".join("%d %d %d %d\n" % s for s in shapes), text=True,
+                             capture_output=True, check=True).stdout.split()
+        run.tiles = int(out[0])
+        return [int(x) for x in out[1:]]
+
+    return run
+
+
+def test_every_sparse_tile_is_reached(sparse_pick):
+    from test_gpu_sparse import SHAPES
+    rng = random.Random(1)
+    log = lambda lo, hi: int(lo * (hi / lo) ** rng.random())                 # noqa: E731
+    got = sparse_pick([(log(17, 4097), 128 * log(1, 225), log(32, 28673), rng.choice([0, 8, 32, 64, 96])) for _ in range(6000)])
+    for i in range(sparse_pick.tiles):
+        assert got.count(i) >= 20, (i, got.count(i))
+    assert sorted(set(sparse_pick(SHAPES))) == list(range(sparse_pick.tiles))   # each of them by one: none is left to the dense kernel
+
+
+# (tokens, K, N, rank), tile (-1: dense kernel), both sides in microseconds: pass over the codes and sparse kernel, dense kernel
+@pytest.mark.parametrize("shape,tiles", [
+    ((4096, 28672, 8192, 64), [2]),              # 36 + 475, 760
+    ((2048, 25600, 5120, 64), [1]),              # 17 + 158, 206
+    ((2048, 4096, 22016, 64), [0, 2]),           # 4 + 186, 215
+    ((4096, 8192, 8192, 64), [2]),               # 12 + 183, 237
+    ((64, 28672, 8192, 64), [-1]),
+    ((1031, 5120, 1024, 64), [-1]),              # 2 + 26, 22
+])
+def test_recorded_shapes_take_the_faster_kernel(sparse_pick, shape, tiles):
+    assert sparse_pick([shape])[0] in tiles

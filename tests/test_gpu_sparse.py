@@ -1,0 +1,188 @@
+"""The GEMM on the sparse INT8 instructions (csrc/gemm_sparse.hip) against the dense one, which the oracle checks
+(test_gpu_parity.py), and against exact integer products: it computes the same sums and the same epilogue, so its outputs
+are the dense kernel's bit for bit."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+# (tokens, K, N, rank): edges of tiles, supersteps and ranks of each tile that the dispatch chooses from
+SHAPES = [
+    (709, 128, 8617, 96),       # 64 x 256: a quarter of a superstep, five tokens in the last tile, odd channels, two chunks of ranks
+    (2487, 128, 2462, 96),
+    (2048, 1024, 8192, 16),     # 64 x 256: nothing ragged
+    (331, 384, 23584, 64),      # 64 x 640
+    (868, 384, 10002, 96),      # 64 x 640, channels end inside a tile
+    (2048, 25600, 5120, 64),    # 64 x 640, fifty supersteps
+    (481, 1920, 26503, 0),      # 128 x 512: 97 tokens in the last tile, no ranks, odd channels
+    (2692, 2048, 4519, 37),     # 128 x 512, four tokens in the last tile, a rank that is no multiple of four
+    (1024, 8192, 28672, 64),    # 128 x 512: nothing ragged
+]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_00422_amd import binding as B
+    B.load()
+
+
+def _layer(M, K, N, r, centered=False, asym=False):
+    from paper_2605_00422_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K + N + r)
+    n1, n2 = B.kron_factor(K)
+    W = torch.randn(N, K, device=DEV, generator=g)
+    U = V = None
+    if r:
+        U = torch.randn(K, r, device=DEV, generator=g).half().float()
+        V = (torch.randn(N, r, device=DEV, generator=g) * 0.1).half().float()
+    q = [torch.linalg.qr(torch.randn(n, n, device=DEV, generator=g))[0].contiguous() for n in (n1, n2)]
+    return B.pack_weights(W, q[0], q[1], U, V, n1, n2, centered=centered, asym=asym), g
+
+
+def _acts(layer, M, K, g, lo, hi):
+    from paper_2605_00422_amd import binding as B
+    act = B.Activations(layer, M)
+    act.q.copy_(torch.randint(lo, hi + 1, (M, K), device=DEV, generator=g))
+    act.q[:, ::7] = hi                                      # equal neighbours at the ends of the range: largest sums
+    act.q[-1, ::3] = lo
+    act.scale.copy_((torch.rand(act.scale.shape, device=DEV, generator=g) + 0.5) * 0.01)
+    if act.T is not None:
+        act.T.copy_(torch.randn(act.T.shape, device=DEV, generator=g))
+    B.code_sums(act.q, act.qsum)
+    return act
+
+
+def _run(layer, act, N, act_bits, gated):
+    from paper_2605_00422_amd import binding as B
+    act.act_bits = act_bits
+    Y = torch.full((act.M, N), float("nan"), device=DEV)
+    acc = torch.full((act.M, N), -7, dtype=torch.int32, device=DEV)
+    B.linear_forward(layer, act, Y, acc)
+    Y2 = torch.full_like(Y, float("nan"))
+    B.linear_forward(layer, act, Y2)
+    H = None
+    if gated:
+        H = torch.full((act.M, N // 2), float("nan"), dtype=torch.bfloat16, device=DEV)
+        B.linear_forward_swiglu(layer, act, H)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y2)
+    return Y, acc, H
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        assert (x is None) == (y is None)
+        if x is not None:
+            assert bool(torch.isfinite(x.float()).all())
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("M,K,N,r", SHAPES)
+def test_same_bits_as_the_dense_kernel(M, K, N, r):
+    from paper_2605_00422_amd import binding as B
+    layer, g = _layer(M, K, N, r)
+    act = _acts(layer, M, K, g, -64, 63)
+    room = act.ws[-(M * K // 2):]
+    room.fill_(0x5a)                                        # where the codes are laid out anew
+    dense = _run(layer, act, N, 8, N % 2 == 0)
+    assert bool((room == 0x5a).all())                       # (the dense kernel leaves it alone)
+    sparse = _run(layer, act, N, 7, N % 2 == 0)
+    assert not bool((room == 0x5a).all()), "the shape is not served by the sparse kernel"
+    _same(sparse, dense)
+    sgn, _ = B.unpack_signs(layer)
+    want = act.q.float() @ sgn.float().t()                  # exact: |acc| <= 64 K < 2^24
+    assert torch.equal(sparse[1].float(), want)
+    # a scratch without the room: the dense kernel
+    act.ws_bytes -= M * K // 2
+    room.fill_(0x5a)
+    _same(_run(layer, act, N, 7, N % 2 == 0), dense)
+    assert bool((room == 0x5a).all())
+
+
+@pytest.mark.parametrize("M,K,N,r", [SHAPES[0], SHAPES[4], SHAPES[7]])
+@pytest.mark.parametrize("where", ["last", "first", "all"])
+def test_codes_wider_than_announced_are_found(M, K, N, r, where):
+    """act_bits says which kernel to start; a code outside [-64, 63] sends its tile to the dense instructions."""
+    from paper_2605_00422_amd import binding as B
+    layer, g = _layer(M, K, N, r)
+    act = _acts(layer, M, K, g, -64, 63)
+    if where == "last":
+        act.q[M - 1, K - 1] = 64
+    elif where == "first":
+        act.q[0, 0] = -65
+        act.q[70, 5] = 127
+    else:
+        act.q.copy_(torch.randint(-127, 128, (M, K), device=DEV, generator=g))
+    B.code_sums(act.q, act.qsum)
+    _same(_run(layer, act, N, 6, N % 2 == 0), _run(layer, act, N, 8, N % 2 == 0))
+
+
+@pytest.mark.parametrize("bits,centered,asym,x", [(6, False, False, torch.bfloat16), (7, False, True, torch.bfloat16),
+                                                  (4, True, True, torch.float32), (8, True, False, torch.bfloat16)])
+def test_whole_layer(bits, centered, asym, x):
+    """decode_forward with the scratch's room and without it."""
+    from paper_2605_00422_amd import binding as B
+    M, K, N, r = 1111, 4096, 9001, 20
+    layer, g = _layer(M, K, N, r, centered, asym)
+    X = torch.randn(M, K, device=DEV, generator=g).to(x)
+    outs = []
+    for room in (True, False):
+        act = B.Activations(layer, M)
+        if not room:
+            act.ws_bytes -= M * K // 2
+        Y = torch.full((M, N), float("nan"), device=DEV)
+        acc = torch.full((M, N), -7, dtype=torch.int32, device=DEV)
+        B.decode_forward(layer, X, act, Y, acc, act_bits=bits)
+        torch.cuda.synchronize()
+        outs.append((Y, acc, act.q, act.T, act.scale))
+    _same(*outs)
+
+
+def test_one_scratch_for_calls_of_several_sizes():
+    """The room for the codes lies at the end of a scratch: a call on fewer tokens leaves the arrival counters of one on
+    more tokens alone."""
+    from paper_2605_00422_amd import binding as B
+    K, N, r = 2048, 11008, 96
+    layer, g = _layer(4096, K, N, r)
+    X = torch.randn(4096, K, device=DEV, generator=g).to(torch.bfloat16)
+    big = B.Activations(layer, 4096)
+    ref = {}
+    for M in (4096, 700):
+        act = B.Activations(layer, M)
+        ref[M] = B.decode_forward(layer, X[:M], act, torch.empty(M, N, device=DEV)).clone()
+    for M in (700, 4096, 700, 4096):
+        act = B.Activations(layer, M)
+        act.ws, act.ws_bytes = big.ws, big.ws_bytes
+        Y = B.decode_forward(layer, X[:M], act, torch.full((M, N), float("nan"), device=DEV))
+        torch.cuda.synchronize()
+        assert torch.equal(Y, ref[M])
+
+
+def test_replayed_from_a_graph():
+    from paper_2605_00422_amd import binding as B
+    M, K, N, r = 1024, 8192, 8192, 32
+    layer, g = _layer(M, K, N, r)
+    act = B.Activations(layer, M)
+    Xs = [torch.randn(M, K, device=DEV, generator=g).to(torch.bfloat16) for _ in range(3)]
+    X, Y = Xs[0].clone(), torch.empty(M, N, device=DEV)
+    want = [B.decode_forward(layer, x, act, Y).clone() for x in Xs]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        B.decode_forward(layer, X, act, Y)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        B.decode_forward(layer, X, act, Y)
+    for x, w in zip(Xs + Xs, want + want):
+        X.copy_(x)
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, w)

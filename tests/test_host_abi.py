@@ -196,6 +196,21 @@ def test_swiglu_entry_points_check_arguments_first(lib):
         B.BWLA_ERR_NULL                                   # zeroed descriptor: no blob
 
 
+def test_forward_calls_of_a_width_check_arguments_first(lib):
+    desc = B.BwlaLayer()
+    fake, odd = c_void_p(0x1000), c_void_p(0x1008)
+    for bits in (1, 9, -6):
+        assert lib.bwla_linear_forward_bits(byref(desc), fake, fake, fake, fake, 100, bits, fake, 1 << 30, fake, None,
+                                            None) == B.BWLA_ERR_UNSUPPORTED
+        assert lib.bwla_linear_forward_swiglu_bits(byref(desc), fake, fake, fake, fake, 100, bits, fake, 1 << 30, fake, None,
+                                                   0, None) == B.BWLA_ERR_UNSUPPORTED
+    assert lib.bwla_linear_forward_bits(None, fake, fake, fake, fake, 100, 6, fake, 1 << 30, fake, None, None) == B.BWLA_ERR_NULL
+    assert lib.bwla_linear_forward_bits(byref(desc), fake, fake, fake, fake, 100, 6, odd, 1 << 30, fake, None, None) == \
+        B.BWLA_ERR_ALIGN
+    assert lib.bwla_linear_forward_swiglu_bits(None, fake, fake, fake, fake, 100, 6, fake, 1 << 30, fake, None, 0, None) == \
+        B.BWLA_ERR_NULL
+
+
 def test_quantizer_entry_points_check_arguments_first(lib):
     """Offline quantizer (include/bwla_quantizer.h): shapes, limits, null pointers, alignment and the
     scratch size are checked on the host; the scratch holds at least the five n x m fp64 arrays."""
