@@ -201,7 +201,8 @@ BWLA_API bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_
  *            layer's mode adds follow (see bwla_layer_t)
  * For a layer with BWLA_MODE_ASYM_ACT the codes are the asymmetric ones (see bwla_pack_weights_mode):
  * d_q holds q - 2^(b-1), d_qsum their sums, d_scale the step (hi - lo) / (2^b - 1).
- *   d_ws     scratch of ws_bytes >= bwla_psp_workspace_size(layer, M) (NULL allowed when that is 0)
+ *   d_ws     scratch of ws_bytes >= bwla_psp_workspace_size(layer, M) (NULL allowed when that is 0; a scratch for M tokens
+ *            also serves fewer)
  */
 BWLA_API bwla_status_t bwla_rotate_quant(const bwla_layer_t* layer, const void* d_X, int xdtype, int64_t M,
                                 int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T,
@@ -294,8 +295,8 @@ BWLA_API bwla_status_t bwla_decode_forward_launches(const bwla_layer_t* layer, i
  * between the rotation's two launches) lives in a fixed array of BWLA_STATIC_SCRATCH_BYTES inside
  * the library's device image, one per GPU, held until the process ends.  The call allocates
  * nothing and calls no allocating routine; it clears the counters it needs with a small kernel.
- *   - A call whose bwla_psp_workspace_size(layer, M), less the sparse GEMM's room, exceeds BWLA_STATIC_SCRATCH_BYTES
- *     returns BWLA_ERR_BUFSIZE and enqueues nothing (decode batches of the common model widths fit; long
+ *   - A call whose part of the scratch for the rotation and projection of M tokens exceeds BWLA_STATIC_SCRATCH_BYTES
+ *     (bwla_psp_workspace_size covers fewer tokens and the sparse GEMM as well, and may be larger) returns BWLA_ERR_BUFSIZE and enqueues nothing (decode batches of the common model widths fit; long
  *     prefills do not: use bwla_decode_forward with a workspace of the caller's).
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap in time on one GPU (two
  *     streams, two host threads) race on it and must be serialized by the caller.

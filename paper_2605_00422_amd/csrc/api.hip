@@ -87,8 +87,14 @@ void* sparse_ws(const bwla_layer_t* L, int64_t M, size_t need, void* d_ws, size_
     if (bytes == 0 || d_ws == nullptr || ws_bytes < sparse_ws_start(need, bytes) + bytes) return nullptr;
     return (char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255);
 }
+// what bwla_rotate_quant needs for M tokens of either type
+size_t rq_need(const bwla_layer_t* L, int64_t M) {
+    const size_t a = rq_ws_bytes(L, bwla_psp_plan_of(L, M, BWLA_X_BF16), M);
+    const size_t b = rq_ws_bytes(L, bwla_psp_plan_of(L, M, BWLA_X_F32), M);
+    return a > b ? a : b;
+}
 void* sparse_ws_of(const bwla_layer_t* L, int64_t M, void* d_ws, size_t ws_bytes) {
-    return sparse_ws(L, M, rq_ws_bytes(L, bwla_make_psp_plan(M, L->K, bwla_rank_u(L)), M), d_ws, ws_bytes);
+    return sparse_ws(L, M, rq_need(L, M), d_ws, ws_bytes);
 }
 inline void* ws_body(void* d_ws) { return d_ws ? (char*)d_ws + BWLA_WS_HEAD : nullptr; }
 
@@ -259,7 +265,12 @@ bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_t M, size
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (M <= 0) return BWLA_ERR_SHAPE;
-    const size_t need = rq_ws_bytes(layer, bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer)), M);
+    // for fewer tokens a call can need more (more slices); from 2048 tokens on there are eight and it only grows
+    size_t need = rq_need(layer, M);
+    for (int64_t m = M < 2048 ? M - 1 : 2048; m > 0; --m) {
+        const size_t n = rq_need(layer, m);
+        if (n > need) need = n;
+    }
     const uint64_t sparse = bwla_gemm_sparse_bytes(layer, M);
     *bytes = sparse == 0 ? need : sparse_ws_start(need, sparse) + (size_t)bwla_align256(sparse);
     return BWLA_OK;
@@ -285,7 +296,7 @@ bwla_status_t bwla_rotate_quant_bits(const bwla_layer_t* layer, const void* d_X,
     if (xdtype != BWLA_X_F32 && xdtype != BWLA_X_BF16) return BWLA_ERR_UNSUPPORTED;
     if (!aligned16(d_X) || !aligned16(d_q) || (d_T && !aligned16(d_T)) || (d_ws && !aligned16(d_ws)))
         return BWLA_ERR_ALIGN;
-    const bwla_psp_plan plan = bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer));
+    const bwla_psp_plan plan = bwla_psp_plan_of(layer, M, xdtype);
     const size_t need = rq_ws_bytes(layer, plan, M);
     if (need > 0 && (!d_ws || ws_bytes < need)) return d_ws ? BWLA_ERR_BUFSIZE : BWLA_ERR_NULL;
     hipStream_t st = (hipStream_t)stream;
@@ -309,7 +320,7 @@ bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_
     if (!aligned16(d_X) || !aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) ||
         (d_ws && !aligned16(d_ws)) || (d_acc && !aligned16(d_acc)))
         return BWLA_ERR_ALIGN;
-    const bwla_psp_plan plan = bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer));
+    const bwla_psp_plan plan = bwla_psp_plan_of(layer, M, xdtype);
     const size_t need = rq_ws_bytes(layer, plan, M);
     if (need > 0 && (!d_ws || ws_bytes < need)) return d_ws ? BWLA_ERR_BUFSIZE : BWLA_ERR_NULL;
     hipStream_t st = (hipStream_t)stream;
@@ -352,7 +363,7 @@ bwla_status_t bwla_decode_forward_static(const bwla_layer_t* layer, const void* 
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (M <= 0 || M > (int64_t)1 << 24) return BWLA_ERR_SHAPE;
-    const bwla_psp_plan plan = bwla_make_psp_plan(M, layer->K, bwla_rank_u(layer));
+    const bwla_psp_plan plan = bwla_psp_plan_of(layer, M, xdtype);
     const size_t need = rq_ws_bytes(layer, plan, M);
     if (need > BWLA_STATIC_SCRATCH_BYTES) return BWLA_ERR_BUFSIZE;
     if (!d_X || !d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;

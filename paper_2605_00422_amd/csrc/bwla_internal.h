@@ -62,7 +62,9 @@ struct bwla_psp_plan {
     int tile_cols;     // columns per tile
     int col_groups;    // tiles across the rank
 };
-bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r);
+// (planes: bwla_rotate_planes_serves the call)
+bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes);
+bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M);
 // Every scratch of bwla_rotate_quant starts with the exchange area of the single-launch decode
 // kernel -- an epoch word, eight arrival counts (64 bytes apart, from byte 64 on), and from byte
 // 1024 on 8 x 96 tagged partial sums of T = x U, 8 bytes each -- at the same place whatever the
@@ -76,6 +78,9 @@ inline uint64_t bwla_psp_counter_bytes(int64_t M) { return bwla_align256((uint64
 inline int bwla_extra_cols(int mode) { return ((mode & BWLA_MODE_ASYM_ACT) ? 2 : 0) + ((mode & BWLA_MODE_ROW_SHIFT) ? 1 : 0); }
 // columns of U = rank of the projection T = X U
 inline int bwla_rank_u(const bwla_layer_t* L) { return L->r - bwla_extra_cols(L->mode); }
+inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
+    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), bwla_rotate_planes_serves(L, xdtype, M));
+}
 inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int64_t M, int r) {
     if (r <= 0 || p.splits <= 1) return 0;
     return (size_t)(bwla_psp_counter_bytes(M) + (uint64_t)p.token_tiles * p.col_groups * p.splits *
@@ -86,7 +91,13 @@ inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int64_t M, int r) {
 size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& plan, int64_t M);
 int bwla_psp_prefill_tile_cols(int rp);
 hipError_t bwla_launch_psp_prefill(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, float* dT,
-                                   void* dws, const bwla_psp_plan& plan, hipStream_t st);
+                                   void* dws, const bwla_psp_plan& plan, hipStream_t st, bool finish = true);
+// Partial tiles that such a launch has left (finish = false), to be added up by workgroups behind the rotation's own in
+// the launch that follows: `blocks` of them (0: nothing to add), 64 x W tiles, S slices each.
+struct bwla_psp_tiles {
+    const float* partials; float* T; int64_t M;
+    int r, tp, S, JG, W, blocks;
+};
 
 // Raises a kernel's dynamic-LDS limit, once per kernel, device and size class, so that steady-state
 // launches, also under stream capture, issue no attribute calls.  Safe to call from several host
@@ -138,11 +149,37 @@ __device__ __forceinline__ bool bwla_partials_arrive(int* counter, int expected,
 }
 #endif
 
+#if defined(__HIPCC__)
+// Workgroup b of t.blocks: T from the partial tiles, every value in slice order, sixteen slices in flight.
+__device__ __forceinline__ void bwla_psp_sum_tiles(const bwla_psp_tiles& t, int b) {
+    const int plane = 16 * t.W, tile = 4 * plane;          // floats: vectors of a tile, stored component by component
+    const int64_t total = ((t.M + 63) >> 6) * t.JG * tile, step = (int64_t)t.blocks * blockDim.x;
+    for (int64_t i = (int64_t)b * blockDim.x + threadIdx.x; i < total; i += step) {
+        const int64_t unit = i / tile;
+        const int e = (int)(i - unit * tile), c = e / plane, v = e - c * plane;
+        const int64_t tt = unit / t.JG;
+        const int64_t tok = tt * 64 + (v * 4) / t.W;
+        const int col = (int)(unit - tt * t.JG) * 64 + (v * 4) % t.W + c;
+        if (tok >= t.M || col >= t.r) continue;
+        const float* p = t.partials + unit * t.S * tile + e;
+        float sum = 0.0f;
+        for (int s = 0; s < t.S; s += 16) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = p[(int64_t)(s + u < t.S ? s + u : t.S - 1) * tile];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) sum += s + u < t.S ? x[u] : 0.0f;
+        }
+        t.T[tok * t.tp + col] = sum;
+    }
+}
+#endif
+
 hipError_t bwla_launch_code_sums(const int8_t* dq, int64_t M, int64_t K, int32_t* dqsum, hipStream_t st);
 // the whole layer in one launch for one bf16 token where the shape allows it (*done says whether)
 hipError_t bwla_launch_rotate_planes(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, int8_t* dq,
                                      float* dscale, int32_t* dqsum, float* dT, int act_bits, hipStream_t st,
-                                     bool* done);
+                                     bool* done, const bwla_psp_tiles& tiles);
 hipError_t bwla_launch_decode_layer(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, int8_t* dq,
                                     float* dscale, int32_t* dqsum, float* dT, void* dws_head, float* dY,
                                     int32_t* dacc, hipStream_t st, bool* done, bool dry_run = false, int act_bits = 6);

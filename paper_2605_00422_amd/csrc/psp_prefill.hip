@@ -30,6 +30,7 @@ struct PfArgs {
     const __half* Ut;                     // packed U: [rp / 16][K / 32][64 lanes][8] fp16
     float* T; int* counters; float* partials;
     int S, JG, kslice;
+    int finish;                           // 0: only leave the partial tiles, the next launch adds them up
 };
 
 template <bool BF16> struct AFrag;
@@ -226,11 +227,15 @@ __global__ __launch_bounds__(PF_THREADS) void psp_prefill_kernel(PfArgs a) {
             store_T(e4, sum);
         } else {
             float* p = ptile + e4;
+            if (!a.finish) {
+                p[0] = sum.x; p[TILE_F4] = sum.y; p[2 * TILE_F4] = sum.z; p[3 * TILE_F4] = sum.w;
+                continue;
+            }
             bwla_store_agent(p, sum.x); bwla_store_agent(p + TILE_F4, sum.y);
             bwla_store_agent(p + 2 * TILE_F4, sum.z); bwla_store_agent(p + 3 * TILE_F4, sum.w);
         }
     }
-    if (a.S == 1) return;
+    if (a.S == 1 || !a.finish) return;
     if (!bwla_partials_arrive(&a.counters[unit], a.S, is_last)) return;
     // last workgroup of this tile: add the S partial tiles in slice order
     const float* pbase = a.partials + (int64_t)unit * a.S * (TILE_F4 * 4);
@@ -282,9 +287,10 @@ hipError_t launch(const PfArgs& a, int blocks, hipStream_t st) {
 int bwla_psp_prefill_tile_cols(int rp) { return rp <= 16 ? 16 : rp <= 32 ? 32 : 64; }
 
 hipError_t bwla_launch_psp_prefill(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, float* dT,
-                                   void* dws, const bwla_psp_plan& plan, hipStream_t st) {
+                                   void* dws, const bwla_psp_plan& plan, hipStream_t st, bool finish) {
     const char* blob = (const char*)L->d_blob;
     PfArgs a;
+    a.finish = finish ? 1 : 0;
     a.X = dX; a.M = M; a.K = L->K; a.r = bwla_rank_u(L); a.rp = (a.r + 15) & ~15; a.tp = L->r;
     a.Ut = (const __half*)(blob + L->off_U);
     a.T = dT;

@@ -35,6 +35,8 @@ struct RpArgs {
     const uint16_t* R2h; const uint16_t* R1h;
     int8_t* q; float* scale; int32_t* qsum;
     float* tmode; int tp; float qmax; int asym, shift;
+    int rot_blocks;                                     // workgroups that rotate; those behind them add up `tiles`
+    bwla_psp_tiles tiles;
 };
 
 template <int N1, int N2, int G, bool STREAM = false>
@@ -60,6 +62,10 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
     constexpr int K = S::K, AT = S::AT, K1 = S::K1, CH2 = S::CH2, STRIPS = S::STRIPS, GPR = S::GPR, PITCH = S::PITCH;
     constexpr int TG = S::TG, NI = S::NI, ITEMS = S::ITEMS;
     extern __shared__ __align__(16) char lds[];
+    if ((int)blockIdx.x >= a.rot_blocks) {
+        bwla_psp_sum_tiles(a.tiles, (int)blockIdx.x - a.rot_blocks);
+        return;
+    }
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int grp = wv / STRIPS, wave = wv - grp * STRIPS;             // token group, strip
     const int tid = (int)threadIdx.x - grp * TG, lane = tid & 63, li = lane & 15, lg = lane >> 4;
@@ -96,7 +102,7 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
     }
 
     // token of round j for my group; a group without a token left repeats the last one and stores nothing
-    const int64_t tstep = (int64_t)gridDim.x * G;
+    const int64_t tstep = (int64_t)a.rot_blocks * G;
     const int64_t t0 = (int64_t)blockIdx.x * G + grp;
     const int rounds = (int)((a.M + tstep - 1) / tstep);
     v4i xpre[NI];
@@ -296,7 +302,7 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
 }
 
 template <int N1, int N2, int G, bool STREAM = false>
-hipError_t launch_planes(const RpArgs& a, int cus, hipStream_t st) {
+hipError_t launch_planes(RpArgs a, int cus, hipStream_t st) {
     using S = RpShape<N1, N2, G, STREAM>;
     static_assert(S::LDS <= RQ_LDS_LIMIT, "the factors and the token rows have to fit LDS");
     static_assert(S::STRIPS <= 16 && N1 % 32 == 0 && N2 % 32 == 0, "shape outside the kernel's layout");
@@ -304,28 +310,34 @@ hipError_t launch_planes(const RpArgs& a, int cus, hipStream_t st) {
     if (e != hipSuccess) return e;
     int64_t grid = (a.M + G - 1) / G;
     if (grid > cus) grid = cus;
-    rotate_planes_kernel<N1, N2, G, STREAM><<<dim3((unsigned)grid), dim3(S::THREADS), S::LDS, st>>>(a);
+    a.rot_blocks = (int)grid;
+    rotate_planes_kernel<N1, N2, G, STREAM><<<dim3((unsigned)(grid + a.tiles.blocks)), dim3(S::THREADS), S::LDS, st>>>(a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// *done = false (nothing launched) when the shape has no kernel here: bf16 tokens, at least one
-// per CU, a factor pair for which the operand-order planes exist and a kernel was built.
+// bf16 tokens, at least one per CU, a factor pair for which the operand-order planes exist and a kernel was built
+bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M) {
+    if (xdtype != BWLA_X_BF16 || L->off_Rd == 0 || M < (int64_t)bwla_device_cus()) return false;
+    const int n1 = L->n1, n2 = L->n2;
+    return (n1 == 160 && n2 == 160) || (n1 == 128 && n2 == 64) || (n1 == 64 && n2 == 64) || (n1 == 224 && n2 == 128);
+}
+
+// *done = false (nothing launched) when the call is not served here
 hipError_t bwla_launch_rotate_planes(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, int8_t* dq,
                                      float* dscale, int32_t* dqsum, float* dT, int act_bits, hipStream_t st,
-                                     bool* done) {
+                                     bool* done, const bwla_psp_tiles& tiles) {
     *done = false;
     const int n1 = L->n1, n2 = L->n2;
-    if (xdtype != BWLA_X_BF16 || L->off_Rd == 0) return hipSuccess;
+    if (!bwla_rotate_planes_serves(L, xdtype, M)) return hipSuccess;
     const int cus = bwla_device_cus();
-    if (M < (int64_t)cus) return hipSuccess;
     const char* blob = (const char*)L->d_blob;
     RpArgs a;
     a.X = (const uint16_t*)dX; a.M = M;
     a.R1h = (const uint16_t*)(blob + L->off_Rd + bwla_decode_planes_r2_bytes(n1, n2));
     a.R2h = a.R1h + bwla_planes_r1h_bytes(n1) / 2;
-    a.q = dq; a.scale = dscale; a.qsum = dqsum;
+    a.q = dq; a.scale = dscale; a.qsum = dqsum; a.tiles = tiles;
     const int ru = bwla_rank_u(L);
     a.tp = L->r; a.tmode = L->mode != 0 ? dT + ru : nullptr;
     a.asym = (L->mode & BWLA_MODE_ASYM_ACT) ? 1 : 0; a.shift = (L->mode & BWLA_MODE_ROW_SHIFT) ? 1 : 0;
@@ -334,8 +346,7 @@ hipError_t bwla_launch_rotate_planes(const bwla_layer_t* L, const void* dX, int 
     if (n1 == 160 && n2 == 160) e = launch_planes<160, 160, 1>(a, cus, st);
     else if (n1 == 128 && n2 == 64) e = launch_planes<128, 64, 4>(a, cus, st);
     else if (n1 == 64 && n2 == 64) e = launch_planes<64, 64, 4>(a, cus, st);
-    else if (n1 == 224 && n2 == 128) e = launch_planes<224, 128, 1, true>(a, cus, st);     // R1 terms: 196 KB, streamed
-    else return hipSuccess;
+    else e = launch_planes<224, 128, 1, true>(a, cus, st);                                  // R1 terms: 196 KB, streamed
     if (e == hipSuccess) *done = true;
     return e;
 }

@@ -1,5 +1,6 @@
-// bwla_rotate_quant: workgroups [0, M) rotate and quantize one token each; for up to 16
-// tokens the workgroups behind them compute the PSP projection T = X U in the same launch.
+// bwla_rotate_quant: workgroups [0, M) rotate and quantize one token each; for few tokens the workgroups behind them
+// compute the PSP projection T = X U in the same launch, for more they add up the partial tiles that a launch of the
+// projection's own has left (bwla_make_psp_plan, bwla_launch_rotate_quant).
 //
 // Rotation (paper Sec. 3.1; App. A.2.2), per token on the row-major n1 x n2 reshape V:
 //   X~[t, c*n2 + d] = sum_{a,b} X[t, a*n2 + b] R1[a,c] R2[b,d]   =   (R1^T (V R2))[c,d]
@@ -41,11 +42,16 @@ struct RqArgs {
     int64_t rot_blocks;      // workgroups below this index rotate token blockIdx.x, the rest project
     int JG;                  // projection workgroups per (token tile, slice): groups of rank tiles
     const uint16_t* R1p; const uint16_t* R2p;          // bf16 term planes of the factors
+    bwla_psp_tiles tiles;    // the workgroups behind the rotation add these up instead of projecting, if there are any
 };
 
 // projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile
 template <bool BF16>
 __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
+    if (a.tiles.blocks > 0) {
+        bwla_psp_sum_tiles(a.tiles, pb);
+        return;
+    }
     const int s = pb % a.S, rest = pb / a.S;
     psp_block<BF16>(lds, a.X, a.M, a.K, a.r, a.U, a.T, a.counters, a.partials, a.S, rest / a.JG, s, a.tp, finish,
                     rest % a.JG, a.JG);
@@ -168,17 +174,25 @@ bool bwla_rotate_supported(int n1, int n2) {
 int bwla_rotate_tiles(int n1, int n2) { return (rq_pad16(n1) / 16) * (rq_pad16(n2) / 16); }
 int bwla_rotate_max_tiles() { return RQ_MAXT * RQ_WAVES; }
 
-bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r) {
+bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes) {
     bwla_psp_plan p;
     const int rp = (r + 15) & ~15;
-    // The projection rides in the rotation launch while that launch stays within about three
-    // workgroups per CU: its short workgroups then finish in the shadow of the rotation, and the
-    // separate projection kernel costs about 8 us at these sizes (64 x 80, rank 64, 320 tokens:
-    // 33.4 -> 25.6 us with 720 workgroups; 128 x 64, rank 64, 320 tokens: 960 workgroups lose, 36.7 -> 38.8).
+    // The projection rides in the rotation launch where its workgroups finish in the rotation's shadow: a rotation
+    // workgroup has a CU to itself and takes about 6 us + K / 1050, the CUs that the last round of them leaves free take a
+    // round of projection workgroups every 5.5 us.  A little beside the shadow is still less than the launch of its own
+    // that the projection needs otherwise (6 to 7 us), and so is a small round behind the rotation.  Not where the kernel
+    // that walks over the tokens serves (planes), which is the faster one by more.  Rotation + projection, riding / in a
+    // launch of its own, and the rotation alone: 8192 columns, rank 64: 128 tokens 16.7 / 21 / 13.3; 255 tokens
+    // 29.8 / 22.7 / 14.3; 25600, rank 32: 128 tokens 28.3 / 34 / 26.6; 5120, rank 32: 257 tokens 16.8 / 23 / 17.
     // (ranks of more than two 16-column tiles are dealt to several workgroups per slice)
     const int jg = rp > 16 * PP_GROUPJT ? (rp / 16 + PP_GROUPJT - 1) / PP_GROUPJT : 1;
-    const int64_t ride = M + ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg;
-    if (M <= 16 || r <= 0 || ride <= 768) {
+    const int64_t riders = ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg, cus = bwla_device_cus();
+    const int64_t beside = (cus - M % cus) % cus;              // CUs that the last round leaves free
+    const bool shadow = beside > 0 && 5.5f * (float)((riders + beside - 1) / beside) <= 9.0f + (float)K / 1050.0f;
+    // (short rows leave room for several workgroups a CU: there it is their number that counts, up to three a CU; 512
+    // columns, rank 64, 384 tokens 11.7 / 18.5)
+    const bool ride = !planes && M <= 768 && (K < 2048 ? M + riders <= 768 : shadow || riders <= 192);
+    if (M <= 16 || r <= 0 || ride) {
         p.token_tiles = (int)((M + 15) / 16);
         p.k_per_split = PP_SLICE;
         p.splits = r > 0 ? (int)((K + PP_SLICE - 1) / PP_SLICE) : 1;
@@ -195,7 +209,6 @@ bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r) {
     p.col_groups = (rp + 63) / 64;
     p.token_tiles = (int)((M + 63) / 64);
     const int64_t units = (int64_t)p.token_tiles * p.col_groups;
-    const int64_t cus = bwla_device_cus();
     int64_t S = 8 * ((cus + 8 * units - 1) / (8 * units));
     const int64_t smax = K / 512 > 1 ? K / 512 : 1;
     if (S > smax) S = smax;
@@ -229,17 +242,32 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     // Few tokens: one launch holds rotation and projection workgroups (a second launch would
     // cost more than it saves).  Many tokens: the projection has a kernel of its own.
     const bool merged = ru > 0 && plan.tile_rows == 16;
-    const int64_t pblocks = merged ? (int64_t)plan.token_tiles * plan.splits * plan.col_groups : 0;
+    int64_t pblocks = merged ? (int64_t)plan.token_tiles * plan.splits * plan.col_groups : 0;
     const size_t plds = merged ? pp_lds_bytes(ru) : 0;
     a.rot_blocks = M;
     hipError_t e;
+    a.tiles = bwla_psp_tiles{};
+    // Up to some 1500 tokens the projection goes first and leaves its partial tiles, and workgroups behind the rotation's
+    // own add them up.  (Handing them over inside its launch -- acknowledged stores, an arrival count, a last workgroup that
+    // reads them back -- was the larger part of its time: 28672 columns, rank 64, 128 tokens 55.8 -> 40.1 us with the
+    // rotation, 8192 at 512 tokens 27.4 -> 21.3, 25600 at 1024 81.7 -> 76.9.  Beyond, there are few slices, the hand-over is
+    // short and the sums stand behind the rotation: 5120 at 2048 tokens 70.4, 72.2 this way; 160 x 160 136.4, 138.2.)
+    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1536;
+    if (leave) {
+        a.tiles = bwla_psp_tiles{a.partials, dT, M, ru, L->r, plan.splits, plan.col_groups, plan.tile_cols, 0};
+        const int64_t values = (int64_t)plan.token_tiles * plan.col_groups * 64 * plan.tile_cols;
+        a.tiles.blocks = (int)(values / 512 < 128 ? values / 512 : 128);
+        pblocks = a.tiles.blocks;
+        e = bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st, false);
+        if (e != hipSuccess) return e;
+    }
     if (!merged) {
         // many bf16 tokens and factors whose operand-order planes fit LDS: the looping kernel with
         // resident factors
         bool done = false;
-        e = bwla_launch_rotate_planes(L, dX, xdtype, M, dq, dscale, dqsum, dT, act_bits, st, &done);
+        e = bwla_launch_rotate_planes(L, dX, xdtype, M, dq, dscale, dqsum, dT, act_bits, st, &done, a.tiles);
         if (e != hipSuccess) return e;
-        if (done) return ru > 0 ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
+        if (done) return ru > 0 && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
     }
     const R3Shape s3 = r3_shape(L->n1, L->n2);
     const size_t split_bytes = xdtype == BWLA_X_BF16 ? bwla_split_rotation_bytes(L, plan, M) : 0;
@@ -271,7 +299,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        if (ru > 0 && !merged) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
+        if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
     if (xdtype == BWLA_X_BF16 && s3.ok) {
@@ -314,14 +342,14 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         else if (s3.at <= 12) e = launch_rotate3<12, 640>(a, grid, threads, ldsl, st, dual);
         else e = launch_rotate3<16, 512>(a, grid, threads, ldsl, st, dual);
         if (e != hipSuccess) return e;
-        if (ru > 0 && !merged) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
+        if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
     const size_t lds = plds > sh.lds_bytes ? plds : sh.lds_bytes;
     const unsigned grid = (unsigned)(M + pblocks);
     e = xdtype == BWLA_X_BF16 ? launch_rotate_f32<true>(a, grid, lds, st) : launch_rotate_f32<false>(a, grid, lds, st);
     if (e != hipSuccess) return e;
-    if (ru > 0 && !merged) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
+    if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
     return hipSuccess;
 }
 
