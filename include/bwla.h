@@ -180,7 +180,7 @@ BWLA_API bwla_status_t bwla_unpack_signs(const bwla_layer_t* layer, int8_t* d_sg
  * The scratch must be zero-filled once when it is allocated and then left to the library: its
  * first 7168 bytes are the exchange area of bwla_decode_forward's single-launch kernel (an epoch
  * that every such launch moves on, arrival counts that every launch returns to zero, partial
- * sums tagged with their epoch), then comes one arrival counter per 16-token tile, which every
+ * sums tagged with their epoch), then come 16 KiB of arrival counters of tiles, which every
  * call returns to zero; everything behind them may be overwritten by each call.  One scratch may
  * serve calls on different layers and token counts; two calls that overlap in time must not
  * share one.

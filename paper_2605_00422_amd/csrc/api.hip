@@ -68,23 +68,19 @@ bwla_status_t check_layer(const bwla_layer_t* L) {
 // aligned) the split rotation's; nothing at all when neither part is needed
 size_t rq_ws_bytes(const bwla_layer_t* L, const bwla_psp_plan& p, int64_t M) {
     const size_t split = bwla_split_rotation_bytes(L, p, M);
-    const size_t psp = bwla_psp_ws_bytes(p, M, bwla_rank_u(L));
-    const size_t body = split ? (size_t)bwla_align256(psp) + split : psp;
+    const size_t body = split ? bwla_split_start(p, bwla_rank_u(L)) + split : bwla_psp_ws_bytes(p, bwla_rank_u(L));
     return body ? (size_t)BWLA_WS_HEAD + body : 0;
 }
-// The sparse GEMM's sums and differences of the codes lie at the end of a scratch.  What a scratch keeps from call to call
-// is at its beginning, and how far that reaches depends on layer and tokens: the head, then an arrival counter per 16
-// tokens, which must stay zero.  A call on any other layer and M' tokens that uses those counters has at least 128 bytes of
-// partial sums a token behind them, so a caller who sized the scratch for it gave it 128 M' bytes more than the M' / 4 that
-// must not be written: starting 64 KiB + (bytes / 64) behind the head, this part never reaches into them.
-size_t sparse_ws_start(size_t need, uint64_t bytes) {
-    const size_t first = (size_t)(BWLA_WS_HEAD + 65536 + bytes / 64);
+// The sparse GEMM's sums and differences of the codes lie at the end of a scratch, behind everything that the rotation of
+// as many tokens uses and behind the counters, which a call on any other layer or token count relies on.
+size_t sparse_ws_start(size_t need) {
+    const size_t first = (size_t)(BWLA_WS_HEAD + BWLA_PSP_COUNTER_BYTES);
     return (size_t)bwla_align256(need > first ? need : first);
 }
 // NULL: the scratch has no room, or the call does not use it
 void* sparse_ws(const bwla_layer_t* L, int64_t M, size_t need, void* d_ws, size_t ws_bytes) {
     const uint64_t bytes = bwla_gemm_sparse_bytes(L, M);
-    if (bytes == 0 || d_ws == nullptr || ws_bytes < sparse_ws_start(need, bytes) + bytes) return nullptr;
+    if (bytes == 0 || d_ws == nullptr || ws_bytes < sparse_ws_start(need) + bytes) return nullptr;
     return (char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255);
 }
 // what bwla_rotate_quant needs for M tokens of either type
@@ -130,7 +126,8 @@ hipError_t bwla_ensure_lds(const void* fn, size_t bytes) {
 // One array per GPU the library runs on, held until the process ends.  `scratch` itself is only the
 // host-side name of the symbol: the device address is asked for once per device (with that device
 // current) and that pointer is what kernels and fills get.
-static __device__ __align__(256) unsigned char scratch[BWLA_STATIC_SCRATCH_BYTES];
+constexpr uint64_t STATIC_SCRATCH_BYTES = BWLA_STATIC_SCRATCH_BYTES + BWLA_PSP_COUNTER_BYTES;
+static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -265,14 +262,18 @@ bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_t M, size
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (M <= 0) return BWLA_ERR_SHAPE;
-    // for fewer tokens a call can need more (more slices); from 2048 tokens on there are eight and it only grows
+    // For fewer tokens a call can need more (more slices).  From 2048 tokens on there are eight and it only grows, up to
+    // the last number of tokens that is split.
     size_t need = rq_need(layer, M);
+    const int64_t last = (int64_t)BWLA_PSP_COUNTERS / 2 * 64;      // (of two column groups; of one: twice that)
+    for (const int64_t m : {last, 2 * last})
+        if (m < M && rq_need(layer, m) > need) need = rq_need(layer, m);
     for (int64_t m = M < 2048 ? M - 1 : 2048; m > 0; --m) {
         const size_t n = rq_need(layer, m);
         if (n > need) need = n;
     }
     const uint64_t sparse = bwla_gemm_sparse_bytes(layer, M);
-    *bytes = sparse == 0 ? need : sparse_ws_start(need, sparse) + (size_t)bwla_align256(sparse);
+    *bytes = sparse == 0 ? need : sparse_ws_start(need) + (size_t)bwla_align256(sparse);
     return BWLA_OK;
 }
 
@@ -365,7 +366,9 @@ bwla_status_t bwla_decode_forward_static(const bwla_layer_t* layer, const void* 
     if (M <= 0 || M > (int64_t)1 << 24) return BWLA_ERR_SHAPE;
     const bwla_psp_plan plan = bwla_psp_plan_of(layer, M, xdtype);
     const size_t need = rq_ws_bytes(layer, plan, M);
-    if (need > BWLA_STATIC_SCRATCH_BYTES) return BWLA_ERR_BUFSIZE;
+    // (of the counters only as many count as the tokens may use)
+    const uint64_t counters = bwla_align256((uint64_t)((M + 15) / 16) * sizeof(int));
+    if (need > 0 && need + counters > STATIC_SCRATCH_BYTES) return BWLA_ERR_BUFSIZE;
     if (!d_X || !d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
     if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
     if (xdtype != BWLA_X_F32 && xdtype != BWLA_X_BF16) return BWLA_ERR_UNSUPPORTED;
@@ -377,12 +380,12 @@ bwla_status_t bwla_decode_forward_static(const bwla_layer_t* layer, const void* 
     if (need > 0) {
         // the arrival counts of the scratch must read zero; a kernel clears them (a memset node would
         // not replay reliably from a captured graph)
-        const int words = (int)(bwla_psp_counter_bytes(M) / sizeof(uint32_t));
+        const int words = (int)(counters / sizeof(uint32_t));
         clear_counts_kernel<<<dim3((unsigned)((words + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
             (uint32_t*)ws, (int)(BWLA_WS_HEAD / sizeof(uint32_t)), words);
         if (hipGetLastError() != hipSuccess) return BWLA_ERR_HIP;
     }
-    return bwla_decode_forward(layer, d_X, xdtype, M, d_q, d_scale, d_qsum, d_T, ws, BWLA_STATIC_SCRATCH_BYTES, d_Y,
+    return bwla_decode_forward(layer, d_X, xdtype, M, d_q, d_scale, d_qsum, d_T, ws, STATIC_SCRATCH_BYTES, d_Y,
                                d_acc, stream);
 }
 

@@ -72,8 +72,11 @@ bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M);
 // call on a scratch agrees on it and no other kernel writes there.  The counters and partial sums
 // of the other kernels follow behind it.
 constexpr uint64_t BWLA_WS_HEAD = 1024 + 8 * 96 * 8;
-// behind the head: one arrival counter per 16 tokens (whatever the plan), padded to 256 bytes
-inline uint64_t bwla_psp_counter_bytes(int64_t M) { return bwla_align256((uint64_t)((M + 15) / 16) * sizeof(int)); }
+// Behind the head: the arrival counters of the projection's tiles.  They must read zero when a call starts, so they too
+// lie at the same place and reach equally far for every layer and token count: no call's partial sums or rotated values
+// come to lie where another's counters are.  A projection of more tiles than that is not split.
+constexpr int BWLA_PSP_COUNTERS = 4096;
+constexpr uint64_t BWLA_PSP_COUNTER_BYTES = BWLA_PSP_COUNTERS * sizeof(int);
 // columns that a layer's mode adds to V and T behind the PSP columns
 inline int bwla_extra_cols(int mode) { return ((mode & BWLA_MODE_ASYM_ACT) ? 2 : 0) + ((mode & BWLA_MODE_ROW_SHIFT) ? 1 : 0); }
 // columns of U = rank of the projection T = X U
@@ -81,10 +84,15 @@ inline int bwla_rank_u(const bwla_layer_t* L) { return L->r - bwla_extra_cols(L-
 inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
     return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), bwla_rotate_planes_serves(L, xdtype, M));
 }
-inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int64_t M, int r) {
+inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int r) {
     if (r <= 0 || p.splits <= 1) return 0;
-    return (size_t)(bwla_psp_counter_bytes(M) + (uint64_t)p.token_tiles * p.col_groups * p.splits *
+    return (size_t)(BWLA_PSP_COUNTER_BYTES + (uint64_t)p.token_tiles * p.col_groups * p.splits *
                                                     p.tile_rows * p.tile_cols * sizeof(float));
+}
+// where the rotation's own part begins
+inline size_t bwla_split_start(const bwla_psp_plan& p, int r) {
+    const size_t psp = bwla_psp_ws_bytes(p, r);
+    return (size_t)bwla_align256(psp > BWLA_PSP_COUNTER_BYTES ? psp : BWLA_PSP_COUNTER_BYTES);
 }
 // Bytes the rotation wants behind the projection's scratch when it is split over several
 // workgroups per token and a second launch (few bf16 tokens, R1 too large for LDS); else 0.

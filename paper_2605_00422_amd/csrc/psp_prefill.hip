@@ -295,7 +295,7 @@ hipError_t bwla_launch_psp_prefill(const bwla_layer_t* L, const void* dX, int xd
     a.Ut = (const __half*)(blob + L->off_U);
     a.T = dT;
     a.counters = (int*)dws;
-    a.partials = dws ? (float*)((char*)dws + bwla_psp_counter_bytes(M)) : nullptr;
+    a.partials = dws ? (float*)((char*)dws + BWLA_PSP_COUNTER_BYTES) : nullptr;
     a.S = plan.splits; a.JG = plan.col_groups; a.kslice = plan.k_per_split;
     const int blocks = plan.token_tiles * plan.col_groups * 8 * ((plan.splits + 7) / 8);
     const bool bf = xdtype == BWLA_X_BF16;

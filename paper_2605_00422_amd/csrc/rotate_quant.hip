@@ -212,7 +212,7 @@ bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes) {
     int64_t S = 8 * ((cus + 8 * units - 1) / (8 * units));
     const int64_t smax = K / 512 > 1 ? K / 512 : 1;
     if (S > smax) S = smax;
-    if (S < 1) S = 1;
+    if (S < 1 || units > BWLA_PSP_COUNTERS) S = 1;
     const int64_t per = (K + S - 1) / S;
     p.k_per_split = (int)(((per + 127) / 128) * 128);
     p.splits = (int)((K + p.k_per_split - 1) / p.k_per_split);
@@ -235,7 +235,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     a.R1p = (const uint16_t*)(blob + L->off_R1p); a.R2p = (const uint16_t*)(blob + L->off_R2p);
     a.q = dq; a.scale = dscale; a.qsum = dqsum; a.T = dT;
     a.counters = (int*)dws;
-    a.partials = dws ? (float*)((char*)dws + bwla_psp_counter_bytes(M)) : nullptr;
+    a.partials = dws ? (float*)((char*)dws + BWLA_PSP_COUNTER_BYTES) : nullptr;
     a.S = plan.splits;
     a.JG = plan.tile_rows == 16 ? plan.col_groups : 1;
     a.xs = nullptr; a.pmax = nullptr;
@@ -274,7 +274,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     if (split_bytes > 0 && dws != nullptr) {
         // few tokens, R1 too large for LDS: several workgroups per token, then a launch that quantizes
         const RsShape rs = rs_shape(s3);
-        a.xs = (float*)((char*)dws + bwla_align256(bwla_psp_ws_bytes(plan, M, ru)));
+        a.xs = (float*)((char*)dws + bwla_split_start(plan, ru));
         a.pmax = a.xs + M * L->K;
         float* zcs = a.pmax + 2 * M * rs.E;            // per token: what the stored codes have to lose
         a.rot_blocks = M * rs.G;

@@ -159,6 +159,7 @@ def test_one_scratch_for_calls_of_several_sizes():
     for M in (700, 4096, 700, 4096):
         act = B.Activations(layer, M)
         act.ws, act.ws_bytes = big.ws, big.ws_bytes
+        act.T.fill_(float("nan"))
         Y = B.decode_forward(layer, X[:M], act, torch.full((M, N), float("nan"), device=DEV))
         torch.cuda.synchronize()
         assert torch.equal(Y, ref[M])
