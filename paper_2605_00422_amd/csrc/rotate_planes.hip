@@ -19,7 +19,11 @@
 // their products with R1 into all output tiles (3 n1/16 MFMAs) -- Z is never whole anywhere.
 // Wavefront w owns the 16 columns d of strip w.  Tokens are pipelined through registers: while the
 // wavefronts work on token j out of LDS, token j + 1 is in flight from HBM into registers, and is
-// converted and written to LDS between the two barriers that every token costs.  G groups of
+// converted and written to LDS between the two barriers that every token costs.  The codes go through
+// LDS too, beside the token rows where there is room, or else in their place at the cost of two more
+// barriers, and leave in whole lines: a wavefront's own are 16 rows of 16 bytes, and every such piece
+// took 4.4 cycles of the CU (9000 of 34000 a token; 4096 tokens of 224 x 128 241 -> 221 us, 160 x 160
+// 218 -> 184, of 128 x 64 50 -> 43, of 64 x 64 22.5 -> 20.2).  G groups of
 // n2 / 16 wavefronts work on G tokens at a time over the one copy of R1 (small factors would
 // otherwise leave most of a CU's SIMDs with a single wavefront).
 #include "bwla_internal.h"
@@ -52,13 +56,18 @@ struct RpShape {
     static constexpr int R1_BYTES = STREAM ? 2 * CHUNK_BYTES : CH2 * CHUNK_BYTES;
     static constexpr int XT_BYTES = N1 * PITCH;
     static constexpr int RED_WORDS = 64;                // per group: [0,16) maxima, [16,32) minima, [32,48) token maxima, [48,64) code sums
-    static constexpr size_t LDS = (size_t)R1_BYTES + (size_t)G * XT_BYTES + (size_t)G * RED_WORDS * 4;
+    static constexpr int CPITCH = N2 + 16;              // bytes per row of codes in LDS, padded: no bank conflicts
+    static constexpr int CB_BYTES = N1 * CPITCH;
+    static constexpr int CITEMS = K / 16, NC = (CITEMS + TG - 1) / TG;      // 16-byte granules of codes per token, per thread
+    // room for the codes beside the token rows, or else in their place
+    static constexpr size_t LDS_OWN = (size_t)R1_BYTES + (size_t)G * (XT_BYTES + CB_BYTES) + (size_t)G * RED_WORDS * 4;
+    static constexpr bool OWN = LDS_OWN <= RQ_LDS_LIMIT;
+    static constexpr size_t LDS = OWN ? LDS_OWN : LDS_OWN - (size_t)G * CB_BYTES;
 };
 
 template <int N1, int N2, int G, bool STREAM = false>
 __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArgs a) {
     using S = RpShape<N1, N2, G, STREAM>;
-    static_assert(!STREAM || G == 1, "streamed R1 terms: one token group");
     constexpr int K = S::K, AT = S::AT, K1 = S::K1, CH2 = S::CH2, STRIPS = S::STRIPS, GPR = S::GPR, PITCH = S::PITCH;
     constexpr int TG = S::TG, NI = S::NI, ITEMS = S::ITEMS;
     extern __shared__ __align__(16) char lds[];
@@ -71,7 +80,8 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
     const int tid = (int)threadIdx.x - grp * TG, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     char* r1 = lds;
     char* xt = lds + S::R1_BYTES + grp * S::XT_BYTES;
-    float* red = reinterpret_cast<float*>(lds + S::R1_BYTES + G * S::XT_BYTES) + grp * S::RED_WORDS;
+    char* cb = S::OWN ? lds + S::R1_BYTES + G * S::XT_BYTES + grp * S::CB_BYTES : xt;
+    float* red = reinterpret_cast<float*>(lds + S::R1_BYTES + G * (S::XT_BYTES + (S::OWN ? S::CB_BYTES : 0))) + grp * S::RED_WORDS;
     int* redi = reinterpret_cast<int*>(red) + 48;
 
     // ---- R1 terms: global -> LDS asynchronously, one KiB per wavefront-wide request.  Resident: all
@@ -106,6 +116,23 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
     const int64_t t0 = (int64_t)blockIdx.x * G + grp;
     const int rounds = (int)((a.M + tstep - 1) / tstep);
     v4i xpre[NI];
+    auto request1 = [&](int64_t t, int e) {
+        const uint16_t* xrow = a.X + (t < a.M ? t : a.M - 1) * K;
+        const int it = tid + e * TG;
+        xpre[e] = *reinterpret_cast<const v4i*>(xrow + (it < ITEMS ? it : 0) * 8);
+    };
+    // the codes of token t from LDS to memory, in whole lines
+    auto write_codes = [&](int64_t t) {
+        int8_t* qrow = a.q + t * K;
+#pragma unroll
+        for (int e = 0; e < S::NC; ++e) {
+            const int it = tid + e * TG;
+            if (it < S::CITEMS) {
+                const int row = it / (N2 / 16), g = it - row * (N2 / 16);
+                *reinterpret_cast<v4i*>(qrow + it * 16) = *reinterpret_cast<const v4i*>(cb + row * S::CPITCH + g * 16);
+            }
+        }
+    };
     auto request = [&](int64_t t) {
         const uint16_t* xrow = a.X + (t < a.M ? t : a.M - 1) * K;
 #pragma unroll
@@ -163,7 +190,7 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
     for (int w = 0; w < STRIPS; ++w) xmax = fmaxf(xmax, red[32 + w]);
     float sx = scale_of(xmax);
     land(sx);
-    request(t0 + tstep);
+    if (!STREAM) request(t0 + tstep);
     __builtin_amdgcn_s_waitcnt(0);                      // my share of the R1 terms has landed (and token 1)
     bwla_lds_barrier();
 
@@ -171,9 +198,11 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
         const int64_t t = t0 + (int64_t)j * tstep;
         const bool live = t < a.M;
         // ================================================================ the two stages, step by step
-        // Every LDS operand is requested one step before the MFMAs that use it (a step: the four
-        // MFMAs of one 32-deep piece of stage 1, or the three of one output tile of stage 2), so
-        // that a wavefront does not stand still for an LDS round trip at every step.
+        // LDS operands are requested two steps (stage 1) or one (stage 2) before the MFMAs that use them (a step: the
+        // four MFMAs of one 32-deep piece of stage 1, or the three of one output tile of stage 2), and nothing moves over
+        // a step's end: left to itself the scheduler puts the reads of two steps together and waits for them at
+        // once (224 x 128 221 -> 205 us at 4096 tokens).
+        if (S::OWN && j > 0 && t - tstep < a.M) write_codes(t - tstep);
         v4f y[AT];
 #pragma unroll
         for (int tc = 0; tc < AT; ++tc) y[tc] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -186,31 +215,39 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
             else
                 return *reinterpret_cast<const v4i*>(r1 + ((ch * 2 + term) * AT + tc) * 1024 + lane * 16);
         };
-        v4i na0 = ld_a(0, 0, 0), na1 = ld_a(0, 0, 1);
 #pragma unroll
         for (int ch = 0; ch < CH2; ++ch) {
             v4f z0 = v4f{0.f, 0.f, 0.f, 0.f}, z1 = z0;
-            v4i nbh = v4i{0, 0, 0, 0}, nbl = nbh;
+            v4i qa0[K1], qa1[K1], qb[2][AT];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) { qa0[kb] = ld_a(ch, kb, 0); qa1[kb] = ld_a(ch, kb, 1); }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kb = 0; kb < K1; ++kb) {
-                const v8h_r a0 = __builtin_bit_cast(v8h_r, na0), a1 = __builtin_bit_cast(v8h_r, na1);
-                if (kb + 1 < K1) { na0 = ld_a(ch, kb + 1, 0); na1 = ld_a(ch, kb + 1, 1); }
-                else if (!STREAM) { nbh = ld_b(ch, 0, 0); nbl = ld_b(ch, 1, 0); }
+                const v8h_r a0 = __builtin_bit_cast(v8h_r, qa0[kb]), a1 = __builtin_bit_cast(v8h_r, qa1[kb]);
+                if (kb + 2 < K1) { qa0[kb + 2] = ld_a(ch, kb + 2, 0); qa1[kb + 2] = ld_a(ch, kb + 2, 1); }
+                else if (!STREAM && kb + 2 == K1) { qb[0][0] = ld_b(ch, 0, 0); qb[1][0] = ld_b(ch, 1, 0); }
                 z0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bl[kb], z0, 0, 0, 0);      // small term first
                 z1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bl[kb], z1, 0, 0, 0);
                 z0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bh[kb], z0, 0, 0, 0);
                 z1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bh[kb], z1, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (STREAM) {
+                // this step's R1 terms have landed, everybody's share; the other buffer is free (all are past the
+                // step before): the next step's terms go there while this one is worked on, and a part of the
+                // next token into registers.  (The first step's terms were waited for with the token.)
+                if (ch > 0) __builtin_amdgcn_s_waitcnt(0);
+                bwla_lds_barrier();
+                if (j + 1 < rounds || ch + 1 < CH2) request_chunk(j * CH2 + ch + 1);
+                if (j + 1 < rounds) {
+#pragma unroll
+                    for (int e = ch * NI / CH2; e < (ch + 1) * NI / CH2; ++e) request1(t + tstep, e);
+                }
+                qb[0][0] = ld_b(ch, 0, 0); qb[1][0] = ld_b(ch, 1, 0);
             }
             // lane (li, lg) holds Z[a = 32 ch + 4 lg + v (z0), 32 ch + 16 + 4 lg + v (z1)][d = li]: the eight
             // contraction positions of an A operand, in the order the R1 terms were stored in.
-            if constexpr (STREAM) {
-                // this step's R1 terms have landed, everybody's share; the other buffer is free (all are
-                // past the step before): the next step's terms go there while this one is worked on
-                __builtin_amdgcn_s_waitcnt(0);
-                bwla_lds_barrier();
-                if (j + 1 < rounds || ch + 1 < CH2) request_chunk(j * CH2 + ch + 1);
-                nbh = ld_b(ch, 0, 0); nbl = ld_b(ch, 1, 0);
-            }
             v8h_r ah, al;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -219,14 +256,15 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
                 ah[e] = h;
                 al[e] = (_Float16)__builtin_fmaf((float)h, -1.0f, f);
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int tc = 0; tc < AT; ++tc) {
-                const v8h_r ch_ = __builtin_bit_cast(v8h_r, nbh), cl_ = __builtin_bit_cast(v8h_r, nbl);
-                if (tc + 1 < AT) { nbh = ld_b(ch, 0, tc + 1); nbl = ld_b(ch, 1, tc + 1); }
-                else if (ch + 1 < CH2) { na0 = ld_a(ch + 1, 0, 0); na1 = ld_a(ch + 1, 0, 1); }
+                const v8h_r ch_ = __builtin_bit_cast(v8h_r, qb[0][tc]), cl_ = __builtin_bit_cast(v8h_r, qb[1][tc]);
+                if (tc + 1 < AT) { qb[0][tc + 1] = ld_b(ch, 0, tc + 1); qb[1][tc + 1] = ld_b(ch, 1, tc + 1); }
                 y[tc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, ch_, y[tc], 0, 0, 0);
                 y[tc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, cl_, y[tc], 0, 0, 0);
                 y[tc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, ch_, y[tc], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         // ================================================================ the token's range; the next token's largest value
@@ -260,32 +298,47 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
             xmax = fmaxf(xmax, red[32 + w]);
         }
         const QuantPlan qp = quant_plan(hi, lo, a.qmax, a.asym != 0);
-        // ================================================================ codes, straight to global memory
+        // ================================================================ codes, to LDS
         // lane holds Yt[d = 16 strip + 4 lg + v][c = 16 tc + li]: four consecutive k = c n2 + d.
         // y * inv + (1.5 * 2^23 + zero point) rounds once, to an integer (ties to even) in the low
         // mantissa bits; clamped as a float, its low byte is the code.
         const float inv = qp.inv * yun, addc = 12582912.0f + qp.zc;
         const float cmin = 12582912.0f + qp.cmin, cmax = 12582912.0f + qp.cmax;
         int lsum = 0;
-        int8_t* qrow = a.q + (live ? t : 0) * K;
 #pragma unroll
         for (int tc = 0; tc < AT; ++tc) {
-            uint32_t cb[4];
+            uint32_t c4[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                cb[v] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(y[tc][v], inv, addc), cmin, cmax));
-            const uint32_t wlo = __builtin_amdgcn_perm(cb[1], cb[0], 0x0c0c0400u);     // bytes: cb0.b0, cb1.b0, 0, 0
-            const uint32_t whi = __builtin_amdgcn_perm(cb[3], cb[2], 0x04000c0cu);     // bytes: 0, 0, cb2.b0, cb3.b0
+                c4[v] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(y[tc][v], inv, addc), cmin, cmax));
+            const uint32_t wlo = __builtin_amdgcn_perm(c4[1], c4[0], 0x0c0c0400u);     // bytes: cb0.b0, cb1.b0, 0, 0
+            const uint32_t whi = __builtin_amdgcn_perm(c4[3], c4[2], 0x04000c0cu);     // bytes: 0, 0, cb2.b0, cb3.b0
             const uint32_t word = wlo | whi;
-            if (live) *reinterpret_cast<uint32_t*>(qrow + (16 * tc + li) * N2 + 16 * wave + 4 * lg) = word;
+            *reinterpret_cast<uint32_t*>(cb + (16 * tc + li) * S::CPITCH + 16 * wave + 4 * lg) = word;
             lsum = __builtin_amdgcn_sdot4((int)word, 0x01010101, lsum, false);
         }
         lsum = dl_wave_sum(lsum);
         if (lane == 0) redi[wave] = lsum;
         // ================================================================ next token into LDS, the one after into flight
+        v4i cq[S::NC];
+        if constexpr (!S::OWN) {                        // the codes lie where the next token goes: out first
+            bwla_lds_barrier();
+#pragma unroll
+            for (int e = 0; e < S::NC; ++e) {
+                const int it = tid + e * TG, row = it / (N2 / 16), g = it - row * (N2 / 16);
+                cq[e] = *reinterpret_cast<const v4i*>(cb + (it < S::CITEMS ? row * S::CPITCH + g * 16 : 0));
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);         // lgkmcnt(0)
+            bwla_lds_barrier();
+            if (live) {
+#pragma unroll
+                for (int e = 0; e < S::NC; ++e)
+                    if (tid + e * TG < S::CITEMS) *reinterpret_cast<v4i*>(a.q + t * K + (tid + e * TG) * 16) = cq[e];
+            }
+        }
         sx = scale_of(xmax);
         land(sx);
-        if (j + 2 < rounds) request(t + 2 * tstep);
+        if (!STREAM && j + 2 < rounds) request(t + 2 * tstep);
         bwla_lds_barrier();
         if (wave == 0 && live) {
             int tot = 0;
@@ -299,6 +352,8 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
             }
         }
     }
+    const int64_t tl = t0 + (int64_t)(rounds - 1) * tstep;
+    if (S::OWN && tl < a.M) write_codes(tl);
 }
 
 template <int N1, int N2, int G, bool STREAM = false>
