@@ -15,6 +15,7 @@
 //                               buffered, one barrier per 128 columns
 #include "bwla_internal.h"
 #include "gemm_tiles.h"
+#include "gemm_epilogue.h"
 
 namespace {
 
@@ -474,185 +475,62 @@ __device__ __forceinline__ void gd_body(
         for (int nt = 0; nt < NTL; ++nt) asm volatile("" : "+v"(w2.w[nt]), "+v"(w3.w[nt]));
     }
 
-    if constexpr (WK > 1) {
-        // every wavefront has drained its copies: the tiles are dead, LDS carries the partial sums
-        __syncthreads();
-        int* red = reinterpret_cast<int*>(smem);
-        constexpr int PER_WAVE = MT * NTL * 16 * 64;
-        if (wk > 0) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        red[(wk - 1) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane] = acc[mt][nt][v];
-        }
-        __syncthreads();
-        if (wk > 0) return;
-#pragma unroll
-        for (int w = 1; w < WK; ++w)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NTL; ++nt)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        acc[mt][nt][v] += red[(w - 1) * PER_WAVE + ((mt * NTL + nt) * 16 + v) * 64 + lane];
-    }
-
+    // (registers enough that a SIMD takes no more wavefronts than its share of the CU's workgroups: with room for one more,
+    // two workgroups of two wavefronts come to lie on the same two SIMDs; 64 x 64 in two, 835 -> 1120 cycles a slice)
+    if constexpr (WK == 2) asm volatile("" ::: "v255");
+    if constexpr (WN == 2) asm volatile("" ::: "v176");
+    // ---- epilogue (gemm_epilogue.h)
+    const EpArgs ep{scale, qsum, alpha, V, T, r, Y, M, N, acc_out, H};
+    EpRows<64 * WK * WN> rows_t(ep, tid);
+    rows_t.request(m_base);
     if constexpr (A4) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NTL; ++nt) acc[mt][nt] = acc[mt][nt] >> 4;    // exact: every operand was 16 x code
     }
-    // ---- epilogue.  Accumulator element v of lane (l32, lg): row 8*(v/4) + 4*lg + v%4, column l32.
-    // Low-rank term on fp16 MFMA 32x32x16: V is stored in fp16 and is an operand as it stands; a token's
-    // row of T is scaled by a power of two 2^k (largest entry near 2^13) and split into two fp16 terms,
-    // T 2^k = hi + lo to 2^-22: two products per 16 ranks and channel tile.  The main term
-    // scale_t alpha_n (2 acc - qsum_t) is formed first, times 2^k of its row, in the accumulator's
-    // registers, the MFMAs add the low-rank products onto it, and 2^-k is applied at the store (powers of
-    // two: exact).  What the epilogue waits for is memory, not arithmetic: all its loads -- scales and code
-    // sums of the rows, the tokens' rows of T, the channels' rows of V, up to 64 ranks at a time -- are
-    // requested in one go before the first use (they were ten dependent round trips per tile when T and V
-    // were fetched step by step: 12 % of the launch at 8192 x 8192 and 4096 tokens).
-    typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-    constexpr int JC = (NB == 2 || NTL == 5) ? 2 : 4;                          // 16-rank steps per chunk (fewer where registers are short)
-    const int JT = (r + 15) >> 4, rp = JT * 16;
-    int ncol[NTL];
-    float al[NTL];
+    char* const t_lds = smem + (WK > 1 ? WK * MT * NTL : WN) * 4096;
+    if constexpr (WK > 1) {
+        // the wavefronts' partial sums meet in LDS, and each takes some tiles of one row of tiles
+        constexpr int PART = MT * NTL * 4096;
+        constexpr int PER_MT = WK / MT, NTW = (NTL + PER_MT - 1) / PER_MT;
+        static_assert(WK % MT == 0 && NTL % NTW == 0, "tiles are dealt out evenly");
+        const int mt = wk / PER_MT, nt0 = (wk % PER_MT) * NTW;
+        char* mine = smem + (mt * NTL + nt0) * 4096;
+        const bool idle = m_base + mt * 32 >= M || nt0 >= NTL;
+        Epilogue<1, NTW, GATED> fin(ep, m_base, mt, n_base + nt0 * 32, lane, mine, t_lds);
+        if (!idle) fin.request();
+        __syncthreads();                                         // every wavefront has drained its copies: the rings are dead
 #pragma unroll
-    for (int nt = 0; nt < NTL; ++nt) {
-        const int n = n_base + nt * 32 + l32;
-        ncol[nt] = n < N ? n : N - 1;
-        al[nt] = __half2float(alpha[ncol[nt]]);
-    }
-    // my token's entries 16 kk + 8 lg .. + 7 of T (zero past the rank)
-    auto load_t = [&](float (&tv)[8], int tmr, int kk) {
-        const int j0 = kk * 16 + 8 * lg;
-        const float* tp = T + (int64_t)tmr * r + j0;
-        if ((r & 3) == 0) {
-            // whole groups of four are inside or outside the row; clamp the address, zero the value
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 t0 = *reinterpret_cast<const float4*>(j0 < r ? tp : T);
-            const float4 t1 = *reinterpret_cast<const float4*>(j0 + 4 < r ? tp + 4 : T);
-            const float4 u0 = j0 < r ? t0 : z, u1 = j0 + 4 < r ? t1 : z;
-            tv[0] = u0.x; tv[1] = u0.y; tv[2] = u0.z; tv[3] = u0.w;
-            tv[4] = u1.x; tv[5] = u1.y; tv[6] = u1.z; tv[7] = u1.w;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) tv[i] = j0 + i < r ? tp[i] : 0.0f;
-        }
-    };
-    uint4 vfr[JC][NTL];                                          // V fragments of the current chunk of ranks
-    auto load_v = [&](int c0) {
-#pragma unroll
-        for (int j = 0; j < JC; ++j) {
-            const int kk = c0 + j < JT ? c0 + j : (JT > 0 ? JT - 1 : 0);
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int nt = 0; nt < NTL; ++nt)
-                vfr[j][nt] = JT > 0 ? *reinterpret_cast<const uint4*>(V + (int64_t)ncol[nt] * rp + kk * 16 + 8 * lg)
-                                    : make_uint4(0, 0, 0, 0);
-        }
-    };
-    load_v(0);
-    const bool one_chunk = JT <= JC;                             // then V stays in registers for both row tiles
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int mrow0 = m_base + mt * 32;
-        if (mrow0 >= M) continue;
-        int tmr = mrow0 + l32;
-        if (tmr > M - 1) tmr = M - 1;
-        // the row's largest magnitude, over all of its ranks
-        float tmax = 0.0f;
-        for (int c0 = 0; c0 < JT; c0 += JC) {
-            float tv[JC][8];
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<v4i*>(smem + wk * PART + (m * NTL + nt) * 4096 + g * 1024 + lane * 16) =
+                        v4i{acc[m][nt][4 * g], acc[m][nt][4 * g + 1], acc[m][nt][4 * g + 2], acc[m][nt][4 * g + 3]};
+        rows_t.put(t_lds);
+        __syncthreads();
+        if (idle) return;
+        v16i u[1][NTW];
 #pragma unroll
-            for (int j = 0; j < JC; ++j) load_t(tv[j], tmr, c0 + j < JT ? c0 + j : JT - 1);
+        for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
-            for (int j = 0; j < JC; ++j)
+            for (int g = 0; g < 4; ++g) {
+                v4i x = *reinterpret_cast<const v4i*>(mine + nt * 4096 + g * 1024 + lane * 16);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) tmax = fmaxf(tmax, fabsf(tv[j][i]));
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));            // the other half of my token's row
-        int kexp = 0;
-        if (tmax > 0.0f && tmax < 3.0e38f) kexp = 13 - ilogbf(tmax);
-        kexp = kexp > 60 ? 60 : (kexp < -60 ? -60 : kexp);
-        float sc[16];
-        int qs[16];
+                for (int w = 1; w < WK; ++w) x += *reinterpret_cast<const v4i*>(mine + w * PART + nt * 4096 + g * 1024 + lane * 16);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            int m = mrow0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-            if (m > M - 1) m = M - 1;
-            sc[v] = scale[m];
-            qs[v] = qsum[m];
-        }
-        // the main term replaces acc in place (as float bits), times 2^k of its row:
-        // result row 8 (v / 4) + 4 lg + v % 4 belongs to the token of lane (that row, any lg)
-        int krow[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            krow[v] = __shfl(kexp, 8 * (v >> 2) + 4 * lg + (v & 3), 64);
-            const float up = __int_as_float((127 + krow[v]) << 23);
-            const int m = mrow0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-#pragma unroll
-            for (int nt = 0; nt < NTL; ++nt) {
-                const int a = 2 * acc[mt][nt][v] - qs[v];
-                if constexpr (!GATED) {
-                    const int n = n_base + nt * 32 + l32;
-                    if (acc_out && m < M && n < N) acc_out[(int64_t)m * N + n] = a;
-                }
-                acc[mt][nt][v] = __float_as_int(sc[v] * al[nt] * (float)a * up);
+                for (int i = 0; i < 4; ++i) u[0][nt][4 * g + i] = x[i];
             }
-        }
-        for (int c0 = 0; c0 < JT; c0 += JC) {
-            if (c0 > 0 || (mt > 0 && !one_chunk)) load_v(c0);
-            float tv[JC][8];
-#pragma unroll
-            for (int j = 0; j < JC; ++j) load_t(tv[j], tmr, c0 + j < JT ? c0 + j : JT - 1);   // (from the caches)
-#pragma unroll
-            for (int j = 0; j < JC; ++j) {
-                if (c0 + j < JT) {
-                    v8h thi, tlo;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float x = ldexpf(tv[j][i], kexp);
-                        const _Float16 h = (_Float16)x;
-                        thi[i] = h;
-                        tlo[i] = (_Float16)(x - (float)h);
-                    }
-#pragma unroll
-                    for (int nt = 0; nt < NTL; ++nt) {
-                        const v8h vb = __builtin_bit_cast(v8h, vfr[j][nt]);
-                        v16f y = __builtin_bit_cast(v16f, acc[mt][nt]);
-                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(tlo, vb, y, 0, 0, 0);
-                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(thi, vb, y, 0, 0, 0);
-                        acc[mt][nt] = __builtin_bit_cast(v16i, y);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float down = __int_as_float((127 - krow[v]) << 23);
-            const int m = mrow0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-#pragma unroll
-            for (int nt = 0; nt < NTL; ++nt) {
-                const int n = n_base + nt * 32 + l32;
-                const float yv = __int_as_float(acc[mt][nt][v]) * down;
-                if constexpr (GATED) {
-                    // lane pairs (n even, n + 1) hold (gate, up) of one token; the even lane stores
-                    const float up = __shfl_xor(yv, 1, 64);
-                    if (m < M && (l32 & 1) == 0 && n + 1 < N) {
-                        const float h = yv / (1.0f + __expf(-yv)) * up;
-                        H[(int64_t)m * (N >> 1) + (n >> 1)] = __builtin_bit_cast(uint16_t, (__bf16)h);
-                    }
-                } else if (m < M && n < N) {
-                    Y[(int64_t)m * N + n] = yv;
-                }
-            }
-        }
+        fin.finish(u);
+    } else {
+        Epilogue<MT, NTL, GATED> fin(ep, m_base, 0, n_base, lane, smem + wn * 4096, t_lds);
+        fin.request();
+        __syncthreads();                                         // everybody has read the last of the ring
+        rows_t.put(t_lds);
+        __syncthreads();
+        fin.finish(acc);
     }
 }
 
@@ -674,8 +552,7 @@ __global__ __launch_bounds__(64 * WK, 1) void gemm_prefill_direct_kernel(GD_PARA
 // that changes little (25600 -> 5120 at 2048 tokens, 64 x 640: 196 us with private rings, 192; the matrix cores are busy
 // for 60 and 58 % of the launch).  What pays is the LDS it frees: two or more workgroups a CU, which hide each other's
 // barriers, prologues and epilogues (28672 -> 8192 at 4096 tokens 733 -> 680 us, 4096 -> 22016 at 2048 259 -> 207).
-// Held to the 256 registers that two workgroups a CU leave, 64 x 384 spills 12 (22 with nibble codes, none gated) and
-// 64 x 512 21 (54, 8), all of them outside the loop.
+// Held to the 256 registers that two workgroups a CU leave, only 64 x 512 with nibble codes spills (28, outside the loop).
 template <int NTL, int NB, int WN, bool GATED, bool A4>
 __global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
     gd_body<NTL, 1, NB, WN, GATED, A4>(GD_ARGS);
@@ -690,9 +567,9 @@ hipError_t launch_streaming(const bwla_layer_t* L, const int8_t* dq, const float
     constexpr int BM = GD_ROWS, BN = WN * NTL * 32;
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
-    const size_t lds = (size_t)WK * NB * GD_TILE;
-    static_assert((size_t)(WK - 1) * GD_MT * NTL * 16 * 64 * 4 <= (size_t)WK * NB * GD_TILE,
-                  "the partial sums must fit into the tile rings");
+    // the rings, then the epilogue's tiles
+    const size_t ring = (size_t)WK * NB * GD_TILE, tail = (size_t)(WK > 1 ? WK * GD_MT * NTL : WN) * 4096 + ep_rows_bytes(L->r);
+    const size_t lds = ring > tail ? ring : tail;
     auto launch = [&](auto kern) -> hipError_t {
         hipError_t e = bwla_ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
