@@ -36,13 +36,13 @@ struct EpArgs {
 };
 constexpr int EP_JC = 4;                                         // steps of 16 ranks at a time
 // bytes of LDS that EpRows fills
-inline __host__ __device__ size_t ep_rows_bytes(int r) { return (size_t)((r + 15) / 16) * 4096 + 768; }
+inline __host__ __device__ size_t ep_rows_bytes(int tokens, int r) { return (size_t)tokens * ((r + 15) / 16 * 64 + 12); }
 
-// The rows of T of a workgroup's 64 tokens as MFMA operands in LDS: [token / 32][16 ranks][hi, lo][lane][8] fp16, and behind
+// The rows of T of a workgroup's tokens as MFMA operands in LDS: [token / 32][16 ranks][hi, lo][lane][8] fp16, and behind
 // them, for each token, 2^k scale, 2^-k and the code sum.
-template <int THREADS>
+template <int THREADS, int TOKENS>
 struct EpRows {
-    static constexpr int TPT = THREADS / 64, MAXP = 4 * (BWLA_MAX_RANK / 16) / TPT;     // threads a token; 4-rank pieces a thread
+    static constexpr int TPT = THREADS / TOKENS, MAXP = 4 * (BWLA_MAX_RANK / 16) / TPT;     // threads a token; 4-rank pieces a thread
     const EpArgs& e;
     const int tid, token, part, JT;
     float x[MAXP][4], sc;
@@ -52,7 +52,7 @@ struct EpRows {
     __device__ __forceinline__ void request(int m_base) {
         const int t = m_base + token < e.M ? m_base + token : e.M - 1;
         sc = e.scale[t];
-        qs = e.qsum[t];
+        qs = e.qsum != nullptr ? e.qsum[t] : 0;
         if (JT == 0) return;
         const float* row = e.T + (int64_t)t * e.r;
         if ((e.r & 3) == 0) {
@@ -106,10 +106,10 @@ struct EpRows {
                 *reinterpret_cast<ep_v4h*>(at + 1024) = lo;
             }
         if (part == 0) {
-            float* info = reinterpret_cast<float*>(lds + JT * 4096);
+            float* info = reinterpret_cast<float*>(lds + TOKENS * 64 * JT);
             info[token] = sc * up;
-            info[64 + token] = __int_as_float((127 - kexp) << 23);
-            info[128 + token] = __int_as_float(qs);
+            info[TOKENS + token] = __int_as_float((127 - kexp) << 23);
+            info[2 * TOKENS + token] = __int_as_float(qs);
         }
     }
 };

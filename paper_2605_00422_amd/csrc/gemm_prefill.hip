@@ -481,7 +481,7 @@ __device__ __forceinline__ void gd_body(
     if constexpr (WN == 2) asm volatile("" ::: "v176");
     // ---- epilogue (gemm_epilogue.h)
     const EpArgs ep{scale, qsum, alpha, V, T, r, Y, M, N, acc_out, H};
-    EpRows<64 * WK * WN> rows_t(ep, tid);
+    EpRows<64 * WK * WN, GD_ROWS> rows_t(ep, tid);
     rows_t.request(m_base);
     if constexpr (A4) {
 #pragma unroll
@@ -568,7 +568,7 @@ hipError_t launch_streaming(const bwla_layer_t* L, const int8_t* dq, const float
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
     // the rings, then the epilogue's tiles
-    const size_t ring = (size_t)WK * NB * GD_TILE, tail = (size_t)(WK > 1 ? WK * GD_MT * NTL : WN) * 4096 + ep_rows_bytes(L->r);
+    const size_t ring = (size_t)WK * NB * GD_TILE, tail = (size_t)(WK > 1 ? WK * GD_MT * NTL : WN) * 4096 + ep_rows_bytes(GD_ROWS, L->r);
     const size_t lds = ring > tail ? ring : tail;
     auto launch = [&](auto kern) -> hipError_t {
         hipError_t e = bwla_ensure_lds((const void*)kern, lds);

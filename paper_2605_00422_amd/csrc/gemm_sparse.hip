@@ -21,12 +21,12 @@
 // the pair at 128 g + 16 m + 8 h + b.  Operand B (columns: tokens): lane half H holds the pairs of groups 2 H and 2 H + 1.
 #include "bwla_internal.h"
 #include "gemm_tiles.h"
+#include "gemm_epilogue.h"
 
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint32_t gs_bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
 // Constants that the compiler is not to fold, so that they stay operands of three-input instructions.  (An instruction
@@ -345,54 +345,55 @@ __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
     __syncthreads();
 
     // ---- epilogue: element v of lane (l32, lg) is channel 8 (v / 4) + 4 lg + v % 4 of token l32; acc = -64 sum.
-    // One row of tiles (32 tokens) at a time: its accumulators go to the wavefront's part of LDS, 4 KiB a tile, and a loop
-    // takes tile after tile from there -- the code is one tile's, not MT x NT copies of it.
-    constexpr int JC = 4;
-    const int JT = (r + 15) >> 4, rp = JT * 16;
+    // T, once for the workgroup, as operands in LDS (gemm_epilogue.h).  Then one row of tiles (32 tokens) at a time: its
+    // accumulators go to the wavefront's part of LDS, 4 KiB a tile, and a loop takes tile after tile from there -- the code
+    // is one tile's, not MT x NT copies of it.
+    constexpr int JC = EP_JC;
+    const int JT = (r + 15) >> 4, w = JT < JC ? JT : JC, inv = w > 0 ? 32768 / w + 1 : 0;
     char* mine = smem + wave * (NT * 4096);
-    struct Vop { uint4 v[JC]; uint2 al[4]; };
+    char* const rows_lds = smem + WN * NT * 4096;
+    const float* const info = reinterpret_cast<const float*>(rows_lds + BM * 64 * JT);
+    {
+        const EpArgs ep{scale, nullptr, alpha, V, T, r, Y, M, N, acc_out, H};
+        EpRows<64 * WN, BM> rows(ep, tid);
+        rows.request(m_base);
+        rows.put(rows_lds);
+    }
+    // V as the contiguous rows of a tile's channels, whole lines a request; alpha of my channels
+    struct Vop { v4i v[JC]; uint2 al[4]; };
     auto load_v = [&](Vop& o, int nt, int c0) {
-        int n = n_base + nt * 32 + l32;
-        if (n > N - 1) n = N - 1;
+        const int n0 = n_base + nt * 32 < N ? n_base + nt * 32 : N - 1;
+        const int last = (N - n0) * 2 * JT - 1;
+        const v4i* base = reinterpret_cast<const v4i*>(V) + (int64_t)n0 * JT * 2;
+        const int c = c0 * 2 + (lane & 7), at = (lane >> 3) * 2 * JT + (c < 2 * JT ? c : 2 * JT - 1);
+        const int step = JT <= JC ? 64 : 16 * JT, first = JT <= JC ? lane : at;
+        if (JT > 0) {
 #pragma unroll
-        for (int j = 0; j < JC; ++j)
-            if (c0 + j < JT) o.v[j] = *reinterpret_cast<const uint4*>(V + (int64_t)n * rp + (c0 + j) * 16 + 8 * lg);
+            for (int j = 0; j < JC; ++j) {
+                const int p = first + (j < JT ? j : 0) * step;
+                o.v[j] = base[p < last ? p : last];
+            }
+        }
+    };
+    auto load_al = [&](Vop& o, int nt) {
         // (alpha is padded to a multiple of 256 bytes: quadruples of a tile that starts inside are readable)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            int c = n_base + nt * 32 + 8 * g + 4 * lg;
-            if (c > N - 1) c = (N - 1) & ~3;
-            o.al[g] = *reinterpret_cast<const uint2*>(alpha + c);
+            int ch = n_base + nt * 32 + 8 * g + 4 * lg;
+            if (ch > N - 1) ch = (N - 1) & ~3;
+            o.al[g] = *reinterpret_cast<const uint2*>(alpha + ch);
         }
     };
-    auto load_t = [&](float (&tv)[8], int tmr, int kk) {
-        const int j0 = kk * 16 + 8 * lg;
-        const float* tp = T + (int64_t)tmr * r + j0;
-        if ((r & 3) == 0) {
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 t0 = *reinterpret_cast<const float4*>(j0 < r ? tp : T);
-            const float4 t1 = *reinterpret_cast<const float4*>(j0 + 4 < r ? tp + 4 : T);
-            const float4 u0 = j0 < r ? t0 : z, u1 = j0 + 4 < r ? t1 : z;
-            tv[0] = u0.x; tv[1] = u0.y; tv[2] = u0.z; tv[3] = u0.w;
-            tv[4] = u1.x; tv[5] = u1.y; tv[6] = u1.z; tv[7] = u1.w;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) tv[i] = j0 + i < r ? tp[i] : 0.0f;
-        }
-    };
+    __syncthreads();
 #pragma unroll 1
     for (int mt = 0; mt < MT; ++mt) {
         const int mrow0 = m_base + mt * 32;
         if (mrow0 >= M) break;
         const int rows = M - mrow0 < 32 ? M - mrow0 : 32;
         const int tmr = mrow0 + (l32 < rows ? l32 : rows - 1);
-        float tv[JC][8];
-#pragma unroll
-        for (int j = 0; j < JC; ++j)
-            if (j < JT) load_t(tv[j], tmr, j);
-        const float sc = scale[tmr];
         Vop vo;
         load_v(vo, 0, 0);
+        load_al(vo, 0);
 #pragma unroll
         for (int mm = 0; mm < MT; ++mm)
             if (mm == mt) {
@@ -403,107 +404,73 @@ __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
                         *reinterpret_cast<v4i*>(mine + nt * 4096 + g * 1024 + lane * 16) =
                             v4i{acc[mm][nt][4 * g], acc[mm][nt][4 * g + 1], acc[mm][nt][4 * g + 2], acc[mm][nt][4 * g + 3]};
             }
-        // the row's largest magnitude, over all of its ranks
-        float tmax = 0.0f;
-#pragma unroll
-        for (int j = 0; j < JC; ++j)
-            if (j < JT) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) tmax = fmaxf(tmax, fabsf(tv[j][i]));
-            }
-        for (int kk = JC; kk < JT; ++kk) {
-            float t2[8];
-            load_t(t2, tmr, kk);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) tmax = fmaxf(tmax, fabsf(t2[i]));
-        }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-        int kexp = 0;
-        if (tmax > 0.0f && tmax < 3.0e38f) kexp = 13 - ilogbf(tmax);
-        kexp = kexp > 60 ? 60 : (kexp < -60 ? -60 : kexp);
-        const float down = __int_as_float((127 - kexp) << 23);
-        const float scu = sc * __int_as_float((121 + kexp) << 23);             // scale 2^k / 64
-        int c0 = 0;
-        do {                                                 // chunks of 64 ranks
-            v8h thi[JC], tlo[JC];
-#pragma unroll
-            for (int j = 0; j < JC; ++j)
-                if (c0 + j < JT) {
-                    if (c0 > 0) load_t(tv[j], tmr, c0 + j);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float x = ldexpf(tv[j][i], kexp);
-                        const _Float16 h = (_Float16)x;
-                        thi[j][i] = h;
-                        tlo[j][i] = (_Float16)(x - (float)h);
-                    }
-                }
-            const bool last = c0 + JC >= JT;
+        const float scu = info[mt * 32 + l32] * 0.015625f, down = info[BM + mt * 32 + l32];       // scale 2^k / 64, 2^-k
 #pragma unroll 1
-            for (int nt = 0; nt < NT; ++nt) {
-                const Vop cur = vo;
-                if (nt + 1 < NT) load_v(vo, nt + 1, c0);
-                else if (!last) load_v(vo, 0, c0 + JC);
-                char* tile = mine + nt * 4096;
-                v16f y;
-                if (c0 == 0) {
+        for (int nt = 0; nt < NT; ++nt) {
+            char* tile = mine + nt * 4096;
+            v16f y;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const v4i u = *reinterpret_cast<const v4i*>(tile + g * 1024 + lane * 16);
-                        const __half2 a0 = __builtin_bit_cast(__half2, cur.al[g].x), a1 = __builtin_bit_cast(__half2, cur.al[g].y);
-                        // (multiples of 64 below 2^30: exact in fp32)
-                        y[4 * g + 0] = -(float)u[0] * (scu * __low2float(a0));
-                        y[4 * g + 1] = -(float)u[1] * (scu * __high2float(a0));
-                        y[4 * g + 2] = -(float)u[2] * (scu * __low2float(a1));
-                        y[4 * g + 3] = -(float)u[3] * (scu * __high2float(a1));
-                        if (!GATED && acc_out) {
-                            const int n = n_base + nt * 32 + 8 * g + 4 * lg;
-                            for (int i = 0; i < 4; ++i)
-                                if (l32 < rows && n + i < N) acc_out[(int64_t)tmr * N + n + i] = -(u[i] >> 6);
-                        }
-                    }
-                } else {
+            for (int g = 0; g < 4; ++g) {
+                const v4i u = *reinterpret_cast<const v4i*>(tile + g * 1024 + lane * 16);
+                const __half2 a0 = __builtin_bit_cast(__half2, vo.al[g].x), a1 = __builtin_bit_cast(__half2, vo.al[g].y);
+                // (multiples of 64 below 2^30: exact in fp32)
+                y[4 * g + 0] = -(float)u[0] * (scu * __low2float(a0));
+                y[4 * g + 1] = -(float)u[1] * (scu * __high2float(a0));
+                y[4 * g + 2] = -(float)u[2] * (scu * __low2float(a1));
+                y[4 * g + 3] = -(float)u[3] * (scu * __high2float(a1));
+                if (!GATED && acc_out) {
+                    const int n = n_base + nt * 32 + 8 * g + 4 * lg;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const v4f u = *reinterpret_cast<const v4f*>(tile + g * 1024 + lane * 16);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) y[4 * g + i] = u[i];
-                    }
+                    for (int i = 0; i < 4; ++i)
+                        if (l32 < rows && n + i < N) acc_out[(int64_t)tmr * N + n + i] = -(u[i] >> 6);
                 }
+            }
+            if (nt + 1 < NT) load_al(vo, nt + 1);
+#pragma unroll 1
+            for (int c0 = 0; c0 < JT; c0 += JC) {
+                // V in operand order, through the tile's place
+#pragma unroll
+                for (int j = 0; j < JC; ++j)
+                    if (j < w) {
+                        const int p = 64 * j + lane, ch = (int)(__umul24((uint32_t)p, (uint32_t)inv) >> 16), c = p - ch * 2 * w;
+                        *reinterpret_cast<v4i*>(tile + (c >> 1) * 1024 + (c & 1) * 512 + ch * 16) = vo.v[j];
+                    }
+                if (c0 + JC < JT) load_v(vo, nt, c0 + JC);
+                else if (nt + 1 < NT) load_v(vo, nt + 1, 0);
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int j = 0; j < JC; ++j)
                     if (c0 + j < JT) {
-                        const v8h vb = __builtin_bit_cast(v8h, cur.v[j]);
-                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, tlo[j], y, 0, 0, 0);
-                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, thi[j], y, 0, 0, 0);
+                        const char* t = rows_lds + mt * (JT * 2048) + (c0 + j) * 2048 + lane * 16;
+                        const ep_v8h vb = *reinterpret_cast<const ep_v8h*>(tile + j * 1024 + lane * 16);
+                        const ep_v8h thi = *reinterpret_cast<const ep_v8h*>(t), tlo = *reinterpret_cast<const ep_v8h*>(t + 1024);
+                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, tlo, y, 0, 0, 0);
+                        y = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb, thi, y, 0, 0, 0);
                     }
-                if (!last) {
+                __builtin_amdgcn_wave_barrier();
+            }
+            if constexpr (!GATED) {
+                // token rows of 128 bytes, 16-byte pieces turned by the row
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        *reinterpret_cast<v4f*>(tile + g * 1024 + lane * 16) = v4f{y[4 * g], y[4 * g + 1], y[4 * g + 2], y[4 * g + 3]};
-                } else if constexpr (!GATED) {
-                    // token rows of 128 bytes, 16-byte pieces turned by the row
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<v4f*>(tile + l32 * 128 + (((2 * g + lg) ^ (l32 & 7)) << 4)) =
+                        v4f{y[4 * g] * down, y[4 * g + 1] * down, y[4 * g + 2] * down, y[4 * g + 3] * down};
+            } else {
+                // h of a token: rows of 32 bytes
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        *reinterpret_cast<v4f*>(tile + l32 * 128 + (((2 * g + lg) ^ (l32 & 7)) << 4)) =
-                            v4f{y[4 * g] * down, y[4 * g + 1] * down, y[4 * g + 2] * down, y[4 * g + 3] * down};
-                } else {
-                    // h of a token: rows of 32 bytes
+                for (int g = 0; g < 4; ++g) {
+                    uint32_t hh = 0;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        uint32_t hh = 0;
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            const float gt = y[4 * g + 2 * i] * down, u = y[4 * g + 2 * i + 1] * down;
-                            const float h = gt / (1.0f + __expf(-gt)) * u;
-                            hh |= (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)h) << (16 * i);
-                        }
-                        *reinterpret_cast<uint32_t*>(tile + l32 * 32 + (2 * g + lg) * 4) = hh;
+                    for (int i = 0; i < 2; ++i) {
+                        const float gt = y[4 * g + 2 * i] * down, u = y[4 * g + 2 * i + 1] * down;
+                        const float h = gt / (1.0f + __expf(-gt)) * u;
+                        hh |= (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)h) << (16 * i);
                     }
+                    *reinterpret_cast<uint32_t*>(tile + l32 * 32 + (2 * g + lg) * 4) = hh;
                 }
             }
-            c0 += JC;
-        } while (c0 < JT);
+        }
+        __builtin_amdgcn_wave_barrier();
         // whole rows of the wavefront's channels
         if constexpr (!GATED) {
             if ((N & 3) == 0) {
@@ -557,10 +524,10 @@ hipError_t launch_sparse(const bwla_layer_t* L, const int8_t* dq, const uint8_t*
     constexpr int BM = 32 * v.mt, BN = 32 * v.nt * v.wn;
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
-    // code ring and two supersteps of weights; the epilogue turns 4 KiB a tile and wavefront in the same place
+    // code ring and two supersteps of weights; in the same place the epilogue turns 4 KiB a tile and wavefront and keeps T
     constexpr size_t ring = (size_t)v.ring * BM * 128 + (size_t)v.wn * 4 * v.nt * 1024, turn = (size_t)v.wn * v.nt * 4096;
-    constexpr size_t lds = ring > turn ? ring : turn;
-    static_assert(lds * v.resident <= 160 * 1024, "");
+    static_assert((ring > turn ? ring : turn) * v.resident <= 160 * 1024 && turn + BM * (BWLA_MAX_RANK / 16 * 64 + 12) <= 160 * 1024, "");
+    const size_t tail = turn + ep_rows_bytes(BM, L->r), lds = ring > tail ? ring : tail;
     auto launch = [&](auto kern) -> hipError_t {
         hipError_t e = bwla_ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
