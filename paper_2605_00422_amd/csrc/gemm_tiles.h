@@ -11,15 +11,11 @@
 // in runs of tiles with the same token rows where their number is a multiple of eight, and each row enters one L2;
 // otherwise up to eight L2s fetch it.  The smallest cost is taken.
 //
-// The constants are fitted to 924 shapes (the projections of the 4096-, 5120- and 8192-wide blocks at 17 to 4096
-// tokens, the others at random: 17 .. 4096 tokens, K 128 .. 28672, N 32 .. 28672, ranks 0 .. 96), each with plain and
-// gated int8 codes and with nibble codes, three layers in turn so that nothing stays in L2.  Over those the choice is
-// within 0.4 / 0.7 / 0.5 % of the best of fifteen tiles on average, and takes 0.896 / 0.891 / 0.913 of the time that
-// two thresholds between large and small private-ring tiles led to; 17 of the 2772 times are more than 2 % above those
-// (the worst by 16 %).  Constants fitted to plain codes alone, without `idle`, `low` and the codes' own time, left 192
-// (the worst by 42 %; 18 tokens of nibble codes on 1280 columns 5.7 -> 7.1 us, 28672 -> 8192 at 1024 tokens, plain,
-// 188 -> 216; without `low` alone, 4096 -> 12288 at 4096 tokens and rank 96 245 -> 268).  Five more tiles that were
-// candidates (64 x 32 for one wavefront, 256 x 128 with rings of two and four, 256 x 160, 64 x 640 with private
+// The constants are fitted to 628 shapes (the projections of the 4096-, 5120- and 8192-wide blocks and others at random:
+// 17 .. 4096 tokens, K 128 .. 28672, N 32 .. 51200, ranks 0 .. 96), each with plain and gated int8 codes and with nibble
+// codes, three layers in turn so that nothing stays in L2.  Over those the choice is within 0.5 / 0.4 / 1.0 % of the best
+// of the ten on average (2.8 / 2.9 / 3.4 % with constants fitted to an epilogue that took twice the time).  Five more tiles
+// that were candidates (64 x 32 for one wavefront, 256 x 128 with rings of two and four, 256 x 160, 64 x 640 with private
 // rings) moved no average by more than 0.1 % and are not built.
 #pragma once
 
@@ -33,17 +29,17 @@ struct GdTile {
 constexpr int GD_TILE_TOKENS = 64;
 constexpr GdTile GD_TILES[] = {
     // few tokens: private rings, the wavefronts of a workgroup share out K
-    {1, 4, 4, 1, 1, 0.69f, {7.96f}, {0.3473f}, 0.1138f, 1.202f, 0.912f},                                                  // 64 x 32, in four
-    {2, 4, 4, 1, 1, 0.62f, {10.30f}, {0.4917f}, 0.0945f, 1.326f, 1.002f},                                                 // 64 x 64, in four
-    {2, 2, 4, 1, 2, 2.28f, {7.93f, 9.71f}, {0.4145f, 0.4223f}, 0.0694f, 1.332f, 0.946f},                                  // 64 x 64, in two
-    {3, 2, 4, 1, 2, 2.11f, {10.44f, 13.07f}, {0.5221f, 0.5891f}, 0.1048f, 1.438f, 0.927f},                                // 64 x 96, in two
+    {1, 4, 4, 1, 1, 1.39f, {4.39f}, {0.3409f}, 0.0920f, 0.369f, 0.953f},                                                   // 64 x 32, in four
+    {2, 4, 4, 1, 1, 1.86f, {4.73f}, {0.4795f}, 0.1366f, 0.486f, 0.895f},                                                   // 64 x 64, in four
+    {2, 2, 4, 1, 2, 1.70f, {5.77f, 7.18f}, {0.3811f, 0.4007f}, 0.0648f, 0.634f, 0.934f},                                   // 64 x 64, in two
+    {3, 2, 4, 1, 2, 1.95f, {7.29f, 10.13f}, {0.5066f, 0.5755f}, 0.0908f, 0.838f, 0.975f},                                  // 64 x 96, in two
     // one ring of codes for four wavefronts (the first: two)
-    {1, 1, 4, 2, 4, 2.27f, {4.46f, 7.54f, 8.57f, 8.88f}, {0.3572f, 0.3201f, 0.3833f, 0.4758f}, 0.0522f, 1.149f, 0.988f},  // 64 x 64
-    {1, 1, 4, 4, 3, 4.91f, {2.49f, 6.66f, 10.52f}, {0.3331f, 0.4092f, 0.6233f}, 0.0662f, 1.323f, 1.020f},                 // 64 x 128
-    {2, 1, 4, 4, 2, 3.39f, {4.37f, 12.24f}, {0.4005f, 0.6627f}, 0.0784f, 1.572f, 1.000f},                                 // 64 x 256
-    {3, 1, 4, 4, 2, 3.60f, {7.23f, 17.55f}, {0.5550f, 0.9247f}, 0.1131f, 1.670f, 1.000f},                                 // 64 x 384
-    {4, 1, 2, 4, 2, 3.85f, {11.71f, 22.08f}, {0.6995f, 1.3362f}, 0.2233f, 1.878f, 1.000f},                                // 64 x 512, ring of two
-    {5, 1, 4, 4, 1, 0.00f, {19.87f}, {0.8199f}, 0.1241f, 2.171f, 0.980f},                                                 // 64 x 640
+    {1, 1, 4, 2, 4, 3.22f, {2.47f, 3.63f, 4.93f, 7.06f}, {0.2795f, 0.3006f, 0.4409f, 0.4146f}, 0.0314f, 0.475f, 1.127f},   // 64 x 64
+    {1, 1, 4, 4, 3, 3.52f, {2.52f, 5.13f, 8.09f}, {0.3036f, 0.4222f, 0.4827f}, 0.0817f, 0.552f, 1.103f},                   // 64 x 128
+    {2, 1, 4, 4, 2, 1.69f, {8.99f, 9.37f}, {0.3721f, 0.6385f}, 0.0796f, 0.803f, 1.027f},                                   // 64 x 256
+    {3, 1, 4, 4, 2, 3.77f, {8.00f, 13.44f}, {0.4317f, 0.8893f}, 0.1199f, 0.869f, 1.092f},                                  // 64 x 384
+    {4, 1, 2, 4, 2, 4.49f, {8.78f, 15.57f}, {0.6888f, 1.2477f}, 0.1249f, 1.179f, 1.087f},                                  // 64 x 512, ring of two
+    {5, 1, 4, 4, 1, 0.00f, {16.35f}, {0.8438f}, 0.2302f, 1.596f, 1.062f},                                                  // 64 x 640
 };
 constexpr int GD_NTILES = sizeof(GD_TILES) / sizeof(GD_TILES[0]);
 
@@ -81,11 +77,11 @@ inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4)
 // the faster one.  The same kind of cost, `step` per superstep of 512 columns; in front of it the pass that turns the codes
 // into sums and differences (a launch, and the codes once in and once out).  It contracts twice the columns an instruction
 // but prepares its operands at more cost, in steps of 512 columns, and its wide tiles start and finish slowly: it wins where
-// tiles are many and rows of K long.  Fitted to 279 shapes (65 .. 4096 tokens, K 256 .. 28672, N 64 .. 51200, 73 of them
-// gated), three layers in turn; it is taken where its cost is 5 % below the dense kernel's.  Over those shapes the choice
-// takes 0.974 of the dense kernel's time (0.968 with the best tile of both every time; 0.62 .. 0.9 where M K N > 1e11), with
-// 2 of 279 times more than 2 % above it; without the 5 %, 9.  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and
-// move the average by less than 0.7 % at ten times as many wrong choices.
+// tiles are many and rows of K long.  Fitted to 945 pairs of shape and form (65 .. 4096 tokens, K 128 .. 28672, N 32 .. 51200,
+// plain and gated), three layers in turn; it is taken where its cost is 3 % below the dense kernel's.  Over those the choice
+// takes 0.992 of the dense kernel's time (0.988 with the best tile of both every time; 0.68 .. 0.9 for the longest), with 2
+// times more than 2 % above it; without the 3 %, 16.  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and move the
+// average by less than 0.7 % at ten times as many wrong choices.
 struct GsTile {
     int mt, nt, wn, ring;         // 32-token tiles and 32-channel tiles a wavefront; wavefronts side by side; pairs in the code ring
     int resident;                 // workgroups a CU holds
@@ -93,9 +89,9 @@ struct GsTile {
 };
 constexpr int GS_MIN_TOKENS = 64;
 constexpr GsTile GS_TILES[] = {
-    {2, 2, 4, 4, 2, 4.92f, {4.13f, 8.09f}, {1.500f, 2.401f}, 0.513f, 1.257f},       // 64 x 256
-    {2, 5, 4, 4, 1, 0.77f, {16.83f}, {2.774f}, 0.829f, 1.675f},                     // 64 x 640
-    {4, 4, 4, 4, 1, 0.69f, {24.61f}, {3.577f}, 1.122f, 2.267f},                     // 128 x 512
+    {2, 2, 4, 4, 2, 6.00f, {3.51f, 7.60f}, {1.289f, 2.061f}, 0.264f, 1.256f},       // 64 x 256
+    {2, 5, 4, 4, 1, 2.33f, {15.80f}, {2.557f}, 0.618f, 2.203f},                     // 64 x 640
+    {4, 4, 4, 4, 1, 1.17f, {23.09f}, {3.298f}, 0.894f, 3.621f},                     // 128 x 512
 };
 constexpr int GS_NTILES = sizeof(GS_TILES) / sizeof(GS_TILES[0]);
 
@@ -119,7 +115,7 @@ inline int gs_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus) {
     int best = -1;
     float cost = gd_cost(GD_TILES[gd_pick(M, K, N, r, cus, false)], M, K, N, r, cus, false);
     for (int i = 0; i < GS_NTILES; ++i) {
-        const float c = 1.05f * gs_cost(GS_TILES[i], M, K, N, r, cus);
+        const float c = 1.03f * gs_cost(GS_TILES[i], M, K, N, r, cus);
         if (c < cost) { cost = c; best = i; }
     }
     return best;

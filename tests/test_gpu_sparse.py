@@ -11,15 +11,16 @@ DEV = "cuda:0"
 
 # (tokens, K, N, rank): edges of tiles, supersteps and ranks of each tile that the dispatch chooses from
 SHAPES = [
-    (709, 128, 8617, 96),       # 64 x 256: a quarter of a superstep, five tokens in the last tile, odd channels, two chunks of ranks
-    (2487, 128, 2462, 96),
-    (2048, 1024, 8192, 16),     # 64 x 256: nothing ragged
-    (331, 384, 23584, 64),      # 64 x 640
-    (868, 384, 10002, 96),      # 64 x 640, channels end inside a tile
+    (848, 384, 21104, 16),      # 64 x 256: three quarters of a superstep, a quarter of the last tile
+    (2859, 512, 4285, 0),       # 64 x 256: odd channels, no ranks
+    (69, 9728, 25770, 37),      # 64 x 256: five tokens in the last tile, a rank that is no multiple of four
+    (80, 16384, 26729, 96),     # 64 x 256: sixteen tokens in the last tile, odd channels, two chunks of ranks
+    (345, 5248, 22035, 16),     # 64 x 640: a quarter of a superstep at the end, odd channels
+    (455, 5632, 19040, 37),     # 64 x 640, channels end inside a tile
     (2048, 25600, 5120, 64),    # 64 x 640, fifty supersteps
-    (481, 1920, 26503, 0),      # 128 x 512: 97 tokens in the last tile, no ranks, odd channels
-    (2692, 2048, 4519, 37),     # 128 x 512, four tokens in the last tile, a rank that is no multiple of four
-    (1024, 8192, 28672, 64),    # 128 x 512: nothing ragged
+    (855, 2944, 16948, 0),      # 128 x 512: 87 tokens in the last tile, no ranks
+    (601, 5120, 20923, 37),     # 128 x 512, odd channels
+    (598, 8064, 20415, 96),     # 128 x 512: two chunks of ranks, three quarters of a superstep at the end
 ]
 
 
@@ -128,7 +129,7 @@ def test_codes_wider_than_announced_are_found(M, K, N, r, where):
 def test_whole_layer(bits, centered, asym, x):
     """decode_forward with the scratch's room and without it."""
     from paper_2605_00422_amd import binding as B
-    M, K, N, r = 1111, 4096, 9001, 20
+    M, K, N, r = 1111, 4096, 22001, 20
     layer, g = _layer(M, K, N, r, centered, asym)
     X = torch.randn(M, K, device=DEV, generator=g).to(x)
     outs = []
@@ -148,7 +149,7 @@ def test_one_scratch_for_calls_of_several_sizes():
     """The room for the codes lies at the end of a scratch: a call on fewer tokens leaves the arrival counters of one on
     more tokens alone."""
     from paper_2605_00422_amd import binding as B
-    K, N, r = 2048, 11008, 96
+    K, N, r = 4096, 22016, 32
     layer, g = _layer(4096, K, N, r)
     X = torch.randn(4096, K, device=DEV, generator=g).to(torch.bfloat16)
     big = B.Activations(layer, 4096)
@@ -167,7 +168,7 @@ def test_one_scratch_for_calls_of_several_sizes():
 
 def test_replayed_from_a_graph():
     from paper_2605_00422_amd import binding as B
-    M, K, N, r = 1024, 8192, 8192, 32
+    M, K, N, r = 1024, 8192, 20480, 32
     layer, g = _layer(M, K, N, r)
     act = B.Activations(layer, M)
     Xs = [torch.randn(M, K, device=DEV, generator=g).to(torch.bfloat16) for _ in range(3)]
