@@ -42,13 +42,13 @@ struct RqArgs {
     int64_t rot_blocks;      // workgroups below this index rotate token blockIdx.x, the rest project
     int JG;                  // projection workgroups per (token tile, slice): groups of rank tiles
     const uint16_t* R1p; const uint16_t* R2p;          // bf16 term planes of the factors
-    bwla_psp_tiles tiles;    // the workgroups behind the rotation add these up instead of projecting, if there are any
+    bwla_psp_tiles tiles;    // S = 0: the workgroups behind the rotation add these up instead of projecting
 };
 
 // projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile
 template <bool BF16>
 __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    if (a.tiles.blocks > 0) {
+    if (a.S == 0) {
         bwla_psp_sum_tiles(a.tiles, pb);
         return;
     }
@@ -258,6 +258,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         const int64_t values = (int64_t)plan.token_tiles * plan.col_groups * 64 * plan.tile_cols;
         a.tiles.blocks = (int)(values / 512 < 128 ? values / 512 : 128);
         pblocks = a.tiles.blocks;
+        a.S = 0;
         e = bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st, false);
         if (e != hipSuccess) return e;
     }
