@@ -352,16 +352,19 @@ def microbench(torch, B):
                     "1 MiB + 4 KiB apart over a flushed 384 MiB buffer / 128 bytes apart over 1 MiB read just before"}
 
 
-def gemm_kernel(cfg):
+def gemm_kernel(cfg, act_bits=8):
     """The kernel that bwla_linear_forward runs for a layer whose channels fill it: the streaming decode GEMM up
     to 16 tokens, then (csrc/gemm_tiles.h) private rings of codes for a single tile of 64 tokens, one ring for the
-    wavefronts side by side beyond that."""
+    wavefronts side by side beyond that; with codes of at most seven bits (bwla_linear_forward_bits) the one on the sparse
+    matrix instructions where tokens are many and rows of K long."""
     if cfg.M <= 16:
         return "gemm_decode_bs_kernel"
+    if act_bits <= 7 and cfg.M >= 2048 and cfg.K >= 8192 and cfg.N >= 4096:
+        return "gemm_sparse_kernel"
     return "gemm_prefill_direct_kernel" if cfg.M <= 64 else "gemm_prefill_shared_kernel"
 
 
-def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=None):
+def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=None, act_bits=8):
     """Roofline of the dominant kernel: the single-launch decode kernel where it serves the layer
     (then the kernel is the layer), else the binary GEMM inside bwla_linear_forward; with the
     whole layer (all launches, all bytes or operations) against the same peak beside it."""
@@ -370,7 +373,7 @@ def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=N
     if launches == 1:
         kernel, t, nbytes = "decode_layer_kernel", us_layer * 1e-6, layer_bytes(cfg)
     else:
-        kernel = gemm_kernel(cfg)
+        kernel = gemm_kernel(cfg, act_bits)
         t, nbytes = us_forward * 1e-6, linear_forward_bytes(cfg)
     tl = us_layer * 1e-6
     if hbm_bound:
@@ -548,7 +551,7 @@ def main():
     best, mode = best_of(res)
     us_layer = best["us_per_layer"]
     us_fwd = best["us_linear_forward"]
-    roof = roofline_for(cfg, w.launches, us_layer, us_fwd, peaks, traffic)
+    roof = roofline_for(cfg, w.launches, us_layer, us_fwd, peaks, traffic, act_bits=w.act_bits)
     line = {
         "metric": "us/layer, W1A6 linear forward (rotate+quant, binary GEMM + PSP + dequant)",
         "value": us_layer, "unit": "us/layer", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -600,7 +603,7 @@ def main():
                 c = dataclasses.replace(c, r=c.r + int(shift) + 2 * int(asym))   # bytes of the extra columns of V and T
             b, _ = best_of(r)
             r["roofline"] = roofline_for(c, ww.launches, b["us_per_layer"], b["us_linear_forward"], peaks, traffic,
-                                         workload=r["workload"])
+                                         workload=r["workload"], act_bits=8 if nibble else bits)
             if not nibble and bits == 4:
                 r["code_bytes_per_launch"] = c.M * c.K
             r["side_kernels"] = [side_kernel_report(c, b["us_rotate_quant"])]

@@ -90,3 +90,19 @@ def test_more_than_one_gpu_is_refused_with_a_message():
                        timeout=120)
     assert p.returncode == 2
     assert "one GPU" in p.stderr and p.stdout.strip() == ""
+
+
+def test_the_kernels_named_for_narrow_codes():
+    """The same with codes of at most seven bits, against the table of the GEMM on the sparse instructions."""
+    import tempfile
+    csrc = os.path.join(ROOT, "paper_2605_00422_amd", "csrc")
+    cfgs = [c for M in (64, 4096) for c in syn.block70b_configs(M)] + [syn.CONFIGS["cfg3_qwen32b_down_m2048"]]
+    with tempfile.TemporaryDirectory() as tmp:
+        src = "#include <cstdio>\n#include \"gemm_tiles.h\"\nint main() {\n" + "".join(
+            f'printf("%d\\n", gs_pick({c.M}, {c.K}, {c.N}, {c.r}, 256) >= 0);\n' for c in cfgs) + "}\n"
+        with open(os.path.join(tmp, "gs.cpp"), "w") as f:
+            f.write(src)
+        subprocess.run(["g++", "-std=c++17", "-I", csrc, "-o", os.path.join(tmp, "gs"), os.path.join(tmp, "gs.cpp")], check=True)
+        sparse = subprocess.run([os.path.join(tmp, "gs")], capture_output=True, text=True, check=True).stdout.split()
+    for c, s in zip(cfgs, sparse):
+        assert (bench.gemm_kernel(c, 6) == "gemm_sparse_kernel") == (s == "1"), c.name
