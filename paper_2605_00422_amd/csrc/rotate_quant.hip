@@ -88,12 +88,10 @@ __global__ __launch_bounds__(THREADS) void rotate_quant3_kernel(RqArgs a) {
 __global__ __launch_bounds__(640) void rotate_split_kernel(RqArgs a) {
     extern __shared__ __align__(16) float lds[];
     if ((int64_t)blockIdx.x < a.rot_blocks) {
-        const RsShape rs = rs_shape(r3_shape(a.n1, a.n2));
-        const int G = rs.G;
+        const int G = rs_shape(r3_shape(a.n1, a.n2)).G;
         const int64_t t = blockIdx.x / G;
         rotate_slice_block(reinterpret_cast<char*>(lds), reinterpret_cast<const uint16_t*>(a.X), t,
-                           (int)(blockIdx.x - t * G), a.K, a.n1, a.n2, a.R1p, a.R2p, a.xs, a.pmax, a.qsum,
-                           a.shift ? reinterpret_cast<unsigned long long*>(a.pmax + 2 * a.M * rs.E) : nullptr);
+                           (int)(blockIdx.x - t * G), a.K, a.n1, a.n2, a.R1p, a.R2p, a.xs, a.pmax, a.qsum);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
         psp_block_at<true>(reinterpret_cast<char*>(lds), a, pb, false);
@@ -279,7 +277,6 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         const RsShape rs = rs_shape(s3);
         a.xs = (float*)((char*)dws + bwla_split_start(plan, ru));
         a.pmax = a.xs + M * L->K;
-        unsigned long long* sums = a.shift ? reinterpret_cast<unsigned long long*>(a.pmax + 2 * M * rs.E) : nullptr;
         a.rot_blocks = M * rs.G;
         const int threads3 = s3.strips > 8 ? 64 * s3.strips : 512;     // the projection wants eight wavefronts
         const size_t pl3 = merged ? pp_lds_bytes(ru, threads3 / 64) : 0;
@@ -293,7 +290,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         const bool psum = merged && a.S > 1;
         const PspSum ps{a.partials, a.T, M, M * RS_QB, a.r, a.S};
         quantize_rows_kernel<<<dim3((unsigned)(M * RS_QB + (psum ? plan.token_tiles : 0))), dim3(512), 0, st>>>(
-            a.xs, a.pmax, rs.E, L->K, dq, dscale, dqsum, a.qmax, a.asym, a.tmode, a.tp, sums,
+            a.xs, a.pmax, rs.E, L->K, dq, dscale, dqsum, a.qmax, a.asym, a.tmode, a.tp,
             a.shift ? a.tmode + (a.asym ? 2 : 0) : nullptr, ps);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -368,7 +365,7 @@ size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& pla
     // 224 x 128 at sixteen tokens 21.6 us against 31.2 in one workgroup per token, at thirty-two
     // 34.5 against 32.0; with more tokens the one-workgroup-per-token kernel keeps the chip busy
     if (M * rs.G + pblocks > 2 * bwla_device_cus()) return 0;
-    return (size_t)(M * L->K + 2 * M * rs.E + 2 * M) * sizeof(float);     // values, extremes, per-token sums of 64 bits
+    return (size_t)(M * L->K + 2 * M * rs.E) * sizeof(float);     // values, extremes
 }
 
 hipError_t bwla_launch_pack_codes_a4(const int8_t* dq, int64_t M, int64_t K, uint8_t* dq4, hipStream_t st) {

@@ -46,8 +46,7 @@ __host__ __device__ inline RsShape rs_shape(const R3Shape& s3) {
 __device__ __forceinline__ void rotate_slice_block(char* lds, const uint16_t* __restrict__ X, int64_t t, int j,
                                                    int64_t K, int n1, int n2, const uint16_t* __restrict__ R1p,
                                                    const uint16_t* __restrict__ R2p, float* __restrict__ xs,
-                                                   float* __restrict__ pmax, int32_t* __restrict__ qsum,
-                                                   unsigned long long* __restrict__ sums) {
+                                                   float* __restrict__ pmax, int32_t* __restrict__ qsum) {
     const R3Shape sh = r3_shape(n1, n2);
     const RsShape rs = rs_shape(sh);
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
@@ -254,19 +253,16 @@ __device__ __forceinline__ void rotate_slice_block(char* lds, const uint16_t* __
         float* pm = pmax + ((t * rs.G + j) * sh.strips + wave) * 2;
         pm[0] = mx;
         pm[1] = mn;
-        if (j == 0 && wave == 0) {                     // the quantizing launch adds its sums up here
-            if (sums) sums[t] = 0;
-            else qsum[t] = 0;
-        }
+        if (j == 0 && wave == 0) qsum[t] = 0;          // the quantizing launch adds its sums up here
     }
 }
 
 // second launch of the split rotation: RS_QB workgroups per token quantize the rotated values, each
 // its share of k, every load in flight at once; the code sum is added up in qsum[t], which the
-// first launch has set to zero (integer adds: the order does not matter).  For a layer with row shifts it is added up in
-// sums[t] instead, below a count of the workgroups that have added theirs (2^40 each), and the last one writes qsum[t] and
-// the shift column, T[t, last] = scale_t * sum_k (q - z) = scale_t * (qsum_t - K zc_t): a launch of its own for that cost
-// 1.3 us and the gap in front of it.  Workgroups from
+// first launch has set to zero (integer adds: the order does not matter).  For a layer with row shifts a count of
+// the workgroups that have added theirs stands above the sum meanwhile (2^24 each; 65536 codes of eight bits stay within 24
+// bits), and the last one leaves the sum alone and writes the shift column, T[t, last] = scale_t * sum_k (q - z) = scale_t *
+// (qsum_t - K zc_t): a launch of its own for that cost 1.3 us and the gap in front of it.  Workgroups from
 // `first` on (one per tile of 16 tokens, none if S == 1) add up the projection's partial tiles.
 struct PspSum {
     const float* partials;
@@ -276,11 +272,11 @@ struct PspSum {
 };
 constexpr int RS_QB = 8;
 constexpr int RS_QI = 4;             // float4 per thread: K <= RS_QB * 512 * RS_QI * 4
+static_assert(RS_QB * 512 * RS_QI * 4 * 128 <= 1 << 23, "code sums of 24 bits");
 __global__ __launch_bounds__(512) void quantize_rows_kernel(const float* __restrict__ xs, const float* __restrict__ pmax,
                                                             int E, int64_t K, int8_t* __restrict__ q,
                                                             float* __restrict__ scale, int32_t* __restrict__ qsum,
                                                             float qmax, int asym, float* __restrict__ tmode, int tp,
-                                                            unsigned long long* __restrict__ sums,
                                                             float* __restrict__ tshift, PspSum ps) {
     __shared__ int redi[8];
     __shared__ float redf[16];
@@ -335,19 +331,18 @@ __global__ __launch_bounds__(512) void quantize_rows_kernel(const float* __restr
     if (tid == 0) {
         int tot = 0;
         for (int w = 0; w < 8; ++w) tot += redi[w];
-        const float sc = quant_scale(hi, lo, qmax, asym != 0);
-        if (sums) {
-            const unsigned long long mine = (1ull << 40) + (unsigned long long)(long long)tot;
-            const long long now = (long long)(atomicAdd(sums + t, mine) + mine);
-            const long long sum = (long long)((unsigned long long)now << 24) >> 24;         // the lower 40 bits, signed
-            if ((now - sum) >> 40 == RS_QB) {
-                qsum[t] = (int32_t)sum;
-                tshift[t * tp] = sc * ((float)(int32_t)sum - (float)K * qp.zc);
+        if (tshift) {
+            const int mine = (1 << 24) + tot, now = atomicAdd(qsum + t, mine) + mine;
+            const int sum = (int)((unsigned)now << 8) >> 8;     // the lower 24 bits, signed
+            if ((now - sum) >> 24 == RS_QB) {
+                qsum[t] = sum;
+                tshift[t * tp] = quant_scale(hi, lo, qmax, asym != 0) * ((float)sum - (float)K * qp.zc);
             }
         } else {
             atomicAdd(qsum + t, tot);
         }
         if (part == 0) {
+            const float sc = quant_scale(hi, lo, qmax, asym != 0);
             scale[t] = sc;
             if (asym && tmode) tmode[t * tp] = tmode[t * tp + 1] = -(sc * qp.zc);
         }
