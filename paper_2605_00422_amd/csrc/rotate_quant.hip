@@ -42,14 +42,16 @@ struct RqArgs {
     int64_t rot_blocks;      // workgroups below this index rotate token blockIdx.x, the rest project
     int JG;                  // projection workgroups per (token tile, slice): groups of rank tiles
     const uint16_t* R1p; const uint16_t* R2p;          // bf16 term planes of the factors
-    bwla_psp_tiles tiles;    // S = 0: the workgroups behind the rotation add these up instead of projecting
 };
 
 // projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile
 template <bool BF16>
 __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    if (a.S == 0) {
-        bwla_psp_sum_tiles(a.tiles, pb);
+    // (bf16 tokens only, and no argument of its own: the other role in the fp32 kernel, or 56 bytes more of arguments, cost
+    // small launches 0.1 us)
+    if (BF16 && a.S < 0) {
+        const int W = a.r <= 16 ? 16 : a.r <= 32 ? 32 : 64;            // bwla_psp_prefill_tile_cols
+        bwla_psp_sum_tiles(bwla_psp_tiles{a.partials, a.T, a.M, a.r, a.tp, -a.S, a.JG, W, (int)(gridDim.x - a.rot_blocks)}, pb);
         return;
     }
     const int s = pb % a.S, rest = pb / a.S;
@@ -246,19 +248,17 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     const size_t plds = merged ? pp_lds_bytes(ru) : 0;
     a.rot_blocks = M;
     hipError_t e;
-    a.tiles = bwla_psp_tiles{};
     // Up to some 1500 tokens the projection goes first and leaves its partial tiles, and workgroups behind the rotation's
     // own add them up.  (Handing them over inside its launch -- acknowledged stores, an arrival count, a last workgroup that
     // reads them back -- was the larger part of its time: 28672 columns, rank 64, 128 tokens 55.8 -> 40.1 us with the
     // rotation, 8192 at 512 tokens 27.4 -> 21.3, 25600 at 1024 81.7 -> 76.9.  Beyond, there are few slices, the hand-over is
     // short and the sums stand behind the rotation: 5120 at 2048 tokens 70.4, 72.2 this way; 160 x 160 136.4, 138.2.)
-    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1536;
+    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1536 && xdtype == BWLA_X_BF16;
     if (leave) {
-        a.tiles = bwla_psp_tiles{a.partials, dT, M, ru, L->r, plan.splits, plan.col_groups, plan.tile_cols, 0};
         const int64_t values = (int64_t)plan.token_tiles * plan.col_groups * 64 * plan.tile_cols;
-        a.tiles.blocks = (int)(values / 512 < 128 ? values / 512 : 128);
-        pblocks = a.tiles.blocks;
-        a.S = 0;
+        pblocks = values / 512 < 128 ? values / 512 : 128;
+        a.S = -plan.splits;
+        a.JG = plan.col_groups;
         e = bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st, false);
         if (e != hipSuccess) return e;
     }
@@ -266,7 +266,9 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         // many bf16 tokens and factors whose operand-order planes fit LDS: the looping kernel with
         // resident factors
         bool done = false;
-        e = bwla_launch_rotate_planes(L, dX, xdtype, M, dq, dscale, dqsum, dT, act_bits, st, &done, a.tiles);
+        e = bwla_launch_rotate_planes(L, dX, xdtype, M, dq, dscale, dqsum, dT, act_bits, st, &done,
+                                       bwla_psp_tiles{a.partials, dT, M, ru, L->r, plan.splits, plan.col_groups, plan.tile_cols,
+                                                      leave ? (int)pblocks : 0});
         if (e != hipSuccess) return e;
         if (done) return ru > 0 && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
     }
