@@ -248,12 +248,13 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     const size_t plds = merged ? pp_lds_bytes(ru) : 0;
     a.rot_blocks = M;
     hipError_t e;
-    // Up to some 1500 tokens the projection goes first and leaves its partial tiles, and workgroups behind the rotation's
+    // Up to some 1800 tokens the projection goes first and leaves its partial tiles, and workgroups behind the rotation's
     // own add them up.  (Handing them over inside its launch -- acknowledged stores, an arrival count, a last workgroup that
     // reads them back -- was the larger part of its time: 28672 columns, rank 64, 128 tokens 55.8 -> 40.1 us with the
     // rotation, 8192 at 512 tokens 27.4 -> 21.3, 25600 at 1024 81.7 -> 76.9.  Beyond, there are few slices, the hand-over is
-    // short and the sums stand behind the rotation: 5120 at 2048 tokens 70.4, 72.2 this way; 160 x 160 136.4, 138.2.)
-    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1536 && xdtype == BWLA_X_BF16;
+    // short and the sums stand behind the rotation: rank 64, 8192 columns at 1537 tokens 42.4 -> 38.8, at 4096 65.9 -> 67.0;
+    // 1024 columns 23.0 -> 21.5 and 38.9 -> 44.7.)
+    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1792 && xdtype == BWLA_X_BF16;
     if (leave) {
         const int64_t values = (int64_t)plan.token_tiles * plan.col_groups * 64 * plan.tile_cols;
         pblocks = values / 512 < 128 ? values / 512 : 128;

@@ -27,8 +27,8 @@ CASES = [
     (256, 64, 64, 64, "bf16"),      # the kernel that walks over the tokens, from its first size on
     (257, 128, 64, 1, "bf16"),
     (700, 160, 160, 8, "bf16"),
-    (1536, 224, 128, 17, "bf16"),   # the largest that leaves its tiles
-    (1537, 128, 64, 17, "bf16"),    # the first that hands them over
+    (1792, 224, 128, 17, "bf16"),   # the largest that leaves its tiles
+    (1793, 128, 64, 17, "bf16"),    # the first that hands them over
     (384, 64, 64, 128, "f32"),      # fp32 tokens
     (1000, 128, 64, 31, "f32"),
     (255, 64, 32, 8, "bf16"),       # rides
