@@ -82,7 +82,8 @@ inline int bwla_extra_cols(int mode) { return ((mode & BWLA_MODE_ASYM_ACT) ? 2 :
 // columns of U = rank of the projection T = X U
 inline int bwla_rank_u(const bwla_layer_t* L) { return L->r - bwla_extra_cols(L->mode); }
 inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
-    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), bwla_rotate_planes_serves(L, xdtype, M));
+    // (up to 16 tokens the plan is the same either way, and a decode call of 6 us does not ask the device twice)
+    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), M > 16 && bwla_rotate_planes_serves(L, xdtype, M));
 }
 inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int r) {
     if (r <= 0 || p.splits <= 1) return 0;

@@ -188,13 +188,14 @@ bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes) {
     // 29.8 / 22.7 / 14.3; 25600, rank 32: 128 tokens 28.3 / 34 / 26.6; 5120, rank 32: 257 tokens 16.8 / 23 / 17.
     // (ranks of more than two 16-column tiles are dealt to several workgroups per slice)
     const int jg = rp > 16 * PP_GROUPJT ? (rp / 16 + PP_GROUPJT - 1) / PP_GROUPJT : 1;
-    const int64_t riders = ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg, cus = bwla_device_cus();
+    const bool always = M <= 16 || r <= 0;
+    const int64_t riders = ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg, cus = always ? 1 : bwla_device_cus();
     const int64_t beside = (cus - M % cus) % cus;              // CUs that the last round leaves free
     const bool shadow = beside > 0 && 5.5f * (float)((riders + beside - 1) / beside) <= 9.0f + (float)K / 1050.0f;
     // (short rows leave room for several workgroups a CU: there it is their number that counts, up to three a CU; 512
     // columns, rank 64, 384 tokens 11.7 / 18.5)
     const bool ride = !planes && M <= 768 && (K < 2048 ? M + riders <= 768 : shadow || riders <= 192);
-    if (M <= 16 || r <= 0 || ride) {
+    if (always || ride) {
         p.token_tiles = (int)((M + 15) / 16);
         p.k_per_split = PP_SLICE;
         p.splits = r > 0 ? (int)((K + PP_SLICE - 1) / PP_SLICE) : 1;
