@@ -174,9 +174,10 @@ BWLA_API bwla_status_t bwla_unpack_signs(const bwla_layer_t* layer, int8_t* d_sg
  * arrival counters, and, for a few tokens of a layer with a large factor R1 (six or more 16-row
  * tiles), the rotated values in fp32 and their extremes between the two launches the rotation
  * then takes.  For more than 64 tokens of a layer that the sparse GEMM serves (K a multiple of 128, N >= 32) it also
- * counts the room in which bwla_linear_forward_bits and bwla_decode_forward lay out the codes for that kernel (about
- * M K bytes, at the scratch's end); a scratch without it is accepted everywhere, and the dense kernel runs.  Returns 0
- * bytes when nothing is used.
+ * counts the room in which bwla_linear_forward_bits and bwla_decode_forward lay out the codes for that kernel
+ * (bwla_code_room_size, about M K bytes, at the scratch's end, whatever N: the scratch serves other layers of these
+ * columns too); a scratch without it is accepted everywhere, and the dense kernel runs.  Returns 0 bytes when nothing is
+ * used.
  * The scratch must be zero-filled once when it is allocated and then left to the library: its
  * first 7168 bytes are the exchange area of bwla_decode_forward's single-launch kernel (an epoch
  * that every such launch moves on, arrival counts that every launch returns to zero, partial
@@ -252,6 +253,18 @@ BWLA_API bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const
                                   size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream);
 
 /*
+ * The same with a room for the codes that is apart from the scratch, for callers whose calls share one scratch and may
+ * overlap where they do not use it: bwla_linear_forward reads its arguments and writes d_Y, and so do these but for d_room.
+ *   d_room   room_bytes >= bwla_code_room_size(layer, M), 16-byte aligned, need not be zeroed; with less (or NULL) the call is
+ *            bwla_linear_forward.  Two calls may share one at the same time if they read the same codes of the same M and K
+ *            (they write the same bytes), or else one after the other.  Serves fewer tokens too.
+ */
+BWLA_API bwla_status_t bwla_code_room_size(const bwla_layer_t* layer, int64_t M, size_t* bytes);
+BWLA_API bwla_status_t bwla_linear_forward_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_room,
+                                  size_t room_bytes, float* d_Y, int32_t* d_acc, void* stream);
+
+/*
  * The whole forward of one layer, steps 1-5 above (paper Sec. 3.1, Sec. 4.1, Eq. 3-4, Sec. 3.2), in
  * one call: what bwla_rotate_quant followed by bwla_linear_forward compute, with the same
  * buffers (d_q, d_scale, d_qsum, d_T are still written; same arguments, same errors) and to the
@@ -279,6 +292,11 @@ BWLA_API bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const
                                                 int64_t M, int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T,
                                                 void* d_ws, size_t ws_bytes, float* d_Y, int32_t* d_acc,
                                                 void* stream);
+/* The same with a room for the codes of the caller's (bwla_linear_forward_room); the end of d_ws is not used for it. */
+BWLA_API bwla_status_t bwla_decode_forward_room(const bwla_layer_t* layer, const void* d_X, int xdtype, int act_bits,
+                                                int64_t M, int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T,
+                                                void* d_ws, size_t ws_bytes, void* d_room, size_t room_bytes,
+                                                float* d_Y, int32_t* d_acc, void* stream);
 
 /*
  * Whether bwla_decode_forward serves (layer, xdtype, M) with its single-launch kernel: *launches
@@ -334,7 +352,10 @@ BWLA_API bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, con
 BWLA_API bwla_status_t bwla_linear_forward_swiglu_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
                                   const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_scratch,
                                   size_t scratch_bytes, void* d_H, void* d_ws, size_t ws_bytes, void* stream);
-
+/* ... and what bwla_linear_forward_room is to it. */
+BWLA_API bwla_status_t bwla_linear_forward_swiglu_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_room,
+                                  size_t room_bytes, void* d_H, void* d_ws, size_t ws_bytes, void* stream);
 
 /*
  * 4-bit activation codes two to a byte (paper Table 3 reports W1A4: codes in [-7, 7]), which halves the

@@ -22,7 +22,8 @@ EXPORTS = ["bwla_status_string", "bwla_version", "bwla_kron_factor", "bwla_packe
            "bwla_linear_forward_swiglu", "bwla_decode_forward_static", "bwla_probe_hbm_read",
            "bwla_probe_mfma_int8", "bwla_decode_forward_launches", "bwla_decode_forward_bits", "bwla_pack_codes_a4",
            "bwla_linear_forward_a4", "bwla_probe_empty_launch", "bwla_probe_load_latency", "bwla_probe_clock",
-           "bwla_linear_forward_bits", "bwla_linear_forward_swiglu_bits"]
+           "bwla_linear_forward_bits", "bwla_linear_forward_swiglu_bits", "bwla_code_room_size", "bwla_decode_forward_room",
+           "bwla_linear_forward_room", "bwla_linear_forward_swiglu_room"]
 
 
 class BwlaLayer(Structure):
@@ -94,6 +95,11 @@ def load() -> ctypes.CDLL:
                                              c_void_p, c_size_t, c_void_p, c_void_p, c_void_p]
     lib.bwla_linear_forward_swiglu_bits.argtypes = [POINTER(BwlaLayer), c_void_p, c_void_p, c_void_p, c_void_p, c_int64,
                                                     c_int, c_void_p, c_size_t, c_void_p, c_void_p, c_size_t, c_void_p]
+    lib.bwla_linear_forward_room.argtypes = lib.bwla_linear_forward_bits.argtypes
+    lib.bwla_linear_forward_swiglu_room.argtypes = lib.bwla_linear_forward_swiglu_bits.argtypes
+    lib.bwla_code_room_size.argtypes = [POINTER(BwlaLayer), c_int64, POINTER(c_size_t)]
+    lib.bwla_decode_forward_room.argtypes = [POINTER(BwlaLayer), c_void_p, c_int, c_int, c_int64, c_void_p, c_void_p, c_void_p,
+                                             c_void_p, c_void_p, c_size_t, c_void_p, c_size_t, c_void_p, c_void_p, c_void_p]
     for name in EXPORTS:
         if name not in ("bwla_status_string", "bwla_version"):
             getattr(lib, name).restype = c_int
@@ -225,8 +231,26 @@ def psp_workspace_size(layer: PackedLayer, M: int) -> int:
     return out.value
 
 
+def code_room_size(layer: PackedLayer, M: int) -> int:
+    out = c_size_t()
+    _check(load().bwla_code_room_size(layer._ref, M, byref(out)), "bwla_code_room_size")
+    return out.value
+
+
 class Activations:
-    """Caller-owned outputs of bwla_rotate_quant for M tokens (allocated once, reused)."""
+    """Caller-owned outputs of bwla_rotate_quant for M tokens (allocated once, reused).
+
+    ws is the scratch of rotate_quant and decode_forward; several Activations may share one, and calls that use it must not
+    overlap.  room (None where nothing uses it) is where decode_forward, linear_forward and linear_forward_swiglu lay out
+    this object's codes for the GEMM on the sparse instructions.  It belongs to this object alone, as q does: calls on
+    different Activations may overlap whatever scratch they share, and so may linear_forward calls of several layers on one
+    (they write the same bytes there)."""
+
+    room = None
+    room_bytes = 0
+    # width of the codes that rotate_quant wrote last: which GEMM is worth starting (the library looks at the codes,
+    # so q may be overwritten with others); 8 = any
+    act_bits = 8
 
     def __init__(self, layer: PackedLayer, M: int):
         import torch
@@ -237,12 +261,12 @@ class Activations:
         self.scale = torch.empty((M,), dtype=torch.float32, device=dev)
         self.qsum = torch.empty((M,), dtype=torch.int32, device=dev)
         self.T = torch.empty((M, d.r), dtype=torch.float32, device=dev) if d.r > 0 else None
-        ws = psp_workspace_size(layer, M)
+        self.room_bytes = code_room_size(layer, M)
+        if self.room_bytes:
+            self.room = torch.empty(self.room_bytes, dtype=torch.uint8, device=dev)
+        ws = psp_workspace_size(layer, M) - self.room_bytes                 # (a scratch may have the room at its end: not this one)
         self.ws_bytes = ws
         self.ws = torch.zeros(max(ws, 16), dtype=torch.uint8, device=dev)   # zero-filled once, as the ABI asks
-        # width of the codes that rotate_quant wrote last: which GEMM is worth starting (the library looks at the codes,
-        # so q may be overwritten with others); 8 = any
-        self.act_bits = 8
 
 
 def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> Activations:
@@ -263,7 +287,12 @@ def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> 
 def decode_forward(layer: PackedLayer, X, act: Activations, Y, acc=None, act_bits: int = 6):
     """bwla_rotate_quant + bwla_linear_forward in one call (one kernel launch where possible)."""
     xd = _xdtype(X)
-    if act_bits == 6:
+    if act.room is not None:
+        _check(load().bwla_decode_forward_room(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
+                                               _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
+                                               _ptr(act.room), act.room_bytes, _ptr(Y), _ptr(acc), _stream()),
+               "bwla_decode_forward_room")
+    elif act_bits == 6:
         _check(load().bwla_decode_forward(layer._ref, _ptr(X), xd, X.shape[0], _ptr(act.q), _ptr(act.scale),
                                           _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes, _ptr(Y), _ptr(acc),
                                           _stream()), "bwla_decode_forward")
@@ -347,13 +376,14 @@ def swiglu_workspace_size(layer: PackedLayer, M: int) -> int:
 
 
 def linear_forward_swiglu(layer: PackedLayer, act: Activations, H, ws=None):
-    """H (bf16, M x N/2) = silu(gate) * up of a layer whose rows interleave gate and up channels."""
+    """H (bf16, M x N/2) = silu(gate) * up of a layer whose rows interleave gate and up channels.  Of `act` only room is
+    written; ws is the gating workspace (swiglu_workspace_size)."""
     nbytes = 0 if ws is None else ws.numel() * ws.element_size()
     if act.act_bits <= 7:
-        _check(load().bwla_linear_forward_swiglu_bits(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum),
-                                                      _ptr(act.T), act.M, act.act_bits, _ptr(act.ws), act.ws_bytes,
+        _check(load().bwla_linear_forward_swiglu_room(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum),
+                                                      _ptr(act.T), act.M, act.act_bits, _ptr(act.room), act.room_bytes,
                                                       _ptr(H), _ptr(ws), nbytes, _stream()),
-               "bwla_linear_forward_swiglu_bits")
+               "bwla_linear_forward_swiglu_room")
         return H
     _check(load().bwla_linear_forward_swiglu(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum),
                                              _ptr(act.T), act.M, _ptr(H), _ptr(ws), nbytes, _stream()),
@@ -362,10 +392,11 @@ def linear_forward_swiglu(layer: PackedLayer, act: Activations, H, ws=None):
 
 
 def linear_forward(layer: PackedLayer, act: Activations, Y, acc=None):
+    """Y from the codes in `act`, of which only room is written."""
     if act.act_bits <= 7:
-        _check(load().bwla_linear_forward_bits(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
-                                               act.M, act.act_bits, _ptr(act.ws), act.ws_bytes, _ptr(Y), _ptr(acc),
-                                               _stream()), "bwla_linear_forward_bits")
+        _check(load().bwla_linear_forward_room(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
+                                               act.M, act.act_bits, _ptr(act.room), act.room_bytes, _ptr(Y), _ptr(acc),
+                                               _stream()), "bwla_linear_forward_room")
         return Y
     _check(load().bwla_linear_forward(layer._ref, _ptr(act.q), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
                                       act.M, _ptr(Y), _ptr(acc), _stream()), "bwla_linear_forward")

@@ -77,20 +77,28 @@ size_t sparse_ws_start(size_t need) {
     const size_t first = (size_t)(BWLA_WS_HEAD + BWLA_PSP_COUNTER_BYTES);
     return (size_t)bwla_align256(need > first ? need : first);
 }
-// NULL: the scratch has no room, or the call does not use it
-void* sparse_ws(const bwla_layer_t* L, int64_t M, size_t need, void* d_ws, size_t ws_bytes) {
-    const uint64_t bytes = bwla_gemm_sparse_bytes(L, M);
-    if (bytes == 0 || d_ws == nullptr || ws_bytes < sparse_ws_start(need) + bytes) return nullptr;
-    return (char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255);
-}
 // what bwla_rotate_quant needs for M tokens of either type
 size_t rq_need(const bwla_layer_t* L, int64_t M) {
     const size_t a = rq_ws_bytes(L, bwla_psp_plan_of(L, M, BWLA_X_BF16), M);
     const size_t b = rq_ws_bytes(L, bwla_psp_plan_of(L, M, BWLA_X_F32), M);
     return a > b ? a : b;
 }
-void* sparse_ws_of(const bwla_layer_t* L, int64_t M, void* d_ws, size_t ws_bytes) {
-    return sparse_ws(L, M, rq_need(L, M), d_ws, ws_bytes);
+// The room that a call may lay codes out in: a caller's own (bwla_code_room_size), or the end of its scratch.
+struct CodeRoom {
+    void* p;                                            // NULL: the dense kernel
+    size_t bytes;
+};
+CodeRoom room_of_scratch(const bwla_layer_t* L, int64_t M, int act_bits, void* d_ws, size_t ws_bytes) {
+    if (act_bits > 7 || M <= GS_MIN_TOKENS || M > (int64_t)1 << 24 || d_ws == nullptr) return {nullptr, 0};
+    const uint64_t bytes = bwla_gemm_sparse_bytes(L, M);
+    if (bytes == 0 || ws_bytes < sparse_ws_start(rq_need(L, M)) + bytes) return {nullptr, 0};
+    return {(char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255), (size_t)bytes};
+}
+// tile of the sparse GEMM for codes of this width, -1: the dense kernel
+int sparse_pick(const bwla_layer_t* L, int64_t M, int act_bits, const CodeRoom& room) {
+    if (act_bits > 7 || M <= GS_MIN_TOKENS || M > (int64_t)1 << 24 || room.p == nullptr) return -1;
+    if (room.bytes < bwla_gemm_sparse_bytes(L, M)) return -1;
+    return bwla_gemm_sparse_pick(L, M);
 }
 inline void* ws_body(void* d_ws) { return d_ws ? (char*)d_ws + BWLA_WS_HEAD : nullptr; }
 
@@ -273,7 +281,16 @@ bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_t M, size
         if (n > need) need = n;
     }
     const uint64_t sparse = bwla_gemm_sparse_bytes(layer, M);
-    *bytes = sparse == 0 ? need : sparse_ws_start(need) + (size_t)bwla_align256(sparse);
+    *bytes = sparse == 0 ? need : sparse_ws_start(need) + (size_t)sparse;
+    return BWLA_OK;
+}
+
+bwla_status_t bwla_code_room_size(const bwla_layer_t* layer, int64_t M, size_t* bytes) {
+    if (!bytes) return BWLA_ERR_NULL;
+    bwla_status_t s = check_layer(layer);
+    if (s != BWLA_OK) return s;
+    if (M <= 0) return BWLA_ERR_SHAPE;
+    *bytes = (size_t)bwla_gemm_sparse_bytes(layer, M);
     return BWLA_OK;
 }
 
@@ -307,9 +324,10 @@ bwla_status_t bwla_rotate_quant_bits(const bwla_layer_t* layer, const void* d_X,
     return BWLA_OK;
 }
 
-bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_X, int xdtype, int act_bits, int64_t M,
-                                  int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T, void* d_ws,
-                                  size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream) {
+// (own: the room for the codes is the caller's, and not the end of the scratch)
+static bwla_status_t whole_forward(const bwla_layer_t* layer, const void* d_X, int xdtype, int act_bits, int64_t M,
+                                   int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T, void* d_ws,
+                                   size_t ws_bytes, const CodeRoom* own, float* d_Y, int32_t* d_acc, void* stream) {
     if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
@@ -319,7 +337,7 @@ bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_
     if (M <= 0 || M > (int64_t)1 << 24) return BWLA_ERR_SHAPE;
     if (xdtype != BWLA_X_F32 && xdtype != BWLA_X_BF16) return BWLA_ERR_UNSUPPORTED;
     if (!aligned16(d_X) || !aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) ||
-        (d_ws && !aligned16(d_ws)) || (d_acc && !aligned16(d_acc)))
+        (d_ws && !aligned16(d_ws)) || (d_acc && !aligned16(d_acc)) || (own && !aligned16(own->p)))
         return BWLA_ERR_ALIGN;
     const bwla_psp_plan plan = bwla_psp_plan_of(layer, M, xdtype);
     const size_t need = rq_ws_bytes(layer, plan, M);
@@ -333,7 +351,22 @@ bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_
     if (done) return BWLA_OK;
     s = bwla_rotate_quant_bits(layer, d_X, xdtype, act_bits, M, d_q, d_scale, d_qsum, d_T, d_ws, ws_bytes, stream);
     if (s != BWLA_OK) return s;
-    return bwla_linear_forward_bits(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, d_ws, ws_bytes, d_Y, d_acc, stream);
+    const CodeRoom room = own ? *own : room_of_scratch(layer, M, act_bits, d_ws, ws_bytes);
+    return bwla_linear_forward_room(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, room.p, room.bytes, d_Y, d_acc, stream);
+}
+
+bwla_status_t bwla_decode_forward_bits(const bwla_layer_t* layer, const void* d_X, int xdtype, int act_bits, int64_t M,
+                                  int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T, void* d_ws,
+                                  size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream) {
+    return whole_forward(layer, d_X, xdtype, act_bits, M, d_q, d_scale, d_qsum, d_T, d_ws, ws_bytes, nullptr, d_Y, d_acc, stream);
+}
+
+bwla_status_t bwla_decode_forward_room(const bwla_layer_t* layer, const void* d_X, int xdtype, int act_bits, int64_t M,
+                                       int8_t* d_q, float* d_scale, int32_t* d_qsum, float* d_T, void* d_ws,
+                                       size_t ws_bytes, void* d_room, size_t room_bytes, float* d_Y, int32_t* d_acc,
+                                       void* stream) {
+    const CodeRoom own{d_room, room_bytes};
+    return whole_forward(layer, d_X, xdtype, act_bits, M, d_q, d_scale, d_qsum, d_T, d_ws, ws_bytes, &own, d_Y, d_acc, stream);
 }
 
 bwla_status_t bwla_decode_forward(const bwla_layer_t* layer, const void* d_X, int xdtype, int64_t M,
@@ -418,6 +451,23 @@ bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8_t* d_q, 
     return e == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
+bwla_status_t bwla_linear_forward_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                       const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_room,
+                                       size_t room_bytes, float* d_Y, int32_t* d_acc, void* stream) {
+    if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
+    if (d_room && !aligned16(d_room)) return BWLA_ERR_ALIGN;
+    bwla_status_t s = check_layer(layer);
+    if (s != BWLA_OK) return s;
+    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes});
+    if (pick < 0) return bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream);
+    if (!d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
+    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
+    if (!aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) || (d_acc && !aligned16(d_acc)))
+        return BWLA_ERR_ALIGN;
+    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, d_Y, d_acc, (hipStream_t)stream, d_room) == hipSuccess
+               ? BWLA_OK : BWLA_ERR_HIP;
+}
+
 bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
                                        const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits, void* d_ws,
                                        size_t ws_bytes, float* d_Y, int32_t* d_acc, void* stream) {
@@ -425,15 +475,8 @@ bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const int8_t* 
     if (d_ws && !aligned16(d_ws)) return BWLA_ERR_ALIGN;
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
-    void* z = act_bits <= 7 && M > GS_MIN_TOKENS && M <= (int64_t)1 << 24 ? sparse_ws_of(layer, M, d_ws, ws_bytes) : nullptr;
-    const int pick = z != nullptr ? bwla_gemm_sparse_pick(layer, M) : -1;
-    if (pick < 0) return bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream);
-    if (!d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
-    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
-    if (!aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) || (d_acc && !aligned16(d_acc)))
-        return BWLA_ERR_ALIGN;
-    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, d_Y, d_acc, (hipStream_t)stream, z) == hipSuccess
-               ? BWLA_OK : BWLA_ERR_HIP;
+    const CodeRoom room = room_of_scratch(layer, M, act_bits, d_ws, ws_bytes);
+    return bwla_linear_forward_room(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, room.p, room.bytes, d_Y, d_acc, stream);
 }
 
 bwla_status_t bwla_pack_codes_a4(const int8_t* d_q, int64_t M, int64_t K, uint8_t* d_q4, void* stream) {
@@ -504,23 +547,35 @@ bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t
                                                                                                     : BWLA_ERR_HIP;
 }
 
+bwla_status_t bwla_linear_forward_swiglu_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                              const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits,
+                                              void* d_room, size_t room_bytes, void* d_H, void* d_ws, size_t ws_bytes,
+                                              void* stream) {
+    if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
+    if (d_room && !aligned16(d_room)) return BWLA_ERR_ALIGN;
+    size_t need = 0;
+    bwla_status_t s = bwla_swiglu_workspace_size(layer, M, &need);
+    if (s != BWLA_OK) return s;
+    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes});
+    if (pick < 0) return bwla_linear_forward_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream);
+    if (!d_q || !d_scale || !d_qsum || !d_H) return BWLA_ERR_NULL;
+    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
+    if (!aligned16(d_q) || !aligned16(d_H) || (d_T && !aligned16(d_T))) return BWLA_ERR_ALIGN;
+    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, nullptr, nullptr, (hipStream_t)stream, d_room,
+                                   (uint16_t*)d_H) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
+}
+
 bwla_status_t bwla_linear_forward_swiglu_bits(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
                                               const int32_t* d_qsum, const float* d_T, int64_t M, int act_bits,
                                               void* d_scratch, size_t scratch_bytes, void* d_H, void* d_ws, size_t ws_bytes,
                                               void* stream) {
     if (act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
     if (d_scratch && !aligned16(d_scratch)) return BWLA_ERR_ALIGN;
-    size_t need = 0;
-    bwla_status_t s = bwla_swiglu_workspace_size(layer, M, &need);
+    bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
-    void* z = act_bits <= 7 && M > GS_MIN_TOKENS ? sparse_ws_of(layer, M, d_scratch, scratch_bytes) : nullptr;
-    const int pick = z != nullptr ? bwla_gemm_sparse_pick(layer, M) : -1;
-    if (pick < 0) return bwla_linear_forward_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream);
-    if (!d_q || !d_scale || !d_qsum || !d_H) return BWLA_ERR_NULL;
-    if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
-    if (!aligned16(d_q) || !aligned16(d_H) || (d_T && !aligned16(d_T))) return BWLA_ERR_ALIGN;
-    return bwla_launch_gemm_sparse(layer, pick, d_q, d_scale, d_T, M, nullptr, nullptr, (hipStream_t)stream, z,
-                                   (uint16_t*)d_H) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
+    const CodeRoom room = room_of_scratch(layer, M, act_bits, d_scratch, scratch_bytes);
+    return bwla_linear_forward_swiglu_room(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, room.p, room.bytes, d_H, d_ws,
+                                           ws_bytes, stream);
 }
 
 }  // extern "C"

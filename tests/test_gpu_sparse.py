@@ -89,7 +89,7 @@ def test_same_bits_as_the_dense_kernel(M, K, N, r):
     from paper_2605_00422_amd import binding as B
     layer, g = _layer(M, K, N, r)
     act = _acts(layer, M, K, g, -64, 63)
-    room = act.ws[-(M * K // 2):]
+    room, ws = act.room, act.ws.clone()
     room.fill_(0x5a)                                        # where the codes are laid out anew
     dense = _run(layer, act, N, 8, N % 2 == 0)
     assert bool((room == 0x5a).all())                       # (the dense kernel leaves it alone)
@@ -99,8 +99,9 @@ def test_same_bits_as_the_dense_kernel(M, K, N, r):
     sgn, _ = B.unpack_signs(layer)
     want = act.q.float() @ sgn.float().t()                  # exact: |acc| <= 64 K < 2^24
     assert torch.equal(sparse[1].float(), want)
-    # a scratch without the room: the dense kernel
-    act.ws_bytes -= M * K // 2
+    assert torch.equal(act.ws, ws)                          # the scratch, which another Activations may use meanwhile
+    # less than the room: the dense kernel
+    act.room_bytes -= 256
     room.fill_(0x5a)
     _same(_run(layer, act, N, 7, N % 2 == 0), dense)
     assert bool((room == 0x5a).all())
@@ -127,7 +128,7 @@ def test_codes_wider_than_announced_are_found(M, K, N, r, where):
 @pytest.mark.parametrize("bits,centered,asym,x", [(6, False, False, torch.bfloat16), (7, False, True, torch.bfloat16),
                                                   (4, True, True, torch.float32), (8, True, False, torch.bfloat16)])
 def test_whole_layer(bits, centered, asym, x):
-    """decode_forward with the scratch's room and without it."""
+    """decode_forward with the room for the codes and without it."""
     from paper_2605_00422_amd import binding as B
     M, K, N, r = 1111, 4096, 22001, 20
     layer, g = _layer(M, K, N, r, centered, asym)
@@ -136,13 +137,51 @@ def test_whole_layer(bits, centered, asym, x):
     for room in (True, False):
         act = B.Activations(layer, M)
         if not room:
-            act.ws_bytes -= M * K // 2
+            act.room_bytes -= 256
         Y = torch.full((M, N), float("nan"), device=DEV)
         acc = torch.full((M, N), -7, dtype=torch.int32, device=DEV)
         B.decode_forward(layer, X, act, Y, acc, act_bits=bits)
         torch.cuda.synchronize()
         outs.append((Y, acc, act.q, act.T, act.scale))
     _same(*outs)
+
+
+@pytest.mark.parametrize("M,K,N,r", [SHAPES[0], SHAPES[8]])
+def test_room_at_the_end_of_a_scratch(M, K, N, r):
+    """The calls of the C ABI that take one scratch for everything: in one of bwla_psp_workspace_size they lay the codes
+    out in its last bytes, in a smaller one nowhere, and the results are the same."""
+    from ctypes import byref
+    from paper_2605_00422_amd import binding as B
+    lib, p, st = B.load(), B._ptr, B._stream()
+    layer, g = _layer(M, K, N, r)
+    X = torch.randn(M, K, device=DEV, generator=g).to(torch.bfloat16)
+    act = B.Activations(layer, M)
+    want = B.decode_forward(layer, X, act, torch.empty(M, N, device=DEV)).clone()
+    H = torch.empty(M, N // 2, dtype=torch.bfloat16, device=DEV) if N % 2 == 0 else None
+    wantH = B.linear_forward_swiglu(layer, act, H).clone() if H is not None else None
+    nbytes = B.psp_workspace_size(layer, M)
+    codes = (p(act.q), p(act.scale), p(act.qsum), p(act.T))
+    for less in (0, 256):
+        ws = torch.zeros(nbytes, dtype=torch.uint8, device=DEV)
+        room = ws[-act.room_bytes:]
+        n = nbytes - less
+
+        def used():
+            torch.cuda.synchronize()
+            u = bool(room[:-256].any())
+            room.zero_()
+            return u
+
+        Y = torch.full((M, N), float("nan"), device=DEV)
+        assert lib.bwla_decode_forward(byref(layer.desc), p(X), B.BWLA_X_BF16, M, *codes, p(ws), n, p(Y), None, st) == B.BWLA_OK
+        assert used() == (less == 0) and torch.equal(Y, want)
+        Y.fill_(float("nan"))
+        assert lib.bwla_linear_forward_bits(byref(layer.desc), *codes, M, 6, p(ws), n, p(Y), None, st) == B.BWLA_OK
+        assert used() == (less == 0) and torch.equal(Y, want)
+        if H is not None:
+            H.fill_(float("nan"))
+            assert lib.bwla_linear_forward_swiglu_bits(byref(layer.desc), *codes, M, 6, p(ws), n, p(H), None, 0, st) == B.BWLA_OK
+            assert used() == (less == 0) and torch.equal(H, wantH)
 
 
 def test_one_scratch_for_calls_of_several_sizes():
