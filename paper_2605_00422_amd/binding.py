@@ -280,7 +280,7 @@ def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> 
         _check(load().bwla_rotate_quant_bits(layer._ref, _ptr(X), xd, act_bits, X.shape[0], _ptr(act.q),
                                              _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws),
                                              act.ws_bytes, _stream()), "bwla_rotate_quant_bits")
-    act.act_bits = act_bits
+    act.act_bits = int(act_bits)
     return act
 
 
@@ -300,7 +300,7 @@ def decode_forward(layer: PackedLayer, X, act: Activations, Y, acc=None, act_bit
         _check(load().bwla_decode_forward_bits(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
                                                _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
                                                _ptr(Y), _ptr(acc), _stream()), "bwla_decode_forward_bits")
-    act.act_bits = act_bits
+    act.act_bits = int(act_bits)
     return Y
 
 

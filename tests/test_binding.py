@@ -78,3 +78,21 @@ def test_objects_from_before_there_was_a_room(lib):
     B.linear_forward(layer, act, Y)
     assert [n for n, _ in lib.calls] == ["bwla_linear_forward", "bwla_linear_forward_swiglu", "bwla_decode_forward",
                                          "bwla_linear_forward_room"]
+
+
+@pytest.mark.parametrize("bits", [6.0, torch.tensor(6), True + 5])
+@pytest.mark.parametrize("call", ["rotate_quant", "decode_forward"])
+def test_width_of_the_codes_in_any_type_that_these_calls_take(lib, call, bits):
+    """The GEMM behind them gets it as a plain integer, as ctypes asks."""
+    layer = _layer()
+    act = B.Activations(layer, 100)
+    X, Y = torch.empty(100, 512, dtype=torch.bfloat16), torch.empty(100, 64)
+    if call == "rotate_quant":
+        B.rotate_quant(layer, X, act, bits)
+    else:
+        B.decode_forward(layer, X, act, Y, act_bits=bits)
+    del lib.calls[:]
+    B.linear_forward(layer, act, Y)
+    B.linear_forward_swiglu(layer, act, Y)
+    for name, args in lib.calls:
+        assert name.endswith("_room") and type(args[6]) is int and args[6] == 6
