@@ -499,17 +499,18 @@ __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
 #pragma unroll 1
                 for (int p0 = 0; p0 < 32 * PR; p0 += 64) {
                     const int p = p0 + lane, row = p / PR, c = p % PR;
-                    const uint4 y = *reinterpret_cast<const uint4*>(mine + (c >> 1) * 4096 + row * 32 + (c & 1) * 16);
+                    const v4i y = *reinterpret_cast<const v4i*>(mine + (c >> 1) * 4096 + row * 32 + (c & 1) * 16);
                     if (row < rows && h_base + c * 8 < N2)
-                        *reinterpret_cast<uint4*>(H + (int64_t)(mrow0 + row) * N2 + h_base + c * 8) = y;
+                        *reinterpret_cast<v4i*>(H + (int64_t)(mrow0 + row) * N2 + h_base + c * 8) = y;
                 }
             } else {
                 constexpr int PR = NT * 16;
 #pragma unroll 1
                 for (int p0 = 0; p0 < 32 * PR; p0 += 64) {
                     const int p = p0 + lane, row = p / PR, c = p % PR;
-                    const uint16_t y = *reinterpret_cast<const uint16_t*>(mine + (c >> 4) * 4096 + row * 32 + (c & 15) * 2);
-                    if (row < rows && h_base + c < N2) H[(int64_t)(mrow0 + row) * N2 + h_base + c] = y;
+                    // (the pair, as it was written: the compiler takes a 16-bit read for one of something else)
+                    const uint32_t y = *reinterpret_cast<const uint32_t*>(mine + (c >> 4) * 4096 + row * 32 + ((c & 15) >> 1) * 4);
+                    if (row < rows && h_base + c < N2) H[(int64_t)(mrow0 + row) * N2 + h_base + c] = (uint16_t)(y >> ((c & 1) * 16));
                 }
             }
         }

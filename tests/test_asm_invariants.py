@@ -273,3 +273,10 @@ def test_sparse_gemm_loop_structure(sparse_asm, tile, gated):
     for i in flags:
         regs = _registers(lines[i].split(",")[0])
         assert not any(_registers(l) & regs for l in lines[i + 1:wait])
+
+
+def test_sparse_gemm_reads_h_from_lds_as_it_was_written(sparse_asm):
+    """The gated epilogue leaves h in LDS as 32-bit pairs and other lanes read it; a 16-bit scalar read is one that the
+    compiler may assume to be of something else, and so move in front of the writes."""
+    assert any(l.startswith("ds_write_b32") or l.startswith("ds_write2_b32") for l in sparse_asm)
+    assert not any(l.startswith(("ds_read_u16", "ds_read_i16")) for l in sparse_asm)
