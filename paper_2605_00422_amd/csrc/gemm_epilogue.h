@@ -24,6 +24,7 @@
 #pragma once
 
 #include "bwla_internal.h"
+#include "gemm_tiles.h"
 
 namespace {
 
@@ -35,8 +36,6 @@ struct EpArgs {
     float* Y; int M, N; int32_t* acc_out; uint16_t* H;
 };
 constexpr int EP_JC = 4;                                         // steps of 16 ranks at a time
-// bytes of LDS that EpRows fills
-inline __host__ __device__ size_t ep_rows_bytes(int tokens, int r) { return (size_t)tokens * ((r + 15) / 16 * 64 + 12); }
 
 // The rows of T of a workgroup's tokens as MFMA operands in LDS: [token / 32][16 ranks][hi, lo][lane][8] fp16, and behind
 // them, for each token, 2^k scale, 2^-k and the code sum.

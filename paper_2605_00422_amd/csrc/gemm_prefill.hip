@@ -208,7 +208,7 @@ hipError_t launch_cfg(const bwla_layer_t* L, const int8_t* dq, const float* dsca
 constexpr int GD_MT = 2;
 constexpr int GD_ROWS = GD_MT * 32;                 // token rows per wavefront
 static_assert(GD_ROWS == GD_TILE_TOKENS, "gemm_tiles.h");
-constexpr int GD_TILE = GD_ROWS * 128;              // bytes of one private code tile
+constexpr int GD_TILE = GD_ROWS * 128;              // bytes of one private code tile (gd_lds_bytes)
 
 // 16-byte position of piece `c16` of row `row` inside its 128-byte LDS row; the XOR key makes
 // the column-wise operand reads conflict free
@@ -560,16 +560,15 @@ __global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_pre
 #undef GD_PARAMS
 #undef GD_ARGS
 
-template <int NTL, int WK, int NB, int WN>
+template <int I>
 hipError_t launch_streaming(const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
                             const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH,
                             bool a4) {
+    constexpr int NTL = GD_TILES[I].ntl, WK = GD_TILES[I].wk, NB = GD_TILES[I].nb, WN = GD_TILES[I].wn;
     constexpr int BM = GD_ROWS, BN = WN * NTL * 32;
     const char* blob = (const char*)L->d_blob;
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((L->N + BN - 1) / BN);
-    // the rings, then the epilogue's tiles
-    const size_t ring = (size_t)WK * NB * GD_TILE, tail = (size_t)(WK > 1 ? WK * GD_MT * NTL : WN) * 4096 + ep_rows_bytes(GD_ROWS, L->r);
-    const size_t lds = ring > tail ? ring : tail;
+    const size_t lds = gd_lds_bytes(GD_TILES[I], L->r);
     auto launch = [&](auto kern) -> hipError_t {
         hipError_t e = bwla_ensure_lds((const void*)kern, lds);
         if (e != hipSuccess) return e;
@@ -594,9 +593,7 @@ hipError_t launch_streaming(const bwla_layer_t* L, const int8_t* dq, const float
 template <int I>
 hipError_t launch_tile(int pick, const bwla_layer_t* L, const int8_t* dq, const float* dscale, const int32_t* dqsum,
                        const float* dT, int64_t M, float* dY, int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4) {
-    constexpr GdTile v = GD_TILES[I];
-    if (pick == I)
-        return launch_streaming<v.ntl, v.wk, v.nb, v.wn>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
+    if (pick == I) return launch_streaming<I>(L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
     if constexpr (I + 1 < GD_NTILES)
         return launch_tile<I + 1>(pick, L, dq, dscale, dqsum, dT, M, dY, dacc, st, dH, a4);
     return hipErrorInvalidValue;

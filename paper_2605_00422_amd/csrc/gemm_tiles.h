@@ -19,11 +19,15 @@
 // rings) moved no average by more than 0.1 % and are not built.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
+
+// bytes of LDS that the epilogue's rows of T fill (EpRows in gemm_epilogue.h)
+inline size_t ep_rows_bytes(int tokens, int r) { return (size_t)tokens * ((r + 15) / 16 * 64 + 12); }
 
 struct GdTile {
     int ntl, wk, nb, wn;          // 32-channel tiles a wavefront; wavefronts that share K; ring depth; wavefronts side by side
-    int resident;                 // workgroups a CU holds (LDS of the tile rings, registers)
+    int resident;                 // workgroups a CU holds (LDS, registers) up to rank 112
     float start, base[4], slice[4], idle, low, a4;
 };
 constexpr int GD_TILE_TOKENS = 64;
@@ -43,13 +47,29 @@ constexpr GdTile GD_TILES[] = {
 };
 constexpr int GD_NTILES = sizeof(GD_TILES) / sizeof(GD_TILES[0]);
 
+// LDS of a workgroup: the code rings, then in their place the epilogue's tiles and rows of T
+inline size_t gd_lds_bytes(const GdTile& v, int r) {
+    const size_t ring = (size_t)v.wk * v.nb * (GD_TILE_TOKENS * 128);
+    const size_t tail = (size_t)(v.wk > 1 ? v.wk * (GD_TILE_TOKENS / 32) * v.ntl : v.wn) * 4096 + ep_rows_bytes(GD_TILE_TOKENS, r);
+    return ring > tail ? ring : tail;
+}
+// Workgroups that a CU's 160 KiB hold: the rows of T grow with the rank, and from 113 on 64 x 96 in two no longer goes
+// twice, nor 64 x 64 with one ring four times.  (Taken for resident as before, they were chosen where half of them had to wait:
+// 2810 tokens of 19968 columns, 906 channels, rank 120 102.7 -> 64.2 us; 335 of 9728, 6927 channels 67.7 -> 39.0; 24 such
+// shapes 0.65 of the time on average, 0.83 at most.)
+inline int gd_resident(const GdTile& v, int r) {
+    const int fit = (int)(160 * 1024 / gd_lds_bytes(v, r));
+    return fit < v.resident ? fit : v.resident;
+}
+
 inline float gd_cost(const GdTile& v, int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4) {
     const int64_t bn = v.wn * v.ntl * 32;
     const int64_t tiles_n = (N + bn - 1) / bn, tiles = (M + GD_TILE_TOKENS - 1) / GD_TILE_TOKENS * tiles_n;
-    const int64_t cap = cus * v.resident;
+    const int resident = gd_resident(v, r);
+    const int64_t cap = cus * resident;
     const float slices = (float)(((K >> 7) + v.wk - 1) / v.wk);
     const int64_t full = tiles / cap, rem = tiles - full * cap;
-    float t = v.start + (float)full * (v.base[v.resident - 1] + v.slice[v.resident - 1] * slices);
+    float t = v.start + (float)full * (v.base[resident - 1] + v.slice[resident - 1] * slices);
     if (rem > 0) {
         const int share = (int)((rem + cus - 1) / cus);
         t += v.base[share - 1] + (v.slice[share - 1] - v.idle * ((float)share - (float)rem / (float)cus)) * slices;

@@ -132,3 +132,38 @@ def test_every_sparse_tile_is_reached(sparse_pick):
 ])
 def test_recorded_shapes_take_the_faster_kernel(sparse_pick, shape, tiles):
     assert sparse_pick([shape])[0] in tiles
+
+
+RESIDENT_DRIVER = """
+#include <cstdio>
+#include "gemm_tiles.h"
+int main() {
+    for (int r = 0; r <= 128; ++r)
+        for (int i = 0; i < GD_NTILES; ++i) {
+            const GdTile& v = GD_TILES[i];
+            // a cost of two rounds and nothing else: how many workgroups does it put side by side?
+            GdTile probe = v;
+            probe.start = probe.idle = probe.low = 0.0f;
+            for (int s = 0; s < 4; ++s) { probe.base[s] = 0.0f; probe.slice[s] = 1.0f; }
+            const long long bn = 32LL * v.ntl * v.wn, K = 128LL * v.wk * 1000;
+            int side = 0;
+            for (int s = 1; s <= 8; ++s)                // s x 256 tiles: one round of 1000 slices up to what is resident
+                if (gd_cost(probe, 64, K, s * 256 * bn, r, 256, false) < 1500.0f) side = s;
+            printf("%d %d %d %zu %d\\n", r, i, v.resident, gd_lds_bytes(v, r), side);
+        }
+}
+"""
+
+
+def test_workgroups_side_by_side_fit_the_lds(tmp_path):
+    """At every rank up to 128: the epilogue's rows of T grow with it.  Up to 112, which the costs were fitted to, all of
+    what the table says."""
+    (tmp_path / "res.cpp").write_text(RESIDENT_DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", str(tmp_path / "res"), str(tmp_path / "res.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "res")], text=True, capture_output=True, check=True).stdout.split("\n")
+    for line in out[:-1]:
+        r, i, resident, lds, side = map(int, line.split())
+        assert side * lds <= 160 * 1024, (r, i, side, lds)
+        assert side == min(resident, 160 * 1024 // lds), (r, i)
+        if r <= 112:
+            assert side == resident, (r, i)
