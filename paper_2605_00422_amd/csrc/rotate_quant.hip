@@ -26,6 +26,7 @@
 #include "rotate_bf16_device.h"
 #include "rotate_split_device.h"
 #include "psp_block_device.h"
+#include "psp_ride.h"
 
 namespace {
 
@@ -176,26 +177,14 @@ bool bwla_rotate_supported(int n1, int n2) {
 int bwla_rotate_tiles(int n1, int n2) { return (rq_pad16(n1) / 16) * (rq_pad16(n2) / 16); }
 int bwla_rotate_max_tiles() { return RQ_MAXT * RQ_WAVES; }
 
-bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes) {
+bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32) {
     bwla_psp_plan p;
     const int rp = (r + 15) & ~15;
-    // The projection rides in the rotation launch where its workgroups finish in the rotation's shadow: a rotation
-    // workgroup has a CU to itself and takes about 6 us + K / 1050, the CUs that the last round of them leaves free take a
-    // round of projection workgroups every 5.5 us.  A little beside the shadow is still less than the launch of its own
-    // that the projection needs otherwise (6 to 7 us), and so is a small round behind the rotation.  Not where the kernel
-    // that walks over the tokens serves (planes), which is the faster one by more.  Rotation + projection, riding / in a
-    // launch of its own, and the rotation alone: 8192 columns, rank 64: 128 tokens 16.7 / 21 / 13.3; 255 tokens
-    // 29.8 / 22.7 / 14.3; 25600, rank 32: 128 tokens 28.3 / 34 / 26.6; 5120, rank 32: 257 tokens 16.8 / 23 / 17.
-    // (ranks of more than two 16-column tiles are dealt to several workgroups per slice)
+    // ranks of more than two 16-column tiles are dealt to several workgroups per slice
     const int jg = rp > 16 * PP_GROUPJT ? (rp / 16 + PP_GROUPJT - 1) / PP_GROUPJT : 1;
     const bool always = M <= 16 || r <= 0;
     const int64_t riders = ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg, cus = always ? 1 : bwla_device_cus();
-    const int64_t beside = (cus - M % cus) % cus;              // CUs that the last round leaves free
-    const bool shadow = beside > 0 && 5.5f * (float)((riders + beside - 1) / beside) <= 9.0f + (float)K / 1050.0f;
-    // (short rows leave room for several workgroups a CU: there it is their number that counts, up to three a CU; 512
-    // columns, rank 64, 384 tokens 11.7 / 18.5)
-    const bool ride = !planes && M <= 768 && (K < 2048 ? M + riders <= 768 : shadow || riders <= 192);
-    if (always || ride) {
+    if (always || psp_rides(M, K, riders, cus, planes, f32)) {
         p.token_tiles = (int)((M + 15) / 16);
         p.k_per_split = PP_SLICE;
         p.splits = r > 0 ? (int)((K + PP_SLICE - 1) / PP_SLICE) : 1;
