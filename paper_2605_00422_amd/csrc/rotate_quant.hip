@@ -45,23 +45,33 @@ struct RqArgs {
     const uint16_t* R1p; const uint16_t* R2p;          // bf16 term planes of the factors
 };
 
+// workgroup pb behind the rotation's own in a launch that adds up the partial tiles of the launch in front (a.S < 0)
+__device__ __forceinline__ void psp_sum_at(const RqArgs& a, int pb) {
+    const int W = a.r <= 16 ? 16 : a.r <= 32 ? 32 : 64;                // bwla_psp_prefill_tile_cols
+    bwla_psp_sum_tiles(bwla_psp_tiles{a.partials, a.T, a.M, a.r, a.tp, -a.S, a.JG, W, (int)(gridDim.x - a.rot_blocks)}, pb);
+}
 // projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile
 template <bool BF16>
 __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    // (bf16 tokens only, and no argument of its own: the other role in the fp32 kernel, or 56 bytes more of arguments, cost
-    // small launches 0.1 us)
-    if (BF16 && a.S < 0) {
-        const int W = a.r <= 16 ? 16 : a.r <= 32 ? 32 : 64;            // bwla_psp_prefill_tile_cols
-        bwla_psp_sum_tiles(bwla_psp_tiles{a.partials, a.T, a.M, a.r, a.tp, -a.S, a.JG, W, (int)(gridDim.x - a.rot_blocks)}, pb);
-        return;
-    }
     const int s = pb % a.S, rest = pb / a.S;
     psp_block<BF16>(lds, a.X, a.M, a.K, a.r, a.U, a.T, a.counters, a.partials, a.S, rest / a.JG, s, a.tp, finish,
                     rest % a.JG, a.JG);
 }
+// (one kernel for both roles, told apart by a word that they load anyway: 56 bytes more of arguments cost small launches
+// 0.1 us)
+__device__ __forceinline__ void psp_either_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
+    if (a.S < 0) {
+        psp_sum_at(a, pb);
+        return;
+    }
+    psp_block_at<true>(lds, a, pb, finish);
+}
 
 // (up to 128 registers, of which fp32 activations spill six: two workgroups a CU where LDS lets them)
-template <bool BF16, int MAXT>
+// SUMS: the workgroups behind add up partial tiles, which is so for bf16 tokens alone.  A form of its own: with both roles
+// in one the rotation itself came out 4 to 6 % slower, in launches of either role and without any (164 x 32 factors: 8 tokens
+// 23.3 -> 22.0 us, 909 tokens 88.3 -> 83.3, 3057 tokens 359 -> 337).
+template <bool BF16, int MAXT, bool SUMS>
 __global__ __launch_bounds__(RQ_THREADS, MAXT <= 4 ? 4 : 2) void rotate_quant_kernel(RqArgs a) {
     extern __shared__ __align__(16) float lds[];
     if ((int64_t)blockIdx.x < a.rot_blocks) {
@@ -69,7 +79,8 @@ __global__ __launch_bounds__(RQ_THREADS, MAXT <= 4 ? 4 : 2) void rotate_quant_ke
                            a.asym != 0, a.shift != 0);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
-        psp_block_at<BF16>(reinterpret_cast<char*>(lds), a, pb);
+        if constexpr (SUMS) psp_sum_at(a, pb);
+        else psp_block_at<BF16>(reinterpret_cast<char*>(lds), a, pb);
     }
 }
 
@@ -83,7 +94,7 @@ __global__ __launch_bounds__(THREADS) void rotate_quant3_kernel(RqArgs a) {
                            a.tp, a.qmax, a.asym != 0, a.shift != 0);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
-        psp_block_at<true>(reinterpret_cast<char*>(lds), a, pb);
+        psp_either_at(reinterpret_cast<char*>(lds), a, pb);
     }
 }
 
@@ -97,7 +108,7 @@ __global__ __launch_bounds__(640) void rotate_split_kernel(RqArgs a) {
                            (int)(blockIdx.x - t * G), a.K, a.n1, a.n2, a.R1p, a.R2p, a.xs, a.pmax, a.qsum);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
-        psp_block_at<true>(reinterpret_cast<char*>(lds), a, pb, false);
+        psp_either_at(reinterpret_cast<char*>(lds), a, pb, false);
     }
 }
 
@@ -121,12 +132,12 @@ hipError_t launch_rotate3(const RqArgs& a, int64_t blocks, int threads, size_t l
 }
 
 // the smallest kernel that holds a wavefront's share of the tiles
-template <bool BF16>
+template <bool BF16, bool SUMS>
 hipError_t launch_rotate_f32(const RqArgs& a, unsigned blocks, size_t lds, hipStream_t st) {
     const int per_wave = (bwla_rotate_tiles(a.n1, a.n2) + RQ_WAVES - 1) / RQ_WAVES;
-    const auto kern = per_wave <= 2   ? rotate_quant_kernel<BF16, 2>
-                      : per_wave <= 4 ? rotate_quant_kernel<BF16, 4>
-                                      : rotate_quant_kernel<BF16, RQ_MAXT>;
+    const auto kern = per_wave <= 2   ? rotate_quant_kernel<BF16, 2, SUMS>
+                      : per_wave <= 4 ? rotate_quant_kernel<BF16, 4, SUMS>
+                                      : rotate_quant_kernel<BF16, RQ_MAXT, SUMS>;
     hipError_t e = bwla_ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<dim3(blocks), dim3(RQ_THREADS), lds, st>>>(a);
@@ -244,7 +255,10 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     // rotation, 8192 at 512 tokens 27.4 -> 21.3, 25600 at 1024 81.7 -> 76.9.  Beyond, there are few slices, the hand-over is
     // short and the sums stand behind the rotation: rank 64, 8192 columns at 1537 tokens 42.4 -> 38.8, at 4096 65.9 -> 67.0;
     // 1024 columns 23.0 -> 21.5 and 38.9 -> 44.7.)
-    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= 1792 && xdtype == BWLA_X_BF16;
+    // (Factors that the fp32 kernel rotates, at its own pace: 137 x 32, rank 96 200 tokens 31.0 -> 27.8; 163 x 32, rank 16 909
+    // tokens 108.0 -> 110.8, 1500 tokens 175.7 -> 179.0.)
+    const R3Shape s3 = r3_shape(L->n1, L->n2);
+    const bool leave = ru > 0 && !merged && plan.splits > 1 && M <= (s3.ok ? 1792 : 768) && xdtype == BWLA_X_BF16;
     if (leave) {
         const int64_t values = (int64_t)plan.token_tiles * plan.col_groups * 64 * plan.tile_cols;
         pblocks = values / 512 < 128 ? values / 512 : 128;
@@ -263,7 +277,6 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         if (e != hipSuccess) return e;
         if (done) return ru > 0 && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
     }
-    const R3Shape s3 = r3_shape(L->n1, L->n2);
     const size_t split_bytes = xdtype == BWLA_X_BF16 ? bwla_split_rotation_bytes(L, plan, M) : 0;
     if (split_bytes > 0 && dws != nullptr) {
         // few tokens, R1 too large for LDS: several workgroups per token, then a launch that quantizes
@@ -335,7 +348,9 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     }
     const size_t lds = plds > sh.lds_bytes ? plds : sh.lds_bytes;
     const unsigned grid = (unsigned)(M + pblocks);
-    e = xdtype == BWLA_X_BF16 ? launch_rotate_f32<true>(a, grid, lds, st) : launch_rotate_f32<false>(a, grid, lds, st);
+    e = xdtype != BWLA_X_BF16 ? launch_rotate_f32<false, false>(a, grid, lds, st)
+        : leave               ? launch_rotate_f32<true, true>(a, grid, lds, st)
+                              : launch_rotate_f32<true, false>(a, grid, lds, st);
     if (e != hipSuccess) return e;
     if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
     return hipSuccess;

@@ -280,3 +280,24 @@ def test_sparse_gemm_reads_h_from_lds_as_it_was_written(sparse_asm):
     compiler may assume to be of something else, and so move in front of the writes."""
     assert any(l.startswith("ds_write_b32") or l.startswith("ds_write2_b32") for l in sparse_asm)
     assert not any(l.startswith(("ds_read_u16", "ds_read_i16")) for l in sparse_asm)
+
+
+def test_rotation_in_fp32_keeps_the_summing_role_in_a_kernel_of_its_own():
+    """rotate_quant_kernel<BF16, tiles, SUMS>: the role that adds up partial tiles (sixteen plain loads in flight) costs the
+    rotation beside it 4 to 6 %, so the form that every other launch takes has none of it."""
+    lines = _device_asm("rotate_quant.hip")
+    forms = set()
+    for i, l in enumerate(lines):
+        m = re.match(r"_ZN.*rotate_quant_kernelILb([01])ELi(\d+)ELb([01])E.*:", l)
+        if not m:
+            continue
+        forms.add(tuple(map(int, m.groups())))
+        run = best = 0
+        for x in lines[i:next(j for j in range(i, len(lines)) if lines[j].startswith(".amdhsa_next_free_vgpr"))]:
+            if x.startswith("global_load_dword ") and not x.endswith("sc1"):
+                run += 1
+                best = max(best, run)
+            elif x.startswith("s_waitcnt") and "vmcnt" in x:
+                run = 0
+        assert (best >= 16) == (m.group(3) == "1"), (m.groups(), best)
+    assert forms == {(b, t, s) for b, s in ((0, 0), (1, 0), (1, 1)) for t in (2, 4, 16)}
