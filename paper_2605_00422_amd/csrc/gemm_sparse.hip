@@ -483,13 +483,26 @@ __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
                         *reinterpret_cast<v4f*>(Y + (int64_t)(mrow0 + row) * N + n_base + c * 4) = y;
                 }
             } else {
-                constexpr int PR = NT * 32;
-#pragma unroll 1
+                // rows that do not start on whole vectors: stores of four channels all the same, at the alignment of one.
+                // (Value by value, every store behind its own read of LDS, such layers took 0.97 of the dense kernel's time,
+                // 1.54 at most, over 103 shapes that the dispatch brings here; now 0.87 and 1.12: 1314 tokens of 2560
+                // columns, 9554 channels 63.7 -> 46.3 us, 552 of 5504, 16725 channels, rank 32 68.7 -> 55.6.)
+                typedef float v4f_one __attribute__((ext_vector_type(4), aligned(4)));
+                constexpr int PR = NT * 8;
+#pragma unroll 4
                 for (int p0 = 0; p0 < 32 * PR; p0 += 64) {
-                    const int p = p0 + lane, row = p / PR, c = p % PR;
-                    const float y = *reinterpret_cast<const float*>(mine + (c >> 5) * 4096 + row * 128 +
-                                                                    ((((c >> 2) & 7) ^ (row & 7)) << 4) + (c & 3) * 4);
-                    if (row < rows && n_base + c < N) Y[(int64_t)(mrow0 + row) * N + n_base + c] = y;
+                    const int p = p0 + lane, row = p / PR, c = p % PR, n = n_base + c * 4;
+                    const v4f y = *reinterpret_cast<const v4f*>(mine + (c >> 3) * 4096 + row * 128 + (((c & 7) ^ (row & 7)) << 4));
+                    float* to = Y + (int64_t)(mrow0 + row) * N + n;
+                    if (row < rows) {
+                        if (n + 3 < N) {
+                            *reinterpret_cast<v4f_one*>(to) = y;
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 3; ++i)
+                                if (n + i < N) to[i] = y[i];
+                        }
+                    }
                 }
             }
         } else {
@@ -504,13 +517,23 @@ __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
                         *reinterpret_cast<v4i*>(H + (int64_t)(mrow0 + row) * N2 + h_base + c * 8) = y;
                 }
             } else {
+                // (eight in flight: 3385 tokens of 512 columns, 10964 channels, rank 16 60.8 -> 56.8 us)
                 constexpr int PR = NT * 16;
 #pragma unroll 1
-                for (int p0 = 0; p0 < 32 * PR; p0 += 64) {
-                    const int p = p0 + lane, row = p / PR, c = p % PR;
-                    // (the pair, as it was written: the compiler takes a 16-bit read for one of something else)
-                    const uint32_t y = *reinterpret_cast<const uint32_t*>(mine + (c >> 4) * 4096 + row * 32 + ((c & 15) >> 1) * 4);
-                    if (row < rows && h_base + c < N2) H[(int64_t)(mrow0 + row) * N2 + h_base + c] = (uint16_t)(y >> ((c & 1) * 16));
+                for (int p0 = 0; p0 < 32 * PR; p0 += 8 * 64) {
+                    uint32_t y[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        // (the pair, as it was written: the compiler takes a 16-bit read for one of something else)
+                        const int p = p0 + 64 * i + lane, row = p / PR, c = p % PR;
+                        y[i] = *reinterpret_cast<const uint32_t*>(mine + (c >> 4) * 4096 + row * 32 + ((c & 15) >> 1) * 4);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int p = p0 + 64 * i + lane, row = p / PR, c = p % PR;
+                        if (row < rows && h_base + c < N2)
+                            H[(int64_t)(mrow0 + row) * N2 + h_base + c] = (uint16_t)(y[i] >> ((c & 1) * 16));
+                    }
                 }
             }
         }

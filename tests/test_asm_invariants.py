@@ -301,3 +301,19 @@ def test_rotation_in_fp32_keeps_the_summing_role_in_a_kernel_of_its_own():
                 run = 0
         assert (best >= 16) == (m.group(3) == "1"), (m.groups(), best)
     assert forms == {(b, t, s) for b, s in ((0, 0), (1, 0), (1, 1)) for t in (2, 4, 16)}
+
+
+@pytest.mark.parametrize("gated", [0, 1])
+@pytest.mark.parametrize("tile", SPARSE)
+def test_sparse_gemm_keeps_stores_in_flight_where_rows_start_anywhere(sparse_asm, tile, gated):
+    """Rows of channels that do not start on whole vectors leave in stores of four as the others do, or, gated, eight at a
+    time: read from LDS and stored value by value, they made the kernel slower than the dense one."""
+    pat = re.compile(r"_ZN.*gemm_sparse_kernelI" + "".join(f"Li{x}E" for x in tile) + f"Lb{gated}E.*:")
+    start = next(i for i, l in enumerate(sparse_asm) if pat.match(l))
+    lines = sparse_asm[start:next(i for i in range(start, len(sparse_asm)) if sparse_asm[i].startswith(".amdhsa_next_free_vgpr"))]
+    if not gated:
+        assert sum(l.startswith("global_store_dwordx4") for l in lines) >= 8      # four of either kind in flight
+    else:
+        behind = [i for i, l in enumerate(lines) if l.startswith("global_store_short")]
+        reads = sum(2 if l.startswith("ds_read2_") else 1 for l in lines[behind[0] - 200:behind[0]] if l.startswith("ds_read"))
+        assert len(behind) == 8 and reads >= 8

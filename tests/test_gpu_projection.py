@@ -33,6 +33,10 @@ CASES = [
     (1000, 128, 64, 31, "f32"),
     (255, 64, 32, 8, "bf16"),       # rides
     (257, 64, 80, 8, "bf16"),       # rides in the shadow of the second round
+    (768, 137, 32, 20, "bf16"),     # factors that the fp32 kernel rotates: the largest that leaves its tiles
+    (769, 137, 32, 20, "bf16"),     # and the first that hands them over
+    (192, 80, 64, 37, "f32"),       # fp32 tokens ride by the number of workgroups
+    (384, 64, 64, 37, "f32"),
 ]
 
 
