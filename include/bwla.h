@@ -170,7 +170,7 @@ BWLA_API bwla_status_t bwla_unpack_signs(const bwla_layer_t* layer, int8_t* d_sg
                                 void* stream);
 
 /*
- * Bytes of scratch bwla_rotate_quant wants for M tokens: split-K partial sums of X U with their
+ * Bytes of scratch bwla_rotate_quant wants for M tokens or fewer: split-K partial sums of X U with their
  * arrival counters, and, for a few tokens of a layer with a large factor R1 (six or more 16-row
  * tiles), the rotated values in fp32 and their extremes between the two launches the rotation
  * then takes.  For more than 64 tokens of a layer that the sparse GEMM serves (K a multiple of 128, N >= 32) it also

@@ -83,6 +83,32 @@ size_t rq_need(const bwla_layer_t* L, int64_t M) {
     const size_t b = rq_ws_bytes(L, bwla_psp_plan_of(L, M, BWLA_X_F32), M);
     return a > b ? a : b;
 }
+// ... and for M tokens or any number below, which can need more (more slices).  What the projection leaves grows with the
+// tokens as long as it rides in the rotation's launch, and else with its tiles of 64 as long as their slices stay the same,
+// which they do from 2048 tokens on: so the last tokens of every stretch that rides or does not, and of every such tile
+// before, are looked at, and the last that are split at all, of two column groups and of one.  Where a token's rotation may
+// be split, which adds its own part, every number of tokens.  (Every one up to 2048 took 0.35 to 0.8 ms of the host.)
+size_t rq_most(const bwla_layer_t* L, int64_t M) {
+    size_t most = rq_need(L, M);
+    auto see = [&](int64_t m) {
+        if (m >= M) return;
+        const size_t n = rq_need(L, m);
+        if (n > most) most = n;
+    };
+    const int64_t slots = (int64_t)BWLA_PSP_COUNTERS / 2 * 64;
+    see(slots);
+    see(2 * slots);
+    for (int64_t m = M - 1 < 2048 ? (M - 1) & ~(int64_t)63 : 2048; m > BWLA_RIDE_TOKENS; m -= 64) see(m);
+    const int64_t split = bwla_split_rotation_tokens(L), cus = bwla_device_cus();
+    const bool planes = bwla_rotate_planes_serves(L, BWLA_X_BF16, cus);
+    int at = 0;
+    for (int64_t m = (M < BWLA_RIDE_TOKENS ? M : BWLA_RIDE_TOKENS); m > 0; --m) {
+        const int now = bwla_psp_rides(L, m, cus, planes && m >= cus, false) | bwla_psp_rides(L, m, cus, false, true) << 1;
+        if (m <= split || (m & 63) == 0 || now != at) see(m);
+        at = now;
+    }
+    return most;
+}
 // The room that a call may lay codes out in: a caller's own (bwla_code_room_size), or the end of its scratch.
 struct CodeRoom {
     void* p;                                            // NULL: the dense kernel
@@ -270,16 +296,7 @@ bwla_status_t bwla_psp_workspace_size(const bwla_layer_t* layer, int64_t M, size
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (M <= 0) return BWLA_ERR_SHAPE;
-    // For fewer tokens a call can need more (more slices).  From 2048 tokens on there are eight and it only grows, up to
-    // the last number of tokens that is split.
-    size_t need = rq_need(layer, M);
-    const int64_t last = (int64_t)BWLA_PSP_COUNTERS / 2 * 64;      // (of two column groups; of one: twice that)
-    for (const int64_t m : {last, 2 * last})
-        if (m < M && rq_need(layer, m) > need) need = rq_need(layer, m);
-    for (int64_t m = M < 2048 ? M - 1 : 2048; m > 0; --m) {
-        const size_t n = rq_need(layer, m);
-        if (n > need) need = n;
-    }
+    const size_t need = rq_most(layer, M);
     const uint64_t sparse = bwla_gemm_sparse_bytes(layer, M);
     *bytes = sparse == 0 ? need : sparse_ws_start(need) + (size_t)sparse;
     return BWLA_OK;

@@ -65,6 +65,9 @@ struct bwla_psp_plan {
 // (planes: bwla_rotate_planes_serves the call; f32: fp32 tokens)
 bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32);
 bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M);
+// whether it rides in the rotation's launch: never beyond this many tokens
+constexpr int64_t BWLA_RIDE_TOKENS = 768;
+bool bwla_psp_rides(const bwla_layer_t* L, int64_t M, int64_t cus, bool planes, bool f32);
 // Every scratch of bwla_rotate_quant starts with the exchange area of the single-launch decode
 // kernel -- an epoch word, eight arrival counts (64 bytes apart, from byte 64 on), and from byte
 // 1024 on 8 x 96 tagged partial sums of T = x U, 8 bytes each -- at the same place whatever the
@@ -98,6 +101,7 @@ inline size_t bwla_split_start(const bwla_psp_plan& p, int r) {
 // Bytes the rotation wants behind the projection's scratch when it is split over several
 // workgroups per token and a second launch (few bf16 tokens, R1 too large for LDS); else 0.
 size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& plan, int64_t M);
+int64_t bwla_split_rotation_tokens(const bwla_layer_t* L);      // never of more tokens than these
 int bwla_psp_prefill_tile_cols(int rp);
 hipError_t bwla_launch_psp_prefill(const bwla_layer_t* L, const void* dX, int xdtype, int64_t M, float* dT,
                                    void* dws, const bwla_psp_plan& plan, hipStream_t st, bool finish = true);

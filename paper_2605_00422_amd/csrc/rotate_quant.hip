@@ -188,14 +188,27 @@ bool bwla_rotate_supported(int n1, int n2) {
 int bwla_rotate_tiles(int n1, int n2) { return (rq_pad16(n1) / 16) * (rq_pad16(n2) / 16); }
 int bwla_rotate_max_tiles() { return RQ_MAXT * RQ_WAVES; }
 
+namespace {
+// ranks of more than two 16-column tiles are dealt to several workgroups per slice
+inline int psp_groups(int r) {
+    const int tiles = (r + 15) / 16;
+    return tiles > PP_GROUPJT ? (tiles + PP_GROUPJT - 1) / PP_GROUPJT : 1;
+}
+inline int64_t psp_riders(int64_t M, int64_t K, int r) { return ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * psp_groups(r); }
+}  // namespace
+
+bool bwla_psp_rides(const bwla_layer_t* L, int64_t M, int64_t cus, bool planes, bool f32) {
+    const int r = bwla_rank_u(L);
+    return M <= 16 || r <= 0 || psp_rides(M, L->K, psp_riders(M, L->K, r), cus, planes, f32);
+}
+
 bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32) {
     bwla_psp_plan p;
     const int rp = (r + 15) & ~15;
-    // ranks of more than two 16-column tiles are dealt to several workgroups per slice
-    const int jg = rp > 16 * PP_GROUPJT ? (rp / 16 + PP_GROUPJT - 1) / PP_GROUPJT : 1;
+    const int jg = psp_groups(r);
     const bool always = M <= 16 || r <= 0;
-    const int64_t riders = ((M + 15) / 16) * ((K + PP_SLICE - 1) / PP_SLICE) * jg, cus = always ? 1 : bwla_device_cus();
-    if (always || psp_rides(M, K, riders, cus, planes, f32)) {
+    const int64_t cus = always ? 1 : bwla_device_cus();
+    if (always || psp_rides(M, K, psp_riders(M, K, r), cus, planes, f32)) {
         p.token_tiles = (int)((M + 15) / 16);
         p.k_per_split = PP_SLICE;
         p.splits = r > 0 ? (int)((K + PP_SLICE - 1) / PP_SLICE) : 1;
@@ -356,24 +369,38 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
     return hipSuccess;
 }
 
-size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& plan, int64_t M) {
+namespace {
+struct SplitRule { RsShape rs; int64_t tokens, workgroups; };           // the most of either; no tokens: never split
+SplitRule split_rule(const bwla_layer_t* L) {
+    SplitRule s{{}, 0, 0};
     const R3Shape s3 = r3_shape(L->n1, L->n2);
-    if (!s3.ok || L->K > (int64_t)RS_QB * 512 * RS_QI * 4) return 0;
+    if (!s3.ok || L->K > (int64_t)RS_QB * 512 * RS_QI * 4 || (s3.resident && s3.at < 6)) return s;
+    s.rs = rs_shape(s3);
+    if (!s.rs.ok) return s;
+    // up to two workgroups per CU (one after the other where LDS lets only one be resident):
+    // 224 x 128 at sixteen tokens 21.6 us against 31.2 in one workgroup per token, at thirty-two
+    // 34.5 against 32.0; with more tokens the one-workgroup-per-token kernel keeps the chip busy
+    s.workgroups = 2 * bwla_device_cus();
+    s.tokens = s.workgroups / s.rs.G;
     // Factors that fit LDS: the split still pays when the second product is long (six or more
     // tiles along n1) and either the strips do not spread evenly over the CU's four SIMDs (n2 = 86:
     // six wavefronts, two SIMDs carry two) or there are at most eight tokens, so that the extra
     // workgroups are free (measured, 128 x 64: 12.1 -> 11.1 us at four tokens, 12.2 -> 11.8 at
     // eight, 12.3 -> 12.9 at sixteen; 128 x 86: 16.7 -> 10.9 at one token, 17.1 -> 12.2 at sixteen).
-    if (s3.resident && !(s3.at >= 6 && ((s3.strips & 3) != 0 || M <= 8))) return 0;
-    const RsShape rs = rs_shape(s3);
-    if (!rs.ok) return 0;
+    if (s3.resident && (s3.strips & 3) == 0 && s.tokens > 8) s.tokens = 8;
+    return s;
+}
+}  // namespace
+
+int64_t bwla_split_rotation_tokens(const bwla_layer_t* L) { return split_rule(L).tokens; }
+
+size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& plan, int64_t M) {
+    const SplitRule s = split_rule(L);
+    if (M > s.tokens) return 0;
     const bool merged = bwla_rank_u(L) > 0 && plan.tile_rows == 16;
     const int64_t pblocks = merged ? (int64_t)plan.token_tiles * plan.splits * plan.col_groups : 0;
-    // up to two workgroups per CU (one after the other where LDS lets only one be resident):
-    // 224 x 128 at sixteen tokens 21.6 us against 31.2 in one workgroup per token, at thirty-two
-    // 34.5 against 32.0; with more tokens the one-workgroup-per-token kernel keeps the chip busy
-    if (M * rs.G + pblocks > 2 * bwla_device_cus()) return 0;
-    return (size_t)(M * L->K + 2 * M * rs.E) * sizeof(float);     // values, extremes
+    if (M * s.rs.G + pblocks > s.workgroups) return 0;
+    return (size_t)(M * L->K + 2 * M * s.rs.E) * sizeof(float);     // values, extremes
 }
 
 hipError_t bwla_launch_pack_codes_a4(const int8_t* dq, int64_t M, int64_t K, uint8_t* dq4, hipStream_t st) {
