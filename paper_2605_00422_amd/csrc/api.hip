@@ -120,11 +120,11 @@ CodeRoom room_of_scratch(const bwla_layer_t* L, int64_t M, int act_bits, void* d
     if (bytes == 0 || ws_bytes < sparse_ws_start(rq_need(L, M)) + bytes) return {nullptr, 0};
     return {(char*)d_ws + ((ws_bytes - bytes) & ~(size_t)255), (size_t)bytes};
 }
-// tile of the sparse GEMM for codes of this width, -1: the dense kernel
-int sparse_pick(const bwla_layer_t* L, int64_t M, int act_bits, const CodeRoom& room) {
+// tile of the sparse GEMM for codes of this width, -1: the dense kernel (*dense: its tile, if it came up)
+int sparse_pick(const bwla_layer_t* L, int64_t M, int act_bits, const CodeRoom& room, int* dense) {
     if (act_bits > 7 || M <= GS_MIN_TOKENS || M > (int64_t)1 << 24 || room.p == nullptr) return -1;
     if (room.bytes < bwla_gemm_sparse_bytes(L, M)) return -1;
-    return bwla_gemm_sparse_pick(L, M);
+    return bwla_gemm_sparse_pick(L, M, dense);
 }
 inline void* ws_body(void* d_ws) { return d_ws ? (char*)d_ws + BWLA_WS_HEAD : nullptr; }
 
@@ -447,9 +447,10 @@ bwla_status_t bwla_code_sums(const int8_t* d_q, int64_t M, int64_t K, int32_t* d
     return bwla_launch_code_sums(d_q, M, K, d_qsum, (hipStream_t)stream) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
-bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
-                                  const int32_t* d_qsum, const float* d_T, int64_t M, float* d_Y,
-                                  int32_t* d_acc, void* stream) {
+// (tile: of the streaming GEMM for token batches, -1: not known)
+static bwla_status_t dense_forward(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                   const int32_t* d_qsum, const float* d_T, int64_t M, float* d_Y, int32_t* d_acc,
+                                   void* stream, int tile) {
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
     if (!d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
@@ -464,8 +465,14 @@ bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8_t* d_q, 
     else if (M <= 16 && bwla_gemm_decode_lds(M, layer->K) <= DECODE_LDS_LIMIT)
         e = bwla_launch_gemm_decode(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, st);
     else
-        e = bwla_launch_gemm_prefill(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, st);
+        e = bwla_launch_gemm_prefill(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, st, nullptr, false, tile);
     return e == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
+}
+
+bwla_status_t bwla_linear_forward(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, float* d_Y,
+                                  int32_t* d_acc, void* stream) {
+    return dense_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream, -1);
 }
 
 bwla_status_t bwla_linear_forward_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
@@ -475,8 +482,9 @@ bwla_status_t bwla_linear_forward_room(const bwla_layer_t* layer, const int8_t* 
     if (d_room && !aligned16(d_room)) return BWLA_ERR_ALIGN;
     bwla_status_t s = check_layer(layer);
     if (s != BWLA_OK) return s;
-    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes});
-    if (pick < 0) return bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream);
+    int tile = -1;
+    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes}, &tile);
+    if (pick < 0) return dense_forward(layer, d_q, d_scale, d_qsum, d_T, M, d_Y, d_acc, stream, tile);
     if (!d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
     if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
     if (!aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) || (d_acc && !aligned16(d_acc)))
@@ -538,9 +546,9 @@ bwla_status_t bwla_swiglu_workspace_size(const bwla_layer_t* layer, int64_t M, s
     return BWLA_OK;
 }
 
-bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
-                                         const int32_t* d_qsum, const float* d_T, int64_t M, void* d_H,
-                                         void* d_ws, size_t ws_bytes, void* stream) {
+static bwla_status_t dense_swiglu(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                  const int32_t* d_qsum, const float* d_T, int64_t M, void* d_H, void* d_ws,
+                                  size_t ws_bytes, void* stream, int tile) {
     size_t need = 0;
     bwla_status_t s = bwla_swiglu_workspace_size(layer, M, &need);
     if (s != BWLA_OK) return s;
@@ -557,11 +565,17 @@ bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t
                                           (uint16_t*)d_H) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
     if (path == 2)
         return bwla_launch_gemm_prefill(layer, d_q, d_scale, d_qsum, d_T, M, nullptr, nullptr, st,
-                                        (uint16_t*)d_H) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
+                                        (uint16_t*)d_H, false, tile) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
     s = bwla_linear_forward(layer, d_q, d_scale, d_qsum, d_T, M, (float*)d_ws, nullptr, stream);
     if (s != BWLA_OK) return s;
     return bwla_launch_swiglu_rows((const float*)d_ws, M, layer->N, (uint16_t*)d_H, st) == hipSuccess ? BWLA_OK
                                                                                                     : BWLA_ERR_HIP;
+}
+
+bwla_status_t bwla_linear_forward_swiglu(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
+                                         const int32_t* d_qsum, const float* d_T, int64_t M, void* d_H,
+                                         void* d_ws, size_t ws_bytes, void* stream) {
+    return dense_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream, -1);
 }
 
 bwla_status_t bwla_linear_forward_swiglu_room(const bwla_layer_t* layer, const int8_t* d_q, const float* d_scale,
@@ -573,8 +587,9 @@ bwla_status_t bwla_linear_forward_swiglu_room(const bwla_layer_t* layer, const i
     size_t need = 0;
     bwla_status_t s = bwla_swiglu_workspace_size(layer, M, &need);
     if (s != BWLA_OK) return s;
-    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes});
-    if (pick < 0) return bwla_linear_forward_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream);
+    int tile = -1;
+    const int pick = sparse_pick(layer, M, act_bits, {d_room, room_bytes}, &tile);
+    if (pick < 0) return dense_swiglu(layer, d_q, d_scale, d_qsum, d_T, M, d_H, d_ws, ws_bytes, stream, tile);
     if (!d_q || !d_scale || !d_qsum || !d_H) return BWLA_ERR_NULL;
     if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
     if (!aligned16(d_q) || !aligned16(d_H) || (d_T && !aligned16(d_T))) return BWLA_ERR_ALIGN;

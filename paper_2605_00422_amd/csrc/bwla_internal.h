@@ -211,12 +211,12 @@ bool bwla_gemm_prefill_streams(const bwla_layer_t* L);
 // (dH not NULL: gated bf16 output instead of Y; only when bwla_gemm_prefill_streams(L))
 hipError_t bwla_launch_gemm_prefill(const bwla_layer_t* L, const int8_t* dq, const float* dscale,
                                     const int32_t* dqsum, const float* dT, int64_t M, float* dY,
-                                    int32_t* dacc, hipStream_t st, uint16_t* dH = nullptr, bool a4 = false);
-// (a4: dq holds nibble-packed codes, K / 2 bytes per token; only when bwla_gemm_prefill_streams(L), no gating)
+                                    int32_t* dacc, hipStream_t st, uint16_t* dH = nullptr, bool a4 = false, int tile = -1);
+// (tile: of the streaming kernel, where it is known already; a4: dq holds nibble-packed codes, K / 2 bytes per token; only when bwla_gemm_prefill_streams(L), no gating)
 // The same for codes of at most 7 bits and more than 64 tokens, on the sparse matrix instructions (gemm_sparse.hip): bytes of
 // scratch (0: not served), the tile to take (-1: the dense kernel is the faster one), the launches.
 uint64_t bwla_gemm_sparse_bytes(const bwla_layer_t* L, int64_t M);
-int bwla_gemm_sparse_pick(const bwla_layer_t* L, int64_t M);
+int bwla_gemm_sparse_pick(const bwla_layer_t* L, int64_t M, int* dense);
 hipError_t bwla_launch_gemm_sparse(const bwla_layer_t* L, int pick, const int8_t* dq, const float* dscale, const float* dT,
                                    int64_t M, float* dY, int32_t* dacc, hipStream_t st, void* dz, uint16_t* dH = nullptr);
 hipError_t bwla_launch_pack_codes_a4(const int8_t* dq, int64_t M, int64_t K, uint8_t* dq4, hipStream_t st);

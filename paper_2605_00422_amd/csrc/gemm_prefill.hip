@@ -606,9 +606,9 @@ bool bwla_gemm_prefill_streams(const bwla_layer_t* L) { return L->N >= 32 && (L-
 
 hipError_t bwla_launch_gemm_prefill(const bwla_layer_t* L, const int8_t* dq, const float* dscale,
                                     const int32_t* dqsum, const float* dT, int64_t M, float* dY,
-                                    int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4) {
+                                    int32_t* dacc, hipStream_t st, uint16_t* dH, bool a4, int tile) {
     if (bwla_gemm_prefill_streams(L))
-        return launch_tile<0>(gd_pick(M, L->K, L->N, L->r, bwla_device_cus(), a4), L, dq, dscale, dqsum, dT, M, dY, dacc, st,
+        return launch_tile<0>(tile >= 0 ? tile : gd_pick(M, L->K, L->N, L->r, bwla_device_cus(), a4), L, dq, dscale, dqsum, dT, M, dY, dacc, st,
                               dH, a4);
     // shapes the streaming kernel does not take (K not a multiple of 128, fewer than 32 channels):
     // LDS-tiled kernel, 64 x 128 or 128 x 128 tiles (it does not gate: the caller goes through Y)

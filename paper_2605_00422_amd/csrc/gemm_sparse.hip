@@ -582,9 +582,9 @@ uint64_t bwla_gemm_sparse_bytes(const bwla_layer_t* L, int64_t M) {
     return gs_code_bytes(L, M) + bwla_align256((uint64_t)((M + 63) / 64) * 4 * bwla_chunks(L->K) * sizeof(uint32_t));
 }
 
-int bwla_gemm_sparse_pick(const bwla_layer_t* L, int64_t M) {
+int bwla_gemm_sparse_pick(const bwla_layer_t* L, int64_t M, int* dense) {
     if (bwla_gemm_sparse_bytes(L, M) == 0) return -1;
-    return gs_pick(M, L->K, L->N, L->r, bwla_device_cus());
+    return gs_pick(M, L->K, L->N, L->r, bwla_device_cus(), dense);
 }
 
 hipError_t bwla_launch_gemm_sparse(const bwla_layer_t* L, int pick, const int8_t* dq, const float* dscale, const float* dT, int64_t M,

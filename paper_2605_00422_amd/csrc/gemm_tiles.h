@@ -82,14 +82,15 @@ inline float gd_cost(const GdTile& v, int64_t M, int64_t K, int64_t N, int r, in
     return t > least ? t : least;
 }
 
-// index into GD_TILES
-inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4) {
+// index into GD_TILES (*least: its cost)
+inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4, float* least = nullptr) {
     int best = 0;
     float cost = gd_cost(GD_TILES[0], M, K, N, r, cus, a4);
     for (int i = 1; i < GD_NTILES; ++i) {
         const float c = gd_cost(GD_TILES[i], M, K, N, r, cus, a4);
         if (c < cost) { cost = c; best = i; }
     }
+    if (least != nullptr) *least = cost;
     return best;
 }
 
@@ -129,11 +130,13 @@ inline float gs_cost(const GsTile& v, int64_t M, int64_t K, int64_t N, int r, in
     return t + 1.5f + (float)(M * K) * 2.0f / 6.3e6f;
 }
 
-// index into GS_TILES, or -1: the dense kernel
-inline int gs_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus) {
+// index into GS_TILES, or -1: the dense kernel (*dense: its tile, so that the launch need not pick again)
+inline int gs_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, int* dense = nullptr) {
     if (M <= GS_MIN_TOKENS) return -1;
     int best = -1;
-    float cost = gd_cost(GD_TILES[gd_pick(M, K, N, r, cus, false)], M, K, N, r, cus, false);
+    float cost;
+    const int d = gd_pick(M, K, N, r, cus, false, &cost);
+    if (dense != nullptr) *dense = d;
     for (int i = 0; i < GS_NTILES; ++i) {
         const float c = 1.03f * gs_cost(GS_TILES[i], M, K, N, r, cus);
         if (c < cost) { cost = c; best = i; }
