@@ -185,24 +185,49 @@ def test_room_at_the_end_of_a_scratch(M, K, N, r):
 
 
 def test_one_scratch_for_calls_of_several_sizes():
-    """The room for the codes lies at the end of a scratch: a call on fewer tokens leaves the arrival counters of one on
-    more tokens alone."""
+    """The room for the codes lies at the end of a scratch, behind the arrival counters: calls that lay codes out there, on
+    fewer tokens and of a layer without a projection among them, leave the counters of the others at zero.  Once in a
+    scratch for the most tokens, once in the smallest that has a room at all."""
+    from ctypes import byref
     from paper_2605_00422_amd import binding as B
-    K, N, r = 4096, 22016, 32
-    layer, g = _layer(4096, K, N, r)
+    lib, p, st = B.load(), B._ptr, B._stream()
+    K, N = 4096, 22016
+    layers = {r: _layer(4096, K, N, r)[0] for r in (32, 0)}
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
     X = torch.randn(4096, K, device=DEV, generator=g).to(torch.bfloat16)
-    big = B.Activations(layer, 4096)
-    ref = {}
-    for M in (4096, 700):
-        act = B.Activations(layer, M)
-        ref[M] = B.decode_forward(layer, X[:M], act, torch.empty(M, N, device=DEV)).clone()
-    for M in (700, 4096, 700, 4096):
-        act = B.Activations(layer, M)
-        act.ws, act.ws_bytes = big.ws, big.ws_bytes
-        act.T.fill_(float("nan"))
-        Y = B.decode_forward(layer, X[:M], act, torch.full((M, N), float("nan"), device=DEV))
+    acts = {r: B.Activations(layers[r], 4096) for r in layers}
+    Y = torch.empty(4096, N, device=DEV)
+    want = {}
+
+    def call(r, M, ws, sparse):
+        """rank, tokens; whether codes are laid out (the kernel is the sparse one)"""
+        layer, act = layers[r], acts[r]
+        if (r, M) not in want:
+            want[r, M] = B.decode_forward(layer, X[:M], act, Y[:M]).clone()
+        tail = ws[-4096 * 16:]                              # the last codes and the flags behind them
+        tail.fill_(0x5a)
+        if act.T is not None:
+            act.T.fill_(float("nan"))
+        Y.fill_(float("nan"))
+        assert lib.bwla_decode_forward(byref(layer.desc), p(X), B.BWLA_X_BF16, M, p(act.q), p(act.scale), p(act.qsum), p(act.T),
+                                       p(ws), ws.numel(), p(Y), None, st) == B.BWLA_OK
         torch.cuda.synchronize()
-        assert torch.equal(Y, ref[M])
+        assert torch.equal(Y[:M], want[r, M]), (r, M)
+        assert not bool(ws[7168:7168 + 16384].any()), (r, M)
+        assert bool((tail != 0x5a).any()) == sparse, (r, M)
+
+    # 4096 tokens hand their projection's sums over inside its launch, which counts arrivals
+    ws = torch.zeros(B.psp_workspace_size(layers[32], 4096), dtype=torch.uint8, device=DEV)
+    for r, M, sparse in ((32, 848, True), (32, 4096, True), (0, 848, True), (32, 4096, True), (32, 200, False), (32, 848, True),
+                         (32, 4096, True)):
+        call(r, M, ws, sparse)
+    # without a projection nothing but the counters lies in front of the room
+    ws = torch.zeros(B.psp_workspace_size(layers[0], 848), dtype=torch.uint8, device=DEV)
+    assert ws.numel() == 7168 + 16384 + B.code_room_size(layers[0], 848)
+    assert B.psp_workspace_size(layers[32], 64) <= ws.numel()
+    for r, M, sparse in ((0, 848, True), (32, 64, False), (0, 848, True), (32, 17, False), (0, 848, True)):
+        call(r, M, ws, sparse)
 
 
 def test_replayed_from_a_graph():
