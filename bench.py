@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the W1A6 linear forward (rotate+quantize, then binary GEMM + PSP + dequant).
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-extra]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-extra] [--details FILE]
 
 A step is one pass of the whole hot path over one batch of synthetic activations: one
 bwla_decode_forward call (rotation, codes, binary GEMM, PSP branch, dequantization: one kernel
@@ -9,7 +9,8 @@ launch where the library has a single-launch kernel for the shape, else the laun
 bwla_rotate_quant and bwla_linear_forward back to back).  Successive steps use different packed
 copies of the layer, 512 MB of them, as the layers of a model are all distinct; and every timed
 region starts behind a pass over a 768 MB buffer, so whatever the number of steps the sign bits
-stream from HBM, not from the 256 MB last-level cache.  Prints one JSON line.
+stream from HBM, not from the 256 MB last-level cache.  Prints one JSON line of some six kilobytes;
+--details writes the whole record, of which that line is the short form.
 """
 from __future__ import annotations
 
@@ -126,12 +127,25 @@ class Workload:
         self.X = X.to(torch.bfloat16) if cfg.x_dtype == "bf16" else X
         self.act = B.Activations(first, cfg.M)
         self.Y = torch.empty((cfg.M, cfg.N), dtype=torch.float32, device=dev)
-        # 1 where bwla_decode_forward has a single-launch kernel for the shape (at any code width)
-        self.launches = B.decode_forward_launches(first, cfg.M, cfg.x_dtype == "bf16")
         if nibble:
             self.q4 = torch.empty((cfg.M, cfg.K // 2), dtype=torch.uint8, device=dev)
-            self.launches = 2
+        self.launches = self.count_launches()
         torch.cuda.synchronize()
+
+    def count_launches(self):
+        """Kernels that a step launches: the nodes of a graph that it is captured into."""
+        import ctypes
+        torch = self.torch
+        self.step(0)                                    # (what a first call sets up is not captured)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g):
+            self.step(0)
+        n = ctypes.c_size_t()
+        # (found through the library's handle, so that it is the runtime that the library launches with)
+        if self.B.load().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) != 0:
+            raise RuntimeError("hipGraphGetNodes")
+        return n.value
 
     def step(self, i):
         L = self.layers[i % len(self.layers)]
@@ -352,28 +366,24 @@ def microbench(torch, B):
                     "1 MiB + 4 KiB apart over a flushed 384 MiB buffer / 128 bytes apart over 1 MiB read just before"}
 
 
-def gemm_kernel(cfg, act_bits=8):
-    """The kernel that bwla_linear_forward runs for a layer whose channels fill it: the streaming decode GEMM up
-    to 16 tokens, then (csrc/gemm_tiles.h) private rings of codes for a single tile of 64 tokens, one ring for the
-    wavefronts side by side beyond that; with codes of at most seven bits (bwla_linear_forward_bits) the one on the sparse
-    matrix instructions where tokens are many and rows of K long."""
-    if cfg.M <= 16:
-        return "gemm_decode_bs_kernel"
-    if act_bits <= 7 and cfg.M >= 2048 and cfg.K >= 8192 and cfg.N >= 4096:
-        return "gemm_sparse_kernel"
-    return "gemm_prefill_direct_kernel" if cfg.M <= 64 else "gemm_prefill_shared_kernel"
+def gemm_kernel(cfg, act_bits=8, nibbles=False):
+    """The kernel that bwla_linear_forward (of codes of this width) runs, as the library's dispatch has it."""
+    from paper_2605_00422_amd import binding as B
+    return B.linear_forward_kernel(cfg.M, cfg.N, cfg.K, cfg.r, act_bits, nibbles)
 
 
-def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=None, act_bits=8):
-    """Roofline of the dominant kernel: the single-launch decode kernel where it serves the layer
-    (then the kernel is the layer), else the binary GEMM inside bwla_linear_forward; with the
-    whole layer (all launches, all bytes or operations) against the same peak beside it."""
+def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=None, act_bits=8, nibbles=False):
+    """Roofline of the dominant kernel: the single-launch decode kernel where it serves the layer (one launch; then the kernel
+    is the layer), else the binary GEMM of bwla_linear_forward, with the pass over the codes in front of it where there is
+    one; with the whole layer (all launches, all bytes or operations) against the same peak beside it.  Operations are
+    those of the dense product and the peak is the dense instructions'; the kernel on the sparse ones, which contract twice
+    the columns an instruction, gets its share of theirs as well."""
     workload = workload or cfg.name
     hbm_bound = layer_bytes(cfg) / (HBM_PEAK_GBPS * 1e9) >= gemm_ops(cfg) / (INT8_PEAK_TOPS * 1e12)
     if launches == 1:
         kernel, t, nbytes = "decode_layer_kernel", us_layer * 1e-6, layer_bytes(cfg)
     else:
-        kernel = gemm_kernel(cfg, act_bits)
+        kernel = gemm_kernel(cfg, act_bits, nibbles)
         t, nbytes = us_forward * 1e-6, linear_forward_bytes(cfg)
     tl = us_layer * 1e-6
     if hbm_bound:
@@ -390,11 +400,12 @@ def roofline_for(cfg, launches, us_layer, us_forward, peaks, traffic, workload=N
         return r
     a = gemm_ops(cfg) / t / 1e12
     pm = peaks.mfma_int8_tops() if peaks else None
-    return {"bound": "mfma", "achieved": a, "peak": INT8_PEAK_TOPS, "unit": "TOP/s", "frac": a / INT8_PEAK_TOPS,
+    sparse = {"frac_of_sparse_peak": a / (2 * INT8_PEAK_TOPS)} if kernel == "gemm_sparse_kernel" else {}
+    return {"bound": "mfma", "achieved": a, "peak": INT8_PEAK_TOPS, "unit": "TOP/s", "frac": a / INT8_PEAK_TOPS, **sparse,
             "traffic": traffic.get((workload, kernel)), "kernel": kernel, "ops_per_launch": gemm_ops(cfg),
             "us_per_launch": t * 1e6,
             "peak_measured": pm, "frac_of_measured": (a / pm if pm else None),
-            "peak_measured_what": "a launch of INT8 16x16x64 MFMAs on register operands only",
+            "peak_measured_what": "a launch of dense INT8 16x16x64 MFMAs on register operands only",
             "layer": {"achieved": gemm_ops(cfg) / tl / 1e12, "frac": gemm_ops(cfg) / tl / 1e12 / INT8_PEAK_TOPS,
                       "ops": gemm_ops(cfg), "us": us_layer, "launches": launches}}
 
@@ -502,6 +513,36 @@ def cpu_baseline(w, budget_s=12.0):
             "host_cpus": os.cpu_count()}
 
 
+def rounded(x, digits=5):
+    """Floats of a record at this many digits."""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: rounded(v, digits) for k, v in x.items()}
+    return [rounded(v, digits) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def short_line(line):
+    """The record on one line of a few kilobytes, which what collects it keeps whole: the headline as it is, of every other
+    workload its times (the faster of stream and graph), kernel and share of the peak, of the quantizer its times."""
+    out = dict(line)
+    short = []
+    for e in line.get("other_workloads", []):
+        best, mode = best_of(e)
+        r = e["roofline"]
+        short.append({"workload": e["workload"], "launches": e["launches_per_layer"], "us": best["us_per_layer"], "gemm": best["us_linear_forward"],
+                      "rotate": best["us_rotate_quant"], "mode": mode, "kernel": r["kernel"], "bound": r["bound"], "frac": r["frac"],
+                      **({"frac_of_sparse_peak": r["frac_of_sparse_peak"]} if "frac_of_sparse_peak" in r else {})})
+    if short:
+        out["other_workloads"] = short
+    if "quantizer" in line:
+        q = line["quantizer"]
+        out["quantizer"] = {"workload": q["workload"], "ms_per_round": q["ms_per_round"],
+                            "okt_rows": {k: q["okt_rows"][k] for k in ("ms", "bound", "achieved", "unit", "frac")},
+                            "down_projection": {k: q["down_projection"][k] for k in ("workload", "ms_per_round")}}
+    return rounded(out)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -512,6 +553,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--no-graph", action="store_true")
     ap.add_argument("--no-peaks", action="store_true", help="skip the measured-ceiling launches")
+    ap.add_argument("--details", metavar="FILE", help="write everything measured there, of which the line is the short form")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run three plain 256 MiB device copies (counter calibration under rocprofv3 --pmc)")
     args = ap.parse_args()
@@ -603,7 +645,7 @@ def main():
                 c = dataclasses.replace(c, r=c.r + int(shift) + 2 * int(asym))   # bytes of the extra columns of V and T
             b, _ = best_of(r)
             r["roofline"] = roofline_for(c, ww.launches, b["us_per_layer"], b["us_linear_forward"], peaks, traffic,
-                                         workload=r["workload"], act_bits=8 if nibble else bits)
+                                         workload=r["workload"], act_bits=bits, nibbles=nibble)
             if not nibble and bits == 4:
                 r["code_bytes_per_launch"] = c.M * c.K
             r["side_kernels"] = [side_kernel_report(c, b["us_rotate_quant"])]
@@ -636,7 +678,10 @@ def main():
         line["quantizer"] = quantizer_report(torch)
     if peaks is not None:
         line["microbench"] = microbench(torch, B)
-    print(json.dumps(line))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(line, f, indent=1)
+    print(json.dumps(short_line(line), separators=(",", ":")))
 
 
 if __name__ == "__main__":

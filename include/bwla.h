@@ -265,6 +265,14 @@ BWLA_API bwla_status_t bwla_linear_forward_room(const bwla_layer_t* layer, const
                                   size_t room_bytes, float* d_Y, int32_t* d_acc, void* stream);
 
 /*
+ * Which kernel these calls run on M tokens of a layer of N channels, K columns and r columns of V, for codes of act_bits with
+ * a room for them (8: without one), or for the nibble-packed codes of bwla_linear_forward_a4: its name as a profiler shows it.
+ * Host arithmetic alone; *name (host) is a constant string.
+ */
+BWLA_API bwla_status_t bwla_linear_forward_kernel(int64_t M, int64_t N, int64_t K, int32_t r, int act_bits, int nibbles,
+                                  const char** name);
+
+/*
  * The whole forward of one layer, steps 1-5 above (paper Sec. 3.1, Sec. 4.1, Eq. 3-4, Sec. 3.2), in
  * one call: what bwla_rotate_quant followed by bwla_linear_forward compute, with the same
  * buffers (d_q, d_scale, d_qsum, d_T are still written; same arguments, same errors) and to the

@@ -23,7 +23,7 @@ EXPORTS = ["bwla_status_string", "bwla_version", "bwla_kron_factor", "bwla_packe
            "bwla_probe_mfma_int8", "bwla_decode_forward_launches", "bwla_decode_forward_bits", "bwla_pack_codes_a4",
            "bwla_linear_forward_a4", "bwla_probe_empty_launch", "bwla_probe_load_latency", "bwla_probe_clock",
            "bwla_linear_forward_bits", "bwla_linear_forward_swiglu_bits", "bwla_code_room_size", "bwla_decode_forward_room",
-           "bwla_linear_forward_room", "bwla_linear_forward_swiglu_room"]
+           "bwla_linear_forward_room", "bwla_linear_forward_swiglu_room", "bwla_linear_forward_kernel"]
 
 
 class BwlaLayer(Structure):
@@ -100,6 +100,7 @@ def load() -> ctypes.CDLL:
     lib.bwla_code_room_size.argtypes = [POINTER(BwlaLayer), c_int64, POINTER(c_size_t)]
     lib.bwla_decode_forward_room.argtypes = [POINTER(BwlaLayer), c_void_p, c_int, c_int, c_int64, c_void_p, c_void_p, c_void_p,
                                              c_void_p, c_void_p, c_size_t, c_void_p, c_size_t, c_void_p, c_void_p, c_void_p]
+    lib.bwla_linear_forward_kernel.argtypes = [c_int64, c_int64, c_int64, c_int32, c_int, c_int, POINTER(c_char_p)]
     for name in EXPORTS:
         if name not in ("bwla_status_string", "bwla_version"):
             getattr(lib, name).restype = c_int
@@ -363,6 +364,13 @@ def linear_forward_a4(layer: PackedLayer, q4, act: Activations, Y, acc=None):
     _check(load().bwla_linear_forward_a4(layer._ref, _ptr(q4), _ptr(act.scale), _ptr(act.qsum), _ptr(act.T),
                                          act.M, _ptr(Y), _ptr(acc), _stream()), "bwla_linear_forward_a4")
     return Y
+
+
+def linear_forward_kernel(M: int, N: int, K: int, r: int, act_bits: int = 8, nibbles: bool = False) -> str:
+    """Name of the kernel that linear_forward (of codes of act_bits), or linear_forward_a4, runs; r: columns of V."""
+    out = c_char_p()
+    _check(load().bwla_linear_forward_kernel(M, N, K, r, act_bits, int(nibbles), byref(out)), "bwla_linear_forward_kernel")
+    return out.value.decode()
 
 
 def code_sums(q, qsum) -> None:

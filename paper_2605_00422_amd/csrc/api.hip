@@ -504,6 +504,24 @@ bwla_status_t bwla_linear_forward_bits(const bwla_layer_t* layer, const int8_t* 
     return bwla_linear_forward_room(layer, d_q, d_scale, d_qsum, d_T, M, act_bits, room.p, room.bytes, d_Y, d_acc, stream);
 }
 
+bwla_status_t bwla_linear_forward_kernel(int64_t M, int64_t N, int64_t K, int32_t r, int act_bits, int nibbles,
+                                         const char** name) {
+    if (!name) return BWLA_ERR_NULL;
+    if (M <= 0 || M > (int64_t)1 << 24 || N <= 0 || N > (int64_t)1 << 24 || K <= 0 || r < 0) return BWLA_ERR_SHAPE;
+    if (K % 32 != 0 || K > BWLA_MAX_K || r > BWLA_MAX_RANK || act_bits < 2 || act_bits > 8) return BWLA_ERR_UNSUPPORTED;
+    bwla_layer_t L = {};
+    L.N = N; L.K = K; L.r = r;
+    const bool streams = bwla_gemm_prefill_streams(&L);
+    if (nibbles && (M <= 16 || !streams)) return BWLA_ERR_UNSUPPORTED;
+    if (bwla_gemm_decode_bs_supported(M, K, r)) *name = "gemm_decode_bs_kernel";
+    else if (M <= 16 && bwla_gemm_decode_lds(M, K) <= DECODE_LDS_LIMIT) *name = "gemm_decode_kernel";
+    else if (!nibbles && act_bits <= 7 && bwla_gemm_sparse_pick(&L, M, nullptr) >= 0) *name = "gemm_sparse_kernel";
+    else if (!streams) *name = "gemm_prefill_kernel";
+    else *name = GD_TILES[gd_pick(M, K, N, r, bwla_device_cus(), nibbles != 0)].wn > 1 ? "gemm_prefill_shared_kernel"
+                                                                                     : "gemm_prefill_direct_kernel";
+    return BWLA_OK;
+}
+
 bwla_status_t bwla_pack_codes_a4(const int8_t* d_q, int64_t M, int64_t K, uint8_t* d_q4, void* stream) {
     if (!d_q || !d_q4) return BWLA_ERR_NULL;
     if (M <= 0 || K <= 0 || M > (int64_t)1 << 24) return BWLA_ERR_SHAPE;

@@ -5,10 +5,21 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 import bench
+from paper_2605_00422_amd import binding as B
 from paper_2605_00422_amd import inputs as syn
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _library():
+    """The kernels' names come from the library's dispatch, which needs no GPU."""
+    if not os.path.exists(B.LIB_PATH):
+        from paper_2605_00422_amd.build import build_library
+        build_library()
 
 
 def test_linear_forward_bytes_of_the_default_workload():
@@ -106,3 +117,61 @@ def test_the_kernels_named_for_narrow_codes():
         sparse = subprocess.run([os.path.join(tmp, "gs")], capture_output=True, text=True, check=True).stdout.split()
     for c, s in zip(cfgs, sparse):
         assert (bench.gemm_kernel(c, 6) == "gemm_sparse_kernel") == (s == "1"), c.name
+
+
+def test_the_kernels_named_are_the_dispatch_s_own():
+    """Beside the listed configurations too, at the widths of codes that decide: (tokens, columns, channels, rank, bits,
+    nibbles), the kernel."""
+    import dataclasses
+    base = syn.CONFIGS["cfg3_qwen32b_down_m2048"]
+    for M, K, N, r, bits, nibbles, kernel in (
+            (512, 8192, 28672, 64, 6, False, "gemm_sparse_kernel"), (512, 8192, 28672, 64, 8, False, "gemm_prefill_shared_kernel"),
+            (2048, 4096, 22016, 64, 6, False, "gemm_sparse_kernel"), (2048, 4096, 22016, 64, 4, True, "gemm_prefill_shared_kernel"),
+            (2048, 8192, 64, 64, 6, False, "gemm_prefill_direct_kernel"), (64, 8192, 28672, 64, 6, False, "gemm_prefill_direct_kernel"),
+            (2048, 4128, 4096, 64, 6, False, "gemm_prefill_kernel"), (16, 4096, 11008, 32, 6, False, "gemm_decode_bs_kernel")):
+        c = dataclasses.replace(base, M=M, K=K, N=N, r=r)
+        assert bench.gemm_kernel(c, bits, nibbles) == kernel, (M, K, N, r, bits, nibbles)
+
+
+def test_share_of_the_peak_says_which_peak():
+    """Operations of the dense product over the dense instructions' peak, for every kernel; the one on the sparse
+    instructions says beside it what share of theirs that is."""
+    cfg = syn.CONFIGS["cfg3_qwen32b_down_m2048"]
+    r = bench.roofline_for(cfg, 4, 318.0, 175.0, None, {}, act_bits=6)
+    assert r["kernel"] == "gemm_sparse_kernel" and r["peak"] == 5000.0
+    assert abs(r["frac"] - bench.gemm_ops(cfg) / 175e-6 / 5e15) < 1e-9
+    assert abs(r["frac_of_sparse_peak"] - r["frac"] / 2) < 1e-12
+    assert "frac_of_sparse_peak" not in bench.roofline_for(cfg, 3, 318.0, 195.0, None, {}, act_bits=8)
+
+
+def test_the_line_stays_short():
+    """What collects the line keeps eight kilobytes of it.  A record of every workload with numbers of full length."""
+    import json
+    third = 1.0 / 3.0
+    cfg = syn.CONFIGS["cfg3_qwen32b_down_m2048"]
+    times = {"us_per_layer": 1e4 * third, "us_per_layer_min": 1e4 * third, "us_per_layer_events": 1e4 * third,
+             "us_linear_forward": 1e4 * third, "us_rotate_quant": 1e4 * third}
+    roof = bench.roofline_for(cfg, 4, 1e4 * third, 1e3 * third, None, {}, act_bits=6)
+    roof.update(peak_measured=1e4 * third, frac_of_measured=third, traffic=10 ** 10)
+    side = bench.side_kernel_report(cfg, 1e3 * third)
+    extra = [{"workload": "cfg3_qwen32b_down_m2048+row_shift+asym", "M": 4096, "K": 28672, "N": 28672, "r": 64, "kron": "224x128",
+              "layer_copies": 99, "launches_per_layer": 4, "stream": times, "graph": times, "roofline": roof,
+              "side_kernels": [side], "effective_tops": 1e3 * third} for _ in range(18)]
+    quantizer = {"workload": "Gaussian 11008 x 4096 (Kronecker 64 x 64), rank 32", "dtype": "f64", "rounds": 2, "ms_total": 1e2 * third,
+                 "svd_iters_per_round": 20, "ms_per_round": 1e2 * third, "loss_history": [third] * 7,
+                 "okt_rows": {"ms": third, "bound": "hbm", "bytes_moved": 1, "achieved": 1e3 * third, "peak": 8e3, "unit": "GB/s",
+                              "frac": third, "flops": 1},
+                 "down_projection": {"workload": "Gaussian 4096 x 11008 (Kronecker 128 x 86), rank 32", "ms_per_round": 1e2 * third,
+                                     "loss_history": [third] * 7}}
+    line = {"metric": "x" * 80, "value": third, "vs_baseline": None, "dtype_detail": "x" * 130, "data": "synthetic",
+            "config": {k: "x" * 20 for k in "abcdefghijkl"}, "timings": {"stream": times, "graph": times}, "roofline": roof,
+            "roofline_prefill": roof, "side_kernels": [side], "cpu_baseline": {"sample": "x" * 120, "value": third},
+            "other_workloads": extra, "block7b_m1": {k: third for k in ("us_seven_layers", "us_four_merged_layers",
+                                                                        "us_gateup_forward", "us_gateup_forward_gated")},
+            "quantizer": quantizer, "microbench": {"what": "x" * 220, "a": third, "b": third, "c": third}}
+    text = json.dumps(bench.short_line(line), separators=(",", ":"))
+    assert len(text) < 7500
+    got = json.loads(text)
+    assert got["value"] == 0.33333 and len(got["other_workloads"]) == 18
+    assert got["other_workloads"][0]["kernel"] == "gemm_sparse_kernel" and got["other_workloads"][0]["us"] == 3333.3
+    assert len(json.dumps(line)) > 8192                     # (as it was printed)
