@@ -263,8 +263,7 @@ class Activations:
         self.qsum = torch.empty((M,), dtype=torch.int32, device=dev)
         self.T = torch.empty((M, d.r), dtype=torch.float32, device=dev) if d.r > 0 else None
         self.room_bytes = code_room_size(layer, M)
-        if self.room_bytes:
-            self.room = torch.empty(self.room_bytes, dtype=torch.uint8, device=dev)
+        self.room = torch.empty(self.room_bytes, dtype=torch.uint8, device=dev) if self.room_bytes else None
         ws = psp_workspace_size(layer, M) - self.room_bytes                 # (a scratch may have the room at its end: not this one)
         self.ws_bytes = ws
         self.ws = torch.zeros(max(ws, 16), dtype=torch.uint8, device=dev)   # zero-filled once, as the ABI asks
@@ -277,11 +276,12 @@ def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> 
         _check(load().bwla_rotate_quant(layer._ref, _ptr(X), xd, X.shape[0], _ptr(act.q), _ptr(act.scale),
                                         _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes, _stream()),
                "bwla_rotate_quant")
+        act.act_bits = 6
     else:
         _check(load().bwla_rotate_quant_bits(layer._ref, _ptr(X), xd, act_bits, X.shape[0], _ptr(act.q),
                                              _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws),
                                              act.ws_bytes, _stream()), "bwla_rotate_quant_bits")
-    act.act_bits = int(act_bits)
+        act.act_bits = int(act_bits)
     return act
 
 
@@ -294,9 +294,12 @@ def decode_forward(layer: PackedLayer, X, act: Activations, Y, acc=None, act_bit
                                                _ptr(act.room), act.room_bytes, _ptr(Y), _ptr(acc), _stream()),
                "bwla_decode_forward_room")
     elif act_bits == 6:
+        # (a call of one token takes the host as long as the GPU: no conversion here)
         _check(load().bwla_decode_forward(layer._ref, _ptr(X), xd, X.shape[0], _ptr(act.q), _ptr(act.scale),
                                           _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes, _ptr(Y), _ptr(acc),
                                           _stream()), "bwla_decode_forward")
+        act.act_bits = 6
+        return Y
     else:
         _check(load().bwla_decode_forward_bits(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
                                                _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
