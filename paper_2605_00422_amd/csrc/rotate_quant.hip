@@ -50,21 +50,17 @@ __device__ __forceinline__ void psp_sum_at(const RqArgs& a, int pb) {
     const int W = a.r <= 16 ? 16 : a.r <= 32 ? 32 : 64;                // bwla_psp_prefill_tile_cols
     bwla_psp_sum_tiles(bwla_psp_tiles{a.partials, a.T, a.M, a.r, a.tp, -a.S, a.JG, W, (int)(gridDim.x - a.rot_blocks)}, pb);
 }
-// projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile
-template <bool BF16>
+// projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile.  EITHER: or the role
+// above, in one kernel, told apart by a word that both load anyway (56 bytes more of arguments cost small launches 0.1 us).
+template <bool BF16, bool EITHER = false>
 __device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    const int s = pb % a.S, rest = pb / a.S;
-    psp_block<BF16>(lds, a.X, a.M, a.K, a.r, a.U, a.T, a.counters, a.partials, a.S, rest / a.JG, s, a.tp, finish,
-                    rest % a.JG, a.JG);
-}
-// (one kernel for both roles, told apart by a word that they load anyway: 56 bytes more of arguments cost small launches
-// 0.1 us)
-__device__ __forceinline__ void psp_either_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    if (a.S < 0) {
+    if (EITHER && a.S < 0) {
         psp_sum_at(a, pb);
         return;
     }
-    psp_block_at<true>(lds, a, pb, finish);
+    const int s = pb % a.S, rest = pb / a.S;
+    psp_block<BF16>(lds, a.X, a.M, a.K, a.r, a.U, a.T, a.counters, a.partials, a.S, rest / a.JG, s, a.tp, finish,
+                    rest % a.JG, a.JG);
 }
 
 // (up to 128 registers, of which fp32 activations spill six: two workgroups a CU where LDS lets them)
@@ -94,7 +90,7 @@ __global__ __launch_bounds__(THREADS) void rotate_quant3_kernel(RqArgs a) {
                            a.tp, a.qmax, a.asym != 0, a.shift != 0);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
-        psp_either_at(reinterpret_cast<char*>(lds), a, pb);
+        psp_block_at<true, true>(reinterpret_cast<char*>(lds), a, pb);
     }
 }
 
@@ -108,7 +104,7 @@ __global__ __launch_bounds__(640) void rotate_split_kernel(RqArgs a) {
                            (int)(blockIdx.x - t * G), a.K, a.n1, a.n2, a.R1p, a.R2p, a.xs, a.pmax, a.qsum);
     } else {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
-        psp_either_at(reinterpret_cast<char*>(lds), a, pb, false);
+        psp_block_at<true, true>(reinterpret_cast<char*>(lds), a, pb, false);
     }
 }
 
