@@ -17,7 +17,12 @@
 // rows.  Cycles behind the loop (workgroups of 48000 to 77000 in all), rank 64, before and after: 64 x 128 tiles 22100 and
 // 11000, 64 x 256 27600 and 19000, 64 x 64 with K in two 25600 and 12700.  Whole launches: 64 tokens of 8192 columns, 28672
 // channels, rank 64 28.1 -> 23.7 us; 257 tokens, 8192 channels 34.8 -> 30.2; 333 of 4096, 11008 channels, rank 32 31.1 ->
-// 25.8; 64 of 4096, 4096 channels 13.3 -> 8.7; 4096 of 28672, 8192 channels 663 -> 647.  Taken back: a loop over tiles out
+// 25.8; 64 of 4096, 4096 channels 13.3 -> 8.7; 4096 of 28672, 8192 channels 663 -> 647.  And nothing waits behind a branch:
+// a store under a condition is one, and so is a look at acc_out for every value; with the reads of a tile's rows each behind the
+// store before, and the branches for sums that nobody asked for, wide tiles of low ranks were slower than with stores straight
+// from registers (806 tokens of 512 columns, 11140 channels, rank 16, 64 x 640 tiles 22.6, 25.9 us; now 21.3; 385 of 1408,
+// 21018, rank 0 26.8, 31.0, 28.1; rank 64, 64 tokens of 8192, 28672 channels 25.3 -> 24.4, 257 of 8192, 8192 30.9 -> 30.0, 2048 of
+// 25600, 5120 193.4 -> 187.7).  Taken back: a loop over tiles out
 // of LDS (less code; its round trips come one after the other: 25.5 -> 27.9 us in the first of these); the weights as the
 // first MFMA operand, so that a lane holds one token (0.5 us less for a single tile, but long products run 8 % slower: the
 // matrix cores' power is the limit there, and the operand that changes from one MFMA to the next costs more on that side).
@@ -123,7 +128,7 @@ struct Epilogue {
     const char* const rows_t;                                    // EpRows' operands ...
     const float* const info;                                     // ... and numbers of this wavefront's first row of tiles
     v4i vf[EP_JC];
-    float al;
+    float al[NT];
 
     __device__ __forceinline__ Epilogue(const EpArgs& e_, int m_base, int mt0, int n_base_, int lane_, char* mine_, const char* t_)
         : e(e_), mrow0(m_base + mt0 * 32), n_base(n_base_), lane(lane_), l32(lane_ & 31), lg(lane_ >> 5), JT((e_.r + 15) >> 4),
@@ -149,12 +154,12 @@ struct Epilogue {
         const int p = 64 * j + lane, ch = (int)(__umul24((uint32_t)p, (uint32_t)inv) >> 16), c = p - ch * 2 * w;     // p / (2 w) for p < 512
         return (c >> 1) * 1024 + (c & 1) * 512 + ch * 16;
     }
-    __device__ __forceinline__ void load_al(int nt) {
-        const int n = n_base + nt * 32 + l32;
-        al = __half2float(e.alpha[n < e.N ? n : e.N - 1]);
-    }
     __device__ __forceinline__ void request() {
-        load_al(0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int n = n_base + nt * 32 + l32;
+            al[nt] = __half2float(e.alpha[n < e.N ? n : e.N - 1]);
+        }
         if (JT > 0) load_v(0, 0);
     }
     __device__ __forceinline__ void finish(v16i (&u)[MT][NT]) {
@@ -162,10 +167,10 @@ struct Epilogue {
         for (int nt = 0; nt < NT; ++nt) {
             const int n0 = n_base + nt * 32;
             // the main term, times 2^k of its row
-            const float a = al;
+            const float a = al[nt];
             v16f y[MT];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const float* at = info + mt * 32 + 8 * g + 4 * lg;
@@ -174,14 +179,24 @@ struct Epilogue {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int w = 2 * u[mt][nt][4 * g + i] - qs[i];
-                        if constexpr (!GATED) {
-                            const int t = mrow0 + mt * 32 + 8 * g + 4 * lg + i;
-                            if (e.acc_out && t < e.M && n0 + l32 < e.N) e.acc_out[(int64_t)t * e.N + n0 + l32] = w;
-                        }
                         y[mt][4 * g + i] = (float)w * (scu[i] * a);
                     }
                 }
-            if (nt + 1 < NT) load_al(nt + 1);
+                if constexpr (!GATED) __builtin_amdgcn_sched_barrier(0);      // (a row of tiles at a time: registers)
+            }
+            if (!GATED && e.acc_out != nullptr) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const v4i qs = *reinterpret_cast<const v4i*>(info + mt * 32 + 8 * g + 4 * lg + 128);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int t = mrow0 + mt * 32 + 8 * g + 4 * lg + i;
+                            if (t < e.M && n0 + l32 < e.N) e.acc_out[(int64_t)t * e.N + n0 + l32] = 2 * u[mt][nt][4 * g + i] - qs[i];
+                        }
+                    }
+            }
 #pragma unroll 1
             for (int c0 = 0; c0 < JT; c0 += EP_JC) {
                 const int w = JT < EP_JC ? JT : EP_JC, inv = 32768 / w + 1;
@@ -212,7 +227,7 @@ struct Epilogue {
                 if (mt > 0 && row0 >= e.M) break;
                 const int rows = e.M - row0 < 32 ? e.M - row0 : 32, N2 = e.N >> 1;
                 const float* down = info + 64 + mt * 32;
-                if (GATED ? (N2 & 1) == 0 : (e.N & 3) == 0) {
+                if (GATED || (e.N & 3) == 0) {
                     // out through LDS, as whole rows of the tile's channels: token rows of 128 bytes, 16-byte pieces turned
                     // by the row
 #pragma unroll
@@ -221,20 +236,46 @@ struct Epilogue {
                         *reinterpret_cast<float*>(mine + row * 128 + (((l32 >> 2) ^ (row & 7)) << 4) + (l32 & 3) * 4) = y[mt][v];
                     }
                     __builtin_amdgcn_wave_barrier();
+                    // (all four reads before the first store: a store is a branch, and reads behind it wait one by one)
+                    v4f out[4];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        const int row = 8 * k + (lane >> 3), n = n0 + (lane & 7) * 4;
-                        const v4f o = *reinterpret_cast<const v4f*>(mine + row * 128 + (((lane & 7) ^ (row & 7)) << 4)) * down[row];
-                        if constexpr (!GATED) {
-                            if (row < rows && n < e.N) *reinterpret_cast<v4f*>(e.Y + (int64_t)(row0 + row) * e.N + n) = o;
-                        } else {
+                        const int row = 8 * k + (lane >> 3);
+                        out[k] = *reinterpret_cast<const v4f*>(mine + row * 128 + (((lane & 7) ^ (row & 7)) << 4)) * down[row];
+                    }
+                    const int n = n0 + (lane & 7) * 4;
+                    if constexpr (!GATED) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int row = 8 * k + (lane >> 3);
+                            if (row < rows && n < e.N) *reinterpret_cast<v4f*>(e.Y + (int64_t)(row0 + row) * e.N + n) = out[k];
+                        }
+                    } else {
+                        auto gate = [&](const v4f& o) -> uint32_t {
                             uint32_t hh = 0;
 #pragma unroll
                             for (int i = 0; i < 2; ++i) {
                                 const float h = o[2 * i] / (1.0f + __expf(-o[2 * i])) * o[2 * i + 1];
                                 hh |= (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)h) << (16 * i);
                             }
-                            if (row < rows && n < e.N) *reinterpret_cast<uint32_t*>(e.H + (int64_t)(row0 + row) * N2 + (n >> 1)) = hh;
+                            return hh;
+                        };
+                        uint16_t* const to = e.H + (int64_t)row0 * N2 + (n >> 1);
+                        if ((N2 & 1) == 0) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const int row = 8 * k + (lane >> 3);
+                                const uint32_t hh = gate(out[k]);
+                                if (row < rows && n < e.N) *reinterpret_cast<uint32_t*>(to + (int64_t)row * N2) = hh;
+                            }
+                        } else {                                 // rows that start on a single value
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const int row = 8 * k + (lane >> 3);
+                                const uint32_t hh = gate(out[k]);
+                                if (row < rows && n < e.N) to[(int64_t)row * N2] = (uint16_t)hh;
+                                if (row < rows && n + 2 < e.N) to[(int64_t)row * N2 + 1] = (uint16_t)(hh >> 16);
+                            }
                         }
                     }
                     __builtin_amdgcn_wave_barrier();
@@ -246,15 +287,7 @@ struct Epilogue {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int row = 8 * g + 4 * lg + i, n = n0 + l32;
-                            const float o = y[mt][4 * g + i] * d[i];
-                            if constexpr (!GATED) {
-                                if (row < rows && n < e.N) e.Y[(int64_t)(row0 + row) * e.N + n] = o;
-                            } else {
-                                const float up = __shfl_xor(o, 1, 64);
-                                const float h = o / (1.0f + __expf(-o)) * up;
-                                if (row < rows && (l32 & 1) == 0 && n + 1 < e.N)
-                                    e.H[(int64_t)(row0 + row) * N2 + (n >> 1)] = __builtin_bit_cast(uint16_t, (__bf16)h);
-                            }
+                            if (row < rows && n < e.N) e.Y[(int64_t)(row0 + row) * e.N + n] = y[mt][4 * g + i] * d[i];
                         }
                     }
                 }

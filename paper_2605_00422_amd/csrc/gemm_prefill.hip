@@ -552,9 +552,10 @@ __global__ __launch_bounds__(64 * WK, 1) void gemm_prefill_direct_kernel(GD_PARA
 // that changes little (25600 -> 5120 at 2048 tokens, 64 x 640: 196 us with private rings, 192; the matrix cores are busy
 // for 60 and 58 % of the launch).  What pays is the LDS it frees: two or more workgroups a CU, which hide each other's
 // barriers, prologues and epilogues (28672 -> 8192 at 4096 tokens 733 -> 680 us, 4096 -> 22016 at 2048 259 -> 207).
-// Held to the 256 registers that two workgroups a CU leave, only 64 x 512 with nibble codes spills (28, outside the loop).
+// With the 256 registers that two workgroups a CU leave none spills; 64 x 128 with nibble codes, held to the 128 at which four
+// share a CU, five, outside the loop.
 template <int NTL, int NB, int WN, bool GATED, bool A4>
-__global__ __launch_bounds__(64 * WN, NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
+__global__ __launch_bounds__(64 * WN, A4 && NTL == 1 && WN == 4 ? 4 : NB == 2 || NTL <= 3 ? 2 : 1) void gemm_prefill_shared_kernel(GD_PARAMS) {
     gd_body<NTL, 1, NB, WN, GATED, A4>(GD_ARGS);
 }
 #undef GD_PARAMS

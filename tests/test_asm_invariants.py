@@ -317,3 +317,26 @@ def test_sparse_gemm_keeps_stores_in_flight_where_rows_start_anywhere(sparse_asm
         behind = [i for i, l in enumerate(lines) if l.startswith("global_store_short")]
         reads = sum(2 if l.startswith("ds_read2_") else 1 for l in lines[behind[0] - 200:behind[0]] if l.startswith("ds_read"))
         assert len(behind) == 8 and reads >= 8
+
+
+@pytest.mark.parametrize("kernel,tile", [("direct", (1, 4, 4)), ("direct", (3, 2, 4)), ("shared", (1, 4, 4)), ("shared", (5, 4, 4))])
+def test_epilogue_reads_a_tile_from_lds_before_it_stores(gemm_asm, kernel, tile):
+    """A store is a branch, and what is read behind it waits by itself: of the four whole-line stores of a tile none has a read
+    of LDS in front of it but the first.  (One by one, 512 columns to 11140 channels at 806 tokens took 25.9 us, 21.3 now.)"""
+    pat = re.compile(rf"^_ZN.*gemm_prefill_{kernel}_kernelI" + "".join(f"Li{x}E" for x in tile) + "Lb0ELb0E.*:")
+    start = next(i for i, l in enumerate(gemm_asm) if pat.match(l))
+    end = next(i for i in range(start, len(gemm_asm)) if ".amdhsa_next_free_vgpr" in gemm_asm[i])
+    lines = [l.strip() for l in gemm_asm[start:end]]
+    last = max(i for i, l in enumerate(lines) if l.startswith("v_mfma_i32"))
+    runs, run, read = [], 0, False
+    for l in lines[last:]:
+        if l.startswith("ds_write"):
+            runs, run = runs + [run] if run else runs, 0
+        elif l.startswith("ds_read"):
+            read = True
+        elif l.startswith("global_store_dwordx4"):
+            if run and read:
+                runs, run = runs + [run], 0
+            run, read = run + 1, False
+    runs.append(run)
+    assert runs and all(n >= 4 for n in runs if n), runs
