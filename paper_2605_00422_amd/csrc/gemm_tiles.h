@@ -11,10 +11,12 @@
 // in runs of tiles with the same token rows where their number is a multiple of eight, and each row enters one L2;
 // otherwise up to eight L2s fetch it.  The smallest cost is taken.
 //
-// The constants are fitted to 628 shapes (the projections of the 4096-, 5120- and 8192-wide blocks and others at random:
-// 17 .. 4096 tokens, K 128 .. 28672, N 32 .. 51200, ranks 0 .. 96), each with plain and gated int8 codes and with nibble
-// codes, three layers in turn so that nothing stays in L2.  Over those the choice is within 0.5 / 0.4 / 1.0 % of the best
-// of the ten on average (2.8 / 2.9 / 3.4 % with constants fitted to an epilogue that took twice the time).  Five more tiles
+// The constants are fitted to 2500 shapes (the projections of the 4096-, 5120- and 8192-wide blocks and others at random:
+// 17 .. 4096 tokens, K 128 .. 28672, N 32 .. 40000, ranks 0 .. 128), each with plain and gated int8 codes and with nibble
+// codes, three layers in turn so that nothing stays in L2, short launches from a graph.  Over those the choice is within
+// 0.7 / 0.8 / 0.4 % of the best of the ten on average, and more than a tenth above it at 1.3 / 1.5 / 1.2 % of them.  (Constants fitted
+// to an epilogue that took longer and to fewer short launches: 1.6 / 1.7 / 0.9 % and 4.6 / 5.5 / 2.9 %; with these 11 % of the
+// calls take 2 % less time or better and 0.5 % that much more.  24 tokens of 512 columns, 270 channels, rank 0 5.4 -> 4.6 us.)  Five more tiles
 // that were candidates (64 x 32 for one wavefront, 256 x 128 with rings of two and four, 256 x 160, 64 x 640 with private
 // rings) moved no average by more than 0.1 % and are not built.
 #pragma once
@@ -33,17 +35,17 @@ struct GdTile {
 constexpr int GD_TILE_TOKENS = 64;
 constexpr GdTile GD_TILES[] = {
     // few tokens: private rings, the wavefronts of a workgroup share out K
-    {1, 4, 4, 1, 1, 1.39f, {4.39f}, {0.3409f}, 0.0920f, 0.369f, 0.953f},                                                   // 64 x 32, in four
-    {2, 4, 4, 1, 1, 1.86f, {4.73f}, {0.4795f}, 0.1366f, 0.486f, 0.895f},                                                   // 64 x 64, in four
-    {2, 2, 4, 1, 2, 1.70f, {5.77f, 7.18f}, {0.3811f, 0.4007f}, 0.0648f, 0.634f, 0.934f},                                   // 64 x 64, in two
-    {3, 2, 4, 1, 2, 1.95f, {7.29f, 10.13f}, {0.5066f, 0.5755f}, 0.0908f, 0.838f, 0.975f},                                  // 64 x 96, in two
+    {1, 4, 4, 1, 1, 1.42f, {4.76f}, {0.3940f}, 0.0963f, 0.353f, 0.954f},                                                  // 64 x 32, in four
+    {2, 4, 4, 1, 1, 1.78f, {4.58f}, {0.4895f}, 0.1293f, 0.541f, 1.030f},                                                  // 64 x 64, in four
+    {2, 2, 4, 1, 2, 1.71f, {5.25f, 6.94f}, {0.3802f, 0.3879f}, 0.0872f, 0.711f, 0.931f},                                  // 64 x 64, in two
+    {3, 2, 4, 1, 2, 1.95f, {7.29f, 10.01f}, {0.5066f, 0.5755f}, 0.0908f, 0.838f, 0.944f},                                 // 64 x 96, in two
     // one ring of codes for four wavefronts (the first: two)
-    {1, 1, 4, 2, 4, 3.22f, {2.47f, 3.63f, 4.93f, 7.06f}, {0.2795f, 0.3006f, 0.4409f, 0.4146f}, 0.0314f, 0.475f, 1.127f},   // 64 x 64
-    {1, 1, 4, 4, 3, 3.52f, {2.52f, 5.13f, 8.09f}, {0.3036f, 0.4222f, 0.4827f}, 0.0817f, 0.552f, 1.103f},                   // 64 x 128
-    {2, 1, 4, 4, 2, 1.69f, {8.99f, 9.37f}, {0.3721f, 0.6385f}, 0.0796f, 0.803f, 1.027f},                                   // 64 x 256
-    {3, 1, 4, 4, 2, 3.77f, {8.00f, 13.44f}, {0.4317f, 0.8893f}, 0.1199f, 0.869f, 1.092f},                                  // 64 x 384
-    {4, 1, 2, 4, 2, 4.49f, {8.78f, 15.57f}, {0.6888f, 1.2477f}, 0.1249f, 1.179f, 1.087f},                                  // 64 x 512, ring of two
-    {5, 1, 4, 4, 1, 0.00f, {16.35f}, {0.8438f}, 0.2302f, 1.596f, 1.062f},                                                  // 64 x 640
+    {1, 1, 4, 2, 4, 3.15f, {2.24f, 3.61f, 5.04f, 7.02f}, {0.2804f, 0.3010f, 0.4477f, 0.4147f}, 0.0345f, 0.654f, 1.102f},  // 64 x 64
+    {1, 1, 4, 4, 3, 3.52f, {1.99f, 5.13f, 7.93f}, {0.3036f, 0.4222f, 0.5095f}, 0.0809f, 0.552f, 1.103f},                  // 64 x 128
+    {2, 1, 4, 4, 2, 1.69f, {8.81f, 9.37f}, {0.3710f, 0.6488f}, 0.0786f, 0.769f, 1.027f},                                  // 64 x 256
+    {3, 1, 4, 4, 2, 3.77f, {8.62f, 13.44f}, {0.4060f, 0.8893f}, 0.1199f, 0.869f, 1.089f},                                 // 64 x 384
+    {4, 1, 2, 4, 2, 4.46f, {9.33f, 15.62f}, {0.6637f, 1.2518f}, 0.1257f, 1.119f, 1.044f},                                 // 64 x 512, ring of two
+    {5, 1, 4, 4, 1, 0.00f, {16.35f}, {0.8438f}, 0.2189f, 1.854f, 1.089f},                                                 // 64 x 640
 };
 constexpr int GD_NTILES = sizeof(GD_TILES) / sizeof(GD_TILES[0]);
 
@@ -100,8 +102,9 @@ inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4,
 // but prepares its operands at more cost, in steps of 512 columns, and its wide tiles start and finish slowly: it wins where
 // tiles are many and rows of K long.  Fitted to 945 pairs of shape and form (65 .. 4096 tokens, K 128 .. 28672, N 32 .. 51200,
 // plain and gated), three layers in turn; it is taken where its cost is 3 % below the dense kernel's.  Over those the choice
-// takes 0.992 of the dense kernel's time (0.988 with the best tile of both every time; 0.68 .. 0.9 for the longest), with 2
-// times more than 2 % above it; without the 3 %, 16.  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and move the
+// took 0.992 of the time of the dense kernel as it was then (0.988 with the best tile of both every time), with 2 times more than
+// 2 % above it; without the 3 %, 16.  Long ones against the dense kernel of before its last epilogue, rank 64: 0.72 (28672 ->
+// 28672 at 4096 tokens), 0.77 (28672 -> 8192), 0.87 (8192 -> 28672), 0.88 (25600 -> 5120 at 2048), 0.92 (4096 -> 22016 gated).  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and move the
 // average by less than 0.7 % at ten times as many wrong choices.
 struct GsTile {
     int mt, nt, wn, ring;         // 32-token tiles and 32-channel tiles a wavefront; wavefronts side by side; pairs in the code ring

@@ -84,6 +84,22 @@ def test_recorded_shapes_take_a_fast_tile(pick, shape, a4, tiles):
 
 
 # ---- the sparse GEMM's tiles (same header)
+# Short rows of K and low ranks, where constants fitted to a slower epilogue had lost time against the kernel of before that
+# epilogue (microseconds: that one, what was taken, now).
+@pytest.mark.parametrize("shape,tiles", [
+    ((24, 512, 270, 0), [(1, 1, 2), (1, 1, 4)]),                     # 4.8, 5.9, 4.6
+    ((23, 384, 868, 0), [(1, 1, 2), (1, 1, 4)]),                     # 4.8, 5.9, 4.6
+    ((25, 384, 666, 0), [(1, 1, 2), (1, 1, 4)]),                     # 5.0, 6.0, 4.8
+    ((806, 512, 11140, 16), [(1, 1, 4), (3, 1, 4)]),                 # 22.6, 25.7, below 18.8
+    ((806, 1408, 11140, 16), [(1, 1, 4), (3, 1, 4)]),                # 30.0, 33.0, 25.3
+    ((385, 1408, 21018, 16), [(1, 1, 4), (3, 1, 4)]),                # (5, 1, 4): 34.3
+])
+def test_short_rows_take_a_fast_tile(pick, shape, tiles):
+    i = pick([shape])[0]
+    ntl, wk, _, wn, _ = pick.tiles[i]
+    assert (ntl, wk, wn) in tiles
+
+
 SPARSE_DRIVER = """
 #include <cstdio>
 #include "gemm_tiles.h"
