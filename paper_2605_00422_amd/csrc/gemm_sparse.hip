@@ -96,9 +96,9 @@ constexpr int gs_vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4
 // (21.6 ns each; dense ones at 1.8, 17.6 ns for half the columns), and beyond four vector instructions for each every
 // further one costs its four cycles.  Hence wide wavefront tiles (the 13 instructions that prepare an operand of weights
 // serve MT contractions) and codes prepared once for all channels: prepared per workgroup on the way to LDS they took a
-// fifth of the instructions and a register-staged copy (28672 -> 8192 at 4096 tokens 545 us; 477 + 36 this way, 760 dense).
-// Whole layer, before and after: 28672 -> 8192 at 4096 tokens 987 -> 830 us, 25600 -> 5120 at 2048 362 -> 329, 4096 -> 22016
-// gated at 2048 247 -> 213.
+// fifth of the instructions and a register-staged copy (28672 -> 8192 at 4096 tokens 545 us; 477 + 36 this way).
+// Pass and GEMM against the dense kernel, in turn on one card, rank 64: 28672 -> 8192 at 4096 tokens 653 -> 490 us, 28672 ->
+// 28672 2288 -> 1643, 25600 -> 5120 at 2048 186 -> 168, 4096 -> 22016 gated at 2048 174 -> 168.
 template <int MT, int NT, int WN, int RING, int RESIDENT, bool GATED>
 __global__ __launch_bounds__(64 * WN, RESIDENT) void gemm_sparse_kernel(
     const uint4* __restrict__ bits, int chunks, int row_tiles, const uint8_t* __restrict__ z, const uint32_t* __restrict__ flags,

@@ -103,9 +103,9 @@ inline int gd_pick(int64_t M, int64_t K, int64_t N, int r, int64_t cus, bool a4,
 // tiles are many and rows of K long.  Fitted to 945 pairs of shape and form (65 .. 4096 tokens, K 128 .. 28672, N 32 .. 51200,
 // plain and gated), three layers in turn; it is taken where its cost is 3 % below the dense kernel's.  Over those the choice
 // took 0.992 of the time of the dense kernel as it was then (0.988 with the best tile of both every time), with 2 times more than
-// 2 % above it; without the 3 %, 16.  Long ones against the dense kernel of before its last epilogue, rank 64: 0.72 (28672 ->
-// 28672 at 4096 tokens), 0.77 (28672 -> 8192), 0.87 (8192 -> 28672), 0.88 (25600 -> 5120 at 2048), 0.92 (4096 -> 22016 gated).  64 x 128, 64 x 384 and 128 x 384 tiles were candidates and move the
-// average by less than 0.7 % at ten times as many wrong choices.
+// 2 % above it; without the 3 %, 16.  Long ones against the dense kernel as it is, rank 64: 0.72 (28672 -> 28672 at 4096
+// tokens), 0.75 (28672 -> 8192), 0.87 (8192 -> 28672), 0.90 (25600 -> 5120 at 2048), 0.96 (4096 -> 22016 gated).  64 x 128,
+// 64 x 384 and 128 x 384 tiles were candidates and move the average by less than 0.7 % at ten times as many wrong choices.
 struct GsTile {
     int mt, nt, wn, ring;         // 32-token tiles and 32-channel tiles a wavefront; wavefronts side by side; pairs in the code ring
     int resident;                 // workgroups a CU holds

@@ -22,8 +22,9 @@
 // converted and written to LDS between the two barriers that every token costs.  The codes go through
 // LDS too, beside the token rows where there is room, or else in their place at the cost of two more
 // barriers, and leave in whole lines: a wavefront's own are 16 rows of 16 bytes, and every such piece
-// took 4.4 cycles of the CU (9000 of 34000 a token; 4096 tokens of 224 x 128 241 -> 221 us, 160 x 160
-// 218 -> 184, of 128 x 64 50 -> 43, of 64 x 64 22.5 -> 20.2).  G groups of
+// took 4.4 cycles of the CU (9000 of 34000 a token of 224 x 128: 241 -> 221 us at 4096 tokens).  With LDS
+// reads kept ahead of the MFMAs (below) besides: 250 -> 205, 160 x 160 217 -> 184, 128 x 64 49 -> 43, 64 x 64
+// 22.5 -> 20.4.  G groups of
 // n2 / 16 wavefronts work on G tokens at a time over the one copy of R1 (small factors would
 // otherwise leave most of a CU's SIMDs with a single wavefront).
 #include "bwla_internal.h"
@@ -201,7 +202,7 @@ __global__ __launch_bounds__((N2 / 16) * 64 * G) void rotate_planes_kernel(RpArg
         // LDS operands are requested two steps (stage 1) or one (stage 2) before the MFMAs that use them (a step: the
         // four MFMAs of one 32-deep piece of stage 1, or the three of one output tile of stage 2), and nothing moves over
         // a step's end: left to itself the scheduler puts the reads of two steps together and waits for them at
-        // once (224 x 128 221 -> 205 us at 4096 tokens).
+        // once (224 x 128, codes through LDS already: 221 -> 205 us at 4096 tokens).
         if (S::OWN && j > 0 && t - tstep < a.M) write_codes(t - tstep);
         v4f y[AT];
 #pragma unroll
