@@ -62,8 +62,9 @@ struct bwla_psp_plan {
     int tile_cols;     // columns per tile
     int col_groups;    // tiles across the rank
 };
-// (planes: bwla_rotate_planes_serves the call; f32: fp32 tokens)
-bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32);
+// (planes: bwla_rotate_planes_serves the call; f32: fp32 tokens; slow: psp_ride.h)
+bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32, bool slow);
+bool bwla_rotation_is_slow(const bwla_layer_t* L, int64_t M, int xdtype);
 bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M);
 // whether it rides in the rotation's launch: never beyond this many tokens
 constexpr int64_t BWLA_RIDE_TOKENS = 768;
@@ -86,7 +87,8 @@ inline int bwla_extra_cols(int mode) { return ((mode & BWLA_MODE_ASYM_ACT) ? 2 :
 inline int bwla_rank_u(const bwla_layer_t* L) { return L->r - bwla_extra_cols(L->mode); }
 inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
     // (up to 16 tokens the plan is the same either way, and a decode call of 6 us does not ask the device twice)
-    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), M > 16 && bwla_rotate_planes_serves(L, xdtype, M), xdtype == BWLA_X_F32);
+    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), M > 16 && bwla_rotate_planes_serves(L, xdtype, M), xdtype == BWLA_X_F32,
+                              bwla_rotation_is_slow(L, M, xdtype));
 }
 inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int r) {
     if (r <= 0 || p.splits <= 1) return 0;

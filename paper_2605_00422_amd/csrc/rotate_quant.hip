@@ -195,16 +195,24 @@ inline int64_t psp_riders(int64_t M, int64_t K, int r) { return ((M + 15) / 16) 
 
 bool bwla_psp_rides(const bwla_layer_t* L, int64_t M, int64_t cus, bool planes, bool f32) {
     const int r = bwla_rank_u(L);
-    return M <= 16 || r <= 0 || psp_rides(M, L->K, psp_riders(M, L->K, r), cus, planes, f32);
+    return M <= 16 || r <= 0 || psp_rides(M, L->K, psp_riders(M, L->K, r), cus, planes, f32,
+                                          bwla_rotation_is_slow(L, M, f32 ? BWLA_X_F32 : BWLA_X_BF16));
 }
 
-bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32) {
+// (asked only where the plan depends on it)
+bool bwla_rotation_is_slow(const bwla_layer_t* L, int64_t M, int xdtype) {
+    if (xdtype == BWLA_X_F32 || M <= 16 || M > BWLA_RIDE_TOKENS) return false;
+    const R3Shape s = r3_shape(L->n1, L->n2);
+    return !s.ok || (!s.resident && s.strips <= 5);
+}
+
+bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32, bool slow) {
     bwla_psp_plan p;
     const int rp = (r + 15) & ~15;
     const int jg = psp_groups(r);
     const bool always = M <= 16 || r <= 0;
     const int64_t cus = always ? 1 : bwla_device_cus();
-    if (always || psp_rides(M, K, psp_riders(M, K, r), cus, planes, f32)) {
+    if (always || psp_rides(M, K, psp_riders(M, K, r), cus, planes, f32, slow)) {
         p.token_tiles = (int)((M + 15) / 16);
         p.k_per_split = PP_SLICE;
         p.splits = r > 0 ? (int)((K + PP_SLICE - 1) / PP_SLICE) : 1;

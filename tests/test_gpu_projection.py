@@ -35,6 +35,8 @@ CASES = [
     (257, 64, 80, 8, "bf16"),       # rides in the shadow of the second round
     (768, 137, 32, 20, "bf16"),     # factors that the fp32 kernel rotates: the largest that leaves its tiles
     (769, 137, 32, 20, "bf16"),     # and the first that hands them over
+    (185, 172, 64, 8, "bf16"),      # a slow rotation, in whose shadow it rides
+    (158, 163, 32, 64, "bf16"),     # likewise, by the fp32 kernel
     (192, 80, 64, 37, "f32"),       # fp32 tokens ride by the number of workgroups
     (384, 64, 64, 37, "f32"),
 ]

@@ -63,3 +63,32 @@ def test_fp32_tokens(rides, shape, want):
 def test_bf16_tokens(rides, shape, want):
     assert rides(*shape, f32=False) == want
     assert not rides(*shape, f32=False, planes=True)
+
+
+SLOW = DRIVER.replace('%d %d", &M', '%d %d %d", &M').replace("int planes, f32;", "int planes, f32, slow;").replace(
+    "&f32) == 5", "&f32, &slow) == 6").replace("planes, f32))", "planes, f32, slow))")
+
+
+# (tokens, n1, n2, rank): bf16 tokens whose rotation takes longer than its row is long; microseconds: riding, in a launch of its own
+@pytest.mark.parametrize("shape,want", [
+    ((185, 172, 64, 8), True),                  # 30.4, 35.8
+    ((185, 192, 64, 8), True),                  # 30.9, 34.9
+    ((185, 256, 48, 8), True),                  # 34.6, 38.9
+    ((185, 200, 80, 8), True),                  # 41.4, 47.1
+    ((158, 163, 32, 64), True),                 # 26.1, 34.4
+    ((400, 163, 32, 8), True),                  # 49.0, 56.1
+    ((158, 172, 64, 64), True),                 # 34.7, 36.9
+    ((230, 172, 64, 8), False),                 # 41.0, 35.8
+    ((230, 200, 80, 8), False),                 # 54.1, 48.2
+    ((230, 163, 32, 64), False),                # 37.8, 35.7
+    ((400, 172, 64, 8), True),                  # 57.8, 62.6
+    ((520, 200, 80, 8), True),                  # 117.7, 125.5
+])
+def test_tokens_of_slow_rotations(tmp_path, shape, want):
+    (tmp_path / "ride.cpp").write_text(SLOW)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", str(tmp_path / "ride"), str(tmp_path / "ride.cpp")], check=True)
+    M, n1, n2, r = shape
+    tiles, K = (r + 15) // 16, n1 * n2
+    riders = (M + 15) // 16 * ((K + 511) // 512) * ((tiles + 1) // 2 if tiles > 2 else 1)
+    out = subprocess.run([str(tmp_path / "ride")], input=f"{M} {K} {riders} 0 0 1\n", text=True, capture_output=True, check=True).stdout
+    assert (out.strip() == "1") == want
