@@ -288,20 +288,21 @@ def rotate_quant(layer: PackedLayer, X, act: Activations, act_bits: int = 6) -> 
 def decode_forward(layer: PackedLayer, X, act: Activations, Y, acc=None, act_bits: int = 6):
     """bwla_rotate_quant + bwla_linear_forward in one call (one kernel launch where possible)."""
     xd = _xdtype(X)
-    if act.room is not None:
-        _check(load().bwla_decode_forward_room(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
+    M = X.shape[0]
+    if M > 64 and act.room is not None:                                     # (up to 64 tokens nothing is laid out)
+        _check(load().bwla_decode_forward_room(layer._ref, _ptr(X), xd, int(act_bits), M, _ptr(act.q),
                                                _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
                                                _ptr(act.room), act.room_bytes, _ptr(Y), _ptr(acc), _stream()),
                "bwla_decode_forward_room")
     elif act_bits == 6:
         # (a call of one token takes the host as long as the GPU: no conversion here)
-        _check(load().bwla_decode_forward(layer._ref, _ptr(X), xd, X.shape[0], _ptr(act.q), _ptr(act.scale),
+        _check(load().bwla_decode_forward(layer._ref, _ptr(X), xd, M, _ptr(act.q), _ptr(act.scale),
                                           _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes, _ptr(Y), _ptr(acc),
                                           _stream()), "bwla_decode_forward")
         act.act_bits = 6
         return Y
     else:
-        _check(load().bwla_decode_forward_bits(layer._ref, _ptr(X), xd, int(act_bits), X.shape[0], _ptr(act.q),
+        _check(load().bwla_decode_forward_bits(layer._ref, _ptr(X), xd, int(act_bits), M, _ptr(act.q),
                                                _ptr(act.scale), _ptr(act.qsum), _ptr(act.T), _ptr(act.ws), act.ws_bytes,
                                                _ptr(Y), _ptr(acc), _stream()), "bwla_decode_forward_bits")
     act.act_bits = int(act_bits)
