@@ -58,8 +58,7 @@ constexpr int RQ_CK = 16;            // contraction indices per streamed factor 
 constexpr int RQ_CLD = RQ_CK + 4;    // LDS pitch of a streamed chunk row
 constexpr int RQ_RING = 3;           // streamed chunks in flight (registers)
 constexpr int PP_SLICE = 512;        // columns of K per projection workgroup
-constexpr int PP_MAXJT = BWLA_MAX_RANK / 16;
-constexpr int PP_GROUPJT = 2;        // 16-column tiles of the rank per projection workgroup when they are dealt out
+constexpr int PP_GROUPJT = 2;        // 16-column tiles of the rank per projection workgroup: more are dealt out
 constexpr size_t RQ_LDS_LIMIT = 160 * 1024 - 256;   // leaves room for the few static bytes
 
 __host__ __device__ inline int rq_pad16(int n) { return (n + 15) & ~15; }
@@ -93,8 +92,8 @@ __host__ __device__ inline RqShape rq_shape(int n1, int n2) {
 }
 
 __host__ __device__ inline size_t pp_lds_bytes(int r, int waves = RQ_WAVES) {
-    const int rp = ((r + 15) >> 4) * 16;
-    return (size_t)waves * (rp / 16) * 64 * 16 + 16;                   // cross-wave reduction
+    const int tiles = (r + 15) >> 4;
+    return (size_t)waves * (tiles < PP_GROUPJT ? tiles : PP_GROUPJT) * 64 * 16 + 16;   // cross-wave reduction
 }
 
 // Exact n / d for n * d < 2^32 with one multiply-high; index arithmetic on run-time factor
