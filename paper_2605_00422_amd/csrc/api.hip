@@ -28,7 +28,8 @@ bwla_status_t check_shape(int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t 
 }
 
 // r counts the columns of V and T; U keeps the PSP columns only
-void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode) {
+// (planes false: without operand-order factors, as a library before laid out pairs that are no multiples of 32)
+void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode, bool planes = true) {
     const uint64_t rp = (uint64_t)((r + 15) & ~15);
     const uint64_t rpu = (uint64_t)((r - bwla_extra_cols(mode) + 15) & ~15);
     uint64_t off = 0;
@@ -42,7 +43,7 @@ void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, 
     L->off_R1p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n1));
     L->off_R2p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n2));
     L->off_Rd = 0;
-    if (bwla_decode_planes_bytes(n1, n2) > 0) { L->off_Rd = off; off = bwla_align256(off + bwla_decode_planes_bytes(n1, n2)); }
+    if (planes && bwla_decode_planes_bytes(n1, n2) > 0) { L->off_Rd = off; off = bwla_align256(off + bwla_decode_planes_bytes(n1, n2)); }
     L->blob_bytes = off;
 }
 
@@ -54,7 +55,7 @@ bwla_status_t check_layer(const bwla_layer_t* L) {
     if ((L->mode & ~(BWLA_MODE_ROW_SHIFT | BWLA_MODE_ASYM_ACT)) != 0 || L->r < bwla_extra_cols(L->mode))
         return BWLA_ERR_SHAPE;
     bwla_layer_t ref;
-    fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode);
+    fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode, L->off_Rd != 0 || bwla_planes_whole(L->n1, L->n2));
     if (ref.off_bits != L->off_bits || ref.off_alpha != L->off_alpha || ref.off_V != L->off_V ||
         ref.off_U != L->off_U || ref.off_R1 != L->off_R1 || ref.off_R2 != L->off_R2 ||
         ref.off_R1p != L->off_R1p || ref.off_R2p != L->off_R2p || ref.off_Rd != L->off_Rd ||
@@ -100,10 +101,9 @@ size_t rq_most(const bwla_layer_t* L, int64_t M) {
     see(2 * slots);
     for (int64_t m = M - 1 < 2048 ? (M - 1) & ~(int64_t)63 : 2048; m > BWLA_RIDE_TOKENS; m -= 64) see(m);
     const int64_t split = bwla_split_rotation_tokens(L), cus = bwla_device_cus();
-    const bool planes = bwla_rotate_planes_serves(L, BWLA_X_BF16, cus);
     int at = 0;
     for (int64_t m = (M < BWLA_RIDE_TOKENS ? M : BWLA_RIDE_TOKENS); m > 0; --m) {
-        const int now = bwla_psp_rides(L, m, cus, planes && m >= cus, false) | bwla_psp_rides(L, m, cus, false, true) << 1;
+        const int now = bwla_psp_rides(L, m, cus, m > 16 && bwla_rotation_walks(L, BWLA_X_BF16, m), false) | bwla_psp_rides(L, m, cus, false, true) << 1;
         if (m <= split || (m & 63) == 0 || now != at) see(m);
         at = now;
     }

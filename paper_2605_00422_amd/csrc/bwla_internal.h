@@ -31,21 +31,23 @@ inline uint64_t bwla_factor_planes_bytes(int n) {
     return (uint64_t)3 * ((n + 15) & ~15) * ((n + 31) & ~31) * 2;
 }
 
-// Factor planes in MFMA operand order (one contiguous KiB per operand), stored for factor pairs
-// that are multiples of 32, n1 up to 256 and n2 up to 160 (0 bytes otherwise), three parts:
+// Factor planes in MFMA operand order (one contiguous KiB per operand), stored for factors up to 256 and 160 of an even n2
+// (0 bytes otherwise), three parts:
 //   R2d  three bf16 terms of R2, (n2 / 16) strips x (n2 / 32) steps x 3 KiB: only for the pairs the
 //        single-launch decode kernel takes (n1 of 32, 64 or 128, n2 of 32 or 64)
-//   R1h  two fp16 terms of 256 R1, (n1 / 32) steps x 2 x (n1 / 16) KiB
-//   R2h  two fp16 terms of 256 R2, (n2 / 16) strips x (n2 / 32) steps x 2 KiB
-inline bool bwla_planes_shape_ok(int n1, int n2) {
+//   R1h  two fp16 terms of 256 R1, padded with zeros to a multiple of 32: steps of 32 x 2 x tiles of 16 KiB
+//   R2h  two fp16 terms of 256 R2, padded likewise: strips of 16 x steps of 32 x 2 KiB
+inline bool bwla_planes_shape_ok(int n1, int n2) { return n1 <= 256 && n2 <= 160 && (n2 & 1) == 0; }
+// (the pairs for which a library before stored them)
+inline bool bwla_planes_whole(int n1, int n2) {
     return n1 >= 32 && n2 >= 32 && n1 <= 256 && n2 <= 160 && (n1 & 31) == 0 && (n2 & 31) == 0;
 }
 inline uint64_t bwla_decode_planes_r2_bytes(int n1, int n2) {
     const bool ok = (n1 == 32 || n1 == 64 || n1 == 128) && (n2 == 32 || n2 == 64);
     return ok ? (uint64_t)(n2 / 16) * (n2 / 32) * 3 * 1024 : 0;
 }
-inline uint64_t bwla_planes_r1h_bytes(int n1) { return (uint64_t)(n1 / 32) * 2 * (n1 / 16) * 1024; }
-inline uint64_t bwla_planes_r2h_bytes(int n2) { return (uint64_t)(n2 / 16) * (n2 / 32) * 2 * 1024; }
+inline uint64_t bwla_planes_r1h_bytes(int n1) { const uint64_t s = (n1 + 31) / 32; return s * 2 * (2 * s) * 1024; }
+inline uint64_t bwla_planes_r2h_bytes(int n2) { return (uint64_t)((n2 + 15) / 16) * ((n2 + 31) / 32) * 2 * 1024; }
 inline uint64_t bwla_decode_planes_bytes(int n1, int n2) {
     if (!bwla_planes_shape_ok(n1, n2)) return 0;
     return bwla_decode_planes_r2_bytes(n1, n2) + bwla_planes_r1h_bytes(n1) + bwla_planes_r2h_bytes(n2);
@@ -62,10 +64,12 @@ struct bwla_psp_plan {
     int tile_cols;     // columns per tile
     int col_groups;    // tiles across the rank
 };
-// (planes: bwla_rotate_planes_serves the call; f32: fp32 tokens; slow: psp_ride.h)
+// (planes: bwla_rotation_walks; f32: fp32 tokens; slow: psp_ride.h)
 bwla_psp_plan bwla_make_psp_plan(int64_t M, int64_t K, int r, bool planes, bool f32, bool slow);
 bool bwla_rotation_is_slow(const bwla_layer_t* L, int64_t M, int xdtype);
 bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M);
+// whether the rotation's workgroups walk over their tokens (a kernel with resident factors): the projection then never rides
+bool bwla_rotation_walks(const bwla_layer_t* L, int xdtype, int64_t M);
 // whether it rides in the rotation's launch: never beyond this many tokens
 constexpr int64_t BWLA_RIDE_TOKENS = 768;
 bool bwla_psp_rides(const bwla_layer_t* L, int64_t M, int64_t cus, bool planes, bool f32);
@@ -85,15 +89,23 @@ constexpr uint64_t BWLA_PSP_COUNTER_BYTES = BWLA_PSP_COUNTERS * sizeof(int);
 inline int bwla_extra_cols(int mode) { return ((mode & BWLA_MODE_ASYM_ACT) ? 2 : 0) + ((mode & BWLA_MODE_ROW_SHIFT) ? 1 : 0); }
 // columns of U = rank of the projection T = X U
 inline int bwla_rank_u(const bwla_layer_t* L) { return L->r - bwla_extra_cols(L->mode); }
-inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
-    // (up to 16 tokens the plan is the same either way, and a decode call of 6 us does not ask the device twice)
-    return bwla_make_psp_plan(M, L->K, bwla_rank_u(L), M > 16 && bwla_rotate_planes_serves(L, xdtype, M), xdtype == BWLA_X_F32,
-                              bwla_rotation_is_slow(L, M, xdtype));
-}
 inline size_t bwla_psp_ws_bytes(const bwla_psp_plan& p, int r) {
     if (r <= 0 || p.splits <= 1) return 0;
     return (size_t)(BWLA_PSP_COUNTER_BYTES + (uint64_t)p.token_tiles * p.col_groups * p.splits *
                                                     p.tile_rows * p.tile_cols * sizeof(float));
+}
+inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdtype) {
+    const int r = bwla_rank_u(L);
+    const bool f32 = xdtype == BWLA_X_F32, slow = bwla_rotation_is_slow(L, M, xdtype);
+    // (up to 16 tokens the plan is the same either way, and a decode call of 6 us does not ask the device twice)
+    const bool walks = M > 16 && bwla_rotation_walks(L, xdtype, M);
+    const bwla_psp_plan p = bwla_make_psp_plan(M, L->K, r, walks, f32, slow);
+    // (what the array of bwla_decode_forward_static holds behind the head and the counters that it clears)
+    constexpr uint64_t room = BWLA_STATIC_SCRATCH_BYTES + BWLA_PSP_COUNTER_BYTES - BWLA_WS_HEAD - 256;
+    if (!walks || r <= 0 || M > BWLA_RIDE_TOKENS || bwla_psp_ws_bytes(p, r) <= room) return p;
+    // (too many partial tiles for it, where those of a riding projection fit: ranks above 64)
+    const bwla_psp_plan riding = bwla_make_psp_plan(M, L->K, r, bwla_rotate_planes_serves(L, xdtype, M), f32, slow);
+    return bwla_psp_ws_bytes(riding, r) <= room ? riding : p;
 }
 // where the rotation's own part begins
 inline size_t bwla_split_start(const bwla_psp_plan& p, int r) {

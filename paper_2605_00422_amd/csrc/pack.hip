@@ -192,7 +192,7 @@ __global__ void factor_planes_kernel(const float* __restrict__ R, int n, int per
     P[2 * plane + i] = (uint16_t)(h3 >> 16);
 }
 
-// Factor planes in MFMA operand order (factor pairs that are multiples of 32 up to 160), one 1 KiB
+// Factor planes in MFMA operand order (both factors padded with zeros to multiples of 32), one 1 KiB
 // block per MFMA operand, lane (li, lg) = lg * 16 + li holding eight 16-bit values:
 //   R2d part (pairs of 32 or 64 only), blocks [strip w][step kb][term p < 3]: term p (bf16; the
 //            three add up to the fp32 value) of R2[b = 32 kb + 8 lg + e][d = 16 w + li]
@@ -202,7 +202,7 @@ __global__ void factor_planes_kernel(const float* __restrict__ R, int n, int per
 //   R2h part, blocks [strip w][step kb][term t < 2]: the same two fp16 terms of 256 R2[b][d]
 __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* __restrict__ R2, int n1, int n2,
                                      int with_r2d, uint16_t* __restrict__ out) {
-    const int at = n1 / 16, k1 = n2 / 32, ch2 = n1 / 32, strips = n2 / 16;
+    const int ch2 = (n1 + 31) / 32, at = 2 * ch2, k1 = (n2 + 31) / 32, strips = (n2 + 15) / 16;
     const int nb2 = with_r2d ? strips * k1 * 3 : 0, nb1 = ch2 * 2 * at, nb2h = strips * k1 * 2;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (nb2 + nb1 + nb2h) * 512) return;
@@ -223,7 +223,8 @@ __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* 
         const int b1 = blk - nb2;
         const int tc = b1 % at, t = (b1 / at) % 2, ch = b1 / (2 * at);
         const int a = 32 * ch + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4);
-        const float v = 256.0f * R1[(int64_t)a * n1 + 16 * tc + li];
+        const int c = 16 * tc + li;
+        const float v = a < n1 && c < n1 ? 256.0f * R1[(int64_t)a * n1 + c] : 0.0f;
         const __half hi = __float2half_rn(v);
         const __half lo = __float2half_rn(v - __half2float(hi));
         out[i] = __half_as_ushort(t == 0 ? hi : lo);
@@ -231,7 +232,8 @@ __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* 
         // R2h, blocks [strip w][step kb][term t < 2]: 256 R2[b = 32 kb + 8 lg + e][d = 16 w + li]
         const int b2 = blk - nb2 - nb1;
         const int t = b2 % 2, kb = (b2 / 2) % k1, w = b2 / (2 * k1);
-        const float v = 256.0f * R2[(int64_t)(32 * kb + 8 * lg + e) * n2 + 16 * w + li];
+        const int b = 32 * kb + 8 * lg + e, d = 16 * w + li;
+        const float v = b < n2 && d < n2 ? 256.0f * R2[(int64_t)b * n2 + d] : 0.0f;
         const __half hi = __float2half_rn(v);
         const __half lo = __float2half_rn(v - __half2float(hi));
         out[i] = __half_as_ushort(t == 0 ? hi : lo);

@@ -377,6 +377,8 @@ hipError_t launch_planes(RpArgs a, int cus, hipStream_t st) {
 bool bwla_rotate_planes_serves(const bwla_layer_t* L, int xdtype, int64_t M) {
     if (xdtype != BWLA_X_BF16 || L->off_Rd == 0 || M < (int64_t)bwla_device_cus()) return false;
     const int n1 = L->n1, n2 = L->n2;
+    // (128 x 64, four tokens a workgroup: up to two a CU half the chip would be idle; 400 tokens 13.0 us, rotate_terms.hip 10.6)
+    if (n1 == 128 && M < 2 * (int64_t)bwla_device_cus()) return false;
     return (n1 == 160 && n2 == 160) || (n1 == 128 && n2 == 64) || (n1 == 64 && n2 == 64) || (n1 == 224 && n2 == 128);
 }
 

@@ -21,47 +21,16 @@
 // them in slice order.
 
 #include "bwla_internal.h"
+#include "rotate_args.h"
 #include "rotate_common.h"
 #include "rotate_f32_device.h"
 #include "rotate_bf16_device.h"
+#include "rotate_terms.h"
 #include "rotate_split_device.h"
 #include "psp_block_device.h"
 #include "psp_ride.h"
 
 namespace {
-
-struct RqArgs {
-    const void* X; int64_t M, K; int n1, n2, r;
-    const float* R1; const float* R2; const __half* U;
-    int8_t* q; float* scale; int32_t* qsum; float* T;
-    int* counters; float* partials; int S;
-    float* xs; float* pmax;  // split rotation: rotated values (M x K) and per-workgroup extremes (M x G x 2)
-    float qmax;              // largest code: 2^(bits-1) - 1
-    int tp;                  // row pitch of T (= r, or r + 1 for a layer with row shifts)
-    float* tmode;            // T + (PSP rank): first of the entries the layer's mode adds to a row, or NULL
-    int asym, shift;         // the layer's mode: asymmetric activation codes, row shift
-    int64_t rot_blocks;      // workgroups below this index rotate token blockIdx.x, the rest project
-    int JG;                  // projection workgroups per (token tile, slice): groups of rank tiles
-    const uint16_t* R1p; const uint16_t* R2p;          // bf16 term planes of the factors
-};
-
-// workgroup pb behind the rotation's own in a launch that adds up the partial tiles of the launch in front (a.S < 0)
-__device__ __forceinline__ void psp_sum_at(const RqArgs& a, int pb) {
-    const int W = a.r <= 16 ? 16 : a.r <= 32 ? 32 : 64;                // bwla_psp_prefill_tile_cols
-    bwla_psp_sum_tiles(bwla_psp_tiles{a.partials, a.T, a.M, a.r, a.tp, -a.S, a.JG, W, (int)(gridDim.x - a.rot_blocks)}, pb);
-}
-// projection workgroup pb of a launch: slice fastest, then the group of rank tiles, then the token tile.  EITHER: or the role
-// above, in one kernel, told apart by a word that both load anyway (56 bytes more of arguments cost small launches 0.1 us).
-template <bool BF16, bool EITHER = false>
-__device__ __forceinline__ void psp_block_at(char* lds, const RqArgs& a, int pb, bool finish = true) {
-    if (EITHER && a.S < 0) {
-        psp_sum_at(a, pb);
-        return;
-    }
-    const int s = pb % a.S, rest = pb / a.S;
-    psp_block<BF16>(lds, a.X, a.M, a.K, a.r, a.U, a.T, a.counters, a.partials, a.S, rest / a.JG, s, a.tp, finish,
-                    rest % a.JG, a.JG);
-}
 
 // (up to 128 registers, of which fp32 activations spill six: two workgroups a CU where LDS lets them)
 // SUMS: the workgroups behind add up partial tiles, which is so for bf16 tokens alone.  A form of its own: with both roles
@@ -320,6 +289,12 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
+    // (the factors as two fp16 terms, any even n2: rotate_terms.hip)
+    if (xdtype == BWLA_X_BF16 && rt_serves(L)) {
+        e = bwla_launch_rotate_terms(L, a, pblocks, merged, st);
+        if (e != hipSuccess) return e;
+        return ru > 0 && !merged && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
+    }
     if (xdtype == BWLA_X_BF16 && s3.ok) {
         // projection workgroups in the same launch want all eight wavefronts; so does a rotation
         // workgroup with one token and resident factors (the extra wavefronts help to fetch them)
@@ -379,6 +354,8 @@ SplitRule split_rule(const bwla_layer_t* L) {
     SplitRule s{{}, 0, 0};
     const R3Shape s3 = r3_shape(L->n1, L->n2);
     if (!s3.ok || L->K > (int64_t)RS_QB * 512 * RS_QI * 4 || (s3.resident && s3.at < 6)) return s;
+    const bool terms = rt_serves(L);
+    if (terms && L->n1 <= 128) return s;
     s.rs = rs_shape(s3);
     if (!s.rs.ok) return s;
     // up to two workgroups per CU (one after the other where LDS lets only one be resident):
@@ -392,6 +369,10 @@ SplitRule split_rule(const bwla_layer_t* L) {
     // workgroups are free (measured, 128 x 64: 12.1 -> 11.1 us at four tokens, 12.2 -> 11.8 at
     // eight, 12.3 -> 12.9 at sixteen; 128 x 86: 16.7 -> 10.9 at one token, 17.1 -> 12.2 at sixteen).
     if (s3.resident && (s3.strips & 3) == 0 && s.tokens > 8) s.tokens = 8;
+    // Pairs that rotate_terms.hip takes: only the long ones, and while the extra workgroups are free (rotation and quantizing
+    // launch against its one: 224 x 128 at one token 13.4 / 15.2 us, at five 13.8 / 15.7, at sixteen 16.0 / 15.8; 160 x 160 13.7 /
+    // 13.9, 14.1 / 14.2, 15.4 / 14.3; but 128 x 86 at one token 12.3 / 8.8, 128 x 64 at two 10.2 / 7.3).
+    if (terms && s.tokens > 8) s.tokens = 8;
     return s;
 }
 }  // namespace

@@ -1,0 +1,132 @@
+"""Rotation and codes of bf16 tokens by the kernel on two fp16 terms (any even n2): every number of tiles along either factor,
+rows that end inside a tile or on no 16-byte boundary, one token a workgroup and workgroups that walk, against fp64."""
+import copy
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_00422_amd import binding as B
+    B.load()
+
+
+# (tokens, n1, n2, rank, bits, row shift, asymmetric)
+CASES = [
+    (1, 16, 32, 8, 6, False, False),        # the smallest pair; the projection rides
+    (16, 32, 16, 0, 8, False, False),
+    (700, 16, 32, 8, 6, True, True),        # several workgroups a CU
+    (3, 48, 16, 5, 4, False, True),         # one strip, steps along n1 half filled
+    (17, 64, 46, 0, 6, False, False),       # pairs of codes at the end of a row
+    (16, 64, 80, 64, 6, False, False),
+    (513, 64, 80, 33, 6, True, False),      # walking, a last round that is not full
+    (5, 128, 86, 32, 6, True, True),        # rows on 4-byte boundaries
+    (300, 128, 86, 0, 8, False, False),     # walking, codes in the rows' place or beside them
+    (2, 128, 64, 96, 6, False, False),
+    (257, 128, 64, 16, 8, False, False),    # the first that walks
+    (511, 128, 64, 0, 6, False, True),
+    (9, 104, 64, 16, 6, False, False),      # n1 no multiple of 16
+    (64, 96, 148, 0, 6, True, False),       # ten strips, the last one not full
+    (600, 80, 80, 8, 6, False, False),
+    (20, 160, 160, 8, 6, False, False),
+    (280, 144, 144, 0, 6, False, False),
+    (9, 172, 64, 8, 6, False, False),       # R1 streamed; one strip of wavefronts a SIMD
+    (270, 200, 80, 8, 6, True, True),
+    (12, 256, 112, 0, 6, False, False),
+    (3, 224, 128, 8, 6, False, False),      # few tokens: the split rotation
+]
+
+
+def _layer(g, n1, n2, r, shift, asym):
+    from paper_2605_00422_amd import binding as B
+    K, N = n1 * n2, 48
+    W = torch.randn(N, K, device=DEV, generator=g)
+    U = torch.randn(K, r, device=DEV, generator=g).half().float() if r else None
+    V = torch.randn(N, r, device=DEV, generator=g).half().float() if r else None
+    R = [torch.linalg.qr(torch.randn(n, n, device=DEV, generator=g))[0].contiguous() for n in (n1, n2)]
+    return B.pack_weights(W, R[0], R[1], U, V, n1, n2, centered=shift, asym=asym), R, U
+
+
+def _check(act, X, R, U, n1, n2, r, bits, shift, asym):
+    M, K = X.shape
+    Xd = X.double()
+    Z = (Xd.view(M * n1, n2) @ R[1].double()).view(M, n1, n2)
+    x = (Z.transpose(1, 2).contiguous().view(M * n2, n1) @ R[0].double()).view(M, n2, n1).transpose(1, 2).reshape(M, K)
+    qmax = (1 << (bits - 1)) - 1
+    # an fp32 rotation is within 1e-4 of 31 steps of the largest value: the window of the parity tests, and 1e-5 of a scale
+    if asym:
+        lo, hi = x.amin(1).clamp(max=0), x.amax(1).clamp(min=0)
+        L = 2 * qmax + 1
+        s = (hi - lo) / L
+        inv = torch.where(s > 0, 1 / s, 0.0)
+        z = torch.round(-lo * inv)
+        v = x * inv[:, None]
+        zc = z - (qmax + 1)
+        near_z = ((-lo * inv) - torch.floor(-lo * inv) - 0.5).abs() < 1e-4 * L / 31
+        want = (torch.round(v) + z[:, None]).clamp(0, L) - (qmax + 1)
+    else:
+        s = x.abs().amax(1) / qmax
+        v = x * torch.where(s > 0, 1 / s, 0.0)[:, None]
+        zc, near_z = torch.zeros(M, device=DEV, dtype=torch.float64), torch.zeros(M, device=DEV, dtype=torch.bool)
+        want = torch.round(v).clamp(-qmax, qmax)
+    assert torch.allclose(act.scale.double(), s, rtol=1e-5, atol=0)
+    off = (act.q.double() - want).abs()
+    near = ((v - torch.floor(v) - 0.5).abs() < 1e-4 * (2 if asym else 1) * qmax / 31) | near_z[:, None]
+    assert bool((off[~near] == 0).all()) and bool((off <= 1).all())
+    assert torch.equal(act.qsum.long(), act.q.long().sum(1))
+    if r:
+        bound = (K / 32 + 104) * 2.0 ** -23 * (Xd.abs() @ U.double().abs())
+        assert bool(((act.T[:, :r].double() - Xd @ U.double()).abs() <= bound).all())
+    if asym:
+        # the zero point the codes were made with, or the next one where it lies on a rounding boundary
+        got = -act.T[:, r].double() / act.scale.double()
+        got = torch.where(act.scale > 0, got, zc)
+        assert bool(((got - zc).abs() <= torch.where(near_z, 1.001, 1e-3)).all())
+        zc = torch.round(got)
+    if shift:
+        sums = act.scale.double() * (act.qsum.double() - K * zc)
+        assert torch.allclose(act.T[:, -1].double(), sums, rtol=1e-5, atol=1e-5 * float(s.max()) * K)
+
+
+@pytest.mark.parametrize("M,n1,n2,r,bits,shift,asym", CASES)
+def test_rotation_of_any_pair(M, n1, n2, r, bits, shift, asym):
+    from paper_2605_00422_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + n1 * n2 + r)
+    layer, R, U = _layer(g, n1, n2, r, shift, asym)
+    act = B.Activations(layer, M)
+    for _ in range(2):                                      # twice on one scratch
+        X = torch.randn(M, n1 * n2, device=DEV, generator=g)
+        X[:, ::89] *= 50.0
+        X[M // 2] *= 1e-20
+        X[M - 1] = 0 if M > 1 else X[0]
+        X = X.to(torch.bfloat16)
+        act.q.fill_(99)
+        B.rotate_quant(layer, X, act, bits)
+        torch.cuda.synchronize()
+        _check(act, X, R, U, n1, n2, r, bits, shift, asym)
+
+
+@pytest.mark.parametrize("M,n1,n2", [(4, 64, 80), (300, 64, 80), (40, 128, 86)])
+def test_layers_packed_without_operand_order_factors(M, n1, n2):
+    """A layer that was packed and kept before its pair had them: the same bytes, fewer of them."""
+    from paper_2605_00422_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    layer, R, U = _layer(g, n1, n2, 16, False, False)
+    old = copy.copy(layer)
+    old.desc = type(layer.desc).from_buffer_copy(layer.desc)
+    old.desc.blob_bytes, old.desc.off_Rd = layer.desc.off_Rd, 0
+    X = torch.randn(M, n1 * n2, device=DEV, generator=g).to(torch.bfloat16)
+    act = B.Activations(old, M)
+    B.rotate_quant(old, X, act)
+    torch.cuda.synchronize()
+    _check(act, X, R, U, n1, n2, 16, 6, False, False)
