@@ -28,8 +28,8 @@ bwla_status_t check_shape(int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t 
 }
 
 // r counts the columns of V and T; U keeps the PSP columns only
-// (planes false: without operand-order factors, as a library before laid out pairs that are no multiples of 32)
-void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode, bool planes = true) {
+// (now false: as a library before laid it out, operand-order factors only of pairs that are multiples of 32)
+void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode, bool now = true) {
     const uint64_t rp = (uint64_t)((r + 15) & ~15);
     const uint64_t rpu = (uint64_t)((r - bwla_extra_cols(mode) + 15) & ~15);
     uint64_t off = 0;
@@ -43,7 +43,8 @@ void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, 
     L->off_R1p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n1));
     L->off_R2p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n2));
     L->off_Rd = 0;
-    if (planes && bwla_decode_planes_bytes(n1, n2) > 0) { L->off_Rd = off; off = bwla_align256(off + bwla_decode_planes_bytes(n1, n2)); }
+    const uint64_t planes = now || bwla_planes_whole(n1, n2) ? bwla_decode_planes_bytes(n1, n2) : 0;
+    if (planes > 0) { L->off_Rd = off; off = bwla_align256(off + planes); }
     L->blob_bytes = off;
 }
 
@@ -54,13 +55,15 @@ bwla_status_t check_layer(const bwla_layer_t* L) {
     if (s != BWLA_OK) return s;
     if ((L->mode & ~(BWLA_MODE_ROW_SHIFT | BWLA_MODE_ASYM_ACT)) != 0 || L->r < bwla_extra_cols(L->mode))
         return BWLA_ERR_SHAPE;
-    bwla_layer_t ref;
-    fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode, L->off_Rd != 0 || bwla_planes_whole(L->n1, L->n2));
-    if (ref.off_bits != L->off_bits || ref.off_alpha != L->off_alpha || ref.off_V != L->off_V ||
-        ref.off_U != L->off_U || ref.off_R1 != L->off_R1 || ref.off_R2 != L->off_R2 ||
-        ref.off_R1p != L->off_R1p || ref.off_R2p != L->off_R2p || ref.off_Rd != L->off_Rd ||
-        ref.blob_bytes != L->blob_bytes)
-        return BWLA_ERR_SHAPE;
+    auto laid_out = [&](bool now) {
+        bwla_layer_t ref;
+        fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode, now);
+        return ref.off_bits == L->off_bits && ref.off_alpha == L->off_alpha && ref.off_V == L->off_V &&
+               ref.off_U == L->off_U && ref.off_R1 == L->off_R1 && ref.off_R2 == L->off_R2 &&
+               ref.off_R1p == L->off_R1p && ref.off_R2p == L->off_R2p && ref.off_Rd == L->off_Rd &&
+               ref.blob_bytes == L->blob_bytes;
+    };
+    if (!laid_out(true) && !laid_out(false)) return BWLA_ERR_SHAPE;
     if (!aligned16(L->d_blob)) return BWLA_ERR_ALIGN;
     return BWLA_OK;
 }

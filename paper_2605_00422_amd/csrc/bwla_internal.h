@@ -32,7 +32,7 @@ inline uint64_t bwla_factor_planes_bytes(int n) {
 }
 
 // Factor planes in MFMA operand order (one contiguous KiB per operand), stored for factors up to 256 and 160 of an even n2
-// (0 bytes otherwise), three parts:
+// (0 bytes otherwise), in this order:
 //   R2d  three bf16 terms of R2, (n2 / 16) strips x (n2 / 32) steps x 3 KiB: only for the pairs the
 //        single-launch decode kernel takes (n1 of 32, 64 or 128, n2 of 32 or 64)
 //   R1h  two fp16 terms of 256 R1, padded with zeros to a multiple of 32: steps of 32 x 2 x tiles of 16 KiB

@@ -207,9 +207,15 @@ __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* 
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (nb2 + nb1 + nb2h) * 512) return;
     const int blk = i >> 9, lane = (i >> 3) & 63, e = i & 7, li = lane & 15, lg = lane >> 4;
-    if (blk < nb2) {
-        const int p = blk % 3, kb = (blk / 3) % k1, w = blk / (3 * k1);
-        const float v = R2[(int64_t)(32 * kb + 8 * lg + e) * n2 + 16 * w + li];
+    auto r1_at = [&](int ch, int tc) -> float {         // R1[a][c = 16 tc + li]
+        const int a = 32 * ch + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4), c = 16 * tc + li;
+        return a < n1 && c < n1 ? R1[(int64_t)a * n1 + c] : 0.0f;
+    };
+    auto r2_at = [&](int w, int kb) -> float {          // R2[b = 32 kb + 8 lg + e][d = 16 w + li]
+        const int b = 32 * kb + 8 * lg + e, d = 16 * w + li;
+        return b < n2 && d < n2 ? R2[(int64_t)b * n2 + d] : 0.0f;
+    };
+    auto bf16_term = [](float v, int p) -> uint16_t {
         auto bf = [](float f) -> uint32_t {
             const uint32_t u = __float_as_uint(f);
             return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
@@ -218,26 +224,17 @@ __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* 
         const float r1 = v - __uint_as_float(h1);
         const uint32_t h2 = bf(r1);
         const uint32_t h3 = bf(r1 - __uint_as_float(h2));
-        out[i] = (uint16_t)((p == 0 ? h1 : p == 1 ? h2 : h3) >> 16);
-    } else if (blk < nb2 + nb1) {
-        const int b1 = blk - nb2;
-        const int tc = b1 % at, t = (b1 / at) % 2, ch = b1 / (2 * at);
-        const int a = 32 * ch + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4);
-        const int c = 16 * tc + li;
-        const float v = a < n1 && c < n1 ? 256.0f * R1[(int64_t)a * n1 + c] : 0.0f;
+        return (uint16_t)((p == 0 ? h1 : p == 1 ? h2 : h3) >> 16);
+    };
+    auto fp16_term = [](float v, int p) -> uint16_t {
         const __half hi = __float2half_rn(v);
-        const __half lo = __float2half_rn(v - __half2float(hi));
-        out[i] = __half_as_ushort(t == 0 ? hi : lo);
-    } else {
-        // R2h, blocks [strip w][step kb][term t < 2]: 256 R2[b = 32 kb + 8 lg + e][d = 16 w + li]
-        const int b2 = blk - nb2 - nb1;
-        const int t = b2 % 2, kb = (b2 / 2) % k1, w = b2 / (2 * k1);
-        const int b = 32 * kb + 8 * lg + e, d = 16 * w + li;
-        const float v = b < n2 && d < n2 ? 256.0f * R2[(int64_t)b * n2 + d] : 0.0f;
-        const __half hi = __float2half_rn(v);
-        const __half lo = __float2half_rn(v - __half2float(hi));
-        out[i] = __half_as_ushort(t == 0 ? hi : lo);
-    }
+        return __half_as_ushort(p == 0 ? hi : __float2half_rn(v - __half2float(hi)));
+    };
+    int j = blk;                                        // block within its part
+    if (j < nb2) { out[i] = bf16_term(r2_at(j / (3 * k1), (j / 3) % k1), j % 3); return; }
+    if ((j -= nb2) < nb1) { out[i] = fp16_term(256.0f * r1_at(j / (2 * at), j % at), (j / at) % 2); return; }
+    j -= nb1;
+    out[i] = fp16_term(256.0f * r2_at(j / (2 * k1), (j / 2) % k1), j % 2);
 }
 
 __global__ void copy_f32_kernel(const float* __restrict__ src, int64_t n, float* __restrict__ dst) {

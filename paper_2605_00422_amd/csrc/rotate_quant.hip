@@ -289,9 +289,8 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
-    // (the factors as two fp16 terms, any even n2: rotate_terms.hip)
-    if (xdtype == BWLA_X_BF16 && rt_serves(L)) {
-        e = bwla_launch_rotate_terms(L, a, pblocks, merged, st);
+    if (rt_serves(L, xdtype != BWLA_X_BF16)) {
+        e = bwla_launch_rotate_terms(L, a, pblocks, merged, xdtype != BWLA_X_BF16, st);
         if (e != hipSuccess) return e;
         return ru > 0 && !merged && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
     }

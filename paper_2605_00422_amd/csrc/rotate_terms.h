@@ -1,4 +1,4 @@
-// Shapes of the rotation on two fp16 terms for any factor pair (rotate_terms.hip).
+// Shapes of the rotation on 16-bit terms for any factor pair (rotate_terms.hip).
 #pragma once
 #include "rotate_args.h"
 
@@ -20,14 +20,14 @@ struct RtArgs {
 namespace {
 
 // M > 1: workgroups walk over that many tokens
-__host__ inline RtShape rt_shape(int n1, int n2, int64_t M, int cus) {
+inline RtShape rt_shape(int n1, int n2, int64_t M, int cus, bool f32 = false) {
     RtShape s;
     s.ch2 = (n1 + 31) >> 5; s.at = 2 * s.ch2;
     s.strips = (n2 + 15) >> 4; s.k1 = (n2 + 31) >> 5;
     s.pitch = s.k1 * 64 + 16;
     s.stream = n1 > 160;
-    s.r1_bytes = (s.stream ? 2 : s.ch2) * 2 * s.at * 1024;
-    s.xt_bytes = s.ch2 * 32 * s.pitch;
+    s.r1_bytes = (s.stream ? 2 : s.ch2) * (s.at <= 4 && !f32 ? 3 : 2) * s.at * 1024;
+    s.xt_bytes = s.ch2 * 32 * s.pitch * (f32 ? 3 : 1);
     s.cb_bytes = (n1 * n2 + 255) & ~255;
     const int limit = (int)RQ_LDS_LIMIT, loaders = s.stream ? 0 : s.strips <= 4 ? 4 : s.strips <= 8 ? 8 - s.strips + (s.strips == 8 ? 2 : 0) : 2;
     s.G = 1; s.own = false; s.threads = 64 * (s.strips + loaders);
@@ -48,16 +48,19 @@ __host__ inline RtShape rt_shape(int n1, int n2, int64_t M, int cus) {
     return s;
 }
 
-// the pairs that it takes: operand-order factors exist, rows of whole pairs of values, and everything fits
-inline bool rt_serves(const bwla_layer_t* L) {
-    if (L->off_Rd == 0 || (L->n2 & 1) != 0) return false;
+// the pairs that it takes: the factors' terms exist, rows of whole pairs of values, and everything fits
+// (fp32 tokens: as three terms beside resident factors, up to 128 x 96)
+inline bool rt_serves(const bwla_layer_t* L, bool f32 = false) {
+    if ((L->n2 & 1) != 0 || (L->off_Rd == 0 && (f32 || L->n1 > 64))) return false;
     const int strips = (L->n2 + 15) >> 4;
     if (L->n1 > 160 && strips > 8) return false;
-    const RtShape s = rt_shape(L->n1, L->n2, 1, 1);
+    if (f32 && (L->n1 > 128 || L->n2 > 96)) return false;
+    const RtShape s = rt_shape(L->n1, L->n2, 1, 1, f32);
     return s.lds_bytes <= RQ_LDS_LIMIT && s.strips <= 10;
 }
 
 }  // namespace
 
-hipError_t bwla_launch_rotate_terms(const bwla_layer_t* L, const RqArgs& a, int64_t pblocks, bool rides, hipStream_t st);
+hipError_t bwla_launch_rotate_terms(const bwla_layer_t* L, const RqArgs& a, int64_t pblocks, bool rides, bool f32, hipStream_t st);
 hipError_t bwla_launch_rotate_terms_many(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st);
+hipError_t bwla_launch_rotate_terms_f32(const RtArgs& b, bool many, int64_t blocks, int threads, size_t lds, hipStream_t st);

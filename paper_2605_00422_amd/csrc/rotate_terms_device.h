@@ -1,5 +1,6 @@
-// Device code of the rotation on two fp16 terms (rotate_terms.hip has the design).
+// Device code of the rotation on 16-bit terms (rotate_terms.hip has the design).
 #pragma once
+#include "rotate_bf16_device.h"
 #include "rotate_terms.h"
 #include "wave_dpp.h"
 
@@ -7,22 +8,34 @@ namespace {
 
 typedef _Float16 v8h_t __attribute__((ext_vector_type(8)));
 
+template <bool BF>
+__device__ __forceinline__ v4f rt_mma(v4i a, v4i b, v4f c) {
+    if constexpr (BF) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a), __builtin_bit_cast(v8h_t, b), c, 0, 0, 0);
+}
+
 // AT, K1M: the most 16-row tiles along n1 (padded to 32) and 32-deep steps along n2.  STREAM: the R1 terms of one step at a
 // time (n1 > 160).  MANY: workgroups walk over their tokens, G groups of wavefronts side by side; else one token a workgroup.
-template <int AT, int K1M, bool STREAM, bool MANY, int THREADS>
+template <int AT, int K1M, bool STREAM, bool MANY, bool F32, int THREADS>
 __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     extern __shared__ __align__(16) float lds_f[];
     const RqArgs& a = b.q;
     if ((int64_t)blockIdx.x >= a.rot_blocks) {
         const int pb = (int)(blockIdx.x - a.rot_blocks);
         if constexpr (MANY) psp_sum_at(a, pb);
-        else psp_block_at<true, true>(reinterpret_cast<char*>(lds_f), a, pb);
+        else psp_block_at<!F32, !F32>(reinterpret_cast<char*>(lds_f), a, pb);
         return;
     }
-    // (the small terms of a product are added up apart where registers allow: fewer roundings at the sum's own magnitude)
-    constexpr bool APART = AT <= 4 || (AT <= 8 && K1M <= 3 && !MANY);
-    constexpr bool LOLO = AT <= 4;
-    constexpr int NI = AT / 2, CH2 = AT / 2;            // 16-byte granules of a token per thread; 32-deep steps along n1
+    // Small terms are added up before the large ones (stage 1), and apart from them over the steps of stage 2 where registers
+    // allow: fewer roundings at the sum's own magnitude.
+    constexpr bool SMALL_FIRST = K1M <= 3;
+    constexpr bool APART = AT > 2 && (AT <= 4 || (AT <= 8 && K1M <= 3 && !MANY));
+    // bf16 tokens and n1 <= 64: the factors and Z as three bf16 terms, six products.  Sums that short are nearer to the exact value
+    // than 22 bits (16 x 32, rms of a scale's error: 9.3e-8 on 16-bit terms, 6.6e-8 on three, 6.0e-8 so: bf16 products leave
+    // the sums of an instruction more room), and the token needs no scale.
+    constexpr bool BF = AT <= 4 && !F32;
+    constexpr int NX = F32 ? 3 : 1, VG = F32 ? 4 : 8;   // terms of the token; its values in 16 bytes
+    constexpr int CH2 = AT / 2, NI = CH2 * (8 / VG);    // 32-deep steps along n1; 16-byte granules of a token per thread
     char* lds = reinterpret_cast<char*>(lds_f);
     const int n1 = a.n1, n2 = a.n2, K = n1 * n2, k1 = b.s.k1, strips = b.s.strips;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwaves = (int)blockDim.x >> 6;
@@ -41,22 +54,34 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     char* cb = b.s.own ? lds + b.s.r1_bytes + G * b.s.xt_bytes + grp * b.s.cb_bytes : xt;
     float* red = reinterpret_cast<float*>(lds + b.s.r1_bytes + G * (b.s.xt_bytes + (b.s.own ? b.s.cb_bytes : 0))) + grp * 64;
     int* redi = reinterpret_cast<int*>(red) + 48;
-    constexpr int chunk_bytes = 2 * AT * 1024;
+    constexpr int CB = BF ? 3 * AT : 2 * AT, chunk_bytes = CB * 1024;     // blocks and bytes of a step of R1
     const int pitch = b.s.pitch;
 
     // ---- R1 terms, global -> LDS, one KiB a request.  Resident: all of them, by the wavefronts behind the groups.  STREAM: the
     // terms of step g into buffer g & 1, by all, requested while the step before is worked on.
-    auto r1_async = [&](int block, char* dst) {
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b.R1h + (block * 64 + (int)(threadIdx.x & 63)) * 8),
+    const int n1p16 = (n1 + 15) & ~15;
+    auto r1_async = [&](int ch, int e, char* dst) {     // block e of step ch
+        const int l = (int)threadIdx.x & 63;
+        const uint16_t* src = b.R1h + ((ch * 2 * AT + e) * 64 + l) * 8;
+        if constexpr (BF) {
+            // (planes of whole rows: sixteen rows of 64 bytes make a block; there is no tile past the rows)
+            const int p = e / AT, c = 16 * (e - p * AT);
+            if (c >= n1p16) {
+                *reinterpret_cast<v4i*>(dst + l * 16) = v4i{0, 0, 0, 0};
+                return;
+            }
+            src = a.R1p + ((p * n1p16 + c + (l & 15)) * (CH2 * 32) + ch * 32 + (l >> 4) * 8);
+        }
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                          (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
     };
     auto request_chunk = [&](int g, int ch) {
-        for (int e = wv; e < 2 * AT; e += G * strips) r1_async(ch * 2 * AT + e, r1 + (g & 1) * chunk_bytes + e * 1024);
+        for (int e = wv; e < CB; e += G * strips) r1_async(ch, e, r1 + (g & 1) * chunk_bytes + e * 1024);
     };
     if (STREAM && helper) return;
     if (!STREAM && helper) {
         const int first = wv - G * strips, step = nwaves - G * strips;
-        for (int e = first; e < CH2 * 2 * AT; e += step) r1_async(e, r1 + e * 1024);
+        for (int e = first; e < CH2 * CB; e += step) r1_async(e / CB, e % CB, r1 + e * 1024);
         bwla_lds_barrier();                             // maxima
         bwla_lds_barrier();                             // token rows
         __builtin_amdgcn_s_waitcnt(0);
@@ -70,30 +95,47 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         return x - grp * TG;
     };
     // ---- the token, then the R2 terms of my strip
-    const int items = K >> 3;
+    const int items = K / VG;
     const int64_t tstep = a.rot_blocks * G, t0 = (int64_t)blockIdx.x * G + grp;
     v4i xpre[NI];
     auto request = [&](int64_t t) {
-        const uint16_t* xrow = reinterpret_cast<const uint16_t*>(a.X) + (t < a.M ? t : a.M - 1) * K;
+        const char* xrow = reinterpret_cast<const char*>(a.X) + (t < a.M ? t : a.M - 1) * K * (16 / VG);
         const int tid = my_tid();
 #pragma unroll
         for (int e = 0; e < NI; ++e) {
             const int it = tid + e * TG;                // (past the last one: the first again)
-            xpre[e] = *reinterpret_cast<const v4i*>(xrow + (it < items ? it : 0) * 8);
+            xpre[e] = *reinterpret_cast<const v4i*>(xrow + (it < items ? it : 0) * 16);
         }
     };
     request(t0);
-    v8h_t bh[K1M], bl[K1M];
+    v4i bh[K1M], bl[K1M], bx[BF ? K1M : 1];
 #pragma unroll
     for (int kb = 0; kb < K1M; ++kb) {
         const int kc = kb < k1 ? kb : 0;
-        bh[kb] = __builtin_bit_cast(v8h_t, *reinterpret_cast<const v4i*>(b.R2h + (((wave * k1 + kc) * 2 + 0) * 64 + lane) * 8));
-        bl[kb] = __builtin_bit_cast(v8h_t, *reinterpret_cast<const v4i*>(b.R2h + (((wave * k1 + kc) * 2 + 1) * 64 + lane) * 8));
+        if constexpr (BF) {
+            const uint16_t* src = a.R2p + ((wave * 16 + li) * (k1 * 32) + kc * 32 + 8 * lg);
+            const int term = strips * 16 * k1 * 32;
+            bh[kb] = *reinterpret_cast<const v4i*>(src);
+            bl[kb] = *reinterpret_cast<const v4i*>(src + term);
+            bx[kb] = *reinterpret_cast<const v4i*>(src + 2 * term);
+        } else {
+            const uint16_t* src = b.R2h + ((wave * k1 + kc) * 2 * 64 + lane) * 8;
+            bh[kb] = *reinterpret_cast<const v4i*>(src);
+            bl[kb] = *reinterpret_cast<const v4i*>(src + 512);
+        }
     }
     if constexpr (STREAM) request_chunk(0, 0);
 
     // largest magnitude of the token in registers: bf16 magnitudes order like their 15 low bits
     auto token_max = [&]() -> float {
+        if constexpr (F32) {
+            float m = 0.0f;
+#pragma unroll
+            for (int e = 0; e < NI; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) m = fmaxf(m, fabsf(__int_as_float(xpre[e][i])));
+            return dl_wave_max_nonneg(m);
+        }
         typedef unsigned short us2 __attribute__((ext_vector_type(2)));
         us2 m = us2{0, 0};
 #pragma unroll
@@ -103,39 +145,77 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         const uint32_t top = m.x > m.y ? m.x : m.y;
         return dl_wave_max_nonneg(__uint_as_float(top << 16));
     };
-    // power of two that puts a token's largest magnitude into [2^2, 2^3) (1 for an all-zero token)
-    auto scale_of = [&](float xmax) -> float {
-        int E = (__float_as_int(xmax) >> 23) & 0xff;
-        E = E < 40 ? 40 : (E > 230 ? 230 : E);
-        return xmax > 0.0f ? __int_as_float((127 + 2 + 127 - E) << 23) : 1.0f;
+    // exponent field E of a token's largest magnitude: the token is scaled by 2^(129 - E), which puts that magnitude into
+    // [2^2, 2^3), and what the two stages make of it by 2^(145 - E) then (256 R1, 256 R2).  Codes and zero points are the
+    // same in that scale, so only the step that is stored goes back.
+    auto exponent_of = [&](float xmax) -> int {
+        const int E = (__float_as_int(xmax) >> 23) & 0xff;
+        return E < 2 ? 2 : E;
     };
     // zeros where a token row ends inside a 32-deep step, and in rows past n1
+    const int plane = CH2 * 32 * pitch;                 // bytes of a term of the token
     auto zero_pads = [&](int tz, int nz) {
         const int cols = (k1 * 32 - n2) >> 1, prow = cols > 0 ? n1 : 0;          // words
         const FastDiv dc(cols > 0 ? cols : 1);
         for (int i = tz; i < prow * cols; i += nz) {
             const int row = dc.div(i);
-            *reinterpret_cast<uint32_t*>(xt + row * pitch + 2 * n2 + 4 * (i - row * cols)) = 0u;
+#pragma unroll
+            for (int p = 0; p < NX; ++p) *reinterpret_cast<uint32_t*>(xt + p * plane + row * pitch + 2 * n2 + 4 * (i - row * cols)) = 0u;
         }
         const int g = k1 * 4, rows = CH2 * 32 - n1;                              // 16-byte granules
         const FastDiv dg(g);
         for (int i = tz; i < rows * g; i += nz) {
             const int row = dg.div(i);
-            *reinterpret_cast<v4i*>(xt + (n1 + row) * pitch + (i - row * g) * 16) = v4i{0, 0, 0, 0};
+#pragma unroll
+            for (int p = 0; p < NX; ++p) *reinterpret_cast<v4i*>(xt + p * plane + (n1 + row) * pitch + (i - row * g) * 16) = v4i{0, 0, 0, 0};
         }
     };
-    // the token in registers -> fp16 rows in LDS, scaled by sx = 2^ex
-    const bool whole = (n2 & 7) == 0;
-    const FastDiv drow(whole ? n2 >> 3 : n2 >> 1);
-    auto land = [&](float sx) {
+    // the token in registers -> fp16 rows in LDS
+    const bool whole = (n2 & (VG - 1)) == 0;
+    const FastDiv drow(whole ? n2 / VG : n2 >> 1);
+    auto land = [&](int E) {
         const int tid = my_tid();
+        const float sx = __int_as_float((256 - E) << 23);
+        if constexpr (F32) {
+            // fp32 values as three fp16 terms: 24 bits and more, down to 2^-28 of the token's largest value
+#pragma unroll
+            for (int e = 0; e < NI; ++e) {
+                const int it = tid + e * TG;
+                uint32_t o[3][2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float r0 = __int_as_float(xpre[e][2 * i]) * sx, r1 = __int_as_float(xpre[e][2 * i + 1]) * sx;
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        const _Float16 h0 = (_Float16)r0, h1 = (_Float16)r1;
+                        r0 -= (float)h0; r1 -= (float)h1;
+                        o[p][i] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
+                    }
+                }
+                if (it < items) {
+                    if (whole) {
+                        const int row = drow.div(it), g = it - row * (n2 >> 2);
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(xt + p * plane + row * pitch + g * 8) = uint2{o[p][0], o[p][1]};
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {                            // pairs of values: n2 is even
+                            const int q = it * 2 + i, row = drow.div(q);
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t*>(xt + p * plane + row * pitch + (q - row * (n2 >> 1)) * 4) = o[p][i];
+                        }
+                    }
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int e = 0; e < NI; ++e) {
             {
                 const int it = tid + e * TG;
-                v4i o;
+                v4i o = xpre[e];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; !BF && i < 4; ++i) {
                     const uint32_t w = (uint32_t)xpre[e][i];
                     o[i] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w << 16) * sx, __uint_as_float(w & 0xffff0000u) * sx));
                 }
@@ -156,7 +236,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     };
     const bool pads = (n2 & 31) != 0 || (n1 & 31) != 0;
     if (pads) zero_pads(tid, TG);
-    {
+    if constexpr (!BF) {
         const float m = token_max();
         if (lane == 0) red[32 + wave] = m;
     }
@@ -166,8 +246,8 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         const int w = (int)threadIdx.x & 15;
         return dl_wave_max_nonneg(w < strips ? p[w] : 0.0f);
     };
-    float sx = scale_of(over_strips(red + 32));
-    land(sx);
+    int E = BF ? 145 : exponent_of(over_strips(red + 32));
+    land(E);
     if constexpr (MANY) {
         if (b.rounds > 1) request(t0 + tstep);
     }
@@ -195,30 +275,51 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
 #pragma unroll
         for (int tc = 0; tc < (APART ? AT : 1); ++tc) ys[tc] = v4f{0.f, 0.f, 0.f, 0.f};
         const char* xa = xt + li * pitch + lg * 16;
-        auto ld_a = [&](int ch, int kb, int half) -> v4i {
-            return *reinterpret_cast<const v4i*>(xa + (32 * ch + 16 * half) * pitch + kb * 64);
+        auto ld_a = [&](int ch, int kb, int half, int p = 0) -> v4i {
+            return *reinterpret_cast<const v4i*>(xa + p * plane + (32 * ch + 16 * half) * pitch + kb * 64);
         };
         v4i n0 = ld_a(0, 0, 0), n1_ = ld_a(0, 0, 1);
 #pragma nounroll
         for (int ch = 0; ch < CH2; ++ch) {
-            v4f z0 = v4f{0.f, 0.f, 0.f, 0.f}, z1 = z0, s0 = z0, s1 = z0;
-            v4i qa0[K1M + 1], qa1[K1M + 1], qb[2][AT];
+            v4f z0 = v4f{0.f, 0.f, 0.f, 0.f}, z1 = z0;
+            v4i qa0[K1M + 1], qa1[K1M + 1], qb[3][AT];
             qa0[0] = n0; qa1[0] = n1_;
             if (k1 > 1) { qa0[1] = ld_a(ch, 1, 0); qa1[1] = ld_a(ch, 1, 1); }
 #pragma unroll
             for (int kb = 0; kb < K1M; ++kb) {
                 if (kb < k1) {
-                    const v8h_t a0 = __builtin_bit_cast(v8h_t, qa0[kb]), a1 = __builtin_bit_cast(v8h_t, qa1[kb]);
+                    const v4i a0 = qa0[kb], a1 = qa1[kb];
                     if (kb + 2 < K1M && kb + 2 < k1) { qa0[kb + 2] = ld_a(ch, kb + 2, 0); qa1[kb + 2] = ld_a(ch, kb + 2, 1); }
-                    if constexpr (APART) {
-                        s0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bl[kb], s0, 0, 0, 0);
-                        s1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bl[kb], s1, 0, 0, 0);
-                    } else {
-                        z0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bl[kb], z0, 0, 0, 0);      // small term first
-                        z1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bl[kb], z1, 0, 0, 0);
+                    if constexpr (F32) {
+                        // the products with the token's small terms (not those of 2^-33 of the result)
+                        const v4i c0 = ld_a(ch, kb, 0, 1), c1 = ld_a(ch, kb, 1, 1);
+                        const v4i d0 = ld_a(ch, kb, 0, 2), d1 = ld_a(ch, kb, 1, 2);
+                        z0 = rt_mma<BF>(d0, bh[kb], z0);
+                        z1 = rt_mma<BF>(d1, bh[kb], z1);
+                        z0 = rt_mma<BF>(c0, bl[kb], z0);
+                        z1 = rt_mma<BF>(c1, bl[kb], z1);
+                        z0 = rt_mma<BF>(c0, bh[kb], z0);
+                        z1 = rt_mma<BF>(c1, bh[kb], z1);
                     }
-                    z0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bh[kb], z0, 0, 0, 0);
-                    z1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bh[kb], z1, 0, 0, 0);
+                    if constexpr (BF) {
+                        z0 = rt_mma<BF>(a0, bx[kb], z0);
+                        z1 = rt_mma<BF>(a1, bx[kb], z1);
+                    }
+                    z0 = rt_mma<BF>(a0, bl[kb], z0);
+                    z1 = rt_mma<BF>(a1, bl[kb], z1);
+                    if constexpr (!SMALL_FIRST) {
+                        z0 = rt_mma<BF>(a0, bh[kb], z0);
+                        z1 = rt_mma<BF>(a1, bh[kb], z1);
+                    }
+                }
+            }
+            if constexpr (SMALL_FIRST) {
+#pragma unroll
+                for (int kb = 0; kb < K1M; ++kb) {
+                    if (kb < k1) {
+                        z0 = rt_mma<BF>(qa0[kb], bh[kb], z0);
+                        z1 = rt_mma<BF>(qa1[kb], bh[kb], z1);
+                    }
                 }
             }
             const char* rb;
@@ -237,15 +338,25 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
             }
             qb[0][0] = *reinterpret_cast<const v4i*>(rb);
             qb[1][0] = *reinterpret_cast<const v4i*>(rb + AT * 1024);
+            if constexpr (BF) qb[2][0] = *reinterpret_cast<const v4i*>(rb + 2 * AT * 1024);
             // lane (li, lg) holds Z[a = 32 ch + 4 lg + v (z0), 32 ch + 16 + 4 lg + v (z1)][d = li]: the eight contraction
             // positions of an A operand, in the order the R1 terms were stored in
-            v8h_t ah, al;
+            v4i ah, al, ax;
+            if constexpr (BF) {
+                const float f[8] = {z0[0], z0[1], z0[2], z0[3], z1[0], z1[1], z1[2], z1[3]};
+                v8bf h1, h2, h3;
+                r3_split3(f, h1, h2, h3);
+                ah = __builtin_bit_cast(v4i, h1); al = __builtin_bit_cast(v4i, h2); ax = __builtin_bit_cast(v4i, h3);
+            } else {
+                v8h_t h1, h2;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float f = APART ? (e < 4 ? z0[e & 3] + s0[e & 3] : z1[e & 3] + s1[e & 3]) : (e < 4 ? z0[e & 3] : z1[e & 3]);
-                const _Float16 h = (_Float16)f;
-                ah[e] = h;
-                al[e] = (_Float16)__builtin_fmaf((float)h, -1.0f, f);
+                for (int e = 0; e < 8; ++e) {
+                    const float f = e < 4 ? z0[e & 3] : z1[e & 3];
+                    const _Float16 h = (_Float16)f;
+                    h1[e] = h;
+                    h2[e] = (_Float16)__builtin_fmaf((float)h, -1.0f, f);
+                }
+                ah = __builtin_bit_cast(v4i, h1); al = __builtin_bit_cast(v4i, h2);
             }
             const int cn = ch + 1 < CH2 ? ch + 1 : 0;
             n0 = ld_a(cn, 0, 0); n1_ = ld_a(cn, 0, 1);
@@ -253,16 +364,21 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
 #pragma unroll
             for (int tc = 0; tc < AT; ++tc) {
                 {
-                    const v8h_t ch_ = __builtin_bit_cast(v8h_t, qb[0][tc]), cl_ = __builtin_bit_cast(v8h_t, qb[1][tc]);
+                    const v4i ch_ = qb[0][tc], cl_ = qb[1][tc];
                     if (tc + 1 < AT) {                 // (a tile past the last one reads what lies behind; never used)
                         qb[0][tc + 1] = *reinterpret_cast<const v4i*>(rb + (tc + 1) * 1024);
                         qb[1][tc + 1] = *reinterpret_cast<const v4i*>(rb + (AT + tc + 1) * 1024);
+                        if constexpr (BF) qb[2][tc + 1] = *reinterpret_cast<const v4i*>(rb + (2 * AT + tc + 1) * 1024);
                     }
                     v4f& small = APART ? ys[tc] : y[tc];
-                    if constexpr (LOLO) small = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, cl_, small, 0, 0, 0);
-                    small = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, ch_, small, 0, 0, 0);
-                    small = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, cl_, small, 0, 0, 0);
-                    y[tc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, ch_, y[tc], 0, 0, 0);
+                    if constexpr (BF) {
+                        small = rt_mma<BF>(ax, ch_, small);
+                        small = rt_mma<BF>(ah, qb[2][tc], small);
+                        small = rt_mma<BF>(al, cl_, small);
+                    }
+                    small = rt_mma<BF>(al, ch_, small);
+                    small = rt_mma<BF>(ah, cl_, small);
+                    y[tc] = rt_mma<BF>(ah, ch_, y[tc]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -272,26 +388,25 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
             for (int tc = 0; tc < AT; ++tc) y[tc] += ys[tc];
         }
         // ---- the token's range (padded rows and columns are exact zeros); the next token's largest value
-        const float yun = 1.52587890625e-05f / sx;      // back from 256 R2, 256 R1 and the token's scale
         float mx = 0.0f, mn = 0.0f;
         if (a.asym) {
 #pragma unroll
             for (int tc = 0; tc < AT; ++tc)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) { mx = fmaxf(mx, y[tc][v]); mn = fminf(mn, y[tc][v]); }
-            mx = dl_wave_max_nonneg(mx) * yun;
-            mn = dl_wave_max_nonneg(-mn) * yun;
+            mx = dl_wave_max_nonneg(mx);
+            mn = dl_wave_max_nonneg(-mn);
         } else {
 #pragma unroll
             for (int tc = 0; tc < AT; ++tc)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) mx = fmaxf(mx, fabsf(y[tc][v]));
-            mx = dl_wave_max_nonneg(mx) * yun;
+            mx = dl_wave_max_nonneg(mx);
             mn = mx;
         }
         if (lane == 0) { red[wave] = mx; red[16 + wave] = mn; }
         if constexpr (MANY) {
-            if (j + 1 < rounds) {
+            if (!BF && j + 1 < rounds) {
                 const float nm = token_max();
                 if (lane == 0) red[32 + wave] = nm;
             }
@@ -299,12 +414,12 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         bwla_lds_barrier();                             // also: everybody is done with the token rows
         const float hi = over_strips(red), lo = -over_strips(red + 16);
         float xmax = 0.0f;
-        if constexpr (MANY) xmax = over_strips(red + 32);
+        if constexpr (MANY && !BF) xmax = over_strips(red + 32);
         const QuantPlan qp = quant_plan(hi, lo, a.qmax, a.asym != 0);
         // ---- codes, to LDS in k order.  Lane holds Yt[d = 16 strip + 4 lg + v][c = 16 tc + li]: four consecutive k.
         // y * inv + (1.5 * 2^23 + zero point) rounds once, to an integer (ties to even) in the low mantissa bits; clamped as a
         // float, its low byte is the code.
-        const float inv = qp.inv * yun, addc = 12582912.0f + qp.zc;
+        const float inv = qp.inv, addc = 12582912.0f + qp.zc;
         const float cmin = 12582912.0f + qp.cmin, cmax = 12582912.0f + qp.cmax;
         int lsum = 0;
         const int d0 = 16 * wave + 4 * lg;
@@ -335,6 +450,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         }
         lsum = dl_wave_sum(lsum);
         if (lane == 0) redi[wave] = lsum;
+        const float sc = ldexpf(quant_scale(hi, lo, a.qmax, a.asym != 0), E - 145);
         if constexpr (MANY) {
             if (!b.s.own) {                             // the codes lie where the next token goes: out first
                 bwla_lds_barrier();
@@ -342,9 +458,9 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
                 bwla_lds_barrier();
             }
             if (j + 1 < rounds) {
-                sx = scale_of(xmax);
+                if constexpr (!BF) E = exponent_of(xmax);
                 if (pads && !b.s.own) zero_pads(tid, TG);
-                land(sx);
+                land(E);
                 if (j + 2 < rounds) request(t + 2 * tstep);
             }
         }
@@ -354,7 +470,6 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
             const int tot = dl_wave_sum(lane < strips ? redi[lane] : 0);
             if (lane == 0) {
                 a.qsum[t] = tot;
-                const float sc = quant_scale(hi, lo, a.qmax, a.asym != 0);
                 a.scale[t] = sc;
                 quant_extras(a.tmode, a.tp, t, a.asym != 0, a.shift != 0, qp, sc, tot, K);
             }
@@ -366,28 +481,38 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     }
 }
 
-template <int AT, int K1M, bool STREAM, bool MANY, int THREADS>
+template <int AT, int K1M, bool STREAM, bool MANY, bool F32, int THREADS>
 hipError_t launch_v(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
     if (threads > THREADS) return hipErrorInvalidValue;
-    const auto kern = rotate_terms_kernel<AT, K1M, STREAM, MANY, THREADS>;
+    const auto kern = rotate_terms_kernel<AT, K1M, STREAM, MANY, F32, THREADS>;
     hipError_t e = bwla_ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<dim3((unsigned)blocks), dim3((unsigned)threads), lds, st>>>(b);
     return hipGetLastError();
 }
 
-// (k1, at: the shape's, the kernels' are at least as large)
+// (k1: the shape's; the kernel's is at least as large)
 template <bool MANY>
 hipError_t launch_terms(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
     const RtShape& s = b.s;
-#define RT_STREAM(A) if (s.stream && s.at == A) return launch_v<A, 4, true, MANY, 512>(b, blocks, threads, lds, st);
+#define RT_STREAM(A) if (s.stream && s.at == A) return launch_v<A, 4, true, MANY, false, 512>(b, blocks, threads, lds, st);
     RT_STREAM(12) RT_STREAM(14) RT_STREAM(16)
 #undef RT_STREAM
 #define RT_CASE(A)                                                                                         \
-    if (s.at == A) return s.k1 <= 2   ? launch_v<A, 2, false, MANY, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
-                          : s.k1 <= 3 ? launch_v<A, 3, false, MANY, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
-                                      : launch_v<A, 5, false, MANY, 768>(b, blocks, threads, lds, st);
+    if (s.at == A) return s.k1 <= 2   ? launch_v<A, 2, false, MANY, false, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
+                          : s.k1 <= 3 ? launch_v<A, 3, false, MANY, false, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
+                                      : launch_v<A, 5, false, MANY, false, 768>(b, blocks, threads, lds, st);
     RT_CASE(2) RT_CASE(4) RT_CASE(6) RT_CASE(8) RT_CASE(10)
+#undef RT_CASE
+    return hipErrorInvalidValue;
+}
+template <bool MANY>
+hipError_t launch_terms_f32(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
+    const RtShape& s = b.s;
+#define RT_CASE(A)                                                                                         \
+    if (s.at == A) return s.k1 <= 2 ? launch_v<A, 2, false, MANY, true, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
+                                    : launch_v<A, 3, false, MANY, true, MANY ? 768 : 512>(b, blocks, threads, lds, st);
+    RT_CASE(2) RT_CASE(4) RT_CASE(6) RT_CASE(8)
 #undef RT_CASE
     return hipErrorInvalidValue;
 }

@@ -1,4 +1,4 @@
-// The walking form of the rotation on two fp16 terms (design and launcher in rotate_terms.hip): a translation unit of its own,
+// The walking form of the rotation on 16-bit terms (design and launcher in rotate_terms.hip): a translation unit of its own,
 // for the time it takes to compile.
 #include "rotate_terms_device.h"
 

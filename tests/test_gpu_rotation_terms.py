@@ -1,4 +1,4 @@
-"""Rotation and codes of bf16 tokens by the kernel on two fp16 terms (any even n2): every number of tiles along either factor,
+"""Rotation and codes by the kernel on 16-bit terms (any even n2; bf16 tokens, and fp32 ones as three terms): every number of tiles along either factor,
 rows that end inside a tile or on no 16-byte boundary, one token a workgroup and workgroups that walk, against fp64."""
 import copy
 
@@ -19,7 +19,7 @@ def _need_gpu():
     B.load()
 
 
-# (tokens, n1, n2, rank, bits, row shift, asymmetric)
+# (tokens, n1, n2, rank, bits, row shift, asymmetric[, type])
 CASES = [
     (1, 16, 32, 8, 6, False, False),        # the smallest pair; the projection rides
     (16, 32, 16, 0, 8, False, False),
@@ -42,6 +42,13 @@ CASES = [
     (270, 200, 80, 8, 6, True, True),
     (12, 256, 112, 0, 6, False, False),
     (3, 224, 128, 8, 6, False, False),      # few tokens: the split rotation
+    (16, 16, 32, 8, 6, False, False, "f32"),    # fp32 tokens: three terms
+    (1, 46, 64, 8, 7, True, True, "f32"),
+    (333, 64, 64, 32, 6, False, False, "f32"),  # riding, several workgroups a CU
+    (20, 128, 86, 0, 8, False, False, "f32"),   # rows on 8-byte boundaries
+    (1030, 64, 80, 8, 6, True, False, "f32"),   # walking
+    (770, 128, 96, 0, 6, False, True, "f32"),   # the largest that it takes
+    (9, 128, 100, 0, 6, False, False, "f32"),    # and the first that it does not
 ]
 
 
@@ -93,11 +100,11 @@ def _check(act, X, R, U, n1, n2, r, bits, shift, asym):
         zc = torch.round(got)
     if shift:
         sums = act.scale.double() * (act.qsum.double() - K * zc)
-        assert torch.allclose(act.T[:, -1].double(), sums, rtol=1e-5, atol=1e-5 * float(s.max()) * K)
+        assert bool(((act.T[:, -1].double() - sums).abs() <= 1e-5 * sums.abs() + 1e-5 * s * K).all())
 
 
-@pytest.mark.parametrize("M,n1,n2,r,bits,shift,asym", CASES)
-def test_rotation_of_any_pair(M, n1, n2, r, bits, shift, asym):
+@pytest.mark.parametrize("M,n1,n2,r,bits,shift,asym,x", [c if len(c) == 8 else c + ("bf16",) for c in CASES])
+def test_rotation_of_any_pair(M, n1, n2, r, bits, shift, asym, x):
     from paper_2605_00422_amd import binding as B
     g = torch.Generator(device=DEV)
     g.manual_seed(M + n1 * n2 + r)
@@ -106,17 +113,19 @@ def test_rotation_of_any_pair(M, n1, n2, r, bits, shift, asym):
     for _ in range(2):                                      # twice on one scratch
         X = torch.randn(M, n1 * n2, device=DEV, generator=g)
         X[:, ::89] *= 50.0
-        X[M // 2] *= 1e-20
-        X[M - 1] = 0 if M > 1 else X[0]
-        X = X.to(torch.bfloat16)
+        X[M // 2] *= 1e-33                                  # (a step of 1e-34 still is a normal number)
+        X[M // 3] *= 1e30
+        X[M - 1] = 0 if M > 3 else X[M - 1]
+        if x == "bf16":
+            X = X.to(torch.bfloat16)
         act.q.fill_(99)
         B.rotate_quant(layer, X, act, bits)
         torch.cuda.synchronize()
         _check(act, X, R, U, n1, n2, r, bits, shift, asym)
 
 
-@pytest.mark.parametrize("M,n1,n2", [(4, 64, 80), (300, 64, 80), (40, 128, 86)])
-def test_layers_packed_without_operand_order_factors(M, n1, n2):
+@pytest.mark.parametrize("M,n1,n2,x", [(4, 64, 80, "bf16"), (300, 64, 80, "f32"), (40, 128, 86, "bf16"), (300, 128, 86, "bf16")])
+def test_layers_packed_without_operand_order_factors(M, n1, n2, x):
     """A layer that was packed and kept before its pair had them: the same bytes, fewer of them."""
     from paper_2605_00422_amd import binding as B
     g = torch.Generator(device=DEV)
@@ -125,7 +134,8 @@ def test_layers_packed_without_operand_order_factors(M, n1, n2):
     old = copy.copy(layer)
     old.desc = type(layer.desc).from_buffer_copy(layer.desc)
     old.desc.blob_bytes, old.desc.off_Rd = layer.desc.off_Rd, 0
-    X = torch.randn(M, n1 * n2, device=DEV, generator=g).to(torch.bfloat16)
+    X = torch.randn(M, n1 * n2, device=DEV, generator=g)
+    X = X.to(torch.bfloat16) if x == "bf16" else X
     act = B.Activations(old, M)
     B.rotate_quant(old, X, act)
     torch.cuda.synchronize()
