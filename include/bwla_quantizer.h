@@ -95,14 +95,16 @@ BWLA_API bwla_status_t bwla_q_svd_square(const double* d_G, int32_t nn, double* 
  * Best rank-k approximation of Y (n x m) in the Frobenius norm (Sec. 3.2: the projection onto the
  * rank-k matrices is the truncated SVD), returned in factors: Y_k = A Bt^T with A = Y V_k (n x k,
  * column j = sigma_j u_j) and Bt = V_k (m x k, orthonormal columns); d_sig (may be NULL) gets the k
- * singular values.  Computed by block subspace iteration on Y^T Y with a block of
- * min(n, m, max(2 k, k + 16)) vectors from a fixed pseudo-random start, re-orthonormalized every
- * iteration through the eigendecomposition of its Gram matrix, and a final Rayleigh-Ritz step.  It
- * stops after `iters` iterations, or earlier once the k leading Ritz values have moved by at most
- * `tol` (relative) in one iteration: the remaining launches then return at once.  (Blocks of more than
- * 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead, have no Ritz
- * values along the way and always run all `iters` iterations.)  The captured
- * energy converges like (sigma_{p+1} / sigma_k)^(4 iterations); a spectrum without a gap behind
+ * singular values.  Computed by block subspace iteration on S = Y^T Y with a block of
+ * min(n, m, max(2 k, k + 16)) vectors from a fixed pseudo-random start, filtered by a Chebyshev polynomial of
+ * degree two in S whose interval ends at the smallest Ritz value, re-orthonormalized every iteration through the
+ * Cholesky factor of its Gram matrix, and a final Rayleigh-Ritz step.  It stops when the work of `iters` plain
+ * iterations is done -- `iters` products with S up to 24, half as many above, which the filter makes up for --
+ * or earlier once the k leading Ritz values have settled: moved by at most `tol` (relative) in one iteration, or
+ * about to move by less than tol / 16 in the next, going by the last two; the remaining launches then return at
+ * once.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead,
+ * are not filtered, have no Ritz values along the way and always run all `iters` iterations.)  The captured
+ * energy converges like T_2(2 sigma_k^2 / sigma_{p+1}^2 - 1)^(-iters); a spectrum without a gap behind
  * sigma_k needs many iterations for the singular vectors themselves.
  * d_ws: bwla_quantizer_workspace_size(n, m, 1, 1, k) bytes.
  */

@@ -31,9 +31,23 @@ __device__ __forceinline__ long q_koff(int k, int kdiv, long kh, long kl) {
     return (long)k * kl;
 }
 
+__device__ __forceinline__ bool q_skipped(const QGemm& g) {
+    const int v = g.skip ? *g.skip : 0;
+    return v != 0 && v != g.skip_but;
+}
+
+// C[o] = alpha x + beta C0[o] (+ gamma C1[o])
+__device__ __forceinline__ double q_combine(const QGemm& g, double x, long o) {
+    const double beta = g.coef ? g.coef[1] : g.beta;
+    x *= g.coef ? g.coef[0] : g.alpha;
+    if (g.C0 && beta != 0.0) x += beta * g.C0[o];
+    if (g.C1 && g.coef) x += g.coef[2] * g.C1[o];
+    return x;
+}
+
 template <bool EASY, bool AK, bool BK>
 __global__ __launch_bounds__(256) void qgemm_kernel(QGemm g) {
-    if (g.skip && *g.skip) return;
+    if (q_skipped(g)) return;
     __shared__ double As[2][TK][LD];
     __shared__ double Bs[2][TK][LD];
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -135,7 +149,6 @@ __global__ __launch_bounds__(256) void qgemm_kernel(QGemm g) {
     }
     const bool direct = g.ksplit == 1;
     double* Cb = direct ? g.C + (long)b * g.bsC : g.partials + ((long)s * g.batch + b) * (long)g.M * g.N;
-    const double* C0b = (direct && g.C0 && g.beta != 0.0) ? g.C0 + (long)b * g.bsC : nullptr;
     const long rs = direct ? g.rsC : g.N;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -146,19 +159,14 @@ __global__ __launch_bounds__(256) void qgemm_kernel(QGemm g) {
                 const int row = i0 + wm + a * 16 + 4 * v + lq, col = j0 + wn + c * 16 + lr;
                 if (row < g.M && col < g.N) {
                     const long o = row * rs + col;
-                    double x = acc[a][c][v];
-                    if (direct) {
-                        x *= g.alpha;
-                        if (C0b) x += g.beta * C0b[o];
-                    }
-                    Cb[o] = x;
+                    Cb[o] = direct ? q_combine(g, acc[a][c][v], (long)b * g.bsC + o) : acc[a][c][v];
                 }
             }
 }
 
-// adds the ksplit partial products in range order and applies alpha, beta, C0
+// adds the ksplit partial products in range order and combines the sum with C0 and C1
 __global__ __launch_bounds__(256) void qgemm_reduce_kernel(QGemm g) {
-    if (g.skip && *g.skip) return;
+    if (q_skipped(g)) return;
     const long per = (long)g.M * g.N, total = per * g.batch;
     for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long)gridDim.x * 256) {
         double x = 0.0;
@@ -166,9 +174,7 @@ __global__ __launch_bounds__(256) void qgemm_reduce_kernel(QGemm g) {
         const long b = e / per, rem = e - b * per;
         const long row = rem / g.N, col = rem - row * g.N;
         const long o = b * g.bsC + row * g.rsC + col;
-        x *= g.alpha;
-        if (g.C0 && g.beta != 0.0) x += g.beta * g.C0[o];
-        g.C[o] = x;
+        g.C[o] = q_combine(g, x, o);
     }
 }
 

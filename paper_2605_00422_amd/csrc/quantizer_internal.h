@@ -19,7 +19,8 @@
 // ksplit > 1 cuts the contraction into ksplit ranges whose partial products go to `partials`
 // (ksplit x batch x M x N, dense) and are added in range order by a second launch, which also
 // applies alpha, beta and C0: deterministic whatever the launch order.
-// `skip` (device, may be NULL): when *skip != 0 the launches return without touching C.
+// `coef` (device, may be NULL): C = coef[0] A B + coef[1] C0 + coef[2] C1 instead, C1 addressed like C; C0 may be C.
+// `skip` (device, may be NULL): the launches return without touching C when *skip is neither 0 nor skip_but.
 struct QGemm {
     const double* A; const double* B; double* C; const double* C0;
     int M, N, K, batch;
@@ -28,7 +29,8 @@ struct QGemm {
     long rsC, bsC;
     double alpha, beta;
     int ksplit; double* partials;
-    const int* skip;
+    const double* C1; const double* coef;
+    const int* skip; int skip_but;
 };
 inline QGemm qgemm_plain(const double* A, const double* B, double* C, int M, int N, int K) {
     QGemm g{};
@@ -87,17 +89,32 @@ hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, 
 //   sig[j]        singular values
 //   Ws[j][:]      column j of G V = s_j u_j            (n x n, row j = that column)
 //   Vs[j][:]      s_j^pw * v_j                          (n x n, row j = that vector; s_j = 0 gives 0)
-// `work` holds 2 n^2 doubles.  conv (may be NULL): {int done; } convergence bookkeeping of the subspace
-// iteration -- when prev_sig is given, done is set once the leading `lead` singular values moved by
-// at most tol relative to the previous call, and prev_sig is replaced.  The launch returns
-// immediately when *skip != 0.
-// sym: G is symmetric positive semidefinite (a Gram matrix): the rotations are not accumulated, v_j is
-// the normalized column j of G V (equal to u_j there), and matrices up to 136 wide stay in LDS.
+// `work` holds 2 n^2 doubles.  it (may be NULL): the bookkeeping of the subspace iteration, below.  The launch
+// returns immediately when *skip != 0.
+// sym: G is symmetric positive semidefinite (a Gram matrix G = B^T B); Ws is not available.  Up to 136 wide the
+// sweeps run in LDS, on the Cholesky factor G = L L^T, and the rotations are not accumulated; sig are eigenvalues:
+//   ortho         the columns of L^T are rotated into X S; Vs[j] = column j of L^-T X, so that B Vs^T has
+//                 orthonormal columns, which are the left singular vectors of B
+//   otherwise     the columns of L; Vs[j] = eigenvector j (pw is not looked at)
+// Wider ones (without ortho) are rotated themselves, v_j being the normalized column j of G V.
+//
+// The subspace iteration on S = Y^T Y filters its block by T_2(2 S / theta - 1), the Chebyshev polynomial
+// that is at most 1 on [0, theta] and grows fastest beyond (Rutishauser's simultaneous iteration, 1970),
+// theta being the smallest Ritz value of the block.  QRitz is what a Jacobi call on the Gram matrix of the
+// filtered block leaves for the next iteration: theta, the coefficients of the filter's two products
+// (QGemm::coef), and how far the Ritz values moved.  power > 0 says that the filter is (S / power)^2 instead.
+struct QRitz { double first[3], second[3], theta, power, moved; };
 struct QJacobi {
     const double* G; int n; double pw;
     double* sig; double* Ws; double* Vs; double* work;
-    double* prev_sig; int lead; double tol; int* done; const int* skip;
-    bool sym;
+    const int* skip;
+    bool sym, ortho;
+    // With it: prev holds n doubles, the squared Ritz values of the iteration before, and is replaced; degree says
+    // whether the block was multiplied by S (1) or filtered (2), scale what its Ritz values are to be multiplied
+    // with in the first case.  From the third call on (call counts from 1) *done is set to `call` once the leading `lead` values have
+    // settled: they moved by at most tol relative, or what the next iteration would move them by, a quotient of two
+    // movements smaller again, is below tol / 16.
+    QRitz* it; double* prev; int lead, degree, call; double tol, scale; int* done;
 };
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st);
 constexpr int BWLA_Q_JACOBI_LDS = 96;        // largest matrix whose two work arrays fit LDS

@@ -18,8 +18,8 @@
 // Up to n = 96 both arrays (2 n^2 doubles, at most 144 KiB) live in LDS, where a round costs an LDS
 // round trip instead of an L2 one; larger matrices work in the caller's scratch (L2-resident).
 // For a symmetric positive semidefinite matrix (the Gram matrices of the subspace iteration) V is not
-// kept at all -- its columns are the normalized columns of the rotated matrix -- so that matrices up
-// to 136 wide fit LDS; there a pair takes two rows of lanes up to n = 128.
+// kept at all -- the sweeps work on a Cholesky factor, below -- so that matrices up to 136 wide fit LDS; there a
+// pair takes two rows of lanes up to n = 128.
 #include "bwla_internal.h"
 #include "quantizer_internal.h"
 
@@ -109,10 +109,19 @@ __device__ __forceinline__ void jrotation(double al, double be, double ga, doubl
 // left and right singular vectors coincide) the right singular vectors are the normalized columns of
 // the rotated G themselves -- orthogonal to the tolerance of the sweeps, and as accurate as eigenvectors
 // as the accumulated ones (both diagonalize G up to eps ||G||) -- at half the work and half the memory.
+// In LDS (FACTOR) G = L L^T is factored first.  A Gram matrix of filtered columns is graded: the squares of their norms
+// may be 1e20 apart.  Sweeps on G itself lose everything below eps ||G||; the columns of L^T carry the grading as
+// scales of columns, which one-sided rotations keep out of the result's relative accuracy (Demmel and Veselic,
+// 1992), and L^-T X orthonormalizes the block to eps times the condition of the columns scaled to length one.  Eigenvectors
+// over roots of eigenvalues are right to eps of the largest column only: at 3e5 between the Ritz values the block was
+// orthonormal to 1e-4, and the next filter lost it.  Times at 64 columns, 11008 x 4096: 490 us for the first two
+// blocks, 320 to 270 for the later ones and 95 where nothing turns, of which some 55 are load, factor, solve and the check
+// (sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded).
 template <int GW, bool LDS, bool ACCV>
 __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
     constexpr int JT = jacobi_threads(GW), JW = JT / 64;
+    constexpr bool FACTOR = LDS && !ACCV;
     const int n = a.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
     extern __shared__ __align__(16) double jlds[];
     double* Wc = LDS ? jlds : a.work;
@@ -123,10 +132,71 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     __shared__ int rotated;
     __shared__ double sg[JMAX];                             // during the sweeps: squared norms of the columns
     __shared__ int ord[JMAX];
+    __shared__ double di[FACTOR ? BWLA_Q_JACOBI_SYM_LDS : 1];           // 1 / L_jj
     for (int e = t; e < ncol * ld; e += JT) {
         const int j = e / ld, i = e - j * ld;
         Wc[e] = i < n && j < n ? a.G[(size_t)i * n + j] : 0.0;
         if (ACCV) Vc[e] = i == j ? 1.0 : 0.0;
+    }
+    // L^T for the triangular solve, column r = row r of L, behind Wc where LDS has room for both
+    double* Lt = LDS && n <= JLDS ? Wc + (size_t)ncol * ld : a.work;
+    const int ldt = n + 1;                                              // (a column of it is written across banks)
+    constexpr int U = GW == 16 ? 1 : GW == 32 ? 2 : 3;                  // elements of a column per lane
+    if constexpr (FACTOR) {
+        // Column j keeps G's entries below the diagonal and is divided by the root of its pivot at the end, so that
+        // a step is one update of what is right of it and one barrier.  A pivot that rounding has eaten (a Gram matrix
+        // singular to working precision) counts as 1e-14 of the diagonal that it came from, and what is below it, which is
+        // as much noise as it is, as nothing: without that, noise grows by squares from step to step.
+        __syncthreads();
+        for (int j = t; j < n; j += JT) sg[j] = 1.0e-14 * Wc[(size_t)j * ld + j];
+        __syncthreads();
+        for (int j = 0; j < n; ++j) {
+            const double* cj = Wc + (size_t)j * ld;
+            const double piv = cj[j], inv = piv > sg[j] && piv > 1.0e-300 ? jrcp(piv) : 0.0;
+            double mine[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) mine[u] = lane + 64 * u < n ? cj[lane + 64 * u] : 0.0;
+            // wavefronts take columns, four at a time so that their LDS reads overlap, lanes rows
+            for (int k0 = j + 1 + w; k0 < n; k0 += 4 * JW) {
+                double f[4], v[4][U];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int k = k0 + q * JW < n ? k0 + q * JW : n - 1;
+                    f[q] = cj[k];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = lane + 64 * u;
+                        v[q][u] = Wc[(size_t)k * ld + (i < n ? i : 0)];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int k = k0 + q * JW;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = lane + 64 * u;
+                        if (k < n && i >= k && i < n) Wc[(size_t)k * ld + i] = fma(-f[q] * inv, mine[u], v[q][u]);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        for (int j = w; j < n; j += JW) {
+            double* cj = Wc + (size_t)j * ld;
+            const double piv = cj[j], floor = sg[j];
+            const bool sound = piv > floor && piv > 1.0e-300;
+            const double root = sqrt(sound ? piv : floor), inv = sound ? 1.0 / root : 0.0;
+            for (int i = lane; i < n; i += 64) {
+                const double l = i < j ? 0.0 : i == j ? root : cj[i] * inv;
+                if (a.ortho) Lt[(size_t)i * ldt + j] = l;
+                else cj[i] = l;
+            }
+            if (lane == 0) di[j] = root > 0.0 ? 1.0 / root : 0.0;
+        }
+        __syncthreads();
+        if (a.ortho)
+            for (int j = w; j < n; j += JW)
+                for (int i = lane; i < n; i += 64) Wc[(size_t)j * ld + i] = Lt[(size_t)j * ldt + i];
     }
     const int np = (n + 1) & ~1;
     constexpr int GROUPS = JT / GW;
@@ -160,7 +230,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         double* xp = Wc + (size_t)p * ld;
         double* yp = Wc + (size_t)q * ld;
         double x[4], y[4];
-        const double al = sg[p], be = sg[q < ncol ? q : 0];
+        double al = sg[p], be = sg[q < ncol ? q : 0];
         double ga = 0.0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -170,6 +240,16 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) ga += x[u] * y[u];
         ga = jgroup_sum<GW>(ga);
+        if (ga * ga > al * be) {                            // carried norms that cancellation has spoilt
+            al = be = 0.0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                al += x[u] * x[u];
+                be += y[u] * y[u];
+            }
+            al = jgroup_sum<GW>(al);
+            be = jgroup_sum<GW>(be);
+        }
         // (|ga| > 1e-15 sqrt(al be), without the root)
         if (live && al > 0.0 && be > 0.0 && ga * ga > 1.0e-30 * (al * be)) {
             double tt, cs;
@@ -266,6 +346,10 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                             }
                         }
                         const double ga = jrow_sum((x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]));
+                        if (ga * ga > nx * ny) {                        // as above
+                            nx = jrow_sum((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]));
+                            ny = jrow_sum((y[0] * y[0] + y[1] * y[1]) + (y[2] * y[2] + y[3] * y[3]));
+                        }
                         const bool turn = nx > 0.0 && ny > 0.0 && ga * ga > 1.0e-30 * (nx * ny);
                         if (turn) {
                             double tt, cs;
@@ -330,7 +414,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         double s = 0.0;
         for (int e = lane; e < n; e += 64) s += Wc[(size_t)j * ld + e] * Wc[(size_t)j * ld + e];
         s = jgroup_sum<64>(s);
-        if (lane == 0) sg[j] = sqrt(s);
+        if (lane == 0) sg[j] = FACTOR ? s : sqrt(s);
     }
     __syncthreads();
     for (int j = t; j < n; j += JT) {
@@ -339,29 +423,115 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         ord[rank] = j;
     }
     __syncthreads();
-    for (int jj = w; jj < n; jj += JW) {
-        const int j = ord[jj];
-        const double s = sg[j];
-        double scale = s > 0.0 ? (a.pw == 0.0 ? 1.0 : pow(s, a.pw)) : 0.0;
-        if (!ACCV && s > 0.0) scale /= s;                   // v_j = the column of the rotated G over its norm
-        for (int e = lane; e < n; e += 64) {
-            if (a.Ws) a.Ws[(size_t)jj * n + e] = Wc[(size_t)j * ld + e];
-            if (a.Vs) a.Vs[(size_t)jj * n + e] = scale * (ACCV ? Vc[(size_t)j * ld + e] : Wc[(size_t)j * ld + e]);
+    if (FACTOR && a.ortho) {
+        // L^T M = X, eight right sides a wavefront, their rows in lanes, from the last row up
+        for (int j0 = 8 * w; j0 < n; j0 += 8 * JW) {
+            double x[8][U];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int j = ord[j0 + q < n ? j0 + q : n - 1];
+                const double s = sg[j], inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = lane + 64 * u;
+                    x[q][u] = i < n ? inv * Wc[(size_t)j * ld + i] : 0.0;
+                }
+            }
+            double row[U], d = di[n - 1];
+            auto fetch = [&](int r, double (&to)[U]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) to[u] = lane + 64 * u < r ? Lt[(size_t)r * ldt + lane + 64 * u] : 0.0;
+            };
+            fetch(n - 1, row);
+            for (int r = n - 1; r >= 0; --r) {
+                double next[U], dn = 0.0;
+                if (r > 0) {
+                    fetch(r - 1, next);
+                    dn = di[r - 1];
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    double v = x[q][0];
+#pragma unroll
+                    for (int u = 1; u < U; ++u) v = r >= 64 * u ? x[q][u] : v;
+                    const double m = jread(v, r & 63) * d;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const double kept = fma(-row[u], m, x[q][u]);
+                        x[q][u] = lane + 64 * u == r ? m : kept;
+                    }
+                }
+                if (r > 0) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) row[u] = next[u];
+                    d = dn;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = lane + 64 * u;
+                    if (j0 + q < n && i < n) a.Vs[(size_t)(j0 + q) * n + i] = x[q][u];
+                }
+        }
+    } else {
+        for (int jj = w; jj < n; jj += JW) {
+            const int j = ord[jj];
+            const double s = sg[j];
+            double scale = 0.0;
+            if (s > 0.0) {
+                // (FACTOR: s is the squared norm of the column)
+                if (FACTOR) scale = 1.0 / sqrt(s);
+                else scale = (a.pw == 0.0 ? 1.0 : pow(s, a.pw)) / (ACCV ? 1.0 : s);
+            }
+            for (int e = lane; e < n; e += 64) {
+                if (a.Ws) a.Ws[(size_t)jj * n + e] = Wc[(size_t)j * ld + e];
+                if (a.Vs) a.Vs[(size_t)jj * n + e] = scale * (ACCV ? Vc[(size_t)j * ld + e] : Wc[(size_t)j * ld + e]);
+            }
         }
     }
-    if (t == 0 && a.prev_sig && a.done) {
-        double worst = 0.0;
-        for (int jj = 0; jj < a.lead && jj < n; ++jj) {
-            const double s = sg[ord[jj]];
-            worst = fmax(worst, fabs(s - a.prev_sig[jj]) / fmax(s, 1.0e-300));
+    if (a.sig)
+        for (int jj = t; jj < n; jj += JT) a.sig[jj] = sg[ord[jj]];
+    if (a.it && w == 0) {
+        // Ritz values of S out of the eigenvalues sg of the filtered block's Gram matrix
+        const double theta = a.it->theta, power = a.it->power, before = a.it->moved;
+        auto ritz = [&](int jj) {
+            const double r = sqrt(sg[ord[jj]]);
+            if (a.degree == 1) return r * a.scale;
+            if (power > 0.0) return power * sqrt(r);
+            return 0.5 * theta * (sqrt(0.5 * (r + 1.0)) + 1.0);         // r = 2 x^2 - 1, x = 2 l / theta - 1
+        };
+        double moved = 0.0;
+        for (int jj = lane; jj < n; jj += 64) {
+            const double l = ritz(jj), l2 = l * l;
+            if (jj < a.lead) moved = fmax(moved, fabs(l2 - a.prev[jj]) / fmax(l2, 1.0e-300));
+            a.prev[jj] = l2;
         }
-        if (worst <= a.tol) *a.done = 1;
-    }
-    __syncthreads();
-    for (int jj = t; jj < n; jj += JT) {
-        const double s = sg[ord[jj]];
-        if (a.sig) a.sig[jj] = s;
-        if (a.prev_sig) a.prev_sig[jj] = s;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) moved = fmax(moved, __shfl_xor(moved, off, 64));
+        if (lane == 0) {
+            const double top = ritz(0), next = ritz(n - 1);
+            // The first call's values are of a block that was not orthonormal, so the first movement is the second's to
+            // the third; a quotient of movements takes two of them.
+            const bool still = a.call >= 3 && moved <= a.tol;
+            const bool soon = a.call >= 4 && moved <= 0.1 * before && moved * (moved / before) <= 0.0625 * a.tol;
+            if (still || soon) *a.done = a.call;
+            // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
+            // orthonormalizing takes out as long as that is small against one.  With values further apart the block is
+            // multiplied by S^2, whose columns span as much, so that nothing is asked of theta.
+            const bool cheb = next > 0.0 && next >= 1.0e-6 * top;
+            const double inv = cheb ? 1.0 / next : top > 0.0 ? 1.0 / top : 0.0;
+            a.it->theta = next;
+            a.it->power = cheb ? 0.0 : top;
+            a.it->moved = moved;
+            a.it->first[0] = cheb ? 2.0 * inv : inv;
+            a.it->first[1] = cheb ? -1.0 : 0.0;
+            a.it->first[2] = 0.0;
+            a.it->second[0] = cheb ? 4.0 * inv : inv;
+            a.it->second[1] = cheb ? -2.0 : 0.0;
+            a.it->second[2] = cheb ? -1.0 : 0.0;
+        }
     }
 }
 
@@ -370,7 +540,9 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st) {
     if (j.n < 1 || j.n > JMAX) return hipErrorInvalidValue;
     const bool in_lds = j.n <= (j.sym ? JLDS_SYM : JLDS);
-    const size_t lds = in_lds ? (size_t)(j.sym ? 1 : 2) * (j.n <= 64 ? (j.n + 7) & ~7 : j.n) * ((j.n + 1) & ~1) * sizeof(double) : 0;
+    const size_t cols = j.n <= 64 ? (j.n + 7) & ~7 : j.n, one = cols * ((j.n + 1) & ~1);
+    const size_t second = j.n > JLDS ? 0 : j.sym ? (size_t)j.n * (j.n + 1) : one;           // L^T, or V
+    const size_t lds = in_lds ? (one + second) * sizeof(double) : 0;
     auto launch = [&](auto kern, int threads) {
         if (lds > 48 * 1024) {
             const hipError_t e = bwla_ensure_lds((const void*)kern, lds);

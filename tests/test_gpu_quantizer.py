@@ -315,6 +315,48 @@ def test_truncate_rank_with_a_gap(n, m, k):
     assert np.max(np.abs(b.T @ b - np.eye(k))) < 1e-12
 
 
+# (blocks of 24, 80, 128 and 132 vectors -- both ways of keeping the Cholesky factor, one to three elements of a column a
+# lane; a spread of 3000 is past what the Chebyshev filter takes, its square past 1e6, and goes by S^2)
+@pytest.mark.parametrize("n,m,k,spread", [(300, 200, 8, 300.0), (300, 256, 40, 300.0), (333, 300, 64, 100.0),
+                                          (300, 280, 66, 300.0), (300, 200, 8, 3000.0), (70, 81, 40, 1.0)])
+def test_truncate_rank_of_a_wide_spectrum(n, m, k, spread):
+    """Singular values far apart: the filtered block's Gram matrix is graded over the fourth power of the spread.
+    A singular value is as good as products with Y are, eps sigma_1 (some 100 roundings of them)."""
+    qb = _qb()
+    rng = np.random.default_rng(n + m)
+    u, v = np.linalg.qr(rng.standard_normal((n, k)))[0], np.linalg.qr(rng.standard_normal((m, k)))[0]
+    edge = 0.02 * (n ** 0.5 + m ** 0.5)
+    Y = 0.02 * rng.standard_normal((n, m)) + (u * (1.5 * edge * np.geomspace(spread, 1, k))) @ v.T
+    A = torch.empty(n, k, dtype=torch.float64, device="cuda")
+    Bt = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    sig = torch.empty(k, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(qb.workspace_size(n, m, 1, 1, k), dtype=torch.uint8, device="cuda")
+    qb.truncate_rank(_dev(Y), k, 60, 1e-14, A, Bt, sig, ws)
+    so = np.linalg.svd(Y, compute_uv=False)
+    assert np.allclose(sig.cpu().numpy(), so[:k], rtol=100 * 2.2e-16 * max(spread, 10.0))
+    assert _rel(A.cpu().numpy() @ Bt.cpu().numpy().T, Q.truncate_rank(Y, k)) < 1e-8
+    b = Bt.cpu().numpy()
+    assert np.max(np.abs(b.T @ b - np.eye(k))) < 1e-12
+
+
+@pytest.mark.parametrize("rank", [0, 1, 4])
+def test_truncate_rank_of_a_matrix_of_lower_rank(rank):
+    """Fewer directions than are asked for: the matrix itself comes back, finite factors and zero singular values."""
+    qb = _qb()
+    n, m, k = 130, 90, 8
+    rng = np.random.default_rng(5)
+    Y = rng.standard_normal((n, rank)) @ rng.standard_normal((rank, m))
+    A = torch.empty(n, k, dtype=torch.float64, device="cuda")
+    Bt = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    sig = torch.empty(k, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(qb.workspace_size(n, m, 1, 1, k), dtype=torch.uint8, device="cuda")
+    qb.truncate_rank(_dev(Y), k, 60, 1e-12, A, Bt, sig, ws)
+    got = A.cpu().numpy() @ Bt.cpu().numpy().T
+    scale = max(float(np.linalg.norm(Y)), 1.0)
+    assert np.linalg.norm(got - Y) < 1e-7 * scale         # (what sweeps on the Gram matrix itself reached: 4e-8)
+    assert np.all(np.isfinite(got)) and np.all(sig.cpu().numpy()[rank:] < 1e-7 * scale)
+
+
 def test_truncate_rank_without_a_gap():
     """A Gaussian matrix: what is unique is the residual energy sum_{j>k} sigma_j^2 (Eckart-Young)."""
     qb = _qb()
