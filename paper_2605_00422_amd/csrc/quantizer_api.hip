@@ -16,7 +16,7 @@ constexpr size_t PART_BYTES = (size_t)64 << 20;   // partial products of split c
 // (n n1) x n2, the rotated rows, and the centered rows / the MM targets.
 struct QPlan {
     int n, m, n1, n2, k, p, jn;
-    size_t big[5], R1, R2, C, A, Bt, A2, Bt2, c, s2, ybar, rowpart, scal, ritz, Q, Q2, Zs, G, Vs, Ws, sig, prev, lam,
+    size_t big[5], R1, R2, C, A, Bt, A2, Bt2, c, s2, rowpart, rowpart2, scal, ritz, Q, Q2, Zs, G, Vs, Ws, sig, prev, lam,
         jwork, flags, partials, bytes;
 };
 
@@ -41,7 +41,7 @@ bwla_status_t make_plan(int64_t n, int64_t m, int32_t n1, int32_t n2, int32_t k,
     P.R1 = take((size_t)n1 * n1 * D); P.R2 = take((size_t)n2 * n2 * D); P.C = take(jj * D);
     P.A = take((size_t)n * k * D); P.Bt = take((size_t)m * k * D);
     P.A2 = take((size_t)n * k * D); P.Bt2 = take((size_t)m * k * D);
-    P.c = take(n * D); P.s2 = take(n * D); P.ybar = take(n * D); P.rowpart = take(n * D);
+    P.c = take(n * D); P.s2 = take(n * D); P.rowpart = take(n * D); P.rowpart2 = take(n * D);
     P.scal = take(64 * D); P.ritz = take(sizeof(QRitz));
     P.Q = take((size_t)m * p * D); P.Q2 = take((size_t)m * p * D); P.Zs = take((size_t)n * p * D);
     P.G = take(jj * D); P.Vs = take(jj * D); P.Ws = take(jj * D);
@@ -91,10 +91,12 @@ void rotate_left(Ctx& x, const double* R1, const double* src, bool transposed, d
 
 // dst rows = src rows times R1 (x) R2 (transposed = false) or times its transpose R1^T (x) R2^T;
 // half = the (n n1) x n2 intermediate src_i R2.  src may equal dst; half must differ from both.
+// coef (may be NULL): times coef[0]
 void rotate_rows(Ctx& x, const double* src, const double* R1, const double* R2, bool transposed, double* half,
-                 double* dst) {
+                 double* dst, const double* coef = nullptr) {
     const QPlan& P = x.P;
     QGemm a = qgemm_plain(src, R2, half, P.n * P.n1, P.n2, P.n2);
+    a.coef = coef;
     if (transposed) { a.csB = P.n2; a.klB = 1; }
     gemm(x, a);
     rotate_left(x, R1, half, transposed, dst);
@@ -111,13 +113,24 @@ const double* residual(Ctx& x, const double* W, const double* A, const double* B
     return Wres;
 }
 
-// big[1] = W - M (when k > 0), big[2] = half-rotated, big[3] = Y = (W - M) R, X = Y H, ybar
-const double* okt(Ctx& x, const double* W, const double* A, const double* Bt, const double* R1, const double* R2,
-                  double* X, double* ybar) {
+// the steps `r` of the rows of big[3] (steps that write an array get it from the caller)
+void rows(Ctx& x, QRows r) {
+    const QPlan& P = x.P;
+    r.Y = x.d(P.big[3]); r.m = P.m; r.part = x.d(P.rowpart); r.part_em = x.d(P.rowpart2);
+    x.ck(bwla_q_launch_rows(r, P.n, x.st));
+}
+QRows row_steps(unsigned steps, const double* c, const double* s2, double* out) {
+    QRows r{};
+    // (written by INIT and EM alone, which callers with arrays of their own to write ask for)
+    r.steps = QROWS_CENTER | steps; r.c = const_cast<double*>(c); r.s2 = const_cast<double*>(s2); r.out = out;
+    return r;
+}
+
+// big[1] = W - M (when k > 0), big[2] = half-rotated, big[3] = Y = (W - M) R
+const double* rotated(Ctx& x, const double* W, const double* A, const double* Bt, const double* R1, const double* R2) {
     const QPlan& P = x.P;
     const double* Wres = residual(x, W, A, Bt, x.d(P.big[1]));
     rotate_rows(x, Wres, R1, R2, false, x.d(P.big[2]), x.d(P.big[3]));
-    x.ck(bwla_q_launch_center(x.d(P.big[3]), X, ybar, P.n, P.m, x.st));
     return Wres;
 }
 
@@ -169,14 +182,11 @@ void polar(Ctx& x, int nn, double* R) {
     gemm(x, g);
 }
 
-// The Procrustes update of one factor, from what the scratch holds: big[2] = half = (W - M) R2,
-// big[3] = Y = (W - M) R and ybar its row means.  Overwrites big[4] (which = 1) or big[4] and big[2]
-// (which = 2, leaving R1^T (W - M) there).
-void procrustes_held(Ctx& x, int which, const double* Wres, const double* R1, const double* c, const double* s2,
-                     double* Rnew) {
+// The Procrustes update of one factor, from what the scratch holds: big[2] = half = (W - M) R2, big[4] = the
+// weighted targets of the rotated rows.  which = 2 leaves R1^T (W - M) in big[2].
+void procrustes_held(Ctx& x, int which, const double* Wres, const double* R1, double* Rnew) {
     const QPlan& P = x.P;
-    double *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *T = x.d(P.big[4]), *ybar = x.d(P.ybar);
-    x.ck(bwla_q_launch_targets(Y, ybar, c, s2, P.n, P.m, T, x.st));
+    double *half = x.d(P.big[2]), *T = x.d(P.big[4]);
     QGemm g{};
     g.batch = 1; g.alpha = 1.0; g.beta = 0.0; g.C = x.d(P.C);
     if (which == 1) {
@@ -202,8 +212,8 @@ void procrustes(Ctx& x, int which, const double* Wres, const double* R1, const d
                 const double* s2, double* Rnew) {
     const QPlan& P = x.P;
     rotate_rows(x, Wres, R1, R2, false, x.d(P.big[2]), x.d(P.big[3]));
-    x.ck(bwla_q_launch_center(x.d(P.big[3]), nullptr, x.d(P.ybar), P.n, P.m, x.st));
-    procrustes_held(x, which, Wres, R1, c, s2, Rnew);
+    rows(x, row_steps(QROWS_TARGETS, c, s2, x.d(P.big[4])));
+    procrustes_held(x, which, Wres, R1, Rnew);
 }
 
 // rank-k truncation of Y (n x m) into A2 (n x k), Bt2 (m x k); lam gets the k leading eigenvalues
@@ -318,15 +328,12 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     times_vs(Q2, m, k, Bt2, nullptr, 0);
 }
 
-// M <- truncation of M - (1/mu) dL/dM; A, Bt in place.  big[4] holds the centered rotated rows of W - M.
-// Leaves the scratch's big arrays stale.
-void psp(Ctx& x, double* A, double* Bt, const double* R1, const double* R2, const double* c,
-         const double* s2, double mu, int iters, double tol, double* lam) {
+// M <- truncation of M - (1/mu) dL/dM; A, Bt in place.  big[3] holds the gradient's rows (QROWS_GRAD) at the rotated rows
+// of W - M, scal the factor that goes with them.  Leaves the scratch's big arrays stale.
+void psp(Ctx& x, double* A, double* Bt, const double* R1, const double* R2, int iters, double tol, double* lam) {
     const QPlan& P = x.P;
-    double *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *X = x.d(P.big[4]), *fac = x.d(P.scal);
-    x.ck(bwla_q_launch_prox_factor(s2, P.n, P.m, mu, fac, x.st));
-    x.ck(bwla_q_launch_gradx(X, c, s2, fac, P.n, P.m, Y, x.st));          // Y <- (G_X H) / mu, sign folded in
-    rotate_rows(x, Y, R1, R2, true, half, Y);                             // back through R^T
+    double* Y = x.d(P.big[3]);
+    rotate_rows(x, Y, R1, R2, true, x.d(P.big[2]), Y, x.d(P.scal));       // back through R^T, sign folded in
     QGemm g{};                                                            // Y <- Y + A Bt^T: the proximal point
     g.A = A; g.B = Bt; g.C = Y; g.C0 = Y; g.M = P.n; g.N = P.m; g.K = P.k; g.batch = 1;
     g.rsA = P.k; g.klA = 1; g.csB = P.k; g.klB = 1; g.rsC = P.m; g.alpha = 1.0; g.beta = 1.0;
@@ -373,8 +380,20 @@ bwla_status_t bwla_q_okt_rows(const double* d_W, const double* d_A, const double
     Ctx x;
     const bwla_status_t s = open_ctx(x, n, m, n1, n2, k, d_ws, ws_bytes, stream);
     if (s != BWLA_OK) return s;
-    okt(x, d_W, d_A, d_Bt, d_R1, d_R2, d_X, d_ybar);
+    rotated(x, d_W, d_A, d_Bt, d_R1, d_R2);
+    QRows r = row_steps(0, nullptr, nullptr, nullptr);
+    r.X = d_X; r.ybar = d_ybar;
+    rows(x, r);
     return finish(x);
+}
+
+// the steps of centered rows that the caller holds
+static hipError_t rows_of(const double* d_X, int64_t n, int64_t m, unsigned steps, double s2_min, const double* d_c,
+                          const double* d_s2, double* part, void* stream) {
+    QRows r{};
+    r.Y = d_X; r.m = (int)m; r.steps = steps; r.c = const_cast<double*>(d_c); r.s2 = const_cast<double*>(d_s2);
+    r.s2_min = s2_min; r.part = part;
+    return bwla_q_launch_rows(r, (int)n, static_cast<hipStream_t>(stream));
 }
 
 static bwla_status_t check_rows(const double* d_X, int64_t n, int64_t m, const double* d_c, const double* d_s2) {
@@ -389,16 +408,14 @@ bwla_status_t bwla_q_init_theta(const double* d_X, int64_t n, int64_t m, double 
                                 void* stream) {
     const bwla_status_t s = check_rows(d_X, n, m, d_c, d_s2);
     if (s != BWLA_OK) return s;
-    return bwla_q_launch_init_theta(d_X, (int)n, (int)m, s2_min, d_c, d_s2, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? BWLA_OK : BWLA_ERR_HIP;
+    return rows_of(d_X, n, m, QROWS_INIT, s2_min, d_c, d_s2, nullptr, stream) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
 bwla_status_t bwla_q_em_step(const double* d_X, int64_t n, int64_t m, double s2_min, double* d_c, double* d_s2,
                              void* stream) {
     const bwla_status_t s = check_rows(d_X, n, m, d_c, d_s2);
     if (s != BWLA_OK) return s;
-    return bwla_q_launch_em(d_X, (int)n, (int)m, s2_min, d_c, d_s2, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? BWLA_OK : BWLA_ERR_HIP;
+    return rows_of(d_X, n, m, QROWS_EM, s2_min, d_c, d_s2, nullptr, stream) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
 bwla_status_t bwla_q_gmm_nll(const double* d_X, int64_t n, int64_t m, const double* d_c, const double* d_s2,
@@ -408,8 +425,11 @@ bwla_status_t bwla_q_gmm_nll(const double* d_X, int64_t n, int64_t m, const doub
     if (!d_out || !d_ws) return BWLA_ERR_NULL;
     if (!aligned16(d_ws)) return BWLA_ERR_ALIGN;
     if (ws_bytes < (size_t)n * sizeof(double)) return BWLA_ERR_BUFSIZE;
-    return bwla_q_launch_nll(d_X, (int)n, (int)m, d_c, d_s2, static_cast<double*>(d_ws), d_out,
-                             static_cast<hipStream_t>(stream)) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
+    double* part = static_cast<double*>(d_ws);
+    if (rows_of(d_X, n, m, QROWS_NLL, 0.0, d_c, d_s2, part, stream) != hipSuccess) return BWLA_ERR_HIP;
+    QRowsFinish f{};
+    f.part = part; f.nll = d_out; f.scale = 1.0 / ((double)n * (double)m); f.n = (int)n;
+    return bwla_q_launch_rows_finish(f, static_cast<hipStream_t>(stream)) == hipSuccess ? BWLA_OK : BWLA_ERR_HIP;
 }
 
 bwla_status_t bwla_q_procrustes(int32_t which, const double* d_Wres, const double* d_R1, const double* d_R2,
@@ -466,8 +486,12 @@ bwla_status_t bwla_q_psp_step(const double* d_W, double* d_A, double* d_Bt, int3
     Ctx x;
     const bwla_status_t s = open_ctx(x, n, m, n1, n2, k, d_ws, ws_bytes, stream);
     if (s != BWLA_OK) return s;
-    okt(x, d_W, d_A, d_Bt, d_R1, d_R2, x.d(x.P.big[4]), nullptr);
-    psp(x, d_A, d_Bt, d_R1, d_R2, d_c, d_s2, mu, iters, tol, x.d(x.P.lam));
+    rotated(x, d_W, d_A, d_Bt, d_R1, d_R2);
+    rows(x, row_steps(QROWS_GRAD, d_c, d_s2, x.d(x.P.big[3])));
+    QRowsFinish f{};
+    f.s2 = d_s2; f.fac = x.d(x.P.scal); f.mu = mu; f.scale = 1.0 / ((double)n * (double)m); f.n = (int)n;
+    x.ck(bwla_q_launch_rows_finish(f, x.st));
+    psp(x, d_A, d_Bt, d_R1, d_R2, iters, tol, x.d(x.P.lam));
     return finish(x);
 }
 
@@ -487,17 +511,28 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
     if (s != BWLA_OK) return s;
     const QPlan& P = x.P;
     const size_t nm = (size_t)P.n * P.m;
-    double *W = x.d(P.big[0]), *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *X = x.d(P.big[4]);
-    double *R1 = x.d(P.R1), *R2 = x.d(P.R2), *A = x.d(P.A), *Bt = x.d(P.Bt), *ybar = x.d(P.ybar);
+    double *W = x.d(P.big[0]), *half = x.d(P.big[2]), *Y = x.d(P.big[3]), *T = x.d(P.big[4]);
+    double *R1 = x.d(P.R1), *R2 = x.d(P.R2), *A = x.d(P.A), *Bt = x.d(P.Bt);
     double* c = d_c ? d_c : x.d(P.c);
     double* s2 = d_s2 ? d_s2 : x.d(P.s2);
     double* lam = x.d(P.lam);
-    double* rowpart = x.d(P.rowpart);
-    double* hist_sink = x.d(P.scal) + 8;
-    int hi = 0;
-    auto record = [&]() {               // L_GMM of the centered rows in X
-        x.ck(bwla_q_launch_nll(X, P.n, P.m, c, s2, rowpart, d_hist ? d_hist + hi : hist_sink, x.st));
-        ++hi;
+    // The steps between two rotations run in one launch over the rows.  Behind it: L_GMM before its EM update to
+    // d_hist[at], behind it to the next entry (and the one after, when there is no proximal step between), the step's factor
+    auto row_work = [&](unsigned steps, double* out, int at, bool again, bool factor, float* f32) {
+        QRows r = row_steps(steps | (d_hist && at >= 0 ? (unsigned)QROWS_NLL : 0u) |
+                            (d_hist && (steps & QROWS_EM) ? (unsigned)QROWS_NLL_EM : 0u), c, s2, out);
+        r.s2_min = s2_min; r.f32 = f32;
+        rows(x, r);
+        if (!(r.steps & (QROWS_NLL | QROWS_NLL_EM)) && !factor) return;
+        QRowsFinish f{};
+        if (r.steps & QROWS_NLL) { f.part = x.d(P.rowpart); f.nll = d_hist + at; }
+        if (r.steps & QROWS_NLL_EM) {
+            f.part_em = x.d(P.rowpart2); f.nll_em = d_hist + at + 1;
+            if (again) f.nll_again = d_hist + at + 2;
+        }
+        if (factor) { f.s2 = s2; f.fac = x.d(P.scal); f.mu = mu; }
+        f.scale = 1.0 / ((double)P.n * P.m); f.n = P.n;
+        x.ck(bwla_q_launch_rows_finish(f, x.st));
     };
     x.ck(bwla_q_launch_convert_f32_f64(d_W, W, nm, x.st));
     if (init_identity) {
@@ -512,40 +547,36 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
         x.ck(bwla_q_launch_fill_value(Bt, (size_t)P.m * k, 0.0, x.st));
         x.ck(bwla_q_launch_fill_value(lam, k, 0.0, x.st));
     }
-    // From here on, at the top of a round, big[2..4] and ybar belong to the current (M, R1, R2): half =
-    // (W - M) R2, Y = (W - M) R, X = Y H.  What a step reads is made once and not again by the step behind
-    // it: the proximal step takes X, the update of R1 half and Y, and R2's half again, as R2 is still the
-    // old one (every step on its own rotated all rows anew: 7 rotations a round, now 3.5, some 200 us each
-    // half on 11008 x 4096).
+    // From here on, at the top of a round, big[2] and big[3] belong to the current (M, R1, R2): half = (W - M) R2,
+    // Y = (W - M) R.  What a step reads is made once and not again by the step behind it: the update of R1 takes half
+    // and Y, and R2's half again, as R2 is still the old one (every step on its own rotated all rows anew: 7 rotations a
+    // round, now 3.5, some 200 us each half on 11008 x 4096).
     const double* Wres = W;                                               // M = 0
     rotate_rows(x, W, R1, R2, false, half, Y);
-    x.ck(bwla_q_launch_center(Y, X, ybar, P.n, P.m, x.st));
-    x.ck(bwla_q_launch_init_theta(X, P.n, P.m, s2_min, c, s2, x.st));
-    record();
     for (int t = 0; t < t_outer; ++t) {
-        x.ck(bwla_q_launch_em(X, P.n, P.m, s2_min, c, s2, x.st));
-        record();
+        const unsigned em = QROWS_EM | (t == 0 ? (unsigned)QROWS_INIT : 0u);
         if (k > 0) {
-            psp(x, A, Bt, R1, R2, c, s2, mu, svd_iters, svd_tol, lam);
-            Wres = okt(x, W, A, Bt, R1, R2, X, ybar);
+            row_work(em | QROWS_GRAD, Y, 3 * t, false, true, nullptr);
+            psp(x, A, Bt, R1, R2, svd_iters, svd_tol, lam);
+            Wres = rotated(x, W, A, Bt, R1, R2);
+            row_work(QROWS_TARGETS, T, 3 * t + 2, false, false, nullptr);
+        } else {
+            row_work(em | QROWS_TARGETS, T, 3 * t, true, false, nullptr);
         }
-        record();
-        procrustes_held(x, 1, Wres, R1, c, s2, R1);
+        procrustes_held(x, 1, Wres, R1, R1);
         rotate_left(x, R1, half, false, Y);
-        x.ck(bwla_q_launch_center(Y, nullptr, ybar, P.n, P.m, x.st));
-        procrustes_held(x, 2, Wres, R1, c, s2, R2);
+        row_work(QROWS_TARGETS, T, -1, false, false, nullptr);
+        procrustes_held(x, 2, Wres, R1, R2);
         if (k > 0 || t + 1 == t_outer) {
             // half = R1^T (W - M) of the update above: one product makes Y.  The next round's update of R1
-            // needs (W - M) R2 there, which the proximal step's okt makes when there is one
+            // needs (W - M) R2 there, which the proximal step makes when there is one
             gemm(x, qgemm_plain(half, R2, Y, P.n * P.n1, P.n2, P.n2));
         } else {
             rotate_rows(x, Wres, R1, R2, false, half, Y);
         }
-        x.ck(bwla_q_launch_center(Y, X, ybar, P.n, P.m, x.st));
-        record();
     }
-    // Y = (W - M)(R1 (x) R2) at the final factors
-    x.ck(bwla_q_launch_convert_f64_f32(Y, d_W_rot, nm, x.st));
+    // Y = (W - M)(R1 (x) R2) at the final factors, and L_GMM of it
+    row_work(t_outer == 0 ? (unsigned)QROWS_INIT : 0u, nullptr, 3 * t_outer, false, false, d_W_rot);
     x.ck(bwla_q_launch_convert_f64_f32(R1, d_R1, (size_t)n1 * n1, x.st));
     x.ck(bwla_q_launch_convert_f64_f32(R2, d_R2, (size_t)n2 * n2, x.st));
     if (k > 0) {

@@ -46,21 +46,30 @@ inline size_t bwla_q_gemm_partial_bytes(int M, int N, int batch, int ksplit) {
 // ---------------------------------------------------------------- row kernels (quantizer_rows.hip)
 hipError_t bwla_q_launch_convert_f32_f64(const float* src, double* dst, size_t count, hipStream_t st);
 hipError_t bwla_q_launch_convert_f64_f32(const double* src, float* dst, size_t count, hipStream_t st);
-// X = Y - row means (X may be NULL: only the means), ybar = the means (may be NULL)
-hipError_t bwla_q_launch_center(const double* Y, double* X, double* ybar, int n, int m, hipStream_t st);
-hipError_t bwla_q_launch_init_theta(const double* X, int n, int m, double s2_min, double* c, double* s2, hipStream_t st);
-hipError_t bwla_q_launch_em(const double* X, int n, int m, double s2_min, double* c, double* s2, hipStream_t st);
-// out[0] = L_GMM; row_part: n doubles of scratch
-hipError_t bwla_q_launch_nll(const double* X, int n, int m, const double* c, const double* s2, double* row_part,
-                             double* out, hipStream_t st);
-// T = lambda_i * (H m_i + ybar_i 1), m_ij = c_i tanh(c_i x_ij / s_i^2), x = y - ybar
-hipError_t bwla_q_launch_targets(const double* Y, const double* ybar, const double* c, const double* s2, int n, int m,
-                                 double* T, hipStream_t st);
-// fac[0] = mu > 0 ? 1 / (n m mu) : min_i s2_i   (the factor that turns (x - m) lambda into -(grad_X) / mu)
-hipError_t bwla_q_launch_prox_factor(const double* s2, int n, int m, double mu, double* fac, hipStream_t st);
-// GX = fac * H[(x - m) lambda]
-hipError_t bwla_q_launch_gradx(const double* X, const double* c, const double* s2, const double* fac, int n, int m,
-                               double* GX, hipStream_t st);
+// The steps of one launch over the rows of an n x m array, in this order (all on x = y, or y - its mean with CENTER):
+//   CENTER    ybar = the row means, X = the centered rows (each may be NULL)
+//   INIT      c, s2 started from x (otherwise read, where a step needs them)
+//   NLL       part[i] = the row's share of -n m L_GMM at (c, s2)
+//   EM        one update of c, s2
+//   NLL_EM    part_em[i] = the same after it
+//   GRAD      out = H[(x - m) / s2], m = c tanh(c x / s2)
+//   TARGETS   out = (H m + ybar 1) / s2
+// f32 (may be NULL) gets y itself.  out may be Y.
+enum : unsigned { QROWS_CENTER = 1, QROWS_INIT = 2, QROWS_NLL = 4, QROWS_EM = 8, QROWS_NLL_EM = 16, QROWS_GRAD = 32,
+                  QROWS_TARGETS = 64 };
+struct QRows {
+    const double* Y; int m; unsigned steps;
+    double* c; double* s2; double s2_min;
+    double* X; double* ybar; double* part; double* part_em; double* out; float* f32;
+};
+hipError_t bwla_q_launch_rows(const QRows& g, int n, hipStream_t st);
+// nll = scale sum(part), nll_em (and nll_again) = scale sum(part_em), and the proximal step's factor to fac[0], with
+// fac[1] = fac[2] = 0, as QGemm::coef takes it (scale = 1 / (n m)); part, part_em, nll_again, fac may be NULL
+struct QRowsFinish {
+    const double* part; const double* part_em; double* nll; double* nll_em; double* nll_again;
+    const double* s2; double* fac; double mu, scale; int n;
+};
+hipError_t bwla_q_launch_rows_finish(const QRowsFinish& f, hipStream_t st);
 // Q[i] = uniform in [-1, 1) from a counter-based hash of (seed, i)
 hipError_t bwla_q_launch_fill_hash(double* Q, size_t count, uint32_t seed, hipStream_t st);
 hipError_t bwla_q_launch_fill_identity(double* R, int n, hipStream_t st);

@@ -1,29 +1,33 @@
 // Row-wise steps of the offline quantizer (paper App. A.1 Algorithm 2; App. A.2.2 for the mixture,
 // its EM updates and the MM targets; App. A.2.3 for the gradient behind the proximal step), fp64.
-// One workgroup of 256 threads per weight row; a row is read from global memory once per pass
-// (it stays in L2 between the passes of one kernel).  Sums are taken per thread in a fixed order,
-// then over the wavefront by butterflies and over the four wavefronts in wavefront order, so that a
-// result does not depend on the launch.
+// One workgroup per weight row, and one kernel for all of them: a launch runs the steps that follow one another
+// on the same row -- center, start or update the mixture, its likelihood before and after, then the targets or the
+// gradient -- with the row in registers, so that a row is read once and written once however many steps there are.
+// Sums are taken per thread in a fixed order, then over the wavefront by butterflies and over the wavefronts in
+// wavefront order, so that a result does not depend on the launch.
 #include "bwla_internal.h"
 #include "quantizer_internal.h"
 
 namespace {
 
 constexpr int RT = 256;
-constexpr int KEEP_M = 10240;
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
 }
-// sum over the workgroup, returned to every thread; `sh` holds 4 doubles
+// sum over the workgroup of T threads, returned to every thread; `sh` holds T / 64 doubles
+template <int T = RT>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
     v = wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < T / 64; i += 4) s += (sh[i] + sh[i + 1]) + (sh[i + 2] + sh[i + 3]);
+    return s;
 }
 
 __global__ void convert_f32_f64_kernel(const float* src, double* dst, size_t count) {
@@ -33,165 +37,176 @@ __global__ void convert_f64_f32_kernel(const double* src, float* dst, size_t cou
     for (size_t e = (size_t)blockIdx.x * RT + threadIdx.x; e < count; e += (size_t)gridDim.x * RT) dst[e] = (float)src[e];
 }
 
-// X = Y H: the row mean taken out (Sec. 3.1, "Transformation Objectives")
-__global__ __launch_bounds__(RT) void center_kernel(const double* Y, double* X, double* ybar, int m) {
-    __shared__ double sh[4];
-    const double* y = Y + (size_t)blockIdx.x * m;
-    double* x = X + (size_t)blockIdx.x * m;
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += y[j];
-    const double mean = block_sum(s, sh) / m;
-    if (X)
-        for (int j = threadIdx.x; j < m; j += RT) x[j] = y[j] - mean;
-    if (ybar && threadIdx.x == 0) ybar[blockIdx.x] = mean;
+// exp(-2 |c x| / s^2) and 2 r^+ - 1 = tanh(c x / s^2) out of it: the two densities' ratio is exp(2 c x / s^2)
+// (App. A.2.2, E step).  The likelihood takes the former and everything else the latter, so one exponential an entry
+// and state of the mixture serves all steps.  The quotient is right to 1e-16, the rounding of what it is added to.
+__device__ __forceinline__ double mix_exp(double x, double c, double inv) { return exp(-2.0 * fabs(c * x * inv)); }
+__device__ __forceinline__ double mix_resp(double e, double x, double c) {
+    const double d = 1.0 + e;                               // in [1, 2]
+    double y = __builtin_amdgcn_rcp(d);                     // 2^-20 or better, and two Newton steps
+    y = fma(fma(-d, y, 1.0), y, y);
+    y = fma(fma(-d, y, 1.0), y, y);
+    const double t = (1.0 - e) * y;
+    return c * x < 0.0 ? -t : t;
 }
 
-// Algorithm 2's empirical start: c = mean |x|, s^2 = mean (|x| - c)^2, floored
-__global__ __launch_bounds__(RT) void init_theta_kernel(const double* X, int m, double s2_min, double* c, double* s2) {
-    __shared__ double sh[4];
-    const double* x = X + (size_t)blockIdx.x * m;
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += fabs(x[j]);
-    const double ci = block_sum(s, sh) / m;
-    double q = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double d = fabs(x[j]) - ci;
-        q += d * d;
-    }
-    const double v = block_sum(q, sh) / m;
-    if (threadIdx.x == 0) {
-        c[blockIdx.x] = ci;
-        s2[blockIdx.x] = fmax(v, s2_min);
-    }
-}
-
-// 2 r^+ - 1 = tanh(c x / s^2): the two densities' ratio is exp(2 c x / s^2) (App. A.2.2, E step).
-// The hyperbolic tangent is what the kernels that use it are bound by (two passes over a row, each with
-// its own tanh, took 460 us on 11008 x 4096 where the row's two reads take some 100).  Rows of up to
-// KEEP_M columns therefore keep the first pass's values in LDS (80 KiB at most: two workgroups a CU stay
-// resident); longer rows compute them twice, as a workgroup would otherwise have a CU to itself.
-__device__ __forceinline__ double signed_resp(double x, double c, double inv_s2) { return tanh(c * x * inv_s2); }
-
-// one EM update of a row's mixture (App. A.2.2): c from the responsibilities at the old parameters,
-// then s^2 with the new c.  `keep` (dynamic LDS, m doubles when KEEP) holds the responsibilities between
-// the two sums.
-template <bool KEEP>
-__global__ __launch_bounds__(RT) void em_kernel(const double* X, int m, double s2_min, double* c, double* s2) {
-    extern __shared__ double keep[];
-    __shared__ double sh[4];
-    const double* x = X + (size_t)blockIdx.x * m;
-    const double c0 = c[blockIdx.x], inv = 1.0 / s2[blockIdx.x];
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double t = signed_resp(x[j], c0, inv);
-        if (KEEP) keep[j] = t;                              // read back by this thread only
-        s += t * x[j];
-    }
-    const double c1 = block_sum(s, sh) / m;
-    double q = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double r = 0.5 * (1.0 + (KEEP ? keep[j] : signed_resp(x[j], c0, inv)));
-        const double dp = x[j] - c1, dm = x[j] + c1;
-        q += r * dp * dp + (1.0 - r) * dm * dm;
-    }
-    const double v = block_sum(q, sh) / m;
-    if (threadIdx.x == 0) {
-        c[blockIdx.x] = c1;
-        s2[blockIdx.x] = fmax(v, s2_min);
-    }
-}
-
-// per-row sums of -log[ 1/2 phi(x; c, s^2) + 1/2 phi(x; -c, s^2) ], in log space
-__global__ __launch_bounds__(RT) void nll_rows_kernel(const double* X, int m, const double* c, const double* s2, double* part) {
-    __shared__ double sh[4];
-    const double* x = X + (size_t)blockIdx.x * m;
-    const double ci = c[blockIdx.x], v = s2[blockIdx.x];
-    const double lognorm = -0.5 * log(2.0 * 3.14159265358979323846 * v), h = 0.5 / v;
-    // sum of max(lp, lm) + log1p(exp(-|lp - lm|)) + log(1/2): the logarithms of up to sixteen factors 1 + e are
-    // taken as one of their product (one special function per entry is left; 243 us with both on 11008 x 4096).
-    // What is carried is the product less one, q <- q + e + q e: a sum of terms that are not negative, so that
-    // an e below the rounding of 1 + e counts as it does in log1p(e).
-    double s = 0.0;
-    for (int j0 = threadIdx.x; j0 < m; j0 += 16 * RT) {
-        double q = 0.0;
-        for (int j = j0; j < m && j < j0 + 16 * RT; j += RT) {
-            const double dp = x[j] - ci, dm = x[j] + ci;
-            const double lp = lognorm - dp * dp * h, lm = lognorm - dm * dm * h;
-            const double hi = fmax(lp, lm), lo = fmin(lp, lm);
-            s -= hi + log(0.5);
-            const double e = exp(lo - hi);
-            q = fma(q, e, q + e);
+// A row of T threads with E entries each in registers (thread t holds entries t, t + T, ...), or, with E = 0, a row of any
+// length that is read again by every step and whose responsibilities are computed again.  What bounds it at 11008 x 4096:
+// the first launch of a round (start, two likelihoods, update, gradient) the vector units, two exponentials an entry and
+// some sums; the others memory (720 MB at 4.7 TB/s).  284, 152, 132 and 163 us a round; with a launch a step
+// (13, responsibilities by tanh kept in LDS between two sums) 2310, and 85 for the result in fp32.
+template <int T, int E>
+__global__ __launch_bounds__(T) void rows_kernel(QRows g) {
+    __shared__ double sh[T / 64];
+    const int m = g.m, t = threadIdx.x;
+    const size_t row = blockIdx.x;
+    const double* y = g.Y + row * m;
+    double x[E ? E : 1], k[E ? E : 1];                      // the centered row; what a step keeps of it
+    double mean = 0.0;
+    // f(x_j, its slot, j) for this thread's entries
+    auto each = [&](auto f) {
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if (t + u * T < m) f(x[u], u, t + u * T);
+        } else {
+            int u = 0;
+            for (int j = t; j < m; j += T, ++u) f(y[j] - mean, u, j);
         }
-        s -= log1p(q);
+    };
+    auto sum = [&](auto f) {
+        double s = 0.0;
+        each([&](double v, int u, int j) { s += f(v, u, j); });
+        return block_sum<T>(s, sh);
+    };
+    if constexpr (E > 0) {
+#pragma unroll
+        for (int u = 0; u < E; ++u) x[u] = t + u * T < m ? y[t + u * T] : 0.0;
     }
-    const double tot = block_sum(s, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
-__global__ __launch_bounds__(RT) void sum_scale_kernel(const double* part, int n, double scale, double* out) {
-    __shared__ double sh[4];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += RT) s += part[i];
-    const double tot = block_sum(s, sh);
-    if (threadIdx.x == 0) out[0] = tot * scale;
+    if (g.f32) each([&](double v, int, int j) { g.f32[row * m + j] = (float)v; });
+    if (g.steps & QROWS_CENTER) {                           // the row mean taken out (Sec. 3.1, "Transformation Objectives")
+        mean = sum([](double v, int, int) { return v; }) / m;
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int u = 0; u < E; ++u) x[u] -= mean;
+        }
+        if (g.ybar && t == 0) g.ybar[row] = mean;
+        if (g.X) each([&](double v, int, int j) { g.X[row * m + j] = v; });
+    }
+    if (!(g.steps & ~QROWS_CENTER)) return;
+    double c = 0.0, v = 1.0;
+    if (g.steps & QROWS_INIT) {                             // Algorithm 2's empirical start: c = mean |x|, s^2 = mean (|x| - c)^2, floored
+        c = sum([](double w, int, int) { return fabs(w); }) / m;
+        v = fmax(sum([&](double w, int, int) { const double d = fabs(w) - c; return d * d; }) / m, g.s2_min);
+    } else {
+        c = g.c[row];
+        v = g.s2[row];
+    }
+    double inv = 1.0 / v;
+    auto resp = [&](double w, int u) { return E > 0 ? k[E > 0 ? u : 0] : mix_resp(mix_exp(w, c, inv), w, c); };
+    // the responsibilities of the state (c, v) into k, and its likelihood: minus the row's sum of
+    // log[ 1/2 phi(x; c, s^2) + 1/2 phi(x; -c, s^2) ] to part[row]
+    auto state = [&](bool nll, double* part) {
+        // sum of max(lp, lm) + log1p(exp(-|lp - lm|)) + log(1/2): the logarithms of up to sixteen factors 1 + e are taken
+        // as one of their product.  What is carried is the product less one, q <- q + e + q e: a sum of terms that are
+        // not negative, so that an e below the rounding of 1 + e counts as it does in log1p(e).
+        double q = 0.0, s = 0.0, d2 = 0.0;
+        int count = 0;
+        const double ac = fabs(c);
+        each([&](double w, int u, int) {
+            const double e = mix_exp(w, c, inv);
+            if (E > 0) k[E > 0 ? u : 0] = mix_resp(e, w, c);
+            if (nll) {
+                const double d = fabs(w) - ac;
+                d2 = fma(d, d, d2);
+                q = fma(q, e, q + e);
+                ++count;
+                if (E == 0 && (u & 15) == 15) {
+                    s -= log1p(q);
+                    q = 0.0;
+                }
+            }
+        });
+        if (nll) {
+            s -= log1p(q);
+            s += 0.5 * inv * d2 + count * (0.5 * log(2.0 * 3.14159265358979323846 * v) + log(2.0));
+            const double tot = block_sum<T>(s, sh);
+            if (t == 0) part[row] = tot;
+        }
+    };
+    if ((E > 0 && (g.steps & (QROWS_EM | QROWS_GRAD | QROWS_TARGETS))) || (g.steps & QROWS_NLL))
+        state(g.steps & QROWS_NLL, g.part);
+    if (g.steps & QROWS_EM) {
+        // one EM update (App. A.2.2): c from the responsibilities at the old parameters, then s^2 with the new c
+        const double c1 = sum([&](double w, int u, int) { return resp(w, u) * w; }) / m;
+        const double v1 = sum([&](double w, int u, int) {
+            const double r = 0.5 * (1.0 + resp(w, u)), dp = w - c1, dm = w + c1;
+            return r * dp * dp + (1.0 - r) * dm * dm;
+        }) / m;
+        c = c1;
+        v = fmax(v1, g.s2_min);
+        inv = 1.0 / v;
+        if (g.steps & (QROWS_NLL_EM | QROWS_GRAD | QROWS_TARGETS))
+            if (E > 0 || (g.steps & QROWS_NLL_EM)) state(g.steps & QROWS_NLL_EM, g.part_em);
+    }
+    if ((g.steps & (QROWS_INIT | QROWS_EM)) && t == 0) {
+        g.c[row] = c;
+        g.s2[row] = v;
+    }
+    if (g.steps & (QROWS_GRAD | QROWS_TARGETS)) {
+        // gradient: H[(x - m) lambda] with m = (2 r - 1) c, lambda = 1 / s^2: minus the gradient of L_GMM in the centered
+        // coordinates, times -n m (App. A.2.2 for d L / d x_ij = (x_ij - m_ij) / (n m s_i^2); App. A.2.3 for the adjoint's H).
+        // targets, on the uncentered rows (App. A.2.2, "MM Surrogate"): H m + ybar 1 (the concave part of the centered
+        // objective majorized by its tangent), times lambda, the weight of the row in the Procrustes matrices
+        const bool grad = g.steps & QROWS_GRAD;
+        auto value = [&](double w, int u) {
+            const double r = c * resp(w, u);
+            return grad ? (w - r) * inv : r;
+        };
+        const double bar = sum([&](double w, int u, int) {
+            const double o = value(w, u);
+            if (E > 0) k[E > 0 ? u : 0] = o;
+            return o;
+        }) / m;
+        double* out = g.out + row * m;
+        each([&](double w, int u, int j) {
+            const double o = E > 0 ? k[E > 0 ? u : 0] : value(w, u);
+            out[j] = grad ? o - bar : inv * (o - bar + mean);
+        });
+    }
 }
 
-// MM targets on the uncentered rotated rows (App. A.2.2, "MM Surrogate"): m_ij = (2 r_ij - 1) c_i at
-// x = y - ybar; target H m_i + ybar_i 1 (the concave part of the centered objective majorized by its
-// tangent); stored times lambda_i = 1 / s_i^2, the weight of the row in the Procrustes matrices
-template <bool KEEP>
-__global__ __launch_bounds__(RT) void targets_kernel(const double* Y, const double* ybar, const double* c, const double* s2,
-                                                     int m, double* T) {
-    extern __shared__ double keep[];
-    __shared__ double sh[4];
-    const double* y = Y + (size_t)blockIdx.x * m;
-    double* tg = T + (size_t)blockIdx.x * m;
-    const double yb = ybar[blockIdx.x], ci = c[blockIdx.x], lam = 1.0 / s2[blockIdx.x];
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double t = ci * signed_resp(y[j] - yb, ci, lam);
-        if (KEEP) keep[j] = t;
-        s += t;
+// what a launch over rows leaves to one workgroup each: the scaled sums of its two likelihoods, and (block 2) the factor
+// that turns (x - m) lambda into minus the gradient over mu, fac[0] = mu > 0 ? 1 / (n m mu) : min_i s2_i, with zeros behind it
+__global__ __launch_bounds__(1024) void rows_finish_kernel(QRowsFinish f) {
+    __shared__ double sh[16];
+    const int t = threadIdx.x;
+    if (blockIdx.x < 2) {
+        const double* part = blockIdx.x == 0 ? f.part : f.part_em;
+        if (!part) return;
+        double s = 0.0;
+        for (int i = t; i < f.n; i += 1024) s += part[i];
+        const double tot = block_sum<1024>(s, sh) * f.scale;
+        if (t == 0) {
+            if (blockIdx.x == 0) f.nll[0] = tot;
+            else {
+                f.nll_em[0] = tot;
+                if (f.nll_again) f.nll_again[0] = tot;
+            }
+        }
+        return;
     }
-    const double mbar = block_sum(s, sh) / m;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double t = KEEP ? keep[j] : ci * signed_resp(y[j] - yb, ci, lam);
-        tg[j] = lam * (t - mbar + yb);
-    }
-}
-
-__global__ __launch_bounds__(RT) void prox_factor_kernel(const double* s2, int n, double nm, double mu, double* fac) {
-    __shared__ double sh[RT];
+    if (!f.fac) return;
     double v = 1.0e300;
-    for (int i = threadIdx.x; i < n; i += RT) v = fmin(v, s2[i]);
-    sh[threadIdx.x] = v;
+    for (int i = t; i < f.n; i += 1024) v = fmin(v, f.s2[i]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
+    if ((t & 63) == 0) sh[t >> 6] = v;
     __syncthreads();
-    for (int o = RT / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) fac[0] = mu > 0.0 ? 1.0 / (nm * mu) : sh[0];
-}
-
-// fac * H[(x - m) lambda]: minus the gradient of L_GMM in the centered coordinates, over mu
-// (App. A.2.2 for d L / d x_ij = (x_ij - m_ij) / (n m s_i^2); App. A.2.3 for the adjoint's H)
-template <bool KEEP>
-__global__ __launch_bounds__(RT) void gradx_kernel(const double* X, const double* c, const double* s2, const double* fac,
-                                                   int m, double* GX) {
-    extern __shared__ double keep[];
-    __shared__ double sh[4];
-    const double* x = X + (size_t)blockIdx.x * m;
-    double* gx = GX + (size_t)blockIdx.x * m;
-    const double ci = c[blockIdx.x], lam = 1.0 / s2[blockIdx.x], f = fac[0];
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double g = (x[j] - ci * signed_resp(x[j], ci, lam)) * lam;
-        if (KEEP) keep[j] = g;
-        s += g;
-    }
-    const double gbar = block_sum(s, sh) / m;
-    for (int j = threadIdx.x; j < m; j += RT) {
-        const double g = KEEP ? keep[j] : (x[j] - ci * signed_resp(x[j], ci, lam)) * lam;
-        gx[j] = f * (g - gbar);
+    if (t == 0) {
+        for (int i = 1; i < 16; ++i) v = fmin(v, sh[i]);
+        f.fac[0] = f.mu > 0.0 ? f.scale / f.mu : v;
+        f.fac[1] = f.fac[2] = 0.0;
     }
 }
 
@@ -293,20 +308,6 @@ __global__ __launch_bounds__(RT) void row_stats_kernel(const double* Y, int m, d
     }
 }
 
-// launches `kept` with a row of m doubles of LDS where that fits, else `again`
-template <typename Kern, typename... Args>
-hipError_t launch_rows(Kern kept, Kern again, int n, int m, hipStream_t st, Args... args) {
-    const size_t lds = (size_t)m * sizeof(double);
-    if (m <= KEEP_M) {
-        const hipError_t e = bwla_ensure_lds((const void*)kept, lds + 64);      // (+ the sums' static words)
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kept, dim3(n), dim3(RT), lds, st, args...);
-    } else {
-        hipLaunchKernelGGL(again, dim3(n), dim3(RT), 0, st, args...);
-    }
-    return hipGetLastError();
-}
-
 inline int flat_blocks(size_t count) {
     const size_t b = (count + RT - 1) / RT;
     return (int)(b < 4096 ? (b ? b : 1) : 4096);
@@ -322,36 +323,21 @@ hipError_t bwla_q_launch_convert_f64_f32(const double* src, float* dst, size_t c
     hipLaunchKernelGGL(convert_f64_f32_kernel, dim3(flat_blocks(count)), dim3(RT), 0, st, src, dst, count);
     return hipGetLastError();
 }
-hipError_t bwla_q_launch_center(const double* Y, double* X, double* ybar, int n, int m, hipStream_t st) {
-    hipLaunchKernelGGL(center_kernel, dim3(n), dim3(RT), 0, st, Y, X, ybar, m);
+hipError_t bwla_q_launch_rows(const QRows& g, int n, hipStream_t st) {
+    // the fewest threads whose registers hold the row
+    const auto launch = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(n), dim3(threads), 0, st, g);
+        return hipGetLastError();
+    };
+    if (g.m <= 1024) return launch(rows_kernel<256, 4>, 256);
+    if (g.m <= 4096) return launch(rows_kernel<256, 16>, 256);
+    if (g.m <= 8192) return launch(rows_kernel<512, 16>, 512);
+    if (g.m <= 16384) return launch(rows_kernel<1024, 16>, 1024);
+    return launch(rows_kernel<256, 0>, 256);
+}
+hipError_t bwla_q_launch_rows_finish(const QRowsFinish& f, hipStream_t st) {
+    hipLaunchKernelGGL(rows_finish_kernel, dim3(f.fac ? 3 : f.part_em ? 2 : 1), dim3(1024), 0, st, f);
     return hipGetLastError();
-}
-hipError_t bwla_q_launch_init_theta(const double* X, int n, int m, double s2_min, double* c, double* s2, hipStream_t st) {
-    hipLaunchKernelGGL(init_theta_kernel, dim3(n), dim3(RT), 0, st, X, m, s2_min, c, s2);
-    return hipGetLastError();
-}
-hipError_t bwla_q_launch_em(const double* X, int n, int m, double s2_min, double* c, double* s2, hipStream_t st) {
-    return launch_rows(em_kernel<true>, em_kernel<false>, n, m, st, X, m, s2_min, c, s2);
-}
-hipError_t bwla_q_launch_nll(const double* X, int n, int m, const double* c, const double* s2, double* row_part,
-                             double* out, hipStream_t st) {
-    hipLaunchKernelGGL(nll_rows_kernel, dim3(n), dim3(RT), 0, st, X, m, c, s2, row_part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sum_scale_kernel, dim3(1), dim3(RT), 0, st, row_part, n, 1.0 / ((double)n * m), out);
-    return hipGetLastError();
-}
-hipError_t bwla_q_launch_targets(const double* Y, const double* ybar, const double* c, const double* s2, int n, int m,
-                                 double* T, hipStream_t st) {
-    return launch_rows(targets_kernel<true>, targets_kernel<false>, n, m, st, Y, ybar, c, s2, m, T);
-}
-hipError_t bwla_q_launch_prox_factor(const double* s2, int n, int m, double mu, double* fac, hipStream_t st) {
-    hipLaunchKernelGGL(prox_factor_kernel, dim3(1), dim3(RT), 0, st, s2, n, (double)n * m, mu, fac);
-    return hipGetLastError();
-}
-hipError_t bwla_q_launch_gradx(const double* X, const double* c, const double* s2, const double* fac, int n, int m,
-                               double* GX, hipStream_t st) {
-    return launch_rows(gradx_kernel<true>, gradx_kernel<false>, n, m, st, X, c, s2, fac, m, GX);
 }
 hipError_t bwla_q_launch_fill_hash(double* Q, size_t count, uint32_t seed, hipStream_t st) {
     hipLaunchKernelGGL(fill_hash_kernel, dim3(flat_blocks(count)), dim3(RT), 0, st, Q, count, seed);
