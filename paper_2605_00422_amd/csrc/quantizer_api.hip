@@ -60,23 +60,10 @@ struct Ctx {
     void ck(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
 };
 
-// picks the split of the contraction: about 1024 workgroups, at least 256 of K per range, partial
-// products within the scratch reserved for them
 void gemm(Ctx& x, QGemm g, const int* skip = nullptr) {
-    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
-    long S = 1;
-    if (tiles < 512) {
-        S = 1024 / tiles;
-        if (S > g.K / 256) S = g.K / 256;
-        const long cap = (long)(PART_BYTES / ((size_t)g.batch * g.M * g.N * sizeof(double)));
-        if (S > cap) S = cap;
-        if (S > 256) S = 256;
-        if (S < 2) S = 1;
-    }
-    g.ksplit = (int)S;
     g.partials = x.d(x.P.partials);
     g.skip = skip;
-    x.ck(bwla_q_launch_gemm(g, x.st));
+    x.ck(bwla_q_launch_gemm(g, PART_BYTES, x.st));
 }
 
 // dst_i = R1^T src_i for every row as an n1 x n2 matrix (transposed: R1 src_i); src must differ from dst

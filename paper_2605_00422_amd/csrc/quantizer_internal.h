@@ -16,8 +16,8 @@
 //   B(k, j) = B[b * bsB + j * csB + (k / kdivB) * khB + (k % kdivB) * klB]
 //   C(i, j) = C[b * bsC + i * rsC + j]            (C0 is addressed like C)
 // kdiv = 0 stands for "no split of the contraction index" (k / kdiv = 0, k % kdiv = k).
-// ksplit > 1 cuts the contraction into ksplit ranges whose partial products go to `partials`
-// (ksplit x batch x M x N, dense) and are added in range order by a second launch, which also
+// The launch picks a kernel and cuts the contraction into ksplit ranges where tiles are few, whose partial products go
+// to `partials` (ksplit x batch x M x N, dense) and are added in range order by a second launch, which also
 // applies alpha, beta and C0: deterministic whatever the launch order.
 // `coef` (device, may be NULL): C = coef[0] A B + coef[1] C0 + coef[2] C1 instead, C1 addressed like C; C0 may be C.
 // `skip` (device, may be NULL): the launches return without touching C when *skip is neither 0 nor skip_but.
@@ -38,10 +38,7 @@ inline QGemm qgemm_plain(const double* A, const double* B, double* C, int M, int
     g.rsA = K; g.klA = 1; g.csB = 1; g.klB = N; g.rsC = N; g.alpha = 1.0; g.beta = 0.0; g.ksplit = 1;
     return g;
 }
-hipError_t bwla_q_launch_gemm(const QGemm& g, hipStream_t st);
-inline size_t bwla_q_gemm_partial_bytes(int M, int N, int batch, int ksplit) {
-    return ksplit > 1 ? (size_t)ksplit * batch * M * N * sizeof(double) : 0;
-}
+hipError_t bwla_q_launch_gemm(QGemm g, size_t partial_bytes, hipStream_t st);
 
 // ---------------------------------------------------------------- row kernels (quantizer_rows.hip)
 hipError_t bwla_q_launch_convert_f32_f64(const float* src, double* dst, size_t count, hipStream_t st);

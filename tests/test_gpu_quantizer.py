@@ -339,6 +339,20 @@ def test_truncate_rank_of_a_wide_spectrum(n, m, k, spread):
     assert np.max(np.abs(b.T @ b - np.eye(k))) < 1e-12
 
 
+# (contractions past 2048 with ragged ends, results of 24 to 80 columns in tiles of 64: the kernels that take operands
+# straight from memory, with and without a split of the contraction)
+@pytest.mark.parametrize("n,m,k", [(2055, 64, 8), (3001, 98, 40), (2500, 2306, 30)])
+def test_truncate_rank_of_long_contractions(n, m, k):
+    qb = _qb()
+    rng = np.random.default_rng(n)
+    Y = (rng.standard_normal((n, k)) * np.linspace(3.0, 1.0, k)) @ rng.standard_normal((k, m)) + 0.05 * rng.standard_normal((n, m))
+    A = torch.empty(n, k, dtype=torch.float64, device="cuda")
+    Bt = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(qb.workspace_size(n, m, 1, 1, k), dtype=torch.uint8, device="cuda")
+    qb.truncate_rank(_dev(Y), k, 40, 1e-14, A, Bt, None, ws)
+    assert _rel(A.cpu().numpy() @ Bt.cpu().numpy().T, Q.truncate_rank(Y, k)) < 1e-8
+
+
 @pytest.mark.parametrize("rank", [0, 1, 4])
 def test_truncate_rank_of_a_matrix_of_lower_rank(rank):
     """Fewer directions than are asked for: the matrix itself comes back, finite factors and zero singular values."""
