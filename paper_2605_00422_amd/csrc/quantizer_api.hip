@@ -100,10 +100,11 @@ const double* residual(Ctx& x, const double* W, const double* A, const double* B
     return Wres;
 }
 
-// the steps `r` of the rows of big[3] (steps that write an array get it from the caller)
+// the steps `r` of the rows of big[3], or of others (steps that write an array get it from the caller)
 void rows(Ctx& x, QRows r) {
     const QPlan& P = x.P;
-    r.Y = x.d(P.big[3]); r.m = P.m; r.part = x.d(P.rowpart); r.part_em = x.d(P.rowpart2);
+    if (!r.Y) r.Y = x.d(P.big[3]);
+    r.m = P.m; r.part = x.d(P.rowpart); r.part_em = x.d(P.rowpart2);
     x.ck(bwla_q_launch_rows(r, P.n, x.st));
 }
 QRows row_steps(unsigned steps, const double* c, const double* s2, double* out) {
@@ -121,16 +122,16 @@ const double* rotated(Ctx& x, const double* W, const double* A, const double* Bt
     return Wres;
 }
 
-// Above this size the polar factor comes from the Newton-Schulz iteration (a few dozen small GEMMs on
-// the matrix cores) instead of the one-workgroup Jacobi SVD, whose time grows with the cube of the size
-// (86: 4 ms, 128: 11 ms, 256: 81 ms).
+// Polar factors come from the Newton-Schulz iteration: up to BWLA_Q_POLAR_MAX in one workgroup, above as a few dozen
+// small products.  Up to this size, which the one-sided Jacobi SVD does in half a millisecond (86: 3 ms, 128: 11 ms), that
+// takes over where the iteration does not converge.
 constexpr int POLAR_JACOBI_MAX = 64;
 constexpr int POLAR_NS_PAIRS = 32;
 
 // polar factor of the jn-sized scratch matrix C (nn x nn) into R
 void polar(Ctx& x, int nn, double* R) {
     const QPlan& P = x.P;
-    if (nn > POLAR_JACOBI_MAX) {
+    if (nn > BWLA_Q_POLAR_MAX) {
         // X <- X (3 I - X^T X) / 2 from X = C / ||C||_F: singular values in (0, 1] rise to 1 (by 3/2 per
         // step while small, then quadratically), the singular vectors stay: X -> U V^T.  Steps come in
         // pairs so that X is back in the same buffer after each; before a pair X^T X is compared with I,
@@ -161,19 +162,22 @@ void polar(Ctx& x, int nn, double* R) {
         x.ck(hipMemcpyAsync(R, Xa, (size_t)nn * nn * sizeof(double), hipMemcpyDeviceToDevice, x.st));
         return;
     }
+    x.ck(bwla_q_launch_polar(x.d(P.C), nn, R, x.done(), nn > POLAR_JACOBI_MAX, x.st));
+    if (nn > POLAR_JACOBI_MAX) return;
     QJacobi j{};
     j.G = x.d(P.C); j.n = nn; j.pw = -1.0; j.sig = x.d(P.sig); j.Ws = x.d(P.Ws); j.Vs = x.d(P.Vs); j.work = x.d(P.jwork);
+    j.skip = x.done();
     x.ck(bwla_q_launch_jacobi(j, x.st));
     QGemm g = qgemm_plain(x.d(P.Ws), x.d(P.Vs), R, nn, nn, nn);
     g.rsA = 1; g.klA = nn;
-    gemm(x, g);
+    gemm(x, g, x.done());
 }
 
-// The Procrustes update of one factor, from what the scratch holds: big[2] = half = (W - M) R2, big[4] = the
+// The Procrustes update of one factor, from half = (W - M) R2 (which = 1), W - M and R1 (2), and big[4] = the
 // weighted targets of the rotated rows.  which = 2 leaves R1^T (W - M) in big[2].
-void procrustes_held(Ctx& x, int which, const double* Wres, const double* R1, double* Rnew) {
+void procrustes_held(Ctx& x, int which, const double* half, const double* Wres, const double* R1, double* Rnew) {
     const QPlan& P = x.P;
-    double *half = x.d(P.big[2]), *T = x.d(P.big[4]);
+    double *left = x.d(P.big[2]), *T = x.d(P.big[4]);
     QGemm g{};
     g.batch = 1; g.alpha = 1.0; g.beta = 0.0; g.C = x.d(P.C);
     if (which == 1) {
@@ -185,9 +189,9 @@ void procrustes_held(Ctx& x, int which, const double* Wres, const double* R1, do
         gemm(x, g);
         polar(x, P.n1, Rnew);
     } else {
-        // P_i = R1^T V_i into `half`, then C2[b][d] = sum_(i,c) P[(i,c)][b] (lambda_i T_i)[(i,c)][d]
-        rotate_left(x, R1, Wres, false, half);
-        g.A = half; g.B = T; g.M = P.n2; g.N = P.n2; g.K = P.n * P.n1;
+        // P_i = R1^T V_i, then C2[b][d] = sum_(i,c) P[(i,c)][b] (lambda_i T_i)[(i,c)][d]
+        rotate_left(x, R1, Wres, false, left);
+        g.A = left; g.B = T; g.M = P.n2; g.N = P.n2; g.K = P.n * P.n1;
         g.rsA = 1; g.klA = P.n2; g.csB = 1; g.klB = P.n2; g.rsC = P.n2;
         gemm(x, g);
         polar(x, P.n2, Rnew);
@@ -200,7 +204,7 @@ void procrustes(Ctx& x, int which, const double* Wres, const double* R1, const d
     const QPlan& P = x.P;
     rotate_rows(x, Wres, R1, R2, false, x.d(P.big[2]), x.d(P.big[3]));
     rows(x, row_steps(QROWS_TARGETS, c, s2, x.d(P.big[4])));
-    procrustes_held(x, which, Wres, R1, Rnew);
+    procrustes_held(x, which, x.d(P.big[2]), Wres, R1, Rnew);
 }
 
 // rank-k truncation of Y (n x m) into A2 (n x k), Bt2 (m x k); lam gets the k leading eigenvalues
@@ -272,16 +276,16 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
         return;
     }
     // Iterations: the block U <- S Q, or T_2(2 S / theta - 1) Q = (4 / theta) S U - 2 U - Q with
-    // U = (2 / theta) S Q - Q, then Q <- U orthonormalized in the basis of its Ritz vectors.  The first is plain, as
-    // theta is not known yet; its Q is the random start as it is (S Q spans the same whatever the basis of Q), whose
-    // singular values are at most some sqrt(m / 3) (1 + sqrt(p / m)), so that theta comes out below the p-th eigenvalue.
+    // U = (2 / theta) S Q - Q, then Q <- U orthonormalized in the basis of its Ritz vectors.  The first is S Q of the random
+    // start as it is (S Q spans the same whatever the basis of Q) and is orthonormalized without Ritz vectors, which are
+    // worth nothing yet (500 us of sweeps); theta is not known there, and the second is S^2 Q.
     //
     // `iters` counts products with S.  What two of them multiply sigma_k / sigma_{p+1} = q by is q^4 plain and
     // 8 q^4 - 8 q^2 + 1 filtered: the filter needs half as many for q up to 1.4, a quarter as the gap closes, and for any wider
     // gap 24 leave nothing to be done.  So beyond 24 half as many are made, which are fewer launches that return at
     // once too.  11008 x 4096, rank 32: 13 iterations of 560 us and 14 calls of the eigensolver became 11 products of 310
-    // in 6 iterations, 1400 empty launches some 500, the whole call 16.5 -> 13.1 ms; the truncation's error against a
-    // 64-bit SVD (1500 x 1024, gaps 1.02 to 2): 7e-9 to 9e-8 -> 4e-12 to 3e-9.
+    // in 6 iterations, 1400 empty launches some 500, the whole call 16.5 -> 13.1 ms (and 0.5 less without Ritz vectors of
+    // the first); the truncation's error against a 64-bit SVD (1500 x 1024, gaps 1.02 to 2): 7e-9 to 9e-8 -> 5e-12 to 3e-9.
     QRitz* ritz = reinterpret_cast<QRitz*>(x.ws + P.ritz);
     const int budget = iters <= 24 ? iters : (iters / 2 > 24 ? iters / 2 : 24);
     QJacobi turn = eig;
@@ -298,12 +302,13 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
         if (two) apply(Q2, Q2, ritz->second, Q2, Q);
         gram(Q2, m, done);
         turn.degree = two ? 2 : 1; turn.call = call;
-        turn.scale = used == 0 ? 1.0 / (sqrt(m / 3.0) * (1.05 + sqrt((double)p / m))) : 1.0;
+        turn.quick = used == 0;
+        turn.scale = used == 0 ? sqrt(3.0 / m) : 1.0;                   // (the start's columns are some sqrt(m / 3) long)
         x.ck(bwla_q_launch_jacobi(turn, x.st));
         times_vs(Q2, m, p, Q, done, call);
         used += two ? 2 : 1;
     }
-    // one more orthonormalization (the Gram matrix is close to I now), then Rayleigh-Ritz
+    // one more orthonormalization (of a block that hardly needs it any more), then Rayleigh-Ritz
     gram(Q, m, nullptr);
     eig.ortho = true;
     x.ck(bwla_q_launch_jacobi(eig, x.st));
@@ -316,16 +321,28 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
 }
 
 // M <- truncation of M - (1/mu) dL/dM; A, Bt in place.  big[3] holds the gradient's rows (QROWS_GRAD) at the rotated rows
-// of W - M, scal the factor that goes with them.  Leaves the scratch's big arrays stale.
-void psp(Ctx& x, double* A, double* Bt, const double* R1, const double* R2, int iters, double tol, double* lam) {
+// of W - M, scal the factor that goes with them.  identity: both factors are I; zero: M is 0.  Leaves the scratch's
+// big arrays stale.
+void psp(Ctx& x, double* A, double* Bt, const double* R1, const double* R2, bool identity, bool zero, int iters, double tol,
+         double* lam) {
     const QPlan& P = x.P;
-    double* Y = x.d(P.big[3]);
-    rotate_rows(x, Y, R1, R2, true, x.d(P.big[2]), Y, x.d(P.scal));       // back through R^T, sign folded in
-    QGemm g{};                                                            // Y <- Y + A Bt^T: the proximal point
-    g.A = A; g.B = Bt; g.C = Y; g.C0 = Y; g.M = P.n; g.N = P.m; g.K = P.k; g.batch = 1;
-    g.rsA = P.k; g.klA = 1; g.csB = P.k; g.klB = 1; g.rsC = P.m; g.alpha = 1.0; g.beta = 1.0;
-    gemm(x, g);
-    truncate(x, Y, iters, tol, x.d(P.A2), x.d(P.Bt2), lam);
+    double *Y = x.d(P.big[3]), *fac = x.d(P.scal);
+    if (identity && zero) {
+        // the proximal point is the factor times the gradient's rows as they stand: it goes into the truncation's result
+        truncate(x, Y, iters, tol, x.d(P.A2), x.d(P.Bt2), lam);
+        x.ck(bwla_q_launch_scale_by(x.d(P.A2), (size_t)P.n * P.k, fac, x.st));
+        x.ck(bwla_q_launch_scale_by(lam, P.k, fac, x.st));
+        x.ck(bwla_q_launch_scale_by(lam, P.k, fac, x.st));
+    } else {
+        rotate_rows(x, Y, R1, R2, true, x.d(P.big[2]), Y, fac);           // back through R^T, sign folded in
+        if (!zero) {
+            QGemm g{};                                                    // Y <- Y + A Bt^T: the proximal point
+            g.A = A; g.B = Bt; g.C = Y; g.C0 = Y; g.M = P.n; g.N = P.m; g.K = P.k; g.batch = 1;
+            g.rsA = P.k; g.klA = 1; g.csB = P.k; g.klB = 1; g.rsC = P.m; g.alpha = 1.0; g.beta = 1.0;
+            gemm(x, g);
+        }
+        truncate(x, Y, iters, tol, x.d(P.A2), x.d(P.Bt2), lam);
+    }
     x.ck(hipMemcpyAsync(A, x.d(P.A2), (size_t)P.n * P.k * sizeof(double), hipMemcpyDeviceToDevice, x.st));
     x.ck(hipMemcpyAsync(Bt, x.d(P.Bt2), (size_t)P.m * P.k * sizeof(double), hipMemcpyDeviceToDevice, x.st));
 }
@@ -478,7 +495,7 @@ bwla_status_t bwla_q_psp_step(const double* d_W, double* d_A, double* d_Bt, int3
     QRowsFinish f{};
     f.s2 = d_s2; f.fac = x.d(x.P.scal); f.mu = mu; f.scale = 1.0 / ((double)n * (double)m); f.n = (int)n;
     x.ck(bwla_q_launch_rows_finish(f, x.st));
-    psp(x, d_A, d_Bt, d_R1, d_R2, iters, tol, x.d(x.P.lam));
+    psp(x, d_A, d_Bt, d_R1, d_R2, false, false, iters, tol, x.d(x.P.lam));
     return finish(x);
 }
 
@@ -505,10 +522,10 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
     double* lam = x.d(P.lam);
     // The steps between two rotations run in one launch over the rows.  Behind it: L_GMM before its EM update to
     // d_hist[at], behind it to the next entry (and the one after, when there is no proximal step between), the step's factor
-    auto row_work = [&](unsigned steps, double* out, int at, bool again, bool factor, float* f32) {
+    auto row_work = [&](unsigned steps, double* out, int at, bool again, bool factor, float* f32, const double* of = nullptr) {
         QRows r = row_steps(steps | (d_hist && at >= 0 ? (unsigned)QROWS_NLL : 0u) |
                             (d_hist && (steps & QROWS_EM) ? (unsigned)QROWS_NLL_EM : 0u), c, s2, out);
-        r.s2_min = s2_min; r.f32 = f32;
+        r.Y = of; r.s2_min = s2_min; r.f32 = f32;
         rows(x, r);
         if (!(r.steps & (QROWS_NLL | QROWS_NLL_EM)) && !factor) return;
         QRowsFinish f{};
@@ -529,31 +546,33 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
         x.ck(bwla_q_launch_convert_f32_f64(d_R1, R1, (size_t)n1 * n1, x.st));
         x.ck(bwla_q_launch_convert_f32_f64(d_R2, R2, (size_t)n2 * n2, x.st));
     }
-    if (k > 0) {                        // M = 0
-        x.ck(bwla_q_launch_fill_value(A, (size_t)P.n * k, 0.0, x.st));
-        x.ck(bwla_q_launch_fill_value(Bt, (size_t)P.m * k, 0.0, x.st));
-        x.ck(bwla_q_launch_fill_value(lam, k, 0.0, x.st));
-    }
+    if (k > 0 && t_outer == 0) x.ck(bwla_q_launch_fill_value(lam, k, 0.0, x.st));       // M = 0, whatever A and Bt hold
     // From here on, at the top of a round, big[2] and big[3] belong to the current (M, R1, R2): half = (W - M) R2,
     // Y = (W - M) R.  What a step reads is made once and not again by the step behind it: the update of R1 takes half
     // and Y, and R2's half again, as R2 is still the old one (every step on its own rotated all rows anew: 7 rotations a
     // round, now 3.5, some 200 us each half on 11008 x 4096).
-    const double* Wres = W;                                               // M = 0
-    rotate_rows(x, W, R1, R2, false, half, Y);
+    // At the start M is 0, and with factors that start at the identity W is its own rotation.
+    const double* Wres = W;
+    const double *half_now = half, *Y_now = Y;
+    if (init_identity) half_now = Y_now = W;
+    else rotate_rows(x, W, R1, R2, false, half, Y);
     for (int t = 0; t < t_outer; ++t) {
         const unsigned em = QROWS_EM | (t == 0 ? (unsigned)QROWS_INIT : 0u);
         if (k > 0) {
-            row_work(em | QROWS_GRAD, Y, 3 * t, false, true, nullptr);
-            psp(x, A, Bt, R1, R2, svd_iters, svd_tol, lam);
+            row_work(em | QROWS_GRAD, Y, 3 * t, false, true, nullptr, Y_now);
+            psp(x, A, Bt, R1, R2, init_identity && t == 0, t == 0, svd_iters, svd_tol, lam);
             Wres = rotated(x, W, A, Bt, R1, R2);
             row_work(QROWS_TARGETS, T, 3 * t + 2, false, false, nullptr);
         } else {
-            row_work(em | QROWS_TARGETS, T, 3 * t, true, false, nullptr);
+            row_work(em | QROWS_TARGETS, T, 3 * t, true, false, nullptr, Y_now);
         }
-        procrustes_held(x, 1, Wres, R1, R1);
-        rotate_left(x, R1, half, false, Y);
+        if (k > 0) half_now = half;
+        procrustes_held(x, 1, half_now, Wres, R1, R1);
+        rotate_left(x, R1, half_now, false, Y);
+        half_now = half;
+        Y_now = Y;
         row_work(QROWS_TARGETS, T, -1, false, false, nullptr);
-        procrustes_held(x, 2, Wres, R1, R2);
+        procrustes_held(x, 2, nullptr, Wres, R1, R2);
         if (k > 0 || t + 1 == t_outer) {
             // half = R1^T (W - M) of the update above: one product makes Y.  The next round's update of R1
             // needs (W - M) R2 there, which the proximal step makes when there is one
@@ -563,7 +582,7 @@ bwla_status_t bwla_quantize_layer(const float* d_W, int64_t n, int64_t m, int32_
         }
     }
     // Y = (W - M)(R1 (x) R2) at the final factors, and L_GMM of it
-    row_work(t_outer == 0 ? (unsigned)QROWS_INIT : 0u, nullptr, 3 * t_outer, false, false, d_W_rot);
+    row_work(t_outer == 0 ? (unsigned)QROWS_INIT : 0u, nullptr, 3 * t_outer, false, false, d_W_rot, Y_now);
     x.ck(bwla_q_launch_convert_f64_f32(R1, d_R1, (size_t)n1 * n1, x.st));
     x.ck(bwla_q_launch_convert_f64_f32(R2, d_R2, (size_t)n2 * n2, x.st));
     if (k > 0) {

@@ -100,7 +100,9 @@ hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, 
 // sym: G is symmetric positive semidefinite (a Gram matrix G = B^T B); Ws is not available.  Up to 136 wide the
 // sweeps run in LDS, on the Cholesky factor G = L L^T, and the rotations are not accumulated; sig are eigenvalues:
 //   ortho         the columns of L^T are rotated into X S; Vs[j] = column j of L^-T X, so that B Vs^T has
-//                 orthonormal columns, which are the left singular vectors of B
+//                 orthonormal columns, which are the left singular vectors of B (without `it`, and for a B that is
+//                 orthonormal to 1e-8: some such columns, and no sig); quick: without sweeps, X = I, and of `it`
+//                 power alone
 //   otherwise     the columns of L; Vs[j] = eigenvector j (pw is not looked at)
 // Wider ones (without ortho) are rotated themselves, v_j being the normalized column j of G V.
 //
@@ -114,14 +116,20 @@ struct QJacobi {
     const double* G; int n; double pw;
     double* sig; double* Ws; double* Vs; double* work;
     const int* skip;
-    bool sym, ortho;
+    bool sym, ortho, quick;
     // With it: prev holds n doubles, the squared Ritz values of the iteration before, and is replaced; degree says
     // whether the block was multiplied by S (1) or filtered (2), scale what its Ritz values are to be multiplied
     // with in the first case.  From the third call on (call counts from 1) *done is set to `call` once the leading `lead` values have
     // settled: they moved by at most tol relative, or what the next iteration would move them by, a quotient of two
-    // movements smaller again, is below tol / 16.
+    // movements smaller again, is below tol / 4.
     QRitz* it; double* prev; int lead, degree, call; double tol, scale; int* done;
 };
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st);
 constexpr int BWLA_Q_JACOBI_LDS = 96;        // largest matrix whose two work arrays fit LDS
 constexpr int BWLA_Q_JACOBI_SYM_LDS = 136;   // ... whose one array does (sym)
+
+// ---------------------------------------------------------------- polar factors (quantizer_polar.hip)
+// R = U V^T of C = U S V^T (n x n, n <= BWLA_Q_POLAR_MAX) by the Newton-Schulz iteration in one workgroup; *done = 1, or 0
+// where it has not converged, which leaves R as it was (always: gives what it has).
+constexpr int BWLA_Q_POLAR_MAX = 96;         // two matrices of that size fit LDS
+hipError_t bwla_q_launch_polar(const double* C, int n, double* R, int* done, bool always, hipStream_t st);

@@ -12,8 +12,8 @@
 // n = 64 a group is one row of 16 lanes -- four pairs per wavefront, all pairs of a round at once,
 // the inner product summed on DPP row operations alone, and the tournament is one of blocks of four
 // columns whose sixteen pairs a wavefront takes in registers; larger matrices give a pair two rows (one
-// lane exchange more) or a whole wavefront (row sums on DPP, the four rows added through lane reads).  Sweeps end when one passes
-// without a rotation (every pair orthogonal to 1e-15 relative) or after 60.  At the end the column
+// lane exchange more) or a whole wavefront (row sums on DPP, the four rows added through lane reads).  Sweeps end when one has
+// found nothing but pairs so nearly orthogonal that it leaves them so to 1e-15, or after 60.  At the end the column
 // norms are the singular values, the normalized columns U, and V holds the right singular vectors.
 // Up to n = 96 both arrays (2 n^2 doubles, at most 144 KiB) live in LDS, where a round costs an LDS
 // round trip instead of an L2 one; larger matrices work in the caller's scratch (L2-resident).
@@ -78,23 +78,17 @@ __device__ __forceinline__ double jrcp(double x) {
 
 // Tangent t, cosine of the plane rotation that makes columns with squared norms al, be and inner product
 // ga orthogonal; the sine is cs * t.  t = sign(d) g / (|d| + sqrt(d^2 + g^2)) with d = be - al, g = 2 ga, both
-// scaled by the power of two of al + be, so that neither square overflows and one that underflows does not count.
-// Root, reciprocal and reciprocal root are the hardware's estimates brought to full precision by Newton steps: the
-// general forms' scaling and special cases, which nothing here needs, made this chain of dependent instructions most
-// of a round.  64 x 64 with V, whole call: 444 us as it is, 453 with z = d / g formed first (a reciprocal more in the
-// chain), 423 with the estimates alone, whose 2^-20 of the inner product waits for the next sweep; 712 with the general
-// forms and norms summed anew for every pair, on a card where the estimates alone took 452.
+// scaled by the power of two of al + be, so that neither square overflows and one that underflows does not count.  The
+// denominator is worked out in fp32: a tangent right to 2^-22 leaves that part of the inner product to the next sweep,
+// which has the square of it to find anyway, and a sweep of steps is a chain of dependent instructions.  The cosine, which
+// the columns' lengths hang on, is the hardware's estimate brought to full precision by Newton steps.
 __device__ __forceinline__ void jrotation(double al, double be, double ga, double& tt, double& cs) {
     const int e = __builtin_amdgcn_frexp_exp(al + be);
     const double d = ldexp(be - al, -e), g = ldexp(ga, 1 - e);
-    const double q = fma(g, g, d * d), e0 = __builtin_amdgcn_rsq(q);
-    double s = q * e0, h = 0.5 * e0;                        // sqrt(q), 1 / (2 sqrt(q))
-    const double r = fma(-h, s, 0.5);
-    s = fma(s, r, s);
-    h = fma(h, r, h);
-    s = fma(fma(-s, s, q), h, s);
-    tt = g * copysign(jrcp(fabs(d) + s), d);
-    const double w = fma(tt, tt, 1.0);                      // in [1, 2]
+    const float df = fabsf((float)d), gf = (float)g;
+    const float den = df + __builtin_amdgcn_sqrtf(fmaf(gf, gf, df * df));
+    tt = g * copysign((double)__builtin_amdgcn_rcpf(den), d);
+    const double w = fma(tt, tt, 1.0);                      // in [1, 2] (and some 2^-20)
     double y = __builtin_amdgcn_rsq(w);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {                           // y += y (1 - w y^2) / 2: full precision from 2^-20
@@ -102,6 +96,13 @@ __device__ __forceinline__ void jrotation(double al, double be, double ga, doubl
         y = fma(0.5 * y, e, y);
     }
     cs = y;
+}
+
+// Whether a rotation (tangent squared t2, inner product ga of columns with squared norms al, be before it) leaves work to a
+// further sweep.  A rotation changes the cosine between one of its columns and a third by t times that of the other, so a
+// sweep that finds none of either beyond 3e-9 leaves none beyond 64 x 1e-17, and needs no further one to say so.
+__device__ __forceinline__ bool jlarge(double t2, double ga, double al, double be) {
+    return t2 > 1.0e-17 || ga * ga > 1.0e-17 * (al * be);
 }
 
 // GW: lanes per pair (16 for n <= 64, 32 for n <= 128, else 64); LDS: the work arrays live in dynamic LDS.
@@ -114,9 +115,9 @@ __device__ __forceinline__ void jrotation(double al, double be, double ga, doubl
 // scales of columns, which one-sided rotations keep out of the result's relative accuracy (Demmel and Veselic,
 // 1992), and L^-T X orthonormalizes the block to eps times the condition of the columns scaled to length one.  Eigenvectors
 // over roots of eigenvalues are right to eps of the largest column only: at 3e5 between the Ritz values the block was
-// orthonormal to 1e-4, and the next filter lost it.  Times at 64 columns, 11008 x 4096: 490 us for the first two
-// blocks, 320 to 270 for the later ones and 95 where nothing turns, of which some 55 are load, factor, solve and the check
-// (sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded).
+// orthonormal to 1e-4, and the next filter lost it.  Times at 64 columns, 11008 x 4096: 90 us without sweeps, 720 for the first
+// block with them, 310 to 255 for the later ones (load, factor, solve and coming from memory as code take 75 of them), 7
+// for one that is orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
 template <int GW, bool LDS, bool ACCV>
 __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
@@ -133,6 +134,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     __shared__ double sg[JMAX];                             // during the sweeps: squared norms of the columns
     __shared__ int ord[JMAX];
     __shared__ double di[FACTOR ? BWLA_Q_JACOBI_SYM_LDS : 1];           // 1 / L_jj
+    __shared__ double iv[FACTOR ? BWLA_Q_JACOBI_SYM_LDS : 1];           // 1 / norms of the columns at the end
     for (int e = t; e < ncol * ld; e += JT) {
         const int j = e / ld, i = e - j * ld;
         Wc[e] = i < n && j < n ? a.G[(size_t)i * n + j] : 0.0;
@@ -143,6 +145,24 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     const int ldt = n + 1;                                              // (a column of it is written across banks)
     constexpr int U = GW == 16 ? 1 : GW == 32 ? 2 : 3;                  // elements of a column per lane
     if constexpr (FACTOR) {
+        if (a.ortho && !a.it) {
+            // A block that is orthonormal to 1e-8 as it is: G^(-1/2) = I - (G - I) / 2 to the square of that, and no sweeps
+            __syncthreads();
+            if (t == 0) rotated = 0;
+            __syncthreads();
+            for (int e = t; e < n * n; e += JT) {
+                const int j = e / n, i = e - j * n;
+                if (!(fabs(Wc[(size_t)j * ld + i] - (i == j ? 1.0 : 0.0)) <= 1.0e-8)) rotated = 1;
+            }
+            __syncthreads();
+            if (!rotated) {
+                for (int e = t; e < n * n; e += JT) {
+                    const int j = e / n, i = e - j * n;
+                    a.Vs[e] = (i == j ? 1.5 : 0.0) - 0.5 * Wc[(size_t)j * ld + i];
+                }
+                return;                                                 // (sig is not asked for)
+            }
+        }
         // Column j keeps G's entries below the diagonal and is divided by the root of its pivot at the end, so that
         // a step is one update of what is right of it and one barrier.  A pivot that rounding has eaten (a Gram matrix
         // singular to working precision) counts as 1e-14 of the diagonal that it came from, and what is below it, which is
@@ -196,7 +216,20 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         __syncthreads();
         if (a.ortho)
             for (int j = w; j < n; j += JW)
-                for (int i = lane; i < n; i += 64) Wc[(size_t)j * ld + i] = Lt[(size_t)j * ldt + i];
+                for (int i = lane; i < n; i += 64) Wc[(size_t)j * ld + i] = a.quick ? (i == j ? 1.0 : 0.0) : Lt[(size_t)j * ldt + i];
+        if (a.quick && w == 0) {
+            // the next filter is (S / power)^2, power some size of the columns
+            double top = 0.0;
+            for (int j = lane; j < n; j += 64) top = fmax(top, sg[j]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) top = fmax(top, __shfl_xor(top, off, 64));
+            top = top > 0.0 ? sqrt(1.0e14 * top) * a.scale : 1.0;
+            if (lane < 3) {
+                a.it->first[lane] = lane ? 0.0 : 1.0 / top;
+                a.it->second[lane] = lane ? 0.0 : 1.0 / top;
+            }
+            if (lane == 0) a.it->power = top;
+        }
     }
     const int np = (n + 1) & ~1;
     constexpr int GROUPS = JT / GW;
@@ -273,8 +306,10 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                 const double c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
                 sg[p] = c2 * (al - g2 + t2 * be);
                 sg[q] = c2 * (be + g2 + t2 * al);
-                rotated = 1;
+                if (jlarge(t2, ga, al, be)) rotated = 1;
             }
+        } else if (live && sl == 0 && (al < 0.0 || be < 0.0)) {
+            rotated = 1;
         }
     };
     // position i of a tournament of m (even): 0 stays, the others move on by one per round
@@ -283,7 +318,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         return i == 0 ? 0 : 1 + (v < 0 ? v + m - 1 : v);
     };
     __syncthreads();
-    for (int sweep = 0; sweep < 60; ++sweep) {
+    for (int sweep = 0; sweep < 60 && !a.quick; ++sweep) {
         if (t == 0) rotated = 0;
         // Squared norms: taken anew at the start of a sweep, carried along by the rotations within it (their
         // error is then that of a sweep's rotations, and a sweep that rotates nothing, the one that ends the
@@ -355,6 +390,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                             double tt, cs;
                             jrotation(nx, ny, ga, tt, cs);
                             const double sn = cs * tt, c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
+                            any |= jlarge(t2, ga, nx, ny);
                             const double mx = c2 * (nx - g2 + t2 * ny);
                             ny = c2 * (ny + g2 + t2 * nx);
                             nx = mx;
@@ -369,7 +405,8 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                                     vy[u] = sn * vu + cs * wu;
                                 }
                             }
-                            any = true;
+                        } else {
+                            any |= nx < 0.0 || ny < 0.0;
                         }
                     }
                     const int cy = by + (g4 ^ 2);                       // whose column the last exchange left here
@@ -418,6 +455,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     }
     __syncthreads();
     for (int j = t; j < n; j += JT) {
+        if (FACTOR) iv[j] = sg[j] > 0.0 ? 1.0 / sqrt(sg[j]) : 0.0;
         int rank = 0;
         for (int i = 0; i < n; ++i) rank += (sg[i] > sg[j] || (sg[i] == sg[j] && i < j)) ? 1 : 0;
         ord[rank] = j;
@@ -430,7 +468,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int j = ord[j0 + q < n ? j0 + q : n - 1];
-                const double s = sg[j], inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+                const double inv = iv[j];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int i = lane + 64 * u;
@@ -481,8 +519,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             const double s = sg[j];
             double scale = 0.0;
             if (s > 0.0) {
-                // (FACTOR: s is the squared norm of the column)
-                if (FACTOR) scale = 1.0 / sqrt(s);
+                if (FACTOR) scale = iv[j];
                 else scale = (a.pw == 0.0 ? 1.0 : pow(s, a.pw)) / (ACCV ? 1.0 : s);
             }
             for (int e = lane; e < n; e += 64) {
@@ -493,7 +530,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     }
     if (a.sig)
         for (int jj = t; jj < n; jj += JT) a.sig[jj] = sg[ord[jj]];
-    if (a.it && w == 0) {
+    if (a.it && !a.quick && w == 0) {
         // Ritz values of S out of the eigenvalues sg of the filtered block's Gram matrix
         const double theta = a.it->theta, power = a.it->power, before = a.it->moved;
         auto ritz = [&](int jj) {
@@ -512,10 +549,9 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int off = 32; off > 0; off >>= 1) moved = fmax(moved, __shfl_xor(moved, off, 64));
         if (lane == 0) {
             const double top = ritz(0), next = ritz(n - 1);
-            // The first call's values are of a block that was not orthonormal, so the first movement is the second's to
-            // the third; a quotient of movements takes two of them.
+            // (the first call has no values, so the first movement is the second's to the third; a quotient takes two)
             const bool still = a.call >= 3 && moved <= a.tol;
-            const bool soon = a.call >= 4 && moved <= 0.1 * before && moved * (moved / before) <= 0.0625 * a.tol;
+            const bool soon = a.call >= 4 && moved <= 0.1 * before && moved * (moved / before) <= 0.25 * a.tol;
             if (still || soon) *a.done = a.call;
             // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
             // orthonormalizing takes out as long as that is small against one.  With values further apart the block is
@@ -545,7 +581,7 @@ hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st) {
     const size_t lds = in_lds ? (one + second) * sizeof(double) : 0;
     auto launch = [&](auto kern, int threads) {
         if (lds > 48 * 1024) {
-            const hipError_t e = bwla_ensure_lds((const void*)kern, lds);
+            const hipError_t e = bwla_ensure_lds((const void*)kern, lds + 8192);             // (and what it holds statically)
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(kern, dim3(1), dim3(threads), lds, st, j);

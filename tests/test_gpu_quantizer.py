@@ -291,6 +291,61 @@ def test_procrustes_updates(n, n1, n2, k):
         assert after <= before * (1 + 1e-12)
 
 
+# (up to 96 the polar factor is the work of one workgroup, in tiles of 16: a tile and one, odd, full, one short of full;
+# C2 has rank n n1 at most, so n is several times n2 / n1)
+@pytest.mark.parametrize("n,n1,n2", [(40, 17, 96), (60, 80, 65), (160, 3, 95), (50, 64, 16)])
+def test_procrustes_of_ragged_factors(n, n1, n2):
+    qb = _qb()
+    _, W, A, Bt, R1, R2 = _problem(6, n, n1, n2, 4)
+    Wres = W - A @ Bt.T
+    c, s2 = Q.init_theta(Q.okt_rows(W, A @ Bt.T, R1, R2))
+    targets, lam = Q.mm_row_targets(Wres, R1, R2, c, s2)
+    for which, nn in ((1, n1), (2, n2)):
+        Rn = torch.empty(nn, nn, dtype=torch.float64, device="cuda")
+        qb.procrustes(which, _dev(Wres), _dev(R1), _dev(R2), _dev(c), _dev(s2), Rn, _ws(n, n1 * n2, n1, n2, 0))
+        got = Rn.cpu().numpy()
+        want = (Q.procrustes_r1(Wres, R2, targets, lam, n1, n2) if which == 1
+                else Q.procrustes_r2(Wres, R1, targets, lam, n1, n2))
+        assert np.max(np.abs(got.T @ got - np.eye(nn))) < 1e-12
+        assert np.max(np.abs(got - want)) < 1e-9
+
+
+@pytest.mark.parametrize("n1", [32, 80])
+def test_procrustes_of_a_singular_matrix(n1):
+    """Rows of V_i that are zero in every row of the layer: C1 is singular, its polar factor not unique, the result finite."""
+    qb = _qb()
+    n, n2 = 40, 16
+    _, W, _, _, R1, R2 = _problem(7, n, n1, n2, 4)
+    Wres = W.reshape(n, n1, n2).copy()
+    Wres[:, :2, :] = 0.0
+    Wres = Wres.reshape(n, n1 * n2)
+    R1, R2 = np.eye(n1), np.eye(n2)
+    c, s2 = Q.init_theta(Q.okt_rows(Wres, np.zeros_like(Wres), R1, R2))
+    Rn = torch.empty(n1, n1, dtype=torch.float64, device="cuda")
+    qb.procrustes(1, _dev(Wres), _dev(R1), _dev(R2), _dev(c), _dev(s2), Rn, _ws(n, n1 * n2, n1, n2, 0))
+    assert np.all(np.isfinite(Rn.cpu().numpy()))
+
+
+@pytest.mark.parametrize("k", [0, 4])
+def test_start_at_the_identity_is_the_start_from_an_identity(k):
+    """Factors that start at the identity are not multiplied by in the first round; the general path says the same."""
+    qb = _qb()
+    n, n1, n2, t = 90, 24, 20, 2
+    m = n1 * n2
+    _, W, _, _, _, _ = _problem(8, n, n1, n2, max(k, 1), planted=0.03)
+    f32 = lambda *s: torch.empty(*s, dtype=torch.float32, device="cuda")
+    out = []
+    for identity in (1, 0):
+        R1, R2 = torch.eye(n1, device="cuda"), torch.eye(n2, device="cuda")
+        Wrot, U, V = f32(n, m), f32(m, k) if k else None, f32(n, k) if k else None
+        hist = torch.empty(1 + 3 * t, dtype=torch.float64, device="cuda")
+        qb.quantize_layer(_dev(W, torch.float32), n1, n2, k, t, R1, R2, Wrot, U, V, None, None, hist, _ws(n, m, n1, n2, k),
+                          svd_tol=1e-14, init_identity=identity)
+        out.append((Wrot.cpu().numpy(), R1.cpu().numpy(), R2.cpu().numpy(), hist.cpu().numpy()))
+    for a, b in zip(*out):
+        assert np.max(np.abs(a - b)) < 1e-6 * max(1.0, np.max(np.abs(a)))      # fp32 results of fp64 work
+
+
 # (the last five: blocks of 80, 128, 132, 160 and 256 vectors -- the Gram matrix's eigenproblem in a row pair of
 # lanes per column pair and in a wavefront per pair with the matrix in LDS; above 136 vectors the block is
 # orthonormalized by the Newton-Schulz iteration and the eigenproblem is solved once, in scratch)
