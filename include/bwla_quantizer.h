@@ -99,7 +99,8 @@ BWLA_API bwla_status_t bwla_q_svd_square(const double* d_G, int32_t nn, double* 
  * min(n, m, max(2 k, k + 16)) vectors from a fixed pseudo-random start, filtered by a Chebyshev polynomial of
  * degree two in S whose interval ends at the smallest Ritz value, re-orthonormalized every iteration through the
  * Cholesky factor of its Gram matrix, and a final Rayleigh-Ritz step.  It stops when the work of `iters` plain
- * iterations is done -- `iters` products with S up to 24, half as many above, which the filter makes up for --
+ * iterations is done -- `iters` products with S up to 24, half as many or a third (at least 24, 64) above, which the
+ * filter makes up for --
  * or earlier once the k leading Ritz values have settled: moved by at most `tol` (relative) in one iteration, or
  * about to move by less than tol / 4 in the next, going by the last two; the remaining launches then return at
  * once.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead,
