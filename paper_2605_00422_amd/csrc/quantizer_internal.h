@@ -99,10 +99,10 @@ hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, 
 // returns immediately when *skip != 0.
 // sym: G is symmetric positive semidefinite (a Gram matrix G = B^T B); Ws is not available.  Up to 136 wide the
 // sweeps run in LDS, on the Cholesky factor G = L L^T, and the rotations are not accumulated; sig are eigenvalues:
-//   ortho         the columns of L^T are rotated into X S; Vs[j] = column j of L^-T X, so that B Vs^T has
-//                 orthonormal columns, which are the left singular vectors of B (without `it`, and for a B that is
-//                 orthonormal to 1e-8: some such columns, and no sig); quick: without sweeps, X = I, and of `it`
-//                 power alone
+//   ortho         the columns of L^T are rotated into X S; Vs[j] = column j of L^-T X, or those of L into V S and
+//                 Vs[j] = v_j / s_j where columns of B are not far apart, so that B Vs^T has orthonormal columns, which
+//                 are the left singular vectors of B (without `it`, and for a B that is orthonormal to 1e-8: some
+//                 such columns, and no sig); quick: without sweeps, X = I, and of `it` power alone
 //   otherwise     the columns of L; Vs[j] = eigenvector j (pw is not looked at)
 // Wider ones (without ortho) are rotated themselves, v_j being the normalized column j of G V.
 //

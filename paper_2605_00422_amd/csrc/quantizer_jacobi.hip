@@ -115,14 +115,17 @@ __device__ __forceinline__ bool jlarge(double t2, double ga, double al, double b
 // scales of columns, which one-sided rotations keep out of the result's relative accuracy (Demmel and Veselic,
 // 1992), and L^-T X orthonormalizes the block to eps times the condition of the columns scaled to length one.  Eigenvectors
 // over roots of eigenvalues are right to eps of the largest column only: at 3e5 between the Ritz values the block was
-// orthonormal to 1e-4, and the next filter lost it.  Times at 64 columns, 11008 x 4096: 90 us without sweeps, 720 for the first
-// block with them, 310 to 255 for the later ones (load, factor, solve and coming from memory as code take 75 of them), 7
-// for one that is orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
+// orthonormal to 1e-4, and the next filter lost it.  Columns of L^T are the less orthogonal to begin with, though, so that
+// blocks whose columns are not far apart go by those of L and the eigenvectors over roots of eigenvalues.
+// Times at 64 columns, 11008 x 4096: 90 us without sweeps, 460 for the first block with them (720 by way of L^T), 290 to 230
+// for the later ones (315 to 255), of which load, factor, norms and coming from memory as code take some 70; 7 for one that is
+// orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
 template <int GW, bool LDS, bool ACCV>
 __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
     constexpr int JT = jacobi_threads(GW), JW = JT / 64;
     constexpr bool FACTOR = LDS && !ACCV;
+    bool rows = a.ortho;                                    // the sweeps rotate the columns of L^T, i.e. the rows of L
     const int n = a.n, t = threadIdx.x, lane = t & 63, w = t >> 6;
     extern __shared__ __align__(16) double jlds[];
     double* Wc = LDS ? jlds : a.work;
@@ -170,6 +173,21 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         __syncthreads();
         for (int j = t; j < n; j += JT) sg[j] = 1.0e-14 * Wc[(size_t)j * ld + j];
         __syncthreads();
+        if (a.ortho && !a.quick) {
+            // columns of B up to 1e6 apart: eigenvectors over roots of eigenvalues leave B Vs^T orthonormal to 1e-10, and the columns
+            // of L are the nearer to orthogonal
+            double most = 0.0, least = 1.0e300;
+            for (int j = lane; j < n; j += 64) {
+                most = fmax(most, sg[j]);
+                least = fmin(least, sg[j]);
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                most = fmax(most, __shfl_xor(most, off, 64));
+                least = fmin(least, __shfl_xor(least, off, 64));
+            }
+            rows = !(most <= 1.0e12 * least);
+        }
         for (int j = 0; j < n; ++j) {
             const double* cj = Wc + (size_t)j * ld;
             const double piv = cj[j], inv = piv > sg[j] && piv > 1.0e-300 ? jrcp(piv) : 0.0;
@@ -208,13 +226,13 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             const double root = sqrt(sound ? piv : floor), inv = sound ? 1.0 / root : 0.0;
             for (int i = lane; i < n; i += 64) {
                 const double l = i < j ? 0.0 : i == j ? root : cj[i] * inv;
-                if (a.ortho) Lt[(size_t)i * ldt + j] = l;
+                if (rows) Lt[(size_t)i * ldt + j] = l;
                 else cj[i] = l;
             }
             if (lane == 0) di[j] = root > 0.0 ? 1.0 / root : 0.0;
         }
         __syncthreads();
-        if (a.ortho)
+        if (rows)
             for (int j = w; j < n; j += JW)
                 for (int i = lane; i < n; i += 64) Wc[(size_t)j * ld + i] = a.quick ? (i == j ? 1.0 : 0.0) : Lt[(size_t)j * ldt + i];
         if (a.quick && w == 0) {
@@ -461,7 +479,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         ord[rank] = j;
     }
     __syncthreads();
-    if (FACTOR && a.ortho) {
+    if (FACTOR && rows) {
         // L^T M = X, eight right sides a wavefront, their rows in lanes, from the last row up
         for (int j0 = 8 * w; j0 < n; j0 += 8 * JW) {
             double x[8][U];
@@ -519,7 +537,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             const double s = sg[j];
             double scale = 0.0;
             if (s > 0.0) {
-                if (FACTOR) scale = iv[j];
+                if (FACTOR) scale = a.ortho ? iv[j] * iv[j] : iv[j];
                 else scale = (a.pw == 0.0 ? 1.0 : pow(s, a.pw)) / (ACCV ? 1.0 : s);
             }
             for (int e = lane; e < n; e += 64) {
