@@ -117,9 +117,8 @@ __device__ __forceinline__ bool jlarge(double t2, double ga, double al, double b
 // over roots of eigenvalues are right to eps of the largest column only: at 3e5 between the Ritz values the block was
 // orthonormal to 1e-4, and the next filter lost it.  Columns of L^T are the less orthogonal to begin with, though, so that
 // blocks whose columns are not far apart go by those of L and the eigenvectors over roots of eigenvalues.
-// Times at 64 columns, 11008 x 4096: 90 us without sweeps, 460 for the first block with them (720 by way of L^T), 290 to 230
-// for the later ones (315 to 255), of which load, factor, norms and coming from memory as code take some 70; 7 for one that is
-// orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
+// Times at 64 columns, 11008 x 4096: 57 us without sweeps, 445 for the first block with them (705 by way of L^T), 275 to 215
+// for the later ones (300 to 240); 7 for one that is orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
 template <int GW, bool LDS, bool ACCV>
 __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
@@ -166,10 +165,12 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                 return;                                                 // (sig is not asked for)
             }
         }
-        // Column j keeps G's entries below the diagonal and is divided by the root of its pivot at the end, so that
-        // a step is one update of what is right of it and one barrier.  A pivot that rounding has eaten (a Gram matrix
-        // singular to working precision) counts as 1e-14 of the diagonal that it came from, and what is below it, which is
-        // as much noise as it is, as nothing: without that, noise grows by squares from step to step.
+        // Four columns a step: every wavefront takes them into registers (rows in lanes) and factors them for itself, then each
+        // updates its share of the columns right of them, one barrier a step.  A column keeps its entries below the diagonal and is
+        // divided by the root of its pivot at the end.  A pivot that rounding has eaten (a Gram matrix singular to working
+        // precision) counts as 1e-14 of the diagonal that it came from, and what is below it, which is as much noise as it
+        // is, as nothing: without that, noise grows by squares from step to step.  (64 columns without sweeps, whole call: a column a
+        // step 72 us, which was the latency of LDS and of the pivot 64 times over; so 57.)
         __syncthreads();
         for (int j = t; j < n; j += JT) sg[j] = 1.0e-14 * Wc[(size_t)j * ld + j];
         __syncthreads();
@@ -188,37 +189,76 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             }
             rows = !(most <= 1.0e12 * least);
         }
-        for (int j = 0; j < n; ++j) {
-            const double* cj = Wc + (size_t)j * ld;
-            const double piv = cj[j], inv = piv > sg[j] && piv > 1.0e-300 ? jrcp(piv) : 0.0;
-            double mine[U];
+        double pc[4][U], ps[4][U];                                      // a step's columns, and over their pivots
+        // the entry of `row`, the same row in all lanes, of a column in registers
+        auto entry = [&](const double (&c)[U], int row) {
+            double v = c[0];
 #pragma unroll
-            for (int u = 0; u < U; ++u) mine[u] = lane + 64 * u < n ? cj[lane + 64 * u] : 0.0;
-            // wavefronts take columns, four at a time so that their LDS reads overlap, lanes rows
-            for (int k0 = j + 1 + w; k0 < n; k0 += 4 * JW) {
-                double f[4], v[4][U];
+            for (int u = 1; u < U; ++u) v = row >= 64 * u ? c[u] : v;
+            return jread(v, row & 63);
+        };
+        auto put_back = [&](int j0) {                                   // (of the step before: others may still have been reading)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int k = k0 + q * JW < n ? k0 + q * JW : n - 1;
-                    f[q] = cj[k];
+            for (int c = 1; c < 4; ++c)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = lane + 64 * u;
+                    if (j0 + c < n && i >= j0 + c && i < n) Wc[(size_t)(j0 + c) * ld + i] = pc[c][u];
+                }
+        };
+        for (int j0 = 0; j0 < n; j0 += 4) {
+            if (w == 0 && j0 > 0) put_back(j0 - 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = lane + 64 * u;
+                    pc[c][u] = j0 + c < n && i < n ? Wc[(size_t)(j0 + c) * ld + i] : 0.0;
+                }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int j = j0 + c < n ? j0 + c : n - 1;
+                const double piv = entry(pc[c], j), inv = j0 + c < n && piv > sg[j] && piv > 1.0e-300 ? jrcp(piv) : 0.0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) ps[c][u] = pc[c][u] * inv;
+#pragma unroll
+                for (int d = c + 1; d < 4; ++d) {
+                    const double f = entry(pc[c], j0 + d < n ? j0 + d : n - 1);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) pc[d][u] = fma(-f, ps[c][u], pc[d][u]);
+                }
+            }
+            for (int k0 = j0 + 4 + w; k0 < n; k0 += 4 * JW) {           // (four at a time so that their LDS reads overlap)
+                double v[4][U];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int k = k0 + x * JW < n ? k0 + x * JW : n - 1;
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int i = lane + 64 * u;
-                        v[q][u] = Wc[(size_t)k * ld + (i < n ? i : 0)];
+                        v[x][u] = Wc[(size_t)k * ld + (i < n ? i : 0)];
                     }
                 }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int k = k0 + q * JW;
+                for (int x = 0; x < 4; ++x) {
+                    const int k = k0 + x * JW < n ? k0 + x * JW : n - 1;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const double f = entry(pc[c], k);
+#pragma unroll
+                        for (int u = 0; u < U; ++u) v[x][u] = fma(-f, ps[c][u], v[x][u]);
+                    }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int i = lane + 64 * u;
-                        if (k < n && i >= k && i < n) Wc[(size_t)k * ld + i] = fma(-f[q] * inv, mine[u], v[q][u]);
+                        if (k0 + x * JW < n && i >= k && i < n) Wc[(size_t)k * ld + i] = v[x][u];
                     }
                 }
             }
             __syncthreads();
         }
+        if (w == 0) put_back((n - 1) & ~3);
+        __syncthreads();
         for (int j = w; j < n; j += JW) {
             double* cj = Wc + (size_t)j * ld;
             const double piv = cj[j], floor = sg[j];
