@@ -55,17 +55,15 @@ __device__ __forceinline__ double jgroup_sum(double v) {
     return v;
 }
 
-// the value of the lane 16 (by32: 32) away under exclusive or: rows of lanes change places
+// the value of the lane 16 (by32: 32) away under exclusive or: rows of lanes change places, by way of the LDS crossbar: a step is
+// bound by the issue of some 110 vector instructions, and a swap of registers takes three for each of these
 __device__ __forceinline__ double jrow_xor(double v, bool by32, int lane) {
-    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const int lo = __double2loint(v), hi = __double2hiint(v);
     if (by32) {
-        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        return lane & 32 ? __hiloint2double((int)h[0], (int)l[0]) : __hiloint2double((int)h[1], (int)l[1]);
+        const int from = (lane ^ 32) * 4;
+        return __hiloint2double(__builtin_amdgcn_ds_bpermute(from, hi), __builtin_amdgcn_ds_bpermute(from, lo));
     }
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return lane & 16 ? __hiloint2double((int)h[0], (int)l[0]) : __hiloint2double((int)h[1], (int)l[1]);
+    return __hiloint2double(__builtin_amdgcn_ds_swizzle(hi, 0x401f), __builtin_amdgcn_ds_swizzle(lo, 0x401f));
 }
 
 // 1 / x to a rounding or two: the hardware's estimate (2^-20 or better) and two Newton steps.  x normal, below 2^1021.
@@ -98,12 +96,10 @@ __device__ __forceinline__ void jrotation(double al, double be, double ga, doubl
     cs = y;
 }
 
-// Whether a rotation (tangent squared t2, inner product ga of columns with squared norms al, be before it) leaves work to a
-// further sweep.  A rotation changes the cosine between one of its columns and a third by t times that of the other, so a
-// sweep that finds none of either beyond 3e-9 leaves none beyond 64 x 1e-17, and needs no further one to say so.
-__device__ __forceinline__ bool jlarge(double t2, double ga, double al, double be) {
-    return t2 > 1.0e-17 || ga * ga > 1.0e-17 * (al * be);
-}
+// Whether a rotation (tangent t; gg, nn the squares of the columns' inner product and of the product of their norms before it)
+// leaves work to a further sweep.  A rotation changes the cosine between one of its columns and a third by t times that of the
+// other, so a sweep that finds none of either beyond 3e-9 leaves none beyond 64 x 1e-17, and needs no further one to say so.
+__device__ __forceinline__ bool jlarge(double t, double gg, double nn) { return fabs(t) > 3.0e-9 || gg > 1.0e-17 * nn; }
 
 // GW: lanes per pair (16 for n <= 64, 32 for n <= 128, else 64); LDS: the work arrays live in dynamic LDS.
 // ACCV: the rotations are accumulated into V.  Without it (a symmetric positive semidefinite G, whose
@@ -117,8 +113,8 @@ __device__ __forceinline__ bool jlarge(double t2, double ga, double al, double b
 // over roots of eigenvalues are right to eps of the largest column only: at 3e5 between the Ritz values the block was
 // orthonormal to 1e-4, and the next filter lost it.  Columns of L^T are the less orthogonal to begin with, though, so that
 // blocks whose columns are not far apart go by those of L and the eigenvectors over roots of eigenvalues.
-// Times at 64 columns, 11008 x 4096: 57 us without sweeps, 445 for the first block with them (705 by way of L^T), 275 to 215
-// for the later ones (300 to 240); 7 for one that is orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
+// Times at 64 columns, 11008 x 4096: 57 us without sweeps, 420 for the first block with them (260 more by way of L^T), 260 to
+// 200 for the later ones (25 more); 7 for one that is orthonormal already.  Sweeps on G itself: 420 and 400, 265 to 150, on plain blocks that are less graded.
 template <int GW, bool LDS, bool ACCV>
 __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
     if (a.skip && *a.skip) return;
@@ -364,7 +360,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                 const double c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
                 sg[p] = c2 * (al - g2 + t2 * be);
                 sg[q] = c2 * (be + g2 + t2 * al);
-                if (jlarge(t2, ga, al, be)) rotated = 1;
+                if (jlarge(tt, ga * ga, al * be)) rotated = 1;
             }
         } else if (live && sl == 0 && (al < 0.0 || be < 0.0)) {
             rotated = 1;
@@ -439,19 +435,21 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                             }
                         }
                         const double ga = jrow_sum((x[0] * y[0] + x[1] * y[1]) + (x[2] * y[2] + x[3] * y[3]));
-                        if (ga * ga > nx * ny) {                        // as above
+                        const double gg = ga * ga;
+                        double nn = nx * ny;
+                        if (!(gg <= nn) || nx < 0.0) {                  // carried norms that cancellation has spoilt
                             nx = jrow_sum((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]));
                             ny = jrow_sum((y[0] * y[0] + y[1] * y[1]) + (y[2] * y[2] + y[3] * y[3]));
+                            nn = nx * ny;
                         }
-                        const bool turn = nx > 0.0 && ny > 0.0 && ga * ga > 1.0e-30 * (nx * ny);
-                        if (turn) {
+                        if (gg > 1.0e-30 * nn) {                        // (never for a zero column)
                             double tt, cs;
                             jrotation(nx, ny, ga, tt, cs);
-                            const double sn = cs * tt, c2 = cs * cs, g2 = 2.0 * tt * ga, t2 = tt * tt;
-                            any |= jlarge(t2, ga, nx, ny);
-                            const double mx = c2 * (nx - g2 + t2 * ny);
-                            ny = c2 * (ny + g2 + t2 * nx);
-                            nx = mx;
+                            const double sn = cs * tt, moves = tt * ga;
+                            any |= jlarge(tt, gg, nn);
+                            // (of the exact angle; off it by the tangent's 2^-22 of what moves, until norms are taken anew)
+                            nx -= moves;
+                            ny += moves;
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
                                 const double xu = x[u], yu = y[u];
@@ -463,8 +461,6 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
                                     vy[u] = sn * vu + cs * wu;
                                 }
                             }
-                        } else {
-                            any |= nx < 0.0 || ny < 0.0;
                         }
                     }
                     const int cy = by + (g4 ^ 2);                       // whose column the last exchange left here
