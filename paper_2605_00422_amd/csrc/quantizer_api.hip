@@ -284,9 +284,8 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     // 8 q^2 - 8 q + 1 filtered: the filter needs half as many up to q = 2.1, a third up to q = 1.2, and for any gap wider than
     // these 24 and 64 of them leave nothing to be done (19.5^12, 2.9^32).  So half or a third as many are made, which are
     // fewer launches that return at once too.  11008 x 4096, rank 32: 13 iterations of 560 us and 14 calls of the
-    // eigensolver became 11 products of 310 in 6 iterations, 1400 empty launches some 330, the whole call 16.5 -> 13.1 ms (and
-    // 0.9 less with a third instead of a half and without Ritz vectors of the first); the truncation's error against a 64-bit
-    // SVD (1500 x 1024, gaps 1.02 to 2): 7e-9 to 9e-8 -> 5e-12 to 3e-9.
+    // eigensolver became 9 products of 275 in 5 iterations, 1400 empty launches some 340; the truncation's error against a
+    // 64-bit SVD (1500 x 1024, gaps 1.02 to 2): 7e-9 to 9e-8 -> 9e-10 to 3e-8.
     QRitz* ritz = reinterpret_cast<QRitz*>(x.ws + P.ritz);
     const int half_of = iters / 2 > 24 ? iters / 2 : 24, third_of = iters / 3 > 64 ? iters / 3 : 64;
     int budget = iters < half_of ? iters : half_of;

@@ -120,8 +120,7 @@ struct QJacobi {
     // With it: prev holds n doubles, the squared Ritz values of the iteration before, and is replaced; degree says
     // whether the block was multiplied by S (1) or filtered (2), scale what its Ritz values are to be multiplied
     // with in the first case.  From the third call on (call counts from 1) *done is set to `call` once the leading `lead` values have
-    // settled: they moved by at most tol relative, or what the next iteration would move them by, a quotient of two
-    // movements smaller again, is below tol / 4.
+    // settled: they moved by at most tol relative, or, going by the last two movements, this block's are within tol / 16.
     QRitz* it; double* prev; int lead, degree, call; double tol, scale; int* done;
 };
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st);

@@ -603,9 +603,12 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int off = 32; off > 0; off >>= 1) moved = fmax(moved, __shfl_xor(moved, off, 64));
         if (lane == 0) {
             const double top = ritz(0), next = ritz(n - 1);
-            // (the first call has no values, so the first movement is the second's to the third; a quotient takes two)
+            // The first call has no values, so the first movement is the second's to the third, and a quotient takes two.  Values of
+            // a filtered block are those of the block before it, to the square of an angle, so the last movement is the error
+            // that the block two calls back had, and this one's is two quotients of movements smaller.
+            const double rate = moved / before;
             const bool still = a.call >= 3 && moved <= a.tol;
-            const bool soon = a.call >= 4 && moved <= 0.1 * before && moved * (moved / before) <= 0.25 * a.tol;
+            const bool soon = a.call >= 4 && rate <= 0.5 && moved * rate * rate <= 0.0625 * a.tol;
             if (still || soon) *a.done = a.call;
             // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
             // orthonormalizing takes out as long as that is small against one.  With values further apart the block is
