@@ -243,6 +243,50 @@ def test_rows_at_the_length_that_lds_keeps(n1, n2):
     assert np.max(np.abs(Rn.cpu().numpy() - want)) < 1e-8
 
 
+# (rows in registers: 4 or 16 entries a thread of 256, 512 and 1024 threads, full and one column past; longer ones read again)
+@pytest.mark.parametrize("m", [1, 63, 1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385, 20000])
+def test_row_steps_at_any_length(m):
+    qb = _qb()
+    n = 3
+    X = Q.center_rows(np.random.default_rng(m).standard_normal((n, m)) + 0.5 * np.sign(np.random.default_rng(m + 1).standard_normal((n, m))))
+    c, s2 = torch.empty(n, dtype=torch.float64, device="cuda"), torch.empty(n, dtype=torch.float64, device="cuda")
+    qb.init_theta(_dev(X), Q.S2_MIN, c, s2)
+    co, s2o = Q.init_theta(X)
+    assert np.allclose(c.cpu().numpy(), co, rtol=1e-12, atol=1e-300) and np.allclose(s2.cpu().numpy(), s2o, rtol=1e-11)
+    qb.em_step(_dev(X), Q.S2_MIN, c, s2)
+    co, s2o = Q.em_step(X, co, s2o)
+    assert np.allclose(c.cpu().numpy(), co, rtol=1e-10, atol=1e-300) and np.allclose(s2.cpu().numpy(), s2o, rtol=1e-10)
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    qb.gmm_nll(_dev(X), c, s2, out, torch.zeros(256, dtype=torch.uint8, device="cuda"))
+    want = Q.gmm_nll(X, co, s2o)
+    assert abs(out.item() - want) < 1e-10 * max(abs(want), 1.0)
+
+
+@pytest.mark.parametrize("n1,n2", [(256, 64), (256, 65)])
+def test_targets_of_long_rows(n1, n2):
+    """Targets of rows that registers still hold (16384 columns) and of longer ones, by way of the update of R2."""
+    qb = _qb()
+    n = 5
+    _, W, _, _, R1, R2 = _problem(9, n, n1, n2, 1)
+    c, s2 = Q.init_theta(Q.okt_rows(W, np.zeros_like(W), R1, R2))
+    targets, lam = Q.mm_row_targets(W, R1, R2, c, s2)
+    Rn = torch.empty(n2, n2, dtype=torch.float64, device="cuda")
+    qb.procrustes(2, _dev(W), _dev(R1), _dev(R2), _dev(c), _dev(s2), Rn, _ws(n, n1 * n2, n1, n2, 0))
+    assert np.max(np.abs(Rn.cpu().numpy() - Q.procrustes_r2(W, R1, targets, lam, n1, n2))) < 1e-9
+
+
+@pytest.mark.parametrize("n,m,k", [(1, 1, 1), (2, 3, 1), (3, 2, 2), (5, 40, 5), (17, 9, 4)])
+def test_truncate_rank_of_tiny_matrices(n, m, k):
+    """Blocks as wide as the matrix: the truncation is exact after one product."""
+    qb = _qb()
+    Y = np.random.default_rng(n * 100 + m).standard_normal((n, m))
+    A = torch.empty(n, k, dtype=torch.float64, device="cuda")
+    Bt = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(qb.workspace_size(n, m, 1, 1, k), dtype=torch.uint8, device="cuda")
+    qb.truncate_rank(_dev(Y), k, 60, 1e-14, A, Bt, None, ws)
+    assert _rel(A.cpu().numpy() @ Bt.cpu().numpy().T, Q.truncate_rank(Y, k)) < 1e-9
+
+
 def test_nll_keeps_the_terms_below_the_rounding_of_one():
     """Entries on a component whose other component is 40 nats down add log1p(exp(-40)) = 4.2e-18 each, less than
     the rounding of 1 + exp(-40).  With s^2 next to 1 / (8 pi) the leading terms, log 2 - log 2, vanish exactly at some
