@@ -73,9 +73,10 @@ BWLA_API bwla_status_t bwla_q_gmm_nll(const double* d_X, int64_t n, int64_t m, c
  * weights taken at the given factors: which = 1 gives the minimizer over R1 of
  * sum_i lambda_i || R1^T V_i R2 - T_i ||_F^2 (polar factor of C1 = sum_i lambda_i V_i R2 T_i^T),
  * which = 2 the minimizer over R2 (C2 = sum_i lambda_i V_i^T R1 T_i); V_i is row i of d_Wres = W - M
- * reshaped, T_i its target.  d_Rnew out, n1 x n1 or n2 x n2.  The polar factor comes from a one-sided
- * Jacobi SVD for factors up to 64 and from the Newton-Schulz iteration X <- X (3 I - X^T X) / 2 on
- * C / ||C||_F above (the same matrix, from small GEMMs instead of a single workgroup); a singular C
+ * reshaped, T_i its target.  d_Rnew out, n1 x n1 or n2 x n2.  The polar factor comes from the Newton-Schulz iteration
+ * X <- X (3 I - X^T X) / 2 on C / ||C||_F -- in one workgroup for factors up to 96, as a chain of small GEMMs
+ * above -- and, for factors up to 64 where that does not converge (a condition beyond some 1e9), from a one-sided Jacobi
+ * SVD; a singular C
  * has no unique one and gives an undefined (finite) result.
  */
 BWLA_API bwla_status_t bwla_q_procrustes(int32_t which, const double* d_Wres, const double* d_R1,
