@@ -192,7 +192,7 @@ __global__ void factor_planes_kernel(const float* __restrict__ R, int n, int per
     P[2 * plane + i] = (uint16_t)(h3 >> 16);
 }
 
-// Factor planes in MFMA operand order (both factors padded with zeros to multiples of 32), one 1 KiB
+// Factor planes in MFMA operand order (factor pairs that are multiples of 32 up to 160), one 1 KiB
 // block per MFMA operand, lane (li, lg) = lg * 16 + li holding eight 16-bit values:
 //   R2d part (pairs of 32 or 64 only), blocks [strip w][step kb][term p < 3]: term p (bf16; the
 //            three add up to the fp32 value) of R2[b = 32 kb + 8 lg + e][d = 16 w + li]
@@ -202,20 +202,14 @@ __global__ void factor_planes_kernel(const float* __restrict__ R, int n, int per
 //   R2h part, blocks [strip w][step kb][term t < 2]: the same two fp16 terms of 256 R2[b][d]
 __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* __restrict__ R2, int n1, int n2,
                                      int with_r2d, uint16_t* __restrict__ out) {
-    const int ch2 = (n1 + 31) / 32, at = 2 * ch2, k1 = (n2 + 31) / 32, strips = (n2 + 15) / 16;
+    const int at = n1 / 16, k1 = n2 / 32, ch2 = n1 / 32, strips = n2 / 16;
     const int nb2 = with_r2d ? strips * k1 * 3 : 0, nb1 = ch2 * 2 * at, nb2h = strips * k1 * 2;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (nb2 + nb1 + nb2h) * 512) return;
     const int blk = i >> 9, lane = (i >> 3) & 63, e = i & 7, li = lane & 15, lg = lane >> 4;
-    auto r1_at = [&](int ch, int tc) -> float {         // R1[a][c = 16 tc + li]
-        const int a = 32 * ch + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4), c = 16 * tc + li;
-        return a < n1 && c < n1 ? R1[(int64_t)a * n1 + c] : 0.0f;
-    };
-    auto r2_at = [&](int w, int kb) -> float {          // R2[b = 32 kb + 8 lg + e][d = 16 w + li]
-        const int b = 32 * kb + 8 * lg + e, d = 16 * w + li;
-        return b < n2 && d < n2 ? R2[(int64_t)b * n2 + d] : 0.0f;
-    };
-    auto bf16_term = [](float v, int p) -> uint16_t {
+    if (blk < nb2) {
+        const int p = blk % 3, kb = (blk / 3) % k1, w = blk / (3 * k1);
+        const float v = R2[(int64_t)(32 * kb + 8 * lg + e) * n2 + 16 * w + li];
         auto bf = [](float f) -> uint32_t {
             const uint32_t u = __float_as_uint(f);
             return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
@@ -224,17 +218,24 @@ __global__ void decode_planes_kernel(const float* __restrict__ R1, const float* 
         const float r1 = v - __uint_as_float(h1);
         const uint32_t h2 = bf(r1);
         const uint32_t h3 = bf(r1 - __uint_as_float(h2));
-        return (uint16_t)((p == 0 ? h1 : p == 1 ? h2 : h3) >> 16);
-    };
-    auto fp16_term = [](float v, int p) -> uint16_t {
+        out[i] = (uint16_t)((p == 0 ? h1 : p == 1 ? h2 : h3) >> 16);
+    } else if (blk < nb2 + nb1) {
+        const int b1 = blk - nb2;
+        const int tc = b1 % at, t = (b1 / at) % 2, ch = b1 / (2 * at);
+        const int a = 32 * ch + (e < 4 ? 4 * lg + e : 16 + 4 * lg + e - 4);
+        const float v = 256.0f * R1[(int64_t)a * n1 + 16 * tc + li];
         const __half hi = __float2half_rn(v);
-        return __half_as_ushort(p == 0 ? hi : __float2half_rn(v - __half2float(hi)));
-    };
-    int j = blk;                                        // block within its part
-    if (j < nb2) { out[i] = bf16_term(r2_at(j / (3 * k1), (j / 3) % k1), j % 3); return; }
-    if ((j -= nb2) < nb1) { out[i] = fp16_term(256.0f * r1_at(j / (2 * at), j % at), (j / at) % 2); return; }
-    j -= nb1;
-    out[i] = fp16_term(256.0f * r2_at(j / (2 * k1), (j / 2) % k1), j % 2);
+        const __half lo = __float2half_rn(v - __half2float(hi));
+        out[i] = __half_as_ushort(t == 0 ? hi : lo);
+    } else {
+        // R2h, blocks [strip w][step kb][term t < 2]: 256 R2[b = 32 kb + 8 lg + e][d = 16 w + li]
+        const int b2 = blk - nb2 - nb1;
+        const int t = b2 % 2, kb = (b2 / 2) % k1, w = b2 / (2 * k1);
+        const float v = 256.0f * R2[(int64_t)(32 * kb + 8 * lg + e) * n2 + 16 * w + li];
+        const __half hi = __float2half_rn(v);
+        const __half lo = __float2half_rn(v - __half2float(hi));
+        out[i] = __half_as_ushort(t == 0 ? hi : lo);
+    }
 }
 
 __global__ void copy_f32_kernel(const float* __restrict__ src, int64_t n, float* __restrict__ dst) {

@@ -289,7 +289,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
-    if (rt_serves(L, xdtype != BWLA_X_BF16)) {
+    if (rt_serves(L, xdtype, M, bwla_device_cus())) {
         e = bwla_launch_rotate_terms(L, a, pblocks, merged, xdtype != BWLA_X_BF16, st);
         if (e != hipSuccess) return e;
         return ru > 0 && !merged && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;
@@ -353,8 +353,6 @@ SplitRule split_rule(const bwla_layer_t* L) {
     SplitRule s{{}, 0, 0};
     const R3Shape s3 = r3_shape(L->n1, L->n2);
     if (!s3.ok || L->K > (int64_t)RS_QB * 512 * RS_QI * 4 || (s3.resident && s3.at < 6)) return s;
-    const bool terms = rt_serves(L);
-    if (terms && L->n1 <= 128) return s;
     s.rs = rs_shape(s3);
     if (!s.rs.ok) return s;
     // up to two workgroups per CU (one after the other where LDS lets only one be resident):
@@ -368,10 +366,6 @@ SplitRule split_rule(const bwla_layer_t* L) {
     // workgroups are free (measured, 128 x 64: 12.1 -> 11.1 us at four tokens, 12.2 -> 11.8 at
     // eight, 12.3 -> 12.9 at sixteen; 128 x 86: 16.7 -> 10.9 at one token, 17.1 -> 12.2 at sixteen).
     if (s3.resident && (s3.strips & 3) == 0 && s.tokens > 8) s.tokens = 8;
-    // Pairs that rotate_terms.hip takes: only the long ones, and while the extra workgroups are free (rotation and quantizing
-    // launch against its one: 224 x 128 at one token 13.4 / 15.2 us, at five 13.8 / 15.7, at sixteen 16.0 / 15.8; 160 x 160 13.7 /
-    // 13.9, 14.1 / 14.2, 15.4 / 14.3; but 128 x 86 at one token 12.3 / 8.8, 128 x 64 at two 10.2 / 7.3).
-    if (terms && s.tokens > 8) s.tokens = 8;
     return s;
 }
 }  // namespace

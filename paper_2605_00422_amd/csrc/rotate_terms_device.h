@@ -1,4 +1,4 @@
-// Device code of the rotation on 16-bit terms (rotate_terms.hip has the design).
+// Device code of the rotation by a group of strip wavefronts (rotate_terms.hip has the design).
 #pragma once
 #include "rotate_bf16_device.h"
 #include "rotate_terms.h"
@@ -14,10 +14,57 @@ __device__ __forceinline__ v4f rt_mma(v4i a, v4i b, v4f c) {
     else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a), __builtin_bit_cast(v8h_t, b), c, 0, 0, 0);
 }
 
+// Both stages of an fp32 token on fp32 MFMA (16x16x4): a lane's four values of a 16-byte read are the contraction indices of four
+// instructions, and the accumulators of stage 1 (Z[a = 4 lg + v][d = li]) are the A operands of stage 2 as they stand.  Each sum in
+// the order of rotate_f32_device.h: the same values to the bit.  wait: the R1 terms have to be waited for.
+template <int AT, int NB, typename Load>
+__device__ __forceinline__ void rotate_terms_f32(Load ld_a, const v4i (&bh)[NB], const char* r1, v4f (&y)[AT], int n1, int n2, bool wait) {
+    auto mul = [](float x, float w, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, w, c, 0, 0, 0); };
+#pragma nounroll
+    for (int ch = 0; ch < AT / 2; ++ch) {
+        const bool two = 32 * ch + 16 < n1;             // (else the second tile is past the rows)
+        v4f z0 = v4f{0.f, 0.f, 0.f, 0.f}, z1 = z0;
+        v4i x0 = ld_a(ch, 0, 0), x1 = ld_a(ch, 0, 1);
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb) {
+            if (16 * kb < n2) {
+                const v4i c0 = x0, c1 = x1;
+                if (16 * (kb + 1) < n2) { x0 = ld_a(ch, kb + 1, 0); x1 = ld_a(ch, kb + 1, 1); }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    z0 = mul(__int_as_float(c0[v]), __int_as_float(bh[kb][v]), z0);
+                    if (two) z1 = mul(__int_as_float(c1[v]), __int_as_float(bh[kb][v]), z1);
+                }
+            }
+        }
+        if (wait && ch == 0) bwla_lds_barrier();
+        const char* rb = r1 + 2 * ch * AT * 1024;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half == 0 || two) {
+                const v4f z = half ? z1 : z0;
+#pragma unroll
+                for (int tc = 0; tc < AT; tc += 2) {
+                    if (16 * tc < n1) {
+                        const v4f w0 = *reinterpret_cast<const v4f*>(rb + (half * AT + tc) * 1024);
+                        const v4f w1 = *reinterpret_cast<const v4f*>(rb + (half * AT + tc + 1) * 1024);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            y[tc] = mul(z[v], w0[v], y[tc]);
+                            y[tc + 1] = mul(z[v], w1[v], y[tc + 1]);
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
+
 // AT, K1M: the most 16-row tiles along n1 (padded to 32) and 32-deep steps along n2.  STREAM: the R1 terms of one step at a
 // time (n1 > 160).  MANY: workgroups walk over their tokens, G groups of wavefronts side by side; else one token a workgroup.
-template <int AT, int K1M, bool STREAM, bool MANY, bool F32, int THREADS>
+template <int AT, int K1M, bool STREAM, bool MANY, RtKind KIND, int THREADS>
 __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
+    constexpr bool F32 = KIND == RT_F32, H16 = KIND == RT_H16, BF = KIND == RT_BF16;
     extern __shared__ __align__(16) float lds_f[];
     const RqArgs& a = b.q;
     if ((int64_t)blockIdx.x >= a.rot_blocks) {
@@ -26,15 +73,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         else psp_block_at<!F32, !F32>(reinterpret_cast<char*>(lds_f), a, pb);
         return;
     }
-    // Small terms are added up before the large ones (stage 1), and apart from them over the steps of stage 2 where registers
-    // allow: fewer roundings at the sum's own magnitude.
-    constexpr bool SMALL_FIRST = K1M <= 3;
-    constexpr bool APART = AT > 2 && (AT <= 4 || (AT <= 8 && K1M <= 3 && !MANY));
-    // bf16 tokens and n1 <= 64: the factors and Z as three bf16 terms, six products.  Sums that short are nearer to the exact value
-    // than 22 bits (16 x 32, rms of a scale's error: 9.3e-8 on 16-bit terms, 6.6e-8 on three, 6.0e-8 so: bf16 products leave
-    // the sums of an instruction more room), and the token needs no scale.
-    constexpr bool BF = AT <= 4 && !F32;
-    constexpr int NX = F32 ? 3 : 1, VG = F32 ? 4 : 8;   // terms of the token; its values in 16 bytes
+    constexpr int VG = F32 ? 4 : 8, TW = BF && !MANY && K1M < 5 ? 2 : 1;       // values in 16 bytes; tiles of stage 2 side by side
     constexpr int CH2 = AT / 2, NI = CH2 * (8 / VG);    // 32-deep steps along n1; 16-byte granules of a token per thread
     char* lds = reinterpret_cast<char*>(lds_f);
     const int n1 = a.n1, n2 = a.n2, K = n1 * n2, k1 = b.s.k1, strips = b.s.strips;
@@ -54,7 +93,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     char* cb = b.s.own ? lds + b.s.r1_bytes + G * b.s.xt_bytes + grp * b.s.cb_bytes : xt;
     float* red = reinterpret_cast<float*>(lds + b.s.r1_bytes + G * (b.s.xt_bytes + (b.s.own ? b.s.cb_bytes : 0))) + grp * 64;
     int* redi = reinterpret_cast<int*>(red) + 48;
-    constexpr int CB = BF ? 3 * AT : 2 * AT, chunk_bytes = CB * 1024;     // blocks and bytes of a step of R1
+    constexpr int CB = BF ? 3 * AT : 2 * AT, chunk_bytes = CB * 1024;     // blocks and bytes of a step of R1 (fp32: two rows of tiles)
     const int pitch = b.s.pitch;
 
     // ---- R1 terms, global -> LDS, one KiB a request.  Resident: all of them, by the wavefronts behind the groups.  STREAM: the
@@ -81,7 +120,29 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     if (STREAM && helper) return;
     if (!STREAM && helper) {
         const int first = wv - G * strips, step = nwaves - G * strips;
-        for (int e = first; e < CH2 * CB; e += step) r1_async(e / CB, e % CB, r1 + e * 1024);
+        if constexpr (F32) {
+            // block ta AT + tc: R1[a = 16 ta + 4 lg + v][c = 16 tc + li], v = 0..3, eight of them in flight
+            const int l = (int)threadIdx.x & 63;
+            for (int e0 = first; e0 < AT * AT; e0 += 8 * step) {
+                v4f t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int e = e0 + u * step < AT * AT ? e0 + u * step : e0, ta = e / AT;
+                    const int row = 16 * ta + 4 * (l >> 4), c = 16 * (e - ta * AT) + (l & 15);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const bool in = row + v < n1 && c < n1;
+                        const float f = a.R1[in ? (row + v) * n1 + c : 0];
+                        t[u][v] = in ? f : 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (e0 + u * step < AT * AT) *reinterpret_cast<v4f*>(r1 + (e0 + u * step) * 1024 + l * 16) = t[u];
+            }
+        } else {
+            for (int e = first; e < CH2 * CB; e += step) r1_async(e / CB, e % CB, r1 + e * 1024);
+        }
         bwla_lds_barrier();                             // maxima
         bwla_lds_barrier();                             // token rows
         __builtin_amdgcn_s_waitcnt(0);
@@ -108,11 +169,20 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         }
     };
     request(t0);
-    v4i bh[K1M], bl[K1M], bx[BF ? K1M : 1];
+    constexpr int NB = F32 ? 2 * K1M : K1M;             // (fp32: R2[b = 16 kb + 4 lg + v][d] in bh[kb])
+    v4i bh[NB], bl[F32 ? 1 : K1M], bx[BF ? K1M : 1];
 #pragma unroll
-    for (int kb = 0; kb < K1M; ++kb) {
+    for (int kb = 0; kb < NB; ++kb) {
         const int kc = kb < k1 ? kb : 0;
-        if constexpr (BF) {
+        if constexpr (F32) {
+            const int row = 16 * kb + 4 * lg, d = 16 * wave + li;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool in = row + v < n2 && d < n2;
+                const float f = a.R2[in ? (row + v) * n2 + d : 0];
+                bh[kb][v] = __float_as_int(in ? f : 0.0f);
+            }
+        } else if constexpr (BF) {
             const uint16_t* src = a.R2p + ((wave * 16 + li) * (k1 * 32) + kc * 32 + 8 * lg);
             const int term = strips * 16 * k1 * 32;
             bh[kb] = *reinterpret_cast<const v4i*>(src);
@@ -128,14 +198,6 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
 
     // largest magnitude of the token in registers: bf16 magnitudes order like their 15 low bits
     auto token_max = [&]() -> float {
-        if constexpr (F32) {
-            float m = 0.0f;
-#pragma unroll
-            for (int e = 0; e < NI; ++e)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) m = fmaxf(m, fabsf(__int_as_float(xpre[e][i])));
-            return dl_wave_max_nonneg(m);
-        }
         typedef unsigned short us2 __attribute__((ext_vector_type(2)));
         us2 m = us2{0, 0};
 #pragma unroll
@@ -145,98 +207,64 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         const uint32_t top = m.x > m.y ? m.x : m.y;
         return dl_wave_max_nonneg(__uint_as_float(top << 16));
     };
-    // exponent field E of a token's largest magnitude: the token is scaled by 2^(129 - E), which puts that magnitude into
+    // H16: exponent field E of a token's largest magnitude: the token is scaled by 2^(129 - E), which puts that magnitude into
     // [2^2, 2^3), and what the two stages make of it by 2^(145 - E) then (256 R1, 256 R2).  Codes and zero points are the
     // same in that scale, so only the step that is stored goes back.
     auto exponent_of = [&](float xmax) -> int {
         const int E = (__float_as_int(xmax) >> 23) & 0xff;
         return E < 2 ? 2 : E;
     };
-    // zeros where a token row ends inside a 32-deep step, and in rows past n1
-    const int plane = CH2 * 32 * pitch;                 // bytes of a term of the token
+    // zeros where a token row ends inside a step along n2 (32 values; fp32: 16), and in rows past n1
     auto zero_pads = [&](int tz, int nz) {
-        const int cols = (k1 * 32 - n2) >> 1, prow = cols > 0 ? n1 : 0;          // words
+        const int words = F32 ? ((n2 + 15) & ~15) : k1 * 16, used = F32 ? n2 : n2 >> 1, cols = words - used;
         const FastDiv dc(cols > 0 ? cols : 1);
-        for (int i = tz; i < prow * cols; i += nz) {
+        for (int i = tz; i < n1 * cols; i += nz) {
             const int row = dc.div(i);
-#pragma unroll
-            for (int p = 0; p < NX; ++p) *reinterpret_cast<uint32_t*>(xt + p * plane + row * pitch + 2 * n2 + 4 * (i - row * cols)) = 0u;
+            *reinterpret_cast<uint32_t*>(xt + row * pitch + 4 * (used + i - row * cols)) = 0u;
         }
-        const int g = k1 * 4, rows = CH2 * 32 - n1;                              // 16-byte granules
+        const int g = words >> 2, rows = CH2 * 32 - n1;                          // 16-byte granules
         const FastDiv dg(g);
         for (int i = tz; i < rows * g; i += nz) {
             const int row = dg.div(i);
-#pragma unroll
-            for (int p = 0; p < NX; ++p) *reinterpret_cast<v4i*>(xt + p * plane + (n1 + row) * pitch + (i - row * g) * 16) = v4i{0, 0, 0, 0};
+            *reinterpret_cast<v4i*>(xt + (n1 + row) * pitch + (i - row * g) * 16) = v4i{0, 0, 0, 0};
         }
     };
-    // the token in registers -> fp16 rows in LDS
+    // the token in registers -> rows in LDS
     const bool whole = (n2 & (VG - 1)) == 0;
     const FastDiv drow(whole ? n2 / VG : n2 >> 1);
     auto land = [&](int E) {
         const int tid = my_tid();
         const float sx = __int_as_float((256 - E) << 23);
-        if constexpr (F32) {
-            // fp32 values as three fp16 terms: 24 bits and more, down to 2^-28 of the token's largest value
-#pragma unroll
-            for (int e = 0; e < NI; ++e) {
-                const int it = tid + e * TG;
-                uint32_t o[3][2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    float r0 = __int_as_float(xpre[e][2 * i]) * sx, r1 = __int_as_float(xpre[e][2 * i + 1]) * sx;
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) {
-                        const _Float16 h0 = (_Float16)r0, h1 = (_Float16)r1;
-                        r0 -= (float)h0; r1 -= (float)h1;
-                        o[p][i] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
-                    }
-                }
-                if (it < items) {
-                    if (whole) {
-                        const int row = drow.div(it), g = it - row * (n2 >> 2);
-#pragma unroll
-                        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(xt + p * plane + row * pitch + g * 8) = uint2{o[p][0], o[p][1]};
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) {                            // pairs of values: n2 is even
-                            const int q = it * 2 + i, row = drow.div(q);
-#pragma unroll
-                            for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t*>(xt + p * plane + row * pitch + (q - row * (n2 >> 1)) * 4) = o[p][i];
-                        }
-                    }
-                }
-            }
-            return;
-        }
 #pragma unroll
         for (int e = 0; e < NI; ++e) {
-            {
-                const int it = tid + e * TG;
-                v4i o = xpre[e];
+            const int it = tid + e * TG;
+            v4i o = xpre[e];
 #pragma unroll
-                for (int i = 0; !BF && i < 4; ++i) {
-                    const uint32_t w = (uint32_t)xpre[e][i];
-                    o[i] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w << 16) * sx, __uint_as_float(w & 0xffff0000u) * sx));
-                }
-                if (it < items) {
-                    if (whole) {
-                        const int row = drow.div(it), g = it - row * (n2 >> 3);
-                        *reinterpret_cast<v4i*>(xt + row * pitch + g * 16) = o;
-                    } else {
+            for (int i = 0; H16 && i < 4; ++i) {
+                const uint32_t w = (uint32_t)xpre[e][i];
+                o[i] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w << 16) * sx, __uint_as_float(w & 0xffff0000u) * sx));
+            }
+            if (it < items) {
+                if (whole) {
+                    const int row = drow.div(it), g = it - row * (n2 / VG);
+                    *reinterpret_cast<v4i*>(xt + row * pitch + g * 16) = o;
+                } else {
+                    // pairs of values: n2 is even
+                    constexpr int PAIRS = VG / 2, W = 4 / PAIRS;                 // of 16 bytes; words of one
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {                            // pairs of values: n2 is even
-                            const int p = it * 4 + i, row = drow.div(p);
-                            *reinterpret_cast<int*>(xt + row * pitch + (p - row * (n2 >> 1)) * 4) = o[i];
-                        }
+                    for (int i = 0; i < PAIRS; ++i) {
+                        const int p = it * PAIRS + i, row = drow.div(p);
+                        char* to = xt + row * pitch + (p - row * (n2 >> 1)) * (4 * W);
+                        if constexpr (W == 1) *reinterpret_cast<int*>(to) = o[i];
+                        else *reinterpret_cast<int2*>(to) = int2{o[2 * i], o[2 * i + 1]};
                     }
                 }
             }
         }
     };
-    const bool pads = (n2 & 31) != 0 || (n1 & 31) != 0;
+    const bool pads = (n2 & (F32 ? 15 : 31)) != 0 || (n1 & 31) != 0;
     if (pads) zero_pads(tid, TG);
-    if constexpr (!BF) {
+    if constexpr (H16) {
         const float m = token_max();
         if (lane == 0) red[32 + wave] = m;
     }
@@ -246,7 +274,8 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         const int w = (int)threadIdx.x & 15;
         return dl_wave_max_nonneg(w < strips ? p[w] : 0.0f);
     };
-    int E = BF ? 145 : exponent_of(over_strips(red + 32));
+    int E = 145;
+    if constexpr (H16) E = exponent_of(over_strips(red + 32));
     land(E);
     if constexpr (MANY) {
         if (b.rounds > 1) request(t0 + tstep);
@@ -269,18 +298,17 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         int lane_o = (int)threadIdx.x & 63;
         if constexpr (MANY) asm volatile("" : "+v"(lane_o));
         const int lane = lane_o, li = lane & 15, lg = lane >> 4;
-        v4f y[AT], ys[APART ? AT : 1];
+        v4f y[AT];
 #pragma unroll
         for (int tc = 0; tc < AT; ++tc) y[tc] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int tc = 0; tc < (APART ? AT : 1); ++tc) ys[tc] = v4f{0.f, 0.f, 0.f, 0.f};
         const char* xa = xt + li * pitch + lg * 16;
-        auto ld_a = [&](int ch, int kb, int half, int p = 0) -> v4i {
-            return *reinterpret_cast<const v4i*>(xa + p * plane + (32 * ch + 16 * half) * pitch + kb * 64);
+        auto ld_a = [&](int ch, int kb, int half) -> v4i {
+            return *reinterpret_cast<const v4i*>(xa + (32 * ch + 16 * half) * pitch + kb * 64);
         };
+        if constexpr (F32) rotate_terms_f32<AT, NB>(ld_a, bh, r1 + lane * 16, y, n1, n2, j == 0);
         v4i n0 = ld_a(0, 0, 0), n1_ = ld_a(0, 0, 1);
 #pragma nounroll
-        for (int ch = 0; ch < CH2; ++ch) {
+        for (int ch = 0; !F32 && ch < CH2; ++ch) {
             v4f z0 = v4f{0.f, 0.f, 0.f, 0.f}, z1 = z0;
             v4i qa0[K1M + 1], qa1[K1M + 1], qb[3][AT];
             qa0[0] = n0; qa1[0] = n1_;
@@ -290,35 +318,15 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
                 if (kb < k1) {
                     const v4i a0 = qa0[kb], a1 = qa1[kb];
                     if (kb + 2 < K1M && kb + 2 < k1) { qa0[kb + 2] = ld_a(ch, kb + 2, 0); qa1[kb + 2] = ld_a(ch, kb + 2, 1); }
-                    if constexpr (F32) {
-                        // the products with the token's small terms (not those of 2^-33 of the result)
-                        const v4i c0 = ld_a(ch, kb, 0, 1), c1 = ld_a(ch, kb, 1, 1);
-                        const v4i d0 = ld_a(ch, kb, 0, 2), d1 = ld_a(ch, kb, 1, 2);
-                        z0 = rt_mma<BF>(d0, bh[kb], z0);
-                        z1 = rt_mma<BF>(d1, bh[kb], z1);
-                        z0 = rt_mma<BF>(c0, bl[kb], z0);
-                        z1 = rt_mma<BF>(c1, bl[kb], z1);
-                        z0 = rt_mma<BF>(c0, bh[kb], z0);
-                        z1 = rt_mma<BF>(c1, bh[kb], z1);
-                    }
-                    if constexpr (BF) {
+                    if constexpr (BF) {                                          // small terms first
                         z0 = rt_mma<BF>(a0, bx[kb], z0);
                         z1 = rt_mma<BF>(a1, bx[kb], z1);
                     }
-                    z0 = rt_mma<BF>(a0, bl[kb], z0);
-                    z1 = rt_mma<BF>(a1, bl[kb], z1);
-                    if constexpr (!SMALL_FIRST) {
+                    if constexpr (!F32) {
+                        z0 = rt_mma<BF>(a0, bl[kb], z0);
+                        z1 = rt_mma<BF>(a1, bl[kb], z1);
                         z0 = rt_mma<BF>(a0, bh[kb], z0);
                         z1 = rt_mma<BF>(a1, bh[kb], z1);
-                    }
-                }
-            }
-            if constexpr (SMALL_FIRST) {
-#pragma unroll
-                for (int kb = 0; kb < K1M; ++kb) {
-                    if (kb < k1) {
-                        z0 = rt_mma<BF>(qa0[kb], bh[kb], z0);
-                        z1 = rt_mma<BF>(qa1[kb], bh[kb], z1);
                     }
                 }
             }
@@ -336,9 +344,12 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
                 if (j == 0 && ch == 0) bwla_lds_barrier();                       // the R1 terms are there
                 rb = r1 + ch * chunk_bytes + lane * 16;
             }
-            qb[0][0] = *reinterpret_cast<const v4i*>(rb);
-            qb[1][0] = *reinterpret_cast<const v4i*>(rb + AT * 1024);
-            if constexpr (BF) qb[2][0] = *reinterpret_cast<const v4i*>(rb + 2 * AT * 1024);
+            auto ld_b = [&](int tc) {
+#pragma unroll
+                for (int p = 0; p < (BF ? 3 : 2); ++p) qb[p][tc] = *reinterpret_cast<const v4i*>(rb + (p * AT + tc) * 1024);
+            };
+#pragma unroll
+            for (int u = 0; u < TW; ++u) ld_b(u);
             // lane (li, lg) holds Z[a = 32 ch + 4 lg + v (z0), 32 ch + 16 + 4 lg + v (z1)][d = li]: the eight contraction
             // positions of an A operand, in the order the R1 terms were stored in
             v4i ah, al, ax;
@@ -362,30 +373,25 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
             n0 = ld_a(cn, 0, 0); n1_ = ld_a(cn, 0, 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int tc = 0; tc < AT; ++tc) {
-                {
-                    const v4i ch_ = qb[0][tc], cl_ = qb[1][tc];
-                    if (tc + 1 < AT) {                 // (a tile past the last one reads what lies behind; never used)
-                        qb[0][tc + 1] = *reinterpret_cast<const v4i*>(rb + (tc + 1) * 1024);
-                        qb[1][tc + 1] = *reinterpret_cast<const v4i*>(rb + (AT + tc + 1) * 1024);
-                        if constexpr (BF) qb[2][tc + 1] = *reinterpret_cast<const v4i*>(rb + (2 * AT + tc + 1) * 1024);
-                    }
-                    v4f& small = APART ? ys[tc] : y[tc];
-                    if constexpr (BF) {
-                        small = rt_mma<BF>(ax, ch_, small);
-                        small = rt_mma<BF>(ah, qb[2][tc], small);
-                        small = rt_mma<BF>(al, cl_, small);
-                    }
-                    small = rt_mma<BF>(al, ch_, small);
-                    small = rt_mma<BF>(ah, cl_, small);
-                    y[tc] = rt_mma<BF>(ah, ch_, y[tc]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        if constexpr (APART) {
+            for (int tc = 0; tc < AT; tc += TW) {       // (the products of TW tiles in turn: those of one wait for each other)
+                if (tc + TW < AT) {
 #pragma unroll
-            for (int tc = 0; tc < AT; ++tc) y[tc] += ys[tc];
+                    for (int u = 0; u < TW; ++u) ld_b(tc + TW + u);
+                }
+                auto mul = [&](v4i x, int p) {
+#pragma unroll
+                    for (int u = 0; u < TW; ++u) y[tc + u] = rt_mma<BF>(x, qb[p][tc + u], y[tc + u]);
+                };
+                if constexpr (BF) {                     // small ones first
+                    mul(ax, 0);
+                    mul(ah, 2);
+                    mul(al, 1);
+                }
+                mul(al, 0);
+                mul(ah, 1);
+                mul(ah, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         // ---- the token's range (padded rows and columns are exact zeros); the next token's largest value
         float mx = 0.0f, mn = 0.0f;
@@ -406,7 +412,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         }
         if (lane == 0) { red[wave] = mx; red[16 + wave] = mn; }
         if constexpr (MANY) {
-            if (!BF && j + 1 < rounds) {
+            if (H16 && j + 1 < rounds) {
                 const float nm = token_max();
                 if (lane == 0) red[32 + wave] = nm;
             }
@@ -414,11 +420,11 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         bwla_lds_barrier();                             // also: everybody is done with the token rows
         const float hi = over_strips(red), lo = -over_strips(red + 16);
         float xmax = 0.0f;
-        if constexpr (MANY && !BF) xmax = over_strips(red + 32);
+        if constexpr (MANY && H16) xmax = over_strips(red + 32);
         const QuantPlan qp = quant_plan(hi, lo, a.qmax, a.asym != 0);
         // ---- codes, to LDS in k order.  Lane holds Yt[d = 16 strip + 4 lg + v][c = 16 tc + li]: four consecutive k.
-        // y * inv + (1.5 * 2^23 + zero point) rounds once, to an integer (ties to even) in the low mantissa bits; clamped as a
-        // float, its low byte is the code.
+        // The integer next to y * inv (ties to even) plus 1.5 * 2^23 and the zero point, clamped as a float, has the code in its
+        // low byte.  (H16: one rounding for the product and the sum, as in rotate_planes.hip; else quant_code's two.)
         const float inv = qp.inv, addc = 12582912.0f + qp.zc;
         const float cmin = 12582912.0f + qp.cmin, cmax = 12582912.0f + qp.cmax;
         int lsum = 0;
@@ -431,7 +437,8 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
                 uint32_t c4[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    c4[v] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(y[tc][v], inv, addc), cmin, cmax));
+                    c4[v] = __float_as_uint(__builtin_amdgcn_fmed3f(H16 ? __builtin_fmaf(y[tc][v], inv, addc) : rintf(y[tc][v] * inv) + addc,
+                                                                    cmin, cmax));
                 const uint32_t wlo = __builtin_amdgcn_perm(c4[1], c4[0], 0x0c0c0400u);     // bytes: c4[0], c4[1], 0, 0
                 const uint32_t whi = __builtin_amdgcn_perm(c4[3], c4[2], 0x04000c0cu);     // bytes: 0, 0, c4[2], c4[3]
                 uint32_t word = wlo | whi;
@@ -450,7 +457,8 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
         }
         lsum = dl_wave_sum(lsum);
         if (lane == 0) redi[wave] = lsum;
-        const float sc = ldexpf(quant_scale(hi, lo, a.qmax, a.asym != 0), E - 145);
+        float sc = quant_scale(hi, lo, a.qmax, a.asym != 0);
+        if constexpr (H16) sc = ldexpf(sc, E - 145);
         if constexpr (MANY) {
             if (!b.s.own) {                             // the codes lie where the next token goes: out first
                 bwla_lds_barrier();
@@ -458,7 +466,7 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
                 bwla_lds_barrier();
             }
             if (j + 1 < rounds) {
-                if constexpr (!BF) E = exponent_of(xmax);
+                if constexpr (H16) E = exponent_of(xmax);
                 if (pads && !b.s.own) zero_pads(tid, TG);
                 land(E);
                 if (j + 2 < rounds) request(t + 2 * tstep);
@@ -481,10 +489,10 @@ __global__ __launch_bounds__(THREADS) void rotate_terms_kernel(RtArgs b) {
     }
 }
 
-template <int AT, int K1M, bool STREAM, bool MANY, bool F32, int THREADS>
+template <int AT, int K1M, bool STREAM, bool MANY, RtKind KIND, int THREADS>
 hipError_t launch_v(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
     if (threads > THREADS) return hipErrorInvalidValue;
-    const auto kern = rotate_terms_kernel<AT, K1M, STREAM, MANY, F32, THREADS>;
+    const auto kern = rotate_terms_kernel<AT, K1M, STREAM, MANY, KIND, THREADS>;
     hipError_t e = bwla_ensure_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     kern<<<dim3((unsigned)blocks), dim3((unsigned)threads), lds, st>>>(b);
@@ -495,14 +503,14 @@ hipError_t launch_v(const RtArgs& b, int64_t blocks, int threads, size_t lds, hi
 template <bool MANY>
 hipError_t launch_terms(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
     const RtShape& s = b.s;
-#define RT_STREAM(A) if (s.stream && s.at == A) return launch_v<A, 4, true, MANY, false, 512>(b, blocks, threads, lds, st);
-    RT_STREAM(12) RT_STREAM(14) RT_STREAM(16)
+#define RT_STREAM(A) if (s.stream && s.at == A) return launch_v<A, 4, true, MANY, RT_BF16, 512>(b, blocks, threads, lds, st);
+    RT_STREAM(10) RT_STREAM(12) RT_STREAM(14) RT_STREAM(16)
 #undef RT_STREAM
 #define RT_CASE(A)                                                                                         \
-    if (s.at == A) return s.k1 <= 2   ? launch_v<A, 2, false, MANY, false, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
-                          : s.k1 <= 3 ? launch_v<A, 3, false, MANY, false, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
-                                      : launch_v<A, 5, false, MANY, false, 768>(b, blocks, threads, lds, st);
-    RT_CASE(2) RT_CASE(4) RT_CASE(6) RT_CASE(8) RT_CASE(10)
+    if (s.at == A) return s.k1 <= 2   ? launch_v<A, 2, false, MANY, RT_BF16, MANY || A >= 8 ? 768 : 512>(b, blocks, threads, lds, st) \
+                          : s.k1 <= 3 ? launch_v<A, 3, false, MANY, RT_BF16, MANY || A >= 8 ? 768 : 512>(b, blocks, threads, lds, st) \
+                                      : launch_v<A, 5, false, MANY, RT_BF16, 768>(b, blocks, threads, lds, st);
+    RT_CASE(2) RT_CASE(4) RT_CASE(6) RT_CASE(8)
 #undef RT_CASE
     return hipErrorInvalidValue;
 }
@@ -510,8 +518,8 @@ template <bool MANY>
 hipError_t launch_terms_f32(const RtArgs& b, int64_t blocks, int threads, size_t lds, hipStream_t st) {
     const RtShape& s = b.s;
 #define RT_CASE(A)                                                                                         \
-    if (s.at == A) return s.k1 <= 2 ? launch_v<A, 2, false, MANY, true, MANY ? 768 : 512>(b, blocks, threads, lds, st) \
-                                    : launch_v<A, 3, false, MANY, true, MANY ? 768 : 512>(b, blocks, threads, lds, st);
+    if (s.at == A) return s.k1 <= 2 ? launch_v<A, 2, false, MANY, RT_F32, MANY || A >= 8 ? 768 : 512>(b, blocks, threads, lds, st) \
+                                    : launch_v<A, 3, false, MANY, RT_F32, MANY || A >= 8 ? 768 : 512>(b, blocks, threads, lds, st);
     RT_CASE(2) RT_CASE(4) RT_CASE(6) RT_CASE(8)
 #undef RT_CASE
     return hipErrorInvalidValue;

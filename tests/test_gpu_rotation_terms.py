@@ -1,4 +1,4 @@
-"""Rotation and codes by the kernel on 16-bit terms (any even n2; bf16 tokens, and fp32 ones as three terms): every number of tiles along either factor,
+"""Rotation and codes by strips (any even n2; bf16 tokens on 16-bit terms of the factors, fp32 ones in fp32): every number of tiles along either factor,
 rows that end inside a tile or on no 16-byte boundary, one token a workgroup and workgroups that walk, against fp64."""
 import copy
 
@@ -42,7 +42,7 @@ CASES = [
     (270, 200, 80, 8, 6, True, True),
     (12, 256, 112, 0, 6, False, False),
     (3, 224, 128, 8, 6, False, False),      # few tokens: the split rotation
-    (16, 16, 32, 8, 6, False, False, "f32"),    # fp32 tokens: three terms
+    (16, 16, 32, 8, 6, False, False, "f32"),    # fp32 tokens
     (1, 46, 64, 8, 7, True, True, "f32"),
     (333, 64, 64, 32, 6, False, False, "f32"),  # riding, several workgroups a CU
     (20, 128, 86, 0, 8, False, False, "f32"),   # rows on 8-byte boundaries
