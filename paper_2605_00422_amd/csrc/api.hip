@@ -27,9 +27,16 @@ bwla_status_t check_shape(int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t 
     return BWLA_OK;
 }
 
+// Operand-order factors as one earlier library stored them, which some blobs still hold: of every pair with an even n2, padded
+// to multiples of 32.  (The same bytes for pairs that are such multiples; of the others nothing reads them.)
+uint64_t padded_planes_bytes(int n1, int n2) {
+    if (n1 > 256 || n2 > 160 || (n2 & 1) != 0) return 0;
+    const uint64_t ch2 = (n1 + 31) / 32, k1 = (n2 + 31) / 32, strips = (n2 + 15) / 16;
+    return bwla_decode_planes_r2_bytes(n1, n2) + (4 * ch2 * ch2 + 2 * strips * k1) * 1024;
+}
+
 // r counts the columns of V and T; U keeps the PSP columns only
-// (now false: as a library before laid it out, operand-order factors only of pairs that are multiples of 32)
-void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode, bool now = true) {
+void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, int32_t r, int32_t mode, bool padded = false) {
     const uint64_t rp = (uint64_t)((r + 15) & ~15);
     const uint64_t rpu = (uint64_t)((r - bwla_extra_cols(mode) + 15) & ~15);
     uint64_t off = 0;
@@ -43,7 +50,7 @@ void fill_layout(bwla_layer_t* L, int64_t N, int64_t K, int32_t n1, int32_t n2, 
     L->off_R1p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n1));
     L->off_R2p = off;   off = bwla_align256(off + bwla_factor_planes_bytes(n2));
     L->off_Rd = 0;
-    const uint64_t planes = now || bwla_planes_whole(n1, n2) ? bwla_decode_planes_bytes(n1, n2) : 0;
+    const uint64_t planes = padded ? padded_planes_bytes(n1, n2) : bwla_decode_planes_bytes(n1, n2);
     if (planes > 0) { L->off_Rd = off; off = bwla_align256(off + planes); }
     L->blob_bytes = off;
 }
@@ -55,15 +62,15 @@ bwla_status_t check_layer(const bwla_layer_t* L) {
     if (s != BWLA_OK) return s;
     if ((L->mode & ~(BWLA_MODE_ROW_SHIFT | BWLA_MODE_ASYM_ACT)) != 0 || L->r < bwla_extra_cols(L->mode))
         return BWLA_ERR_SHAPE;
-    auto laid_out = [&](bool now) {
+    auto laid_out = [&](bool padded) {
         bwla_layer_t ref;
-        fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode, now);
+        fill_layout(&ref, L->N, L->K, L->n1, L->n2, L->r, L->mode, padded);
         return ref.off_bits == L->off_bits && ref.off_alpha == L->off_alpha && ref.off_V == L->off_V &&
                ref.off_U == L->off_U && ref.off_R1 == L->off_R1 && ref.off_R2 == L->off_R2 &&
                ref.off_R1p == L->off_R1p && ref.off_R2p == L->off_R2p && ref.off_Rd == L->off_Rd &&
                ref.blob_bytes == L->blob_bytes;
     };
-    if (!laid_out(true) && !laid_out(false)) return BWLA_ERR_SHAPE;
+    if (!laid_out(false) && !laid_out(true)) return BWLA_ERR_SHAPE;
     if (!aligned16(L->d_blob)) return BWLA_ERR_ALIGN;
     return BWLA_OK;
 }

@@ -31,23 +31,21 @@ inline uint64_t bwla_factor_planes_bytes(int n) {
     return (uint64_t)3 * ((n + 15) & ~15) * ((n + 31) & ~31) * 2;
 }
 
-// Factor planes in MFMA operand order (one contiguous KiB per operand), stored for factors up to 256 and 160 of an even n2
-// (0 bytes otherwise), in this order:
+// Factor planes in MFMA operand order (one contiguous KiB per operand), stored for factor pairs
+// that are multiples of 32, n1 up to 256 and n2 up to 160 (0 bytes otherwise), three parts:
 //   R2d  three bf16 terms of R2, (n2 / 16) strips x (n2 / 32) steps x 3 KiB: only for the pairs the
 //        single-launch decode kernel takes (n1 of 32, 64 or 128, n2 of 32 or 64)
-//   R1h  two fp16 terms of 256 R1, padded with zeros to a multiple of 32: steps of 32 x 2 x tiles of 16 KiB
-//   R2h  two fp16 terms of 256 R2, padded likewise: strips of 16 x steps of 32 x 2 KiB
-inline bool bwla_planes_shape_ok(int n1, int n2) { return n1 <= 256 && n2 <= 160 && (n2 & 1) == 0; }
-// (the pairs for which a library before stored them)
-inline bool bwla_planes_whole(int n1, int n2) {
+//   R1h  two fp16 terms of 256 R1, (n1 / 32) steps x 2 x (n1 / 16) KiB
+//   R2h  two fp16 terms of 256 R2, (n2 / 16) strips x (n2 / 32) steps x 2 KiB
+inline bool bwla_planes_shape_ok(int n1, int n2) {
     return n1 >= 32 && n2 >= 32 && n1 <= 256 && n2 <= 160 && (n1 & 31) == 0 && (n2 & 31) == 0;
 }
 inline uint64_t bwla_decode_planes_r2_bytes(int n1, int n2) {
     const bool ok = (n1 == 32 || n1 == 64 || n1 == 128) && (n2 == 32 || n2 == 64);
     return ok ? (uint64_t)(n2 / 16) * (n2 / 32) * 3 * 1024 : 0;
 }
-inline uint64_t bwla_planes_r1h_bytes(int n1) { const uint64_t s = (n1 + 31) / 32; return s * 2 * (2 * s) * 1024; }
-inline uint64_t bwla_planes_r2h_bytes(int n2) { return (uint64_t)((n2 + 15) / 16) * ((n2 + 31) / 32) * 2 * 1024; }
+inline uint64_t bwla_planes_r1h_bytes(int n1) { return (uint64_t)(n1 / 32) * 2 * (n1 / 16) * 1024; }
+inline uint64_t bwla_planes_r2h_bytes(int n2) { return (uint64_t)(n2 / 16) * (n2 / 32) * 2 * 1024; }
 inline uint64_t bwla_decode_planes_bytes(int n1, int n2) {
     if (!bwla_planes_shape_ok(n1, n2)) return 0;
     return bwla_decode_planes_r2_bytes(n1, n2) + bwla_planes_r1h_bytes(n1) + bwla_planes_r2h_bytes(n2);

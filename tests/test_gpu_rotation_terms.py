@@ -125,15 +125,19 @@ def test_rotation_of_any_pair(M, n1, n2, r, bits, shift, asym, x):
 
 
 @pytest.mark.parametrize("M,n1,n2,x", [(4, 64, 80, "bf16"), (300, 64, 80, "f32"), (40, 128, 86, "bf16"), (300, 128, 86, "bf16")])
-def test_layers_packed_without_operand_order_factors(M, n1, n2, x):
-    """A layer that was packed and kept before its pair had them: the same bytes, fewer of them."""
+def test_layers_packed_with_operand_order_factors(M, n1, n2, x):
+    """A layer that was packed and kept when pairs like its own had them: more bytes behind the same ones."""
     from paper_2605_00422_amd import binding as B
     g = torch.Generator(device=DEV)
     g.manual_seed(M)
     layer, R, U = _layer(g, n1, n2, 16, False, False)
+    up = lambda n, to: (n + to - 1) // to                   # noqa: E731
     old = copy.copy(layer)
     old.desc = type(layer.desc).from_buffer_copy(layer.desc)
-    old.desc.blob_bytes, old.desc.off_Rd = layer.desc.off_Rd, 0
+    size = (4 * up(n1, 32) ** 2 + 2 * up(n2, 16) * up(n2, 32)) * 1024
+    old.desc.off_Rd, old.desc.blob_bytes = layer.desc.blob_bytes, layer.desc.blob_bytes + up(size, 256) * 256
+    old.blob = torch.cat([layer.blob[:layer.desc.blob_bytes], torch.full((up(size, 256) * 256,), 255, dtype=torch.uint8, device=DEV)])
+    old.desc.d_blob = old.blob.data_ptr()
     X = torch.randn(M, n1 * n2, device=DEV, generator=g)
     X = X.to(torch.bfloat16) if x == "bf16" else X
     act = B.Activations(old, M)
