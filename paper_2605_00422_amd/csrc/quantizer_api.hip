@@ -16,7 +16,7 @@ constexpr size_t PART_BYTES = (size_t)64 << 20;   // partial products of split c
 // (n n1) x n2, the rotated rows, and the centered rows / the MM targets.
 struct QPlan {
     int n, m, n1, n2, k, p, jn;
-    size_t big[5], R1, R2, C, A, Bt, A2, Bt2, c, s2, rowpart, rowpart2, scal, ritz, Q, Q2, Zs, G, Vs, Ws, sig, prev, lam,
+    size_t big[5], R1, R2, C, A, Bt, A2, Bt2, c, s2, rowpart, rowpart2, scal, norm, ritz, Q, Q2, Zs, G, Vs, Ws, sig, prev, lam,
         jwork, flags, partials, bytes;
 };
 
@@ -42,7 +42,7 @@ bwla_status_t make_plan(int64_t n, int64_t m, int32_t n1, int32_t n2, int32_t k,
     P.A = take((size_t)n * k * D); P.Bt = take((size_t)m * k * D);
     P.A2 = take((size_t)n * k * D); P.Bt2 = take((size_t)m * k * D);
     P.c = take(n * D); P.s2 = take(n * D); P.rowpart = take(n * D); P.rowpart2 = take(n * D);
-    P.scal = take(64 * D); P.ritz = take(sizeof(QRitz));
+    P.scal = take(64 * D); P.norm = take(D); P.ritz = take(sizeof(QRitz));
     P.Q = take((size_t)m * p * D); P.Q2 = take((size_t)m * p * D); P.Zs = take((size_t)n * p * D);
     P.G = take(jj * D); P.Vs = take(jj * D); P.Ws = take(jj * D);
     P.sig = take(P.jn * D); P.prev = take(P.jn * D); P.lam = take(P.jn * D);
@@ -243,8 +243,9 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
         auto ns_ortho = [&](double* src, double* dst) {                 // src is overwritten; result in dst
             x.ck(bwla_q_launch_set_int(done, 0, x.st));
             gram(src, m, nullptr);
-            x.ck(bwla_q_launch_gram_inv_norm(G, p, x.d(P.scal), x.st));
-            x.ck(bwla_q_launch_scale_by(src, (size_t)m * p, x.d(P.scal), x.st));
+            // (not to scal: a proximal step's factor waits there for the truncation to end)
+            x.ck(bwla_q_launch_gram_inv_norm(G, p, x.d(P.norm), x.st));
+            x.ck(bwla_q_launch_scale_by(src, (size_t)m * p, x.d(P.norm), x.st));
             auto step = [&](const double* a, double* b, const int* skip) {
                 gram(a, m, skip);
                 QGemm u = qgemm_plain(a, G, b, m, p, p);                  // b = 1.5 a - 0.5 a G
