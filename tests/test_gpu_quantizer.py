@@ -108,6 +108,25 @@ def test_em_floor_and_degenerate_rows():
     assert np.allclose(s2.cpu().numpy(), s2o, rtol=1e-12)
 
 
+# (rows in registers, and a row that is read again by every step)
+@pytest.mark.parametrize("m", [2048, 16386])
+@pytest.mark.parametrize("c0", [1.0, 1e-3, 1e-8, 1e-200])
+def test_em_step_keeps_the_digits_of_a_small_c(m, c0):
+    """c = mean of x tanh(c x / s^2), terms of one sign, with c far below s: all of them small.  A term is right to some four roundings
+    and a sum of m to log2 m more of them (threads' sums and trees), against 80 bits."""
+    qb = _qb()
+    n = 4
+    X = np.random.default_rng(m).standard_normal((n, m))
+    c, s2 = _dev(np.full(n, c0)), _dev(np.full(n, 1.1))
+    qb.em_step(_dev(X), Q.S2_MIN, c, s2)
+    x, c80, v80 = X.astype(np.longdouble), np.longdouble(c0), np.longdouble(1.1)
+    t = np.tanh(c80 * x / v80)
+    want = (t * x).mean(1)
+    assert np.max(np.abs(c.cpu().numpy() - want) / want) < (8 + np.log2(m)) * 2.0 ** -52
+    v = ((1 + t) / 2 * (x - want[:, None]) ** 2 + (1 - t) / 2 * (x + want[:, None]) ** 2).mean(1)
+    assert np.max(np.abs(s2.cpu().numpy() - v) / v) < (8 + np.log2(m)) * 2.0 ** -52
+
+
 @pytest.mark.parametrize("nn", [1, 2, 5, 16, 33, 64, 100, 160, 224, 256])
 def test_svd_square_against_lapack(nn):
     """One-sided Jacobi: singular values, orthogonality and the reconstruction G = U S V^T."""
