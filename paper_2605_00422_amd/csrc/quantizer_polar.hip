@@ -5,8 +5,8 @@
 // quadratically, and the singular vectors stay.  X and G = X^T X live in LDS (rows of n + 2 doubles: the 16 rows of an
 // operand along k and the four of one along rows each spread over all banks), both products are fp64 MFMAs, tiles of
 // 16 x 16 dealt to eight wavefronts.  X starts as C / ||C||_F; the first G gives a closer bound on the largest singular
-// value, its largest absolute row sum, and the first step is scaled by it.  When G is I to 1e-7 the step that follows
-// leaves I to rounding, and the last one is done.  A singular C, or one of condition beyond 1e9, does not get there in 64
+// value, its largest absolute row sum, and the first step is scaled by it.  When every entry of G is that of I to 3e-9 the step that
+// follows leaves 3/4 (G - I)^2, at most n x 0.75e-17 an entry and so I to rounding, and the last one is done.  A singular C, or one of condition beyond 1e9, does not get there in 64
 // steps: `done` stays 0 and R as it was, unless `always`.
 //
 // Bound by the chain of steps: two products of 256 MFMAs (64 wide) on one CU's matrix cores, 4096 cycles each, and five
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(PT) void polar_kernel(const double* C, int n, doubl
             return g;
         });
         off = largest(off);                                 // (its barriers are G's too)
-        converged = off <= 1.0e-7;
+        converged = off <= 3.0e-9;
         double f = 1.0;
         if (step == 0) {
             double sum = 0.0;

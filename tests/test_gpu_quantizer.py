@@ -373,6 +373,23 @@ def test_procrustes_of_ragged_factors(n, n1, n2):
         assert np.max(np.abs(got - want)) < 1e-9
 
 
+@pytest.mark.parametrize("n1", [16, 48, 64, 80, 96])
+def test_procrustes_is_orthogonal_to_rounding(n1):
+    """An entry of R^T R is a sum of n1 products, sqrt(n1) eps off by their roundings; the largest of n1^2, and as much again from the
+    products that made R: within 16 times that.  Matrices of condition 1 to 1e5, whose iterations end at different distances."""
+    qb = _qb()
+    n, n2 = 300, 16
+    for seed in range(3):
+        rng = np.random.default_rng(seed * 7 + n1)
+        W = rng.standard_normal((n, n1 * n2)) * np.exp(rng.standard_normal((1, n1 * n2)) * (0.2 + seed))
+        R1, R2 = np.linalg.qr(rng.standard_normal((n1, n1)))[0], np.linalg.qr(rng.standard_normal((n2, n2)))[0]
+        c, s2 = np.abs(rng.standard_normal(n)) * 0.3 + 0.5, np.abs(rng.standard_normal(n)) * 0.3 + 0.2
+        R = torch.empty(n1, n1, dtype=torch.float64, device="cuda")
+        qb.procrustes(1, _dev(W), _dev(R1), _dev(R2), _dev(c), _dev(s2), R, _ws(n, n1 * n2, n1, n2, 0))
+        r = R.cpu().numpy().astype(np.longdouble)
+        assert np.max(np.abs(r.T @ r - np.eye(n1))) < 16 * 2.0 ** -52 * np.sqrt(n1)
+
+
 @pytest.mark.parametrize("n1", [32, 80])
 def test_procrustes_of_a_singular_matrix(n1):
     """Rows of V_i that are zero in every row of the layer: C1 is singular, its polar factor not unique, the result finite."""
