@@ -289,7 +289,7 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
         if (ru > 0 && !merged && !leave) return bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st);
         return hipSuccess;
     }
-    if (rt_serves(L, xdtype, M, bwla_device_cus())) {
+    if (rt_serves(L, xdtype, M, bwla_device_cus(), merged ? pblocks : 0)) {
         e = bwla_launch_rotate_terms(L, a, pblocks, merged, xdtype != BWLA_X_BF16, st);
         if (e != hipSuccess) return e;
         return ru > 0 && !merged && !leave ? bwla_launch_psp_prefill(L, dX, xdtype, M, dT, dws, plan, st) : hipSuccess;

@@ -58,9 +58,14 @@ hipError_t bwla_launch_rotate_terms(const bwla_layer_t* L, const RqArgs& a, int6
 // More tokens than CUs, in rows long enough that a token has a CU to itself: walking, with the projection in front, 128 x 64 at 300
 // tokens takes 16.8 us, a workgroup a token with the projection riding 18.4; 16 x 32 at 512 tokens 11 and 6.7.  With R1 streamed
 // where one token is in flight a workgroup, walking saves nothing that the projection could not ride behind: rank 32, 257 tokens,
-// 144 x 112 42.3 walking and 32.8 riding, 200 x 80 58.8 and 47.6; two in flight 172 x 64 29.1 and 31.7.
+// 144 x 112 42.3 walking and 32.8 riding, 200 x 80 58.8 and 47.6; two in flight 172 x 64 29.1 and 31.7.  Nor with R1 resident and seven
+// strips or more (six and few rows), of which one token is in flight too, before the second round is half full:
+// 257 tokens 48 x 96 17.9 and 8.8, 48 x 112 23.4 and 16.9, 128 x 112 39.1 and 31.2, 300 tokens 80 x 128 30.7 and 25.2.
 bool bwla_rotation_walks(const bwla_layer_t* L, int xdtype, int64_t M) {
     if (bwla_rotate_planes_serves(L, xdtype, M)) return true;
-    return xdtype == BWLA_X_BF16 && L->K >= 2048 && M > bwla_device_cus() && (L->n1 <= 128 || L->n2 <= 64) &&
-           rt_serves(L, xdtype, M, bwla_device_cus());
+    const int64_t cus = bwla_device_cus();
+    if (xdtype != BWLA_X_BF16 || L->K < 2048 || M <= cus || (L->n1 > 128 && L->n2 > 64)) return false;
+    if (2 * M <= 3 * cus && (L->n2 > 96 || (L->n2 > 80 && L->n1 <= 64))) return false;
+    if (M < 2 * cus && L->n1 > 128 && L->n2 <= 16) return false;       // (rt_serves: not where the projection rides)
+    return rt_serves(L, xdtype, M, cus, 0);
 }

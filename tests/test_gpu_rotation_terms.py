@@ -49,6 +49,18 @@ CASES = [
     (1030, 64, 80, 8, 6, True, False, "f32"),   # walking
     (770, 128, 96, 0, 6, False, True, "f32"),   # the largest that it takes
     (9, 128, 100, 0, 6, False, False, "f32"),    # and the first that it does not
+    # calls on either side of the lines that leave a pair to the other kernels: one strip or two with R1 streamed, ten strips
+    (64, 144, 16, 8, 6, False, False), (256, 160, 16, 32, 6, True, False), (300, 144, 16, 32, 6, False, False),
+    (512, 192, 16, 0, 6, False, True), (513, 192, 16, 0, 6, False, False), (1024, 256, 16, 8, 6, False, False),
+    (64, 224, 32, 0, 6, False, False), (128, 192, 24, 8, 6, False, False), (129, 192, 24, 8, 6, False, False),
+    (64, 112, 160, 0, 6, False, False), (64, 96, 160, 8, 6, False, False),
+    # riding and walking: seven and eight strips, six and few rows, a token or one and a half a CU
+    (257, 48, 96, 32, 6, False, False), (384, 64, 112, 32, 6, True, True), (385, 64, 112, 32, 6, False, False),
+    (300, 128, 128, 64, 6, False, False),
+    # fp32: uneven pairs, the projection's workgroups beside them or none, rounds that two groups a workgroup take as well as three
+    (64, 80, 16, 0, 6, False, False, "f32"), (64, 96, 32, 8, 6, True, False, "f32"), (257, 80, 48, 0, 6, False, False, "f32"),
+    (600, 80, 48, 0, 6, False, True, "f32"), (700, 48, 80, 0, 6, False, False, "f32"), (256, 112, 32, 32, 6, False, False, "f32"),
+    (256, 104, 16, 32, 6, False, False, "f32"), (300, 112, 80, 32, 6, False, False, "f32"), (1024, 96, 48, 0, 6, False, False, "f32"),
 ]
 
 
