@@ -102,9 +102,8 @@ BWLA_API bwla_status_t bwla_q_svd_square(const double* d_G, int32_t nn, double* 
  * Cholesky factor of its Gram matrix, and a final Rayleigh-Ritz step.  It stops when the work of `iters` plain
  * iterations is done -- `iters` products with S up to 24, half as many or a third (at least 24, 64) above, which the
  * filter makes up for --
- * or earlier once the k leading Ritz values have settled: moved by at most `tol` (relative) in one iteration, or are
- * within tol / 16, going by their last two movements; the remaining launches then return at
- * once.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead,
+ * or earlier once the k leading Ritz values have settled, moved by at most `tol` (relative) in one iteration; the
+ * remaining launches then return at once.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead,
  * are not filtered, have no Ritz values along the way and always run all `iters` iterations.)  The captured
  * energy converges like T_2(2 sigma_k^2 / sigma_{p+1}^2 - 1)^(-iters); a spectrum without a gap behind
  * sigma_k needs many iterations for the singular vectors themselves.

@@ -586,7 +586,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int jj = t; jj < n; jj += JT) a.sig[jj] = sg[ord[jj]];
     if (a.it && !a.quick && w == 0) {
         // Ritz values of S out of the eigenvalues sg of the filtered block's Gram matrix
-        const double theta = a.it->theta, power = a.it->power, before = a.it->moved;
+        const double theta = a.it->theta, power = a.it->power;
         auto ritz = [&](int jj) {
             const double r = sqrt(sg[ord[jj]]);
             if (a.degree == 1) return r * a.scale;
@@ -603,13 +603,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int off = 32; off > 0; off >>= 1) moved = fmax(moved, __shfl_xor(moved, off, 64));
         if (lane == 0) {
             const double top = ritz(0), next = ritz(n - 1);
-            // The first call has no values, so the first movement is the second's to the third, and a quotient takes two.  Values of
-            // a filtered block are those of the block before it, to the square of an angle, so the last movement is the error
-            // that the block two calls back had, and this one's is two quotients of movements smaller.
-            const double rate = moved / before;
-            const bool still = a.call >= 3 && moved <= a.tol;
-            const bool soon = a.call >= 4 && rate <= 0.5 && moved * rate * rate <= 0.0625 * a.tol;
-            if (still || soon) *a.done = a.call;
+            if (a.call >= 3 && moved <= a.tol) *a.done = a.call;        // (the first call has no values)
             // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
             // orthonormalizing takes out as long as that is small against one.  With values further apart the block is
             // multiplied by S^2, whose columns span as much, so that nothing is asked of theta.
@@ -617,7 +611,6 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             const double inv = cheb ? 1.0 / next : top > 0.0 ? 1.0 / top : 0.0;
             a.it->theta = next;
             a.it->power = cheb ? 0.0 : top;
-            a.it->moved = moved;
             a.it->first[0] = cheb ? 2.0 * inv : inv;
             a.it->first[1] = cheb ? -1.0 : 0.0;
             a.it->first[2] = 0.0;

@@ -474,6 +474,50 @@ def test_truncate_rank_of_a_wide_spectrum(n, m, k, spread):
     assert np.max(np.abs(b.T @ b - np.eye(k))) < 1e-12
 
 
+def _spectrum(n, m, s, seed):
+    """A matrix of the given singular values, and its truncation."""
+    rng = np.random.default_rng(seed)
+    p = min(n, m)
+    u, v = np.linalg.qr(rng.standard_normal((n, p)))[0], np.linalg.qr(rng.standard_normal((m, p)))[0]
+    s = np.sort(np.asarray(s))[::-1]
+    return (u * s) @ v.T, lambda k: (u[:, :k] * s[:k]) @ v[:, :k].T
+
+
+def _truncated(Y, k, iters, tol):
+    qb = _qb()
+    n, m = Y.shape
+    A = torch.empty(n, k, dtype=torch.float64, device="cuda")
+    Bt = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(qb.workspace_size(n, m, 1, 1, k), dtype=torch.uint8, device="cuda")
+    qb.truncate_rank(_dev(Y), k, iters, tol, A, Bt, None, ws)
+    b = Bt.cpu().numpy()
+    assert np.max(np.abs(b.T @ b - np.eye(k))) < 1e-12
+    return A.cpu().numpy() @ b.T
+
+
+@pytest.mark.parametrize("factor", [3.0, 5.0, 10.0])
+@pytest.mark.parametrize("n,m,k", [(400, 300, 8), (900, 640, 32)])
+def test_truncate_rank_stops_no_farther_than_plain_iterations(n, m, k, factor):
+    """Leading values in one group above the rest: subspace iteration without a filter, stopped by the same rule (the leading Ritz values
+    moved by at most tol), is not nearer to the truncation where it stops -- but for the rounding of products with Y, 1e-13."""
+    p = min(n, m)
+    rng = np.random.default_rng(1)
+    Y, best = _spectrum(n, m, np.concatenate([factor * (1 + 0.01 * rng.uniform(0, 1, k)), rng.uniform(0.05, 1.0, p - k)]), 5)
+    want = best(k)
+    for iters, tol in ((200, 1e-12), (60, 1e-14)):
+        block, before = np.linalg.qr(rng.standard_normal((m, max(2 * k, k + 16))))[0], None
+        for _ in range(iters):
+            w, g = np.linalg.eigh((Y @ block).T @ (Y @ block))
+            w, nxt = w[::-1], np.linalg.qr(Y.T @ (Y @ block))[0]
+            if before is not None and np.max(np.abs(w[:k] ** 2 - before[:k] ** 2) / w[:k] ** 2) <= tol:
+                break
+            before, block = w, nxt
+        z = Y @ block
+        g = np.linalg.eigh(z.T @ z)[1][:, ::-1][:, :k]
+        plain = _rel(z @ g @ (block @ g).T, want)
+        assert _rel(_truncated(Y, k, iters, tol), want) <= max(plain, 1e-13)
+
+
 # (contractions past 2048 with ragged ends, results of 24 to 80 columns in tiles of 64: the kernels that take operands
 # straight from memory, with and without a split of the contraction)
 @pytest.mark.parametrize("n,m,k", [(2055, 64, 8), (3001, 98, 40), (2500, 2306, 30)])
