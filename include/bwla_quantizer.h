@@ -98,15 +98,18 @@ BWLA_API bwla_status_t bwla_q_svd_square(const double* d_G, int32_t nn, double* 
  * column j = sigma_j u_j) and Bt = V_k (m x k, orthonormal columns); d_sig (may be NULL) gets the k
  * singular values.  Computed by block subspace iteration on S = Y^T Y with a block of
  * min(n, m, max(2 k, k + 16)) vectors from a fixed pseudo-random start, filtered by a Chebyshev polynomial of
- * degree two in S whose interval ends at the smallest Ritz value, re-orthonormalized every iteration through the
- * Cholesky factor of its Gram matrix, and a final Rayleigh-Ritz step.  It stops when the work of `iters` plain
- * iterations is done -- `iters` products with S up to 24, half as many or a third (at least 24, 64) above, which the
- * filter makes up for --
- * or earlier once the k leading Ritz values have settled, moved by at most `tol` (relative) in one iteration; the
- * remaining launches then return at once.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by the Newton-Schulz iteration instead,
- * are not filtered, have no Ritz values along the way and always run all `iters` iterations.)  The captured
- * energy converges like T_2(2 sigma_k^2 / sigma_{p+1}^2 - 1)^(-iters); a spectrum without a gap behind
- * sigma_k needs many iterations for the singular vectors themselves.
+ * degree two in S whose interval ends at the smallest Ritz value theta, re-orthonormalized every iteration through the
+ * Cholesky factor of its Gram matrix, and a final Rayleigh-Ritz step.  (With Ritz values more than 1e6 apart, i.e. singular values
+ * 1000 apart, what the first of the filter's two products leaves of the large directions in the columns of the small ones is taken out
+ * before the second; a block whose theta is below 1e-13 of the largest, which is rounding, goes by S^2.)
+ * It stops after N products with S, N = min(iters, max(24, iters / 2), max(64, iters / 3)), and one more where that is even
+ * and above two, which do the work of `iters` plain ones; or earlier once the k leading Ritz values have settled, moved by at
+ * most `tol` (relative) in one iteration: the remaining launches then return at once.
+ * The energy that is missed falls by (sigma_{p+1} / sigma_k)^4 with each of the first three products, and by
+ * T_2(2 sigma_k^2 / theta - 1)^2 with each two of the others, theta rising to sigma_p^2; a spectrum without a gap behind sigma_k
+ * needs many iterations for the singular vectors themselves.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by
+ * the Newton-Schulz iteration instead, are not filtered, have no Ritz values along the way and always run all `iters` iterations
+ * of one product.)
  * d_ws: bwla_quantizer_workspace_size(n, m, 1, 1, k) bytes.
  */
 BWLA_API bwla_status_t bwla_q_truncate_rank(const double* d_Y, int64_t n, int64_t m, int32_t k, int32_t iters,

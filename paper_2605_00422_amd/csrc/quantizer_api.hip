@@ -291,6 +291,7 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     const int half_of = iters / 2 > 24 ? iters / 2 : 24, third_of = iters / 3 > 64 ? iters / 3 : 64;
     int budget = iters < half_of ? iters : half_of;
     if (third_of < budget) budget = third_of;
+    if (budget > 2) budget |= 1;            // (one, and pairs of which the first may count for one: a spectrum far apart)
     QJacobi turn = eig;
     turn.ortho = true; turn.it = ritz; turn.prev = x.d(P.prev); turn.lead = k; turn.tol = tol; turn.done = done; turn.skip = done;
     auto apply = [&](const double* src, double* dst, const double* coef, const double* c0, const double* c1) {
@@ -302,7 +303,10 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     for (int used = 0, call = 1; used < budget; ++call) {
         const bool two = used > 0 && used + 2 <= budget;
         apply(Q, Q2, two ? ritz->first : nullptr, two ? Q : nullptr, nullptr);
-        if (two) apply(Q2, Q2, ritz->second, Q2, Q);
+        if (two) {
+            x.ck(bwla_q_launch_deflate(Q, Q2, m, p, ritz, x.d(P.prev), done, x.st));
+            apply(Q2, Q2, ritz->second, Q2, Q);
+        }
         gram(Q2, m, done);
         turn.degree = two ? 2 : 1; turn.call = call;
         turn.quick = used == 0;

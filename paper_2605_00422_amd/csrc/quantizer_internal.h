@@ -110,8 +110,9 @@ hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, 
 // that is at most 1 on [0, theta] and grows fastest beyond (Rutishauser's simultaneous iteration, 1970),
 // theta being the smallest Ritz value of the block.  QRitz is what a Jacobi call on the Gram matrix of the
 // filtered block leaves for the next iteration: theta, the coefficients of the filter's two products
-// (QGemm::coef).  power > 0 says that the filter is (S / power)^2 instead.
-struct QRitz { double first[3], second[3], theta, power; };
+// (QGemm::coef).  power > 0 says that the filter is (S / power)^2 instead, power < 0 that it is S / -power and the second product
+// of no account; wide that the Ritz values are far apart, and the first product is to be deflated (below).
+struct QRitz { double first[3], second[3], theta, power; int wide; };
 struct QJacobi {
     const double* G; int n; double pw;
     double* sig; double* Ws; double* Vs; double* work;
@@ -124,6 +125,10 @@ struct QJacobi {
     QRitz* it; double* prev; int lead, degree, call; double tol, scale; int* done;
 };
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st);
+// Where it->wide: takes out of each column j of U (m x p, a filter's first product of the orthonormal block Q) what it has of the columns of Q whose
+// Ritz values are 100 times its own and more: rounding, as Q^T S Q is diagonal.  prev: the squared Ritz values.
+hipError_t bwla_q_launch_deflate(const double* Q, double* U, int m, int p, const QRitz* it, const double* prev, const int* skip,
+                                 hipStream_t st);
 constexpr int BWLA_Q_JACOBI_LDS = 96;        // largest matrix whose two work arrays fit LDS
 constexpr int BWLA_Q_JACOBI_SYM_LDS = 136;   // ... whose one array does (sym)
 

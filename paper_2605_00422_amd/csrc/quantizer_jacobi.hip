@@ -272,17 +272,30 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             for (int j = w; j < n; j += JW)
                 for (int i = lane; i < n; i += 64) Wc[(size_t)j * ld + i] = a.quick ? (i == j ? 1.0 : 0.0) : Lt[(size_t)j * ldt + i];
         if (a.quick && w == 0) {
-            // the next filter is (S / power)^2, power some size of the columns
-            double top = 0.0;
-            for (int j = lane; j < n; j += 64) top = fmax(top, sg[j]);
+            // the next filter is (S / power)^2, power some size of the columns; or S / power, once, where pivots 1e5 apart say that
+            // S^2 would leave nothing of the small directions
+            double top = 0.0, most = 0.0, least = 1.0e300;
+            for (int j = lane; j < n; j += 64) {
+                top = fmax(top, sg[j]);
+                most = fmax(most, di[j]);
+                least = fmin(least, di[j]);
+            }
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) top = fmax(top, __shfl_xor(top, off, 64));
+            for (int off = 32; off > 0; off >>= 1) {
+                top = fmax(top, __shfl_xor(top, off, 64));
+                most = fmax(most, __shfl_xor(most, off, 64));
+                least = fmin(least, __shfl_xor(least, off, 64));
+            }
             top = top > 0.0 ? sqrt(1.0e14 * top) * a.scale : 1.0;
+            const bool once = !(most <= 1.0e5 * least);
             if (lane < 3) {
                 a.it->first[lane] = lane ? 0.0 : 1.0 / top;
-                a.it->second[lane] = lane ? 0.0 : 1.0 / top;
+                a.it->second[lane] = once ? (lane == 1 ? 1.0 : 0.0) : lane ? 0.0 : 1.0 / top;
             }
-            if (lane == 0) a.it->power = top;
+            if (lane == 0) {
+                a.it->power = once ? -top : top;
+                a.it->wide = 0;
+            }
         }
     }
     const int np = (n + 1) & ~1;
@@ -590,6 +603,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         auto ritz = [&](int jj) {
             const double r = sqrt(sg[ord[jj]]);
             if (a.degree == 1) return r * a.scale;
+            if (power < 0.0) return -power * r;
             if (power > 0.0) return power * sqrt(r);
             return 0.5 * theta * (sqrt(0.5 * (r + 1.0)) + 1.0);         // r = 2 x^2 - 1, x = 2 l / theta - 1
         };
@@ -605,12 +619,18 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             const double top = ritz(0), next = ritz(n - 1);
             if (a.call >= 3 && moved <= a.tol) *a.done = a.call;        // (the first call has no values)
             // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
-            // orthonormalizing takes out as long as that is small against one.  With values further apart the block is
-            // multiplied by S^2, whose columns span as much, so that nothing is asked of theta.
-            const bool cheb = next > 0.0 && next >= 1.0e-6 * top;
+            // orthonormalizing takes out as long as that is small against one.  With values further apart (wide) what the first
+            // of the two products has left is taken out before the second, which is eps (2 top / theta) then.  Where theta is all
+            // rounding, a block of lower rank, it is multiplied by S^2, deflated likewise: nothing is asked of theta.
+            // (Singular values k to 3000 apart had gone by S^2, whose products are not worth more than plain ones, and 1e4 apart
+            // and more lost the small ones in it: one of 1e4 over a bulk of 1, rank 8 of 400 x 300, 2 % behind the rank, 66 products in
+            // place of 200, energy lost beyond the best's 4.5e-3, now 6e-16 and plain
+            // ones 1.8e-14.)
+            const bool cheb = next > 0.0 && next >= 1.0e-13 * top;
             const double inv = cheb ? 1.0 / next : top > 0.0 ? 1.0 / top : 0.0;
             a.it->theta = next;
             a.it->power = cheb ? 0.0 : top;
+            a.it->wide = next >= 1.0e-6 * top ? 0 : 1;
             a.it->first[0] = cheb ? 2.0 * inv : inv;
             a.it->first[1] = cheb ? -1.0 : 0.0;
             a.it->first[2] = 0.0;
@@ -618,6 +638,49 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             a.it->second[1] = cheb ? -2.0 : 0.0;
             a.it->second[2] = cheb ? -1.0 : 0.0;
         }
+    }
+}
+
+// A workgroup a column of U: its products with the columns of Q in front, rows shared by the wavefronts and columns in lanes, then
+// the rows again less those.  Returns at once but for wide blocks.
+constexpr int DT = 512, DU = (BWLA_Q_JACOBI_SYM_LDS + 63) / 64;
+__global__ __launch_bounds__(DT) void deflate_kernel(const double* Q, double* U, int m, int p, const QRitz* it, const double* prev,
+                                                     const int* skip) {
+    if (*skip || !it->wide) return;
+    __shared__ double part[DT / 64][64 * DU];
+    const int j = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const double mine = prev[j];
+    double e[DU];
+    bool front[DU], any = false;
+#pragma unroll
+    for (int u = 0; u < DU; ++u) {
+        const int i = lane + 64 * u;
+        front[u] = i < j && prev[i < j ? i : j] > 1.0e4 * mine;
+        any |= front[u];
+        e[u] = 0.0;
+    }
+    if (__ballot(any) == 0) return;                         // (the same in every wavefront)
+    for (int r = w; r < m; r += DT / 64) {
+        const double v = U[(size_t)r * p + j];
+#pragma unroll
+        for (int u = 0; u < DU; ++u)
+            if (front[u]) e[u] = fma(Q[(size_t)r * p + lane + 64 * u], v, e[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < DU; ++u) part[w][lane + 64 * u] = e[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < DU; ++u) {
+        e[u] = 0.0;
+        for (int i = 0; i < DT / 64; ++i) e[u] += part[i][lane + 64 * u];
+    }
+    for (int r = w; r < m; r += DT / 64) {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < DU; ++u)
+            if (front[u]) s = fma(Q[(size_t)r * p + lane + 64 * u], e[u], s);
+        s = jgroup_sum<64>(s);
+        if (lane == 0) U[(size_t)r * p + j] -= s;
     }
 }
 
@@ -646,4 +709,11 @@ hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st) {
     if (j.n <= 64) return launch(jacobi_kernel<16, true, true>, jacobi_threads(16));
     if (in_lds) return launch(jacobi_kernel<64, true, true>, jacobi_threads(64));
     return launch(jacobi_kernel<64, false, true>, jacobi_threads(64));
+}
+
+hipError_t bwla_q_launch_deflate(const double* Q, double* U, int m, int p, const QRitz* it, const double* prev, const int* skip,
+                                 hipStream_t st) {
+    if (p < 1 || p > BWLA_Q_JACOBI_SYM_LDS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(deflate_kernel, dim3(p), dim3(DT), 0, st, Q, U, m, p, it, prev, skip);
+    return hipGetLastError();
 }

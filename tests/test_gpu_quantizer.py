@@ -451,7 +451,7 @@ def test_truncate_rank_with_a_gap(n, m, k):
 
 
 # (blocks of 24, 80, 128 and 132 vectors -- both ways of keeping the Cholesky factor, one to three elements of a column a
-# lane; a spread of 3000 is past what the Chebyshev filter takes, its square past 1e6, and goes by S^2)
+# lane; a spread of 3000, its square past 1e6, has the filter's first product deflated)
 @pytest.mark.parametrize("n,m,k,spread", [(300, 200, 8, 300.0), (300, 256, 40, 300.0), (333, 300, 64, 100.0),
                                           (300, 280, 66, 300.0), (300, 200, 8, 3000.0), (70, 81, 40, 1.0)])
 def test_truncate_rank_of_a_wide_spectrum(n, m, k, spread):
@@ -516,6 +516,24 @@ def test_truncate_rank_stops_no_farther_than_plain_iterations(n, m, k, factor):
         g = np.linalg.eigh(z.T @ z)[1][:, ::-1][:, :k]
         plain = _rel(z @ g @ (block @ g).T, want)
         assert _rel(_truncated(Y, k, iters, tol), want) <= max(plain, 1e-13)
+
+
+# (blocks of 24, 64 and 132 vectors)
+@pytest.mark.parametrize("n,m,k", [(400, 300, 8), (900, 640, 32), (300, 280, 66)])
+@pytest.mark.parametrize("top", [[3e3], [1e4], [1e5, 3e3, 1e2], [1e6]])
+def test_truncate_rank_with_one_value_far_above(n, m, k, top):
+    """A few strong directions over values of which the smallest wanted one is 2 % above the others: what the truncation loses beyond the
+    best is what its values have moved in the last iteration (tol); what is measured, besides, the result's rounding, eps sigma_1 times the
+    residual."""
+    p = min(n, m)
+    rng = np.random.default_rng(1)
+    lead = 1.02 + np.linspace(0.3, 0, k)
+    lead[:len(top)] = top
+    s = np.sort(np.concatenate([lead, rng.uniform(0.05, 1.0, p - k)]))[::-1]
+    Y, _ = _spectrum(n, m, s, 5)
+    got = _truncated(Y, k, 200, 1e-12)
+    best = np.sum(s[k:] ** 2)
+    assert abs(np.sum((Y - got) ** 2) / best - 1) < 1e-12 + 4 * 2.0 ** -52 * s[0] / np.sqrt(best)
 
 
 # (contractions past 2048 with ragged ends, results of 24 to 80 columns in tiles of 64: the kernels that take operands
