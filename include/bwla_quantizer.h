@@ -103,8 +103,9 @@ BWLA_API bwla_status_t bwla_q_svd_square(const double* d_G, int32_t nn, double* 
  * 1000 apart, what the first of the filter's two products leaves of the large directions in the columns of the small ones is taken out
  * before the second; a block whose theta is below 1e-13 of the largest, which is rounding, goes by S^2.)
  * It stops after N products with S, N = min(iters, max(24, iters / 2), max(64, iters / 3)), and one more where that is even
- * and above two, which do the work of `iters` plain ones; or earlier once the k leading Ritz values have settled, moved by at
- * most `tol` (relative) in one iteration: the remaining launches then return at once.
+ * and above two, which do the work of `iters` plain ones; or earlier once the k leading Ritz values have settled: moved by at
+ * most `tol` (relative) in one iteration, or the last two movements say that the block is as near as plain iterations that
+ * stop by such a movement come at most.  The remaining launches then return at once.
  * The energy that is missed falls by (sigma_{p+1} / sigma_k)^4 with each of the first three products, and by
  * T_2(2 sigma_k^2 / theta - 1)^2 with each two of the others, theta rising to sigma_p^2; a spectrum without a gap behind sigma_k
  * needs many iterations for the singular vectors themselves.  (Blocks of more than 136 vectors, i.e. k > 68, are orthonormalized by

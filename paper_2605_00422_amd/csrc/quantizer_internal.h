@@ -110,9 +110,9 @@ hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, 
 // that is at most 1 on [0, theta] and grows fastest beyond (Rutishauser's simultaneous iteration, 1970),
 // theta being the smallest Ritz value of the block.  QRitz is what a Jacobi call on the Gram matrix of the
 // filtered block leaves for the next iteration: theta, the coefficients of the filter's two products
-// (QGemm::coef).  power > 0 says that the filter is (S / power)^2 instead, power < 0 that it is S / -power and the second product
+// (QGemm::coef), and how far the leading values moved.  power > 0 says that the filter is (S / power)^2 instead, power < 0 that it is S / -power and the second product
 // of no account; wide that the Ritz values are far apart, and the first product is to be deflated (below).
-struct QRitz { double first[3], second[3], theta, power; int wide; };
+struct QRitz { double first[3], second[3], theta, power, moved; int wide; };
 struct QJacobi {
     const double* G; int n; double pw;
     double* sig; double* Ws; double* Vs; double* work;
@@ -121,7 +121,7 @@ struct QJacobi {
     // With it: prev holds n doubles, the squared Ritz values of the iteration before, and is replaced; degree says
     // whether the block was multiplied by S (1) or filtered (2), scale what its Ritz values are to be multiplied
     // with in the first case.  From the third call on (call counts from 1) *done is set to `call` once the leading `lead` values have
-    // settled: they moved by at most tol relative.
+    // settled: they moved by at most tol relative, or the block is by now where plain iterations would be when theirs have.
     QRitz* it; double* prev; int lead, degree, call; double tol, scale; int* done;
 };
 hipError_t bwla_q_launch_jacobi(const QJacobi& j, hipStream_t st);

@@ -599,7 +599,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int jj = t; jj < n; jj += JT) a.sig[jj] = sg[ord[jj]];
     if (a.it && !a.quick && w == 0) {
         // Ritz values of S out of the eigenvalues sg of the filtered block's Gram matrix
-        const double theta = a.it->theta, power = a.it->power;
+        const double theta = a.it->theta, power = a.it->power, before = a.it->moved;
         auto ritz = [&](int jj) {
             const double r = sqrt(sg[ord[jj]]);
             if (a.degree == 1) return r * a.scale;
@@ -617,7 +617,17 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
         for (int off = 32; off > 0; off >>= 1) moved = fmax(moved, __shfl_xor(moved, off, 64));
         if (lane == 0) {
             const double top = ritz(0), next = ritz(n - 1);
-            if (a.call >= 3 && moved <= a.tol) *a.done = a.call;        // (the first call has no values)
+            // Values of a filtered block are those of the block before it, to the square of an angle.  So the movement is the error e
+            // that the block two calls back had, and this one's is two quotients of movements smaller.  Plain iterations that
+            // stop with a movement of at most tol return the block behind it, one product on: with a quotient f = (theta / l_k)^2 a
+            // product their e lies between f^2 tol and f tol, by where the last movement has fallen.  Where this one's is not above
+            // the smaller of them it is as near as any of theirs.  (The first call has no values; a quotient takes two movements, and
+            // counts as no smaller than the filter can make it, T_2(2 l_k / theta - 1)^-2: the first blocks' need not be of a kind.)
+            const double gap = next / ritz(a.lead < n ? a.lead - 1 : n - 1), gap2 = gap * gap;
+            const double xk = 2.0 / gap - 1.0, tk = 2.0 * xk * xk - 1.0, rate = fmax(moved / before, 1.0 / (tk * tk));
+            const bool still = a.call >= 3 && moved <= a.tol;
+            const bool there = a.call >= 4 && rate <= 0.5 && moved * rate * rate <= gap2 * gap2 * a.tol;
+            if (still || there) *a.done = a.call;
             // A product leaves eps top of the largest direction in every column, T_2 so eps (2 top / theta)^2 of it, which
             // orthonormalizing takes out as long as that is small against one.  With values further apart (wide) what the first
             // of the two products has left is taken out before the second, which is eps (2 top / theta) then.  Where theta is all
@@ -631,6 +641,7 @@ __global__ __launch_bounds__(jacobi_threads(GW)) void jacobi_kernel(QJacobi a) {
             a.it->theta = next;
             a.it->power = cheb ? 0.0 : top;
             a.it->wide = next >= 1.0e-6 * top ? 0 : 1;
+            a.it->moved = moved;
             a.it->first[0] = cheb ? 2.0 * inv : inv;
             a.it->first[1] = cheb ? -1.0 : 0.0;
             a.it->first[2] = 0.0;
