@@ -348,23 +348,34 @@ hipError_t bwla_launch_rotate_quant(const bwla_layer_t* L, const void* dX, int x
 }
 
 namespace {
-struct SplitRule { RsShape rs; int64_t tokens, workgroups; };           // the most of either; no tokens: never split
+// the most tokens (none: never split), workgroups, and workgroups with half of the projection's counted
+struct SplitRule { RsShape rs; int64_t tokens, workgroups, halved; };
 SplitRule split_rule(const bwla_layer_t* L) {
-    SplitRule s{{}, 0, 0};
+    SplitRule s{{}, 0, 0, 0};
     const R3Shape s3 = r3_shape(L->n1, L->n2);
     if (!s3.ok || L->K > (int64_t)RS_QB * 512 * RS_QI * 4 || (s3.resident && s3.at < 6)) return s;
     s.rs = rs_shape(s3);
     if (!s.rs.ok) return s;
-    // up to two workgroups per CU (one after the other where LDS lets only one be resident):
-    // 224 x 128 at sixteen tokens 21.6 us against 31.2 in one workgroup per token, at thirty-two
-    // 34.5 against 32.0; with more tokens the one-workgroup-per-token kernel keeps the chip busy
-    s.workgroups = 2 * bwla_device_cus();
-    s.tokens = s.workgroups / s.rs.G;
+    // Not where a wavefront a strip does it sooner (rotate_terms.hip, at any of 1 to 16 tokens; split / there: 96 x 32 8.5 to 9.8 us /
+    // 6.2 to 6.6, 96 x 64 8.8 to 9.2 / 6.5 to 6.8, 96 x 96 9.8 to 10.7 / 9.8, 112 x 48 and 128 x 32 9.3 to 10.1 / 9.1; but 96 x 100 11.3 to
+    // 12.9 / 14.5 to 14.9, 112 x 96 9.7 to 11.0 / 11.5 to 11.8).
+    const bool strips = rt_fits(L->n1, L->n2, false);
+    if (strips && s3.resident && (L->n2 <= 48 || (L->n1 <= 96 && L->n2 <= 96))) return s;
+    // One workgroup a CU, and two, one after the other where LDS lets only one be resident, where a token in one workgroup takes as
+    // long as that (128 x 86: 24 tokens 12.1 / 12.7 us, 40 tokens 18.1 / 12.7; 144 x 112 24 tokens 12.9 / 16.7, 32 tokens 19.4 / 16.7;
+    // 224 x 128 16 tokens 14.0 / 25.1, 32 tokens 22.1 / 25.1; 160 x 160 14.2 / 25.6, 40 tokens 23.2 / 25.7)
+    // (What the projection adds is a second workgroup on some CUs; rank 32: 128 x 86 32 tokens 14.5 / 12.7, 144 x 80 24 tokens
+    // 11.3 / 15.8; ten strips again 128 x 160 32 tokens 17.1 / 20.8.)
+    const int64_t cus = bwla_device_cus();
+    const bool one = strips && L->n1 <= 176;
+    s.workgroups = 2 * cus;
+    s.halved = one && s3.strips <= 8 ? cus : 2 * cus;
+    s.tokens = (one ? cus : 2 * cus) / s.rs.G;
     // Factors that fit LDS: the split still pays when the second product is long (six or more
     // tiles along n1) and either the strips do not spread evenly over the CU's four SIMDs (n2 = 86:
     // six wavefronts, two SIMDs carry two) or there are at most eight tokens, so that the extra
-    // workgroups are free (measured, 128 x 64: 12.1 -> 11.1 us at four tokens, 12.2 -> 11.8 at
-    // eight, 12.3 -> 12.9 at sixteen; 128 x 86: 16.7 -> 10.9 at one token, 17.1 -> 12.2 at sixteen).
+    // workgroups are free (split / one workgroup a token: 128 x 64 8.8 / 9.5 us at one token, 9.4 / 9.8 at eight; 128 x 86
+    // 10.5 / 12.3 at one token, 11.9 / 12.6 at sixteen).
     if (s3.resident && (s3.strips & 3) == 0 && s.tokens > 8) s.tokens = 8;
     return s;
 }
@@ -377,7 +388,7 @@ size_t bwla_split_rotation_bytes(const bwla_layer_t* L, const bwla_psp_plan& pla
     if (M > s.tokens) return 0;
     const bool merged = bwla_rank_u(L) > 0 && plan.tile_rows == 16;
     const int64_t pblocks = merged ? (int64_t)plan.token_tiles * plan.splits * plan.col_groups : 0;
-    if (M * s.rs.G + pblocks > s.workgroups) return 0;
+    if (M * s.rs.G + pblocks > s.workgroups || M * s.rs.G + pblocks / 2 > s.halved) return 0;
     return (size_t)(M * L->K + 2 * M * s.rs.E) * sizeof(float);     // values, extremes
 }
 

@@ -89,12 +89,15 @@ inline bool rt_f32_sooner(int n1, int n2, int64_t M, int64_t cus, int64_t riders
 // ten strips whose registers would not do: with R1 streamed (64 tokens: 160 x 160 32.9 us, rotate_bf16_device.h 26.3; 144 x 144
 // 31.2, 25.3), or walking over few tokens (96 x 148: 257 tokens 42.1, 33.3; 400 tokens 42.1, 41.5; but 700 tokens 57.9, 61.0), or
 // ten with n1 above 96 and a token a workgroup (112 x 160: 128 tokens 21.8, 20.4; 96 x 160 14.2, 16.2).
+inline bool rt_fits(int n1, int n2, bool f32) {
+    return (n2 & 1) == 0 && n1 <= (f32 ? 128 : 256) && n2 <= (f32 ? 96 : n1 > 128 ? 128 : 160) &&
+           rt_shape(n1, n2, 1, 1, f32 ? RT_F32 : RT_BF16).lds_bytes <= RQ_LDS_LIMIT;
+}
 inline bool rt_serves(const bwla_layer_t* L, int xdtype, int64_t M, int64_t cus, int64_t riders) {
     const int n1 = L->n1, n2 = L->n2;
     const bool f32 = xdtype != BWLA_X_BF16;
-    if ((n2 & 1) != 0 || n1 > (f32 ? 128 : 256) || n2 > (f32 ? 96 : n1 > 128 ? 128 : 160)) return false;
+    if (!rt_fits(n1, n2, f32)) return false;
     const RtShape one = rt_shape(n1, n2, 1, 1, f32 ? RT_F32 : RT_BF16);
-    if (one.lds_bytes > RQ_LDS_LIMIT) return false;
     if (f32) return !rt_f32_sooner(n1, n2, M, cus, riders, one);
     if (n2 > 128 && M > cus && M < 2 * cus) return false;
     if (n2 > 144 && n1 > 96 && M <= cus) return false;

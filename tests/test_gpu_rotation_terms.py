@@ -54,6 +54,10 @@ CASES = [
     (512, 192, 16, 0, 6, False, True), (513, 192, 16, 0, 6, False, False), (1024, 256, 16, 8, 6, False, False),
     (64, 224, 32, 0, 6, False, False), (128, 192, 24, 8, 6, False, False), (129, 192, 24, 8, 6, False, False),
     (64, 112, 160, 0, 6, False, False), (64, 96, 160, 8, 6, False, False),
+    # few tokens, split over workgroups or not
+    (1, 96, 32, 8, 6, False, False), (16, 96, 96, 32, 6, True, True), (20, 112, 48, 0, 6, False, False),
+    (32, 128, 86, 0, 6, False, False), (33, 128, 86, 0, 6, False, False), (24, 144, 112, 8, 6, False, False),
+    (29, 144, 112, 0, 6, False, True), (40, 160, 160, 0, 6, False, False), (33, 224, 112, 8, 6, False, False),
     # riding and walking: seven and eight strips, six and few rows, a token or one and a half a CU
     (257, 48, 96, 32, 6, False, False), (384, 64, 112, 32, 6, True, True), (385, 64, 112, 32, 6, False, False),
     (300, 128, 128, 64, 6, False, False),
