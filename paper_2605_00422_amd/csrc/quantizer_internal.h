@@ -86,8 +86,6 @@ hipError_t bwla_q_launch_pow_vec(const double* src, double pw, int count, double
 // dst[i][j] = src[i][j] * pow(lam[j], pw) (fp32 out, n x k; lam <= 0 gives 0)
 hipError_t bwla_q_launch_scale_cols_f32(const double* src, const double* lam, double pw, int n, int k, float* dst,
                                         hipStream_t st);
-// row-wise binarization statistics of Algorithm 2's last step: mu_i = mean_j y_ij, alpha_i = mean_j |y_ij - mu_i|
-hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, double* absdev, hipStream_t st);
 
 // ---------------------------------------------------------------- one-sided Jacobi (quantizer_jacobi.hip)
 // Singular value decomposition G = U S V^T of a square n x n matrix (n <= 256) by Hestenes'

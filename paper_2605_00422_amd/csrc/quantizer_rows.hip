@@ -42,7 +42,7 @@ __global__ void convert_f64_f32_kernel(const double* src, float* dst, size_t cou
 // takes e and everything else the quotient, so one exponential an entry and state of the mixture serves all steps.
 // exp(-y) = 2^-k (1 + p) with k = y / ln 2 to the nearest integer and p = exp(k ln 2 - y) - 1 by its Taylor series to the thirteenth
 // power (what follows is 1.2e-17 of p); rest from p, as 1 - e would be off by a rounding of one: with c = 1e-8 s that was 5e-11 of the
-// next c.  (A call of exp and 1 - e: the same time, 154 us a launch of update and gradient at 11008 x 4096.)
+// next c.  (With a call of exp and 1 - e one round at 11008 x 4096 takes as long.)
 __device__ __forceinline__ void mix_exp(double x, double c, double inv, double& e, double& rest) {
     double y = 2.0 * fabs(c * x * inv);
     y = y > 800.0 ? 800.0 : y;                              // (exp(-800) is 0; a NaN stays)
@@ -315,22 +315,6 @@ __global__ void scale_cols_f32_kernel(const double* src, const double* lam, doub
     }
 }
 
-// Algorithm 2, "Final binarization": shift = row mean, scale = row mean of |y - shift|
-__global__ __launch_bounds__(RT) void row_stats_kernel(const double* Y, int m, double* mean, double* absdev) {
-    __shared__ double sh[4];
-    const double* y = Y + (size_t)blockIdx.x * m;
-    double s = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) s += y[j];
-    const double mu = block_sum(s, sh) / m;
-    double a = 0.0;
-    for (int j = threadIdx.x; j < m; j += RT) a += fabs(y[j] - mu);
-    const double ad = block_sum(a, sh) / m;
-    if (threadIdx.x == 0) {
-        mean[blockIdx.x] = mu;
-        absdev[blockIdx.x] = ad;
-    }
-}
-
 inline int flat_blocks(size_t count) {
     const size_t b = (count + RT - 1) / RT;
     return (int)(b < 4096 ? (b ? b : 1) : 4096);
@@ -401,9 +385,5 @@ hipError_t bwla_q_launch_pow_vec(const double* src, double pw, int count, double
 hipError_t bwla_q_launch_scale_cols_f32(const double* src, const double* lam, double pw, int n, int k, float* dst,
                                         hipStream_t st) {
     hipLaunchKernelGGL(scale_cols_f32_kernel, dim3(flat_blocks((size_t)n * k)), dim3(RT), 0, st, src, lam, pw, n, k, dst);
-    return hipGetLastError();
-}
-hipError_t bwla_q_launch_row_stats(const double* Y, int n, int m, double* mean, double* absdev, hipStream_t st) {
-    hipLaunchKernelGGL(row_stats_kernel, dim3(n), dim3(RT), 0, st, Y, m, mean, absdev);
     return hipGetLastError();
 }
