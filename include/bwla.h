@@ -322,8 +322,10 @@ BWLA_API bwla_status_t bwla_decode_forward_launches(const bwla_layer_t* layer, i
  * the library's device image, one per GPU, held until the process ends.  The call allocates
  * nothing and calls no allocating routine; it clears the counters it needs with a small kernel.
  *   - A call whose part of the scratch for the rotation and projection of M tokens exceeds BWLA_STATIC_SCRATCH_BYTES
- *     (bwla_psp_workspace_size covers fewer tokens and the sparse GEMM as well, and may be larger) returns BWLA_ERR_BUFSIZE and enqueues nothing (decode batches of the common model widths fit; long
- *     prefills do not: use bwla_decode_forward with a workspace of the caller's).
+ *     (bwla_psp_workspace_size covers fewer tokens and the sparse GEMM as well, and may be larger) returns BWLA_ERR_BUFSIZE and
+ *     enqueues nothing (decode batches of the common model widths fit; long prefills do not: use bwla_decode_forward with a
+ *     workspace of the caller's).  With a PSP rank of 0, where the rotated values are all that it would hold, the rotation
+ *     goes without them instead: a code on a rounding boundary may then differ from bwla_decode_forward's.
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap in time on one GPU (two
  *     streams, two host threads) race on it and must be serialized by the caller.
  *   - The first call on a device looks the array's address up (once per device and process).

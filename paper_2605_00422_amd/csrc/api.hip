@@ -428,13 +428,20 @@ bwla_status_t bwla_decode_forward_static(const bwla_layer_t* layer, const void* 
     const size_t need = rq_ws_bytes(layer, plan, M);
     // (of the counters only as many count as the tokens may use)
     const uint64_t counters = bwla_align256((uint64_t)((M + 15) / 16) * sizeof(int));
-    if (need > 0 && need + counters > STATIC_SCRATCH_BYTES) return BWLA_ERR_BUFSIZE;
+    // (a rank of zero uses a scratch for the split rotation alone, and has others that need none)
+    const bool without = need > 0 && need + counters > STATIC_SCRATCH_BYTES && bwla_rank_u(layer) <= 0;
+    if (!without && need > 0 && need + counters > STATIC_SCRATCH_BYTES) return BWLA_ERR_BUFSIZE;
     if (!d_X || !d_q || !d_scale || !d_qsum || !d_Y) return BWLA_ERR_NULL;
     if (layer->r > 0 && !d_T) return BWLA_ERR_NULL;
     if (xdtype != BWLA_X_F32 && xdtype != BWLA_X_BF16) return BWLA_ERR_UNSUPPORTED;
     if (!aligned16(d_X) || !aligned16(d_q) || !aligned16(d_Y) || (d_T && !aligned16(d_T)) ||
         (d_acc && !aligned16(d_acc)))
         return BWLA_ERR_ALIGN;
+    if (without) {
+        if (bwla_launch_rotate_quant(layer, d_X, xdtype, M, d_q, d_scale, d_qsum, d_T, nullptr, plan, (hipStream_t)stream, 6) != hipSuccess)
+            return BWLA_ERR_HIP;
+        return bwla_linear_forward_room(layer, d_q, d_scale, d_qsum, d_T, M, 6, nullptr, 0, d_Y, d_acc, stream);
+    }
     void* ws = nullptr;
     if (static_scratch_ptr(&ws) != hipSuccess) return BWLA_ERR_HIP;
     if (need > 0) {
