@@ -101,7 +101,8 @@ inline bwla_psp_plan bwla_psp_plan_of(const bwla_layer_t* L, int64_t M, int xdty
     // (what the array of bwla_decode_forward_static holds behind the head and the counters that it clears)
     constexpr uint64_t room = BWLA_STATIC_SCRATCH_BYTES + BWLA_PSP_COUNTER_BYTES - BWLA_WS_HEAD - 256;
     if (!walks || r <= 0 || M > BWLA_RIDE_TOKENS || bwla_psp_ws_bytes(p, r) <= room) return p;
-    // (too many partial tiles for it, where those of a riding projection fit: ranks above 64)
+    // (too many partial tiles for it, where those of a riding projection fit: ranks of 65 to 96, a few tokens past a token a CU of rows
+    // of some 14000 values, for every caller.  224 x 64, rank 80, 257 to 272 tokens: 49 to 52 us, where p takes 36)
     const bwla_psp_plan riding = bwla_make_psp_plan(M, L->K, r, bwla_rotate_planes_serves(L, xdtype, M), f32, slow);
     return bwla_psp_ws_bytes(riding, r) <= room ? riding : p;
 }

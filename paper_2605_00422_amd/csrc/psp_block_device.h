@@ -32,8 +32,8 @@ __device__ __forceinline__ void psp_sum_partials(const float* __restrict__ parti
 
 // ================================================================== PSP projection T = X U
 // A workgroup takes 16 tokens, one 512-column slice of K and up to PP_GROUPJT 16-column tiles of
-// the rank (group jg of JG): the fp32 MFMAs of a wavefront grow with the tiles it carries (six
-// tiles: 96 of them, 1.3 us), so wide ranks are dealt to more workgroups.
+// the rank (group jg of JG): a wavefront's operands of U and its MFMAs (of fp32 tokens 16 a tile) grow with the tiles it carries,
+// so wide ranks are dealt to more workgroups.
 // finish = false: with more than one slice the workgroup only leaves its partial tile; a later
 // launch adds them up (psp_sum_partials) and the arrival counters are not touched.
 template <bool BF16>

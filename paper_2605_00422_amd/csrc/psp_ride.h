@@ -1,24 +1,27 @@
 // Whether the projection T = X U of M > 16 tokens rides in the rotation's launch (psp_block_device.h) or has one of its
 // own in front or behind (psp_prefill.hip).  Host arithmetic without HIP types: a CPU test compiles it by itself.
 //
-// It rides where its workgroups (`riders`) finish in the rotation's shadow: a rotation workgroup has a CU to itself and
-// takes about 6 us + K / 1050, the CUs that the last round of them leaves free take a round of projection workgroups every
-// 5.5 us.  A little beside the shadow is still less than the launch of its own that the projection needs otherwise (6 to
-// 7 us), and so is a small round behind the rotation.  Not where the kernel that walks over the tokens serves (planes),
-// which is the faster one by more.  Rotation + projection, riding / in a launch of its own, and the rotation alone: 8192
-// columns, rank 64: 128 tokens 16.7 / 21 / 13.3; 255 tokens 29.8 / 22.7 / 14.3; 25600, rank 32: 128 tokens 28.3 / 34 / 26.6;
-// 5120, rank 32: 257 tokens 16.8 / 23 / 17.
+// It rides where its workgroups (`riders`) finish in the rotation's shadow: a rotation workgroup has a CU to itself, the CUs that
+// the last round of them leaves free take a round of projection workgroups at a time.  A little beside the shadow is still less
+// than the launch of its own that the projection needs otherwise (4 to 7 us), and so is a small round behind the rotation.
+// Not where a kernel that walks over the tokens serves (planes), which is the faster one by more.
+// The shadow of 9 us + K / 1050 and the 5.5 us a round are those of rotate_bf16_device.h and of projections on fp32 MFMA; with
+// rotate_terms.hip and bf16 MFMA both are shorter, and it is their quotient that counts.  Rotation + projection, riding / in a launch
+// of its own, us, * where the rule takes the second: 128 x 64, rank 64: 128 tokens 13.2 / 16.6, 158 15.6 / 16.9 *, 255 23.0 / 19.0 *;
+// 160 x 160, rank 32: 128 tokens 26.9 / 32.6, 185 34.8 / 33.2 *; 64 x 80, rank 32: 185 tokens 7.7 / 12.4, rank 64: 158 tokens
+// 8.9 / 13.4 *, 256 tokens 12.9 / 13.8 *; 128 x 86, rank 64: 96 tokens 13.7 / 20.6, 200 tokens 25.2 / 21.2 *.  Of 805 calls (15 pairs of
+// bf16 tokens, 7 of fp32 ones, 17 to 650 tokens, ranks 8, 32, 64) in which the two differ by 0.3 us it takes the better one to
+// within 5 % in 732; in the others, as those above, it does not ride where riding would be the better by up to a half.
 //
 // Those are bf16 tokens.  Of fp32 tokens the rotation takes longer, and the projection's own launch reads twice the bytes
 // and hands its sums over inside (bwla_launch_rotate_quant): there it rides as well while that launch stays within about
-// three workgroups a CU.  5120 columns, rank 37, 192 tokens 13.9 / 26.7, 320 tokens 21.6 / 32.4; 4096, rank 37, 384 tokens
-// 18.5 / 27.2; 8192, rank 64, 173 tokens 25.2 / 33.2; of 40 whole layers at random that ride by this alone 0.87 of the time
-// on average, 0.99 at most.  (bf16 tokens in the same fp32 kernel, whose factors are too long for the other: 1.00, 1.10.)
+// three workgroups a CU.  64 x 80, rank 32, 200 tokens 11.2 / 21.9, 333 tokens 16.1 / 26.2; 64 x 64, rank 32, 400 tokens
+// 13.3 / 21.3, but rank 64 17.3 / 26.3 *; 128 x 64, rank 64, 173 tokens 21.1 / 30.6.
 //
-// And of bf16 tokens whose rotation is a slow one (`slow`: factors too large for LDS with five strips of wavefronts or fewer, or
-// that the fp32 kernel rotates) the shadow is 1.75 times as long: 172 x 64 29 us, 200 x 80 40, 163 x 32 25.  Rank 8, 185 tokens,
-// riding / in a launch of its own: 172 x 64 30.4 / 35.8, 200 x 80 41.4 / 47.1; 163 x 32, 400 tokens 49.1 / 56.1, 172 x 64 57.8 / 62.6;
-// rank 64, 158 tokens 172 x 64 34.7 / 36.9, 192 x 64 38.0 / 36.5, 256 x 48 39.6 / 40.0, 163 x 32 26.1 / 34.4.
+// And of bf16 tokens whose rotation is a slow one for its length (`slow`: factors too large for the LDS of rotate_bf16_device.h with
+// five strips of wavefronts or fewer, or too long for it) the shadow is 1.75 times as long.  Rank 8, 185 tokens: 172 x 64
+// 20.2 / 23.6, 200 x 80 29.0 / 31.8, 163 x 32 19.1 / 24.4, 256 x 48 26.5 / 32.1; 200 tokens 172 x 64 22.1 / 23.4 *; rank 64, 158 tokens
+// 172 x 64 24.2 / 25.2, 256 x 48 28.8 / 33.5, 163 x 32 19.2 / 26.8.
 #pragma once
 
 #include <stdint.h>

@@ -279,14 +279,14 @@ void truncate(Ctx& x, const double* Y, int iters, double tol, double* A2, double
     // Iterations: the block U <- S Q, or T_2(2 S / theta - 1) Q = (4 / theta) S U - 2 U - Q with
     // U = (2 / theta) S Q - Q, then Q <- U orthonormalized in the basis of its Ritz vectors.  The first is S Q of the random
     // start as it is (S Q spans the same whatever the basis of Q) and is orthonormalized without Ritz vectors, which are
-    // worth nothing yet (500 us of sweeps); theta is not known there, and the second is S^2 Q.
+    // worth nothing yet (500 us of sweeps); theta is not known there, and the second is S^2 Q, or S Q where its pivots are far apart.
     //
     // `iters` counts products with S.  What two of them multiply sigma_k^2 / sigma_{p+1}^2 = q by is q^2 plain and
     // 8 q^2 - 8 q + 1 filtered: the filter needs half as many up to q = 2.1, a third up to q = 1.2, and for any gap wider than
     // these 24 and 64 of them leave nothing to be done (19.5^12, 2.9^32).  So half or a third as many are made, which are
     // fewer launches that return at once too.  11008 x 4096, rank 32: 13 iterations of 560 us and 14 calls of the
-    // eigensolver became 9 products of 275 in 5 iterations, 1400 empty launches some 340; the truncation's error against a
-    // 64-bit SVD (1500 x 1024, gaps 1.02 to 2): 7e-9 to 9e-8 -> 9e-10 to 3e-8.
+    // eigensolver became 11 products of 280 in 6 iterations, 1400 empty launches some 346; the truncation's error, tol 1e-12, rank 32 of
+    // 900 x 640, gaps of 2, 10 and 50 %: 4.8e-7, 2.2e-7, 8.1e-8 -> 1.9e-7, 7.4e-8, 3.3e-9.  Values far apart: quantizer_jacobi.hip.
     QRitz* ritz = reinterpret_cast<QRitz*>(x.ws + P.ritz);
     const int half_of = iters / 2 > 24 ? iters / 2 : 24, third_of = iters / 3 > 64 ? iters / 3 : 64;
     int budget = iters < half_of ? iters : half_of;

@@ -10,7 +10,7 @@
 // steps: `done` stays 0 and R as it was, unless `always`.
 //
 // Bound by the chain of steps: two products of 256 MFMAs (64 wide) on one CU's matrix cores, 4096 cycles each, and five
-// barriers.  The Procrustes matrices of 11008 x 4096 with 64 x 64 factors: 87 and 92 us, against 465 and 425 with the Jacobi
+// barriers.  The Procrustes matrices of 11008 x 4096 with 64 x 64 factors: 97 us each, against 465 and 425 with the Jacobi
 // SVD and the product of its factors; a 86 x 86 one was 200 launches of small products.
 #include "bwla_internal.h"
 #include "quantizer_internal.h"

@@ -42,7 +42,8 @@ __global__ void convert_f64_f32_kernel(const double* src, float* dst, size_t cou
 // takes e and everything else the quotient, so one exponential an entry and state of the mixture serves all steps.
 // exp(-y) = 2^-k (1 + p) with k = y / ln 2 to the nearest integer and p = exp(k ln 2 - y) - 1 by its Taylor series to the thirteenth
 // power (what follows is 1.2e-17 of p); rest from p, as 1 - e would be off by a rounding of one: with c = 1e-8 s that was 5e-11 of the
-// next c.  (With a call of exp and 1 - e one round at 11008 x 4096 takes as long.)
+// next c.  (Launches at 11008 x 4096, 154, 128, 174 and 320 us with a call of exp and 1 - e: 162, 135,
+// 178 and 335.)
 __device__ __forceinline__ void mix_exp(double x, double c, double inv, double& e, double& rest) {
     double y = 2.0 * fabs(c * x * inv);
     y = y > 800.0 ? 800.0 : y;                              // (exp(-800) is 0; a NaN stays)
@@ -70,7 +71,7 @@ __device__ __forceinline__ double mix_resp(double e, double rest, double x, doub
 // A row of T threads with E entries each in registers (thread t holds entries t, t + T, ...), or, with E = 0, a row of any
 // length that is read again by every step and whose responsibilities are computed again.  What bounds it at 11008 x 4096:
 // the first launch of a round (start, two likelihoods, update, gradient) the vector units, two exponentials an entry and
-// some sums; the others memory (720 MB at 4.7 TB/s).  284, 152, 132 and 163 us a round; with a launch a step
+// some sums; the others memory (720 MB at 4.7 TB/s).  304, 162, 136 and 177 us a round; with a launch a step
 // (13, responsibilities by tanh kept in LDS between two sums) 2310, and 85 for the result in fp32.
 template <int T, int E>
 __global__ __launch_bounds__(T) void rows_kernel(QRows g) {

@@ -34,7 +34,9 @@ def rides(tmp_path_factory):
     return run
 
 
-# (tokens, K, rank), rides; microseconds of the rotation with the projection: riding, in a launch of its own
+# (tokens, K, rank), rides; microseconds of the rotation with the projection: riding, in a launch of its own, with the rotations of
+# rotate_bf16_device.h and rotate_f32_device.h (those by strips: csrc/psp_ride.h).  The library asks the rule only of calls that no
+# walking rotation takes.
 @pytest.mark.parametrize("shape,want", [
     ((192, 5120, 37), True),                    # 13.9, 26.7
     ((320, 5120, 37), True),                    # 21.6, 32.4
