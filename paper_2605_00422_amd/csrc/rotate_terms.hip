@@ -12,7 +12,8 @@
 // (Two fp16 terms for all pairs were nearer to the exact value with ordinary tokens, but not with those that have one channel far
 // above the others, where nothing averages 22 bits out: a channel 1e8 above, 128 x 86, 700 tokens, the largest error of a scale
 // 4.4e-7 against 2.1e-7 and 9.6e-6 of the 8-bit codes against 1.6e-6.  Pairs too long for rotate_bf16_device.h, whose bf16 tokens
-// the fp32 kernel rotated: 172 x 64 at 128 tokens, rms of a scale's error 2.3e-7 there and 1.5e-7 on three bf16 terms.)
+// the fp32 kernel rotated: 172 x 64 at 128 tokens, rms of a scale's error 2.3e-7 there and 1.5e-7 on three bf16 terms.  Of those it
+// rotates few tokens still where n2 is up to 16, or up to 32 with n1 above 192: rt_serves says which calls stay elsewhere, and why.)
 //
 // Factors and rows are padded with zeros to multiples of 32.  Wavefront w of a group owns the 16 columns d of
 // strip w, and alternates between the stages per 32-deep step of the long product, so that Z is never whole anywhere.
